@@ -111,7 +111,7 @@ int pipesd_seq_reset(pipesd_kv *kv, int32_t seq);
 
 /* Commit n more tokens (host array) to client `seq`: afterwards keys/values are cached for all
  * committed tokens but the last, which is pending.  Runs the same forward as a verify pass in row
- * blocks (128 rows on a bf16 model, 32 on an fp32 one), without the LM head.  Returns after the work is enqueued on `stream`.
+ * blocks (128 rows; 32 on an fp32 model whose head_dim is no multiple of 16), without the LM head.  Returns after the work is enqueued on `stream`.
  * ENOMEM if the pool cannot hold the new rows. */
 int pipesd_prefill(pipesd_model *model, pipesd_kv *kv, int32_t seq, const int32_t *tokens, int32_t n,
                    void *stream);

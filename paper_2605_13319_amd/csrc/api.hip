@@ -41,9 +41,9 @@ struct pipesd_model {
   std::vector<float*> attn_norm, ffn_norm;
   std::vector<void*> wqkv, wo, wgu, wdown;  // fp32: row-major stacks; bf16: matrix-core tiles
   double* theta = nullptr;
-  // activation workspace (rows x width, fp32)
-  float *xres = nullptr, *hbuf = nullptr, *qkv = nullptr, *qbuf = nullptr, *attn_out = nullptr, *gu = nullptr,
-        *act2 = nullptr, *logits = nullptr, *rope_cs = nullptr;
+  // activation workspace (rows x width, fp32; all but the last two: fp32 models only)
+  float *xres = nullptr, *qkv = nullptr, *qbuf = nullptr, *attn_out = nullptr, *act2 = nullptr, *logits = nullptr,
+        *rope_cs = nullptr;
   unsigned* counters = nullptr;
   ActArena arena{};  // bf16 path: per-layer activation buffers (passes of up to 32 rows)
   int pass_act_tiles = 2;  // row tiles of the buffers of the pass being enqueued
@@ -101,6 +101,11 @@ struct pipesd_kv {
 };
 
 static constexpr int kCounterSlots = 1 << 16;
+
+// Rows per pass of an fp32 model's prompt blocks: 128 where the matrix-core attention takes the head size (the general kernel
+// keeps a pass's query rows in LDS).  Rows beyond 32 are more workgroups of the same launches: a
+// 120-token prompt into 2 layers of width 256 is 11 launches instead of four times twenty.
+static int f32_pass_rows(const pipesd_config& c) { return c.head_dim % 16 == 0 ? 128 : kMaxRows; }
 
 static int dev_alloc(pipesd_model* m, void** p, size_t bytes) {
   if (hipMalloc(p, bytes ? bytes : 256) != hipSuccess) return PIPESD_ENOMEM;
@@ -234,16 +239,16 @@ static int build_device_model(pipesd_model* m, const pipesd_weights* w) {
   if ((rc = dev_alloc(m, (void**)&m->theta, th.size() * 8))) return rc;
   HIP_TRY(hipMemcpy(m->theta, th.data(), th.size() * 8, hipMemcpyHostToDevice));
 
-  const size_t R = kMaxRows;
-  if ((rc = dev_alloc(m, (void**)&m->xres, R * d * 4))) return rc;
-  if ((rc = dev_alloc(m, (void**)&m->hbuf, R * (size_t)(d > qd ? d : qd) * 4))) return rc;
-  if ((rc = dev_alloc(m, (void**)&m->qkv, R * nqkv * 4))) return rc;
-  if ((rc = dev_alloc(m, (void**)&m->qbuf, R * qd * 4))) return rc;
-  if ((rc = dev_alloc(m, (void**)&m->attn_out, R * qd * 4))) return rc;
-  if ((rc = dev_alloc(m, (void**)&m->gu, R * 2 * (size_t)F * 4))) return rc;
-  if ((rc = dev_alloc(m, (void**)&m->act2, R * (size_t)F * 4))) return rc;
-  const size_t RP = c.dtype == PIPESD_BF16 ? kMaxPassRows : kMaxRows;  // rows of the largest pass
-  if ((rc = dev_alloc(m, (void**)&m->logits, RP * (size_t)V * 4))) return rc;
+  const size_t RP = c.dtype == PIPESD_BF16 ? kMaxPassRows : f32_pass_rows(c);  // rows of the largest pass
+  if (c.dtype == PIPESD_F32) {
+    if ((rc = dev_alloc(m, (void**)&m->xres, RP * d * 4))) return rc;
+    if ((rc = dev_alloc(m, (void**)&m->qkv, RP * nqkv * 4))) return rc;
+    if ((rc = dev_alloc(m, (void**)&m->qbuf, RP * qd * 4))) return rc;
+    if ((rc = dev_alloc(m, (void**)&m->attn_out, RP * qd * 4))) return rc;
+    if ((rc = dev_alloc(m, (void**)&m->act2, RP * (size_t)F * 4))) return rc;
+  }
+  const size_t RL = c.dtype == PIPESD_BF16 ? kMaxPassRows : kMaxRows;  // rows of the largest pass with logits
+  if ((rc = dev_alloc(m, (void**)&m->logits, RL * (size_t)V * 4))) return rc;
   if ((rc = dev_alloc(m, (void**)&m->rope_cs, RP * c.head_dim * 4))) return rc;
   // decision scratch: softmax partials of every row of the largest pass, scan sums per client
   if ((rc = dev_alloc(m, (void**)&m->row_stats, ((size_t)kMaxPassRows * 64 * 2 + 64) * 4))) return rc;
@@ -312,14 +317,15 @@ extern "C" size_t pipesd_kv_block_bytes(const pipesd_model* model, int32_t block
 static int ensure_attn_scratch(pipesd_model* m, size_t floats);
 
 // Floats of attention partials the largest pass over a pool of `pool_tokens` cached tokens can need:
-// a client brings at most kMaxRows rows and ceil(context / chunk) splits, the contexts of the
+// a client brings at most kMaxRows rows (a prompt block of an fp32 model up to 128) and ceil(context / chunk) splits, the contexts of the
 // clients of a pass add up to at most the pool, and a pass holds at most kMaxPassClients clients.
 static size_t attn_scratch_bound(const pipesd_model* m, int64_t pool_tokens) {
-  const int chunk = attn_chunk_tokens(m->cfg.dtype);
+  const int chunk = attn_chunk_tokens(m->cfg.dtype, m->cfg.head_dim);
   const int64_t clients = m->cfg.dtype == PIPESD_BF16 ? kMaxPassClients : 1;
   const int64_t splits = pool_tokens / chunk + clients;
   // (the streaming kernel splits no finer but rounds a head group's rows up to whole pairs of 16-row tiles)
-  const int64_t group_rows = (int64_t)(m->cfg.n_q_heads / m->cfg.n_kv_heads) * kMaxRows + 31;
+  const int64_t rows = m->cfg.dtype == PIPESD_BF16 ? kMaxRows : f32_pass_rows(m->cfg);  // of one client
+  const int64_t group_rows = (int64_t)(m->cfg.n_q_heads / m->cfg.n_kv_heads) * rows + 31;
   return (size_t)splits * (size_t)(group_rows * m->cfg.n_kv_heads) * (m->cfg.head_dim + 4);
 }
 
@@ -644,6 +650,24 @@ static GemmCall gemm_call(pipesd_model* m, const void* wp, int N, int K, int row
   return c;
 }
 
+static GemmF32Call gemm_f32_call(pipesd_model* m, const float* act, int lda, const void* w, int N, int K, int rows,
+                                 const float* gain, int epi, float* out, int ldo) {
+  GemmF32Call c{};
+  c.act = act;
+  c.lda = lda;
+  c.w = (const float*)w;
+  c.N = N;
+  c.K = K;
+  c.m = rows;
+  c.gain = gain;
+  c.eps = m->cfg.rms_eps;
+  c.epi = epi;
+  c.out = out;
+  c.ldo = ldo;
+  c.rope_cs = m->rope_cs;
+  return c;
+}
+
 // The rows of one pass: one client's k + 1 rows, or (bf16) the rows of up to 16 clients one after
 // the other, at most 128 in all.
 constexpr int kPrefillRows = 128;  // rows per pass of prompt ingestion (bf16)
@@ -664,14 +688,14 @@ static int run_pass(pipesd_model* m, pipesd_kv* kv, const PassLayout& pl, bool w
   const int rows = pl.rows;
   const bool bf = c.dtype == PIPESD_BF16;
   const bool single = pl.n_clients == 1;
-  if (pl.n_clients < 1 || pl.n_clients > kMaxPassClients || rows < 1 || rows > (bf ? kMaxPassRows : kMaxRows) ||
+  if (pl.n_clients < 1 || pl.n_clients > kMaxPassClients || rows < 1 || rows > (bf ? kMaxPassRows : f32_pass_rows(c)) ||
       (!bf && !single))
     return PIPESD_EINVAL;
   const int32_t seq = pl.client[0].seq;
   const int start_pos = pl.client[0].start_pos;
   // one client: the block table pointer is the client's own; several: the tables' common base + an offset per row
   KvView view = view_of(kv, single ? seq : 0);
-  const int chunk = attn_chunk_tokens(c.dtype);
+  const int chunk = attn_chunk_tokens(c.dtype, c.head_dim);
   const int nsplit = attn_nsplit(start_pos + rows, chunk);  // (one client)
   RowMap map{};
   AttnBatch ab{};
@@ -764,9 +788,15 @@ static int run_pass(pipesd_model* m, pipesd_kv* kv, const PassLayout& pl, bool w
     if (c.dtype == PIPESD_F32) {
       {
         ProfScope ps(m, PIPESD_PROF_GEMM_QKV, st);
-        HIP_TRY(launch_rmsnorm_rows(m->xres, m->attn_norm[l], c.rms_eps, rows, d, m->hbuf, st));
-        HIP_TRY(launch_gemm_f32(m->hbuf, d, (const float*)m->wqkv[l], nqkv, d, rows, m->qkv, nqkv, 0, st));
-        HIP_TRY(launch_rope_append_f32(m->qkv, rows, start_pos, l, c.n_q_heads, view, m->rope_cs, m->qbuf, st));
+        const bool rope = gemm_f32_fuses_rope(c.head_dim);
+        GemmF32Call g = gemm_f32_call(m, m->xres, d, m->wqkv[l], nqkv, d, rows, m->attn_norm[l], rope ? EPI_QKV : EPI_STORE,
+                                      rope ? m->qbuf : m->qkv, rope ? qd : nqkv);
+        g.kv = view;
+        g.layer = l;
+        g.start_pos = start_pos;
+        g.n_q_heads = c.n_q_heads;
+        HIP_TRY(launch_gemm_f32(g, st));
+        if (!rope) HIP_TRY(launch_rope_append_f32(m->qkv, rows, start_pos, l, c.n_q_heads, view, m->rope_cs, m->qbuf, st));
       }
       {
         ProfScope ps(m, PIPESD_PROF_ATTN, st);
@@ -774,17 +804,15 @@ static int run_pass(pipesd_model* m, pipesd_kv* kv, const PassLayout& pl, bool w
       }
       {
         ProfScope ps(m, PIPESD_PROF_GEMM_O, st);
-        HIP_TRY(launch_gemm_f32(m->attn_out, qd, (const float*)m->wo[l], d, qd, rows, m->xres, d, 1, st));
+        HIP_TRY(launch_gemm_f32(gemm_f32_call(m, m->attn_out, qd, m->wo[l], d, qd, rows, nullptr, EPI_RESID, m->xres, d), st));
       }
       {
         ProfScope ps(m, PIPESD_PROF_GEMM_GATEUP, st);
-        HIP_TRY(launch_rmsnorm_rows(m->xres, m->ffn_norm[l], c.rms_eps, rows, d, m->hbuf, st));
-        HIP_TRY(launch_gemm_f32(m->hbuf, d, (const float*)m->wgu[l], 2 * F, d, rows, m->gu, 2 * F, 0, st));
-        HIP_TRY(launch_silu_mul(m->gu, rows, F, m->act2, st));
+        HIP_TRY(launch_gemm_f32(gemm_f32_call(m, m->xres, d, m->wgu[l], 2 * F, d, rows, m->ffn_norm[l], EPI_SWIGLU, m->act2, F), st));
       }
       {
         ProfScope ps(m, PIPESD_PROF_GEMM_DOWN, st);
-        HIP_TRY(launch_gemm_f32(m->act2, F, (const float*)m->wdown[l], d, F, rows, m->xres, d, 1, st));
+        HIP_TRY(launch_gemm_f32(gemm_f32_call(m, m->act2, F, m->wdown[l], d, F, rows, nullptr, EPI_RESID, m->xres, d), st));
       }
     } else {
       {
@@ -837,8 +865,7 @@ static int run_pass(pipesd_model* m, pipesd_kv* kv, const PassLayout& pl, bool w
   if (want_logits) {
     if (c.dtype == PIPESD_F32) {
       ProfScope ps(m, PIPESD_PROF_GEMM_LMHEAD, st);
-      HIP_TRY(launch_rmsnorm_rows(m->xres, m->final_norm, c.rms_eps, rows, d, m->hbuf, st));
-      HIP_TRY(launch_gemm_f32(m->hbuf, d, (const float*)m->lm_head, V, d, rows, m->logits, V, 0, st));
+      HIP_TRY(launch_gemm_f32(gemm_f32_call(m, m->xres, d, m->lm_head, V, d, rows, m->final_norm, EPI_STORE, m->logits, V), st));
     } else {
       GemmCall g = gemm_call(m, m->lm_head, V, d, rows, ar.xa(c.n_layers), ar.sa(c.n_layers), norm_parts, EPI_STORE);
       ProfGemm pg(m, PIPESD_PROF_GEMM_LMHEAD, g);
@@ -893,7 +920,7 @@ extern "C" int pipesd_prefill(pipesd_model* model, pipesd_kv* kv, int32_t seq, c
   const int32_t cached_before = start;
   int rc = ensure_blocks(kv, seq, start + (int32_t)rows.size(), st);
   if (rc) return rc;
-  const size_t block = model->cfg.dtype == PIPESD_BF16 ? kPrefillRows : kMaxRows;  // rows per pass
+  const size_t block = model->cfg.dtype == PIPESD_BF16 ? kPrefillRows : f32_pass_rows(model->cfg);  // rows per pass
   for (size_t i = 0; i < rows.size(); i += block) {
     const int nr = (int)((rows.size() - i < block) ? rows.size() - i : block);
     rc = run_rows(model, kv, seq, rows.data() + i, nr, start + (int)i, false, st);

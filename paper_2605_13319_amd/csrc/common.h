@@ -118,14 +118,6 @@ hipError_t launch_setup_rows(int dtype, const void* tok_emb, const PassTokens& t
                              const float* gain, void* xpk, int act_tiles, float* ssq_out, int ssq_stride,
                              RowMap* map_dev, hipStream_t st);
 
-// ---- fp32 path (plain ALU kernels) ----
-hipError_t launch_rmsnorm_rows(const float* x, const float* gain, float eps, int m, int d, float* out, hipStream_t st);
-hipError_t launch_gemm_f32(const float* act, int lda, const float* w, int N, int K, int m, float* out, int ldo,
-                           int add_to_out, hipStream_t st);
-hipError_t launch_rope_append_f32(const float* qkv, int m, int start_pos, int layer, int n_q_heads, const KvView& kv,
-                                  const float* rope_cs, float* qbuf, hipStream_t st);
-hipError_t launch_silu_mul(const float* gu, int m, int d_ffn, float* act2, hipStream_t st);
-
 // ---- bf16 path: skinny GEMM on the matrix cores over re-tiled weights ----
 enum GemmEpilogue { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_QKV = 3 };
 enum PackMode { PACK_PLAIN = 0, PACK_HALVES = 1 };
@@ -181,6 +173,27 @@ struct PackSrc {
 };
 hipError_t launch_pack_bf16(const PackSrc& s, int n_src, int K, int mode, int pair_span, void* dst, int ntiles,
                             hipStream_t st);
+
+// ---- fp32 path (kernels_f32.hip; EPI_* as in the bf16 path) ----
+struct GemmF32Call {
+  const float* act;   // [m][lda]
+  int lda;
+  const float* w;     // [N][K]; SWIGLU: the gate rows, then the up rows
+  int N, K, m;
+  const float* gain;  // fused RMSNorm of the rows of `act`, or nullptr
+  float eps;
+  int epi;
+  float* out;         // STORE: [m][ldo]; RESID: added to; SWIGLU: silu(gate) * up [m][ldo]; QKV: queries [m][ldo]
+  int ldo;
+  // QKV (rotary, cache append)
+  KvView kv;
+  int layer, start_pos, n_q_heads;
+  const float* rope_cs;
+};
+hipError_t launch_gemm_f32(const GemmF32Call& c, hipStream_t st);
+bool gemm_f32_fuses_rope(int head_dim);  // EPI_QKV takes this head size (else: STORE, then launch_rope_append_f32)
+hipError_t launch_rope_append_f32(const float* qkv, int m, int start_pos, int layer, int n_q_heads, const KvView& kv,
+                                  const float* rope_cs, float* qbuf, hipStream_t st);
 
 // ---- activation buffers of the bf16 path ----
 // Every tensor that one step of a pass hands to the next has its own buffer PER LAYER, so within a
@@ -249,7 +262,9 @@ struct AttnCall {
   unsigned* counters = nullptr;   // streaming kernel: kAttnCounters arrival counters, zero between launches
 };
 int attn_nsplit(int total_tokens, int chunk);
-int attn_chunk_tokens(int dtype);  // tokens per workgroup of the attention kernel for this cache type
+constexpr int kAttnF32Split = 256;  // tokens per workgroup of the fp32 cache's kernel (head_dim a multiple of 16)
+int attn_chunk_tokens(int dtype, int head_dim);  // tokens per workgroup of the attention kernel for this cache
+hipError_t launch_attn_f32(const AttnCall& c, int nsplit, hipStream_t st);  // fp32 cache, head_dim a multiple of 16
 // Passes of at most kMaxRows rows per client, and prompt blocks of up to 128 rows alone in their
 // pass (bf16 cache), take the streaming kernel.  Fills span,
 // nsplit, part_off and count_off of every client of `b` (row_off, m, start_pos, table_off given) and

@@ -509,10 +509,10 @@ __global__ __launch_bounds__(64) void attn_merge_packed_kernel(const float* part
 }
 
 // merge the splits of one (row, head): o = sum_s e^{m_s - M} o_s / sum_s e^{m_s - M} l_s, splits taken
-// in index order.  h/8 threads per (row, head), 8 consecutive elements each (fp32 cache path).
+// in index order.  ceil(h/8) threads per (row, head), 8 consecutive elements each (fp32 cache path).
 __global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restrict__ part, int m, int n_q_heads, int h,
                                                            int nsplit, float* __restrict__ out) {
-  const int tpp = h / 8;  // threads per pair
+  const int tpp = (h + 7) / 8;  // threads per pair
   const int gt = blockIdx.x * blockDim.x + threadIdx.x;
   const int pair = gt / tpp, e0 = (gt % tpp) * 8;  // pair = head * m + r
   if (pair >= m * n_q_heads) return;
@@ -530,12 +530,13 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(const float* __restri
     const float wgt = expf(ms - M);
     L += ps[h + 1] * wgt;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i] += ps[e0 + i] * wgt;
+    for (int i = 0; i < 8; ++i) acc[i] += ps[min(e0 + i, h - 1)] * wgt;
   }
 #pragma unroll
   for (int i = 0; i < 8; ++i) acc[i] /= L;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) out[((size_t)r * n_q_heads + head) * h + e0 + i] = acc[i];
+  for (int i = 0; i < 8; ++i)
+    if (e0 + i < h) out[((size_t)r * n_q_heads + head) * h + e0 + i] = acc[i];
 }
 
 int attn_nsplit(int total_tokens, int chunk) { return (total_tokens + chunk - 1) / chunk; }
@@ -544,8 +545,12 @@ hipError_t launch_attention(const AttnCall& c, hipStream_t st) {
   const int h = c.kv.head_dim;
   const int total = c.start_pos + c.m;
   const int nsplit = attn_nsplit(total, c.chunk);
-  if (c.dtype == PIPESD_F32) {
-    if (c.chunk > kAttnChunkMax) return hipErrorInvalidValue;
+  if (c.dtype == PIPESD_F32 && h % 16 == 0) {
+    if (c.chunk != kAttnF32Split) return hipErrorInvalidValue;
+    const hipError_t e = launch_attn_f32(c, nsplit, st);
+    if (e != hipSuccess || nsplit == 1) return e;
+  } else if (c.dtype == PIPESD_F32) {
+    if (c.chunk > kAttnChunkMax || c.m > kMaxRows) return hipErrorInvalidValue;
     const size_t lds = (size_t)(2 * kAttnChunkMax * (h + 1) + kMaxRows * h + kMaxRows * kAttnChunkMax) * sizeof(float);
     dim3 grid(c.kv.n_kv_heads, nsplit);
     attn_partial_kernel<float><<<grid, kAttnThreads, lds, st>>>(c.q, c.kv, c.layer, c.m, c.start_pos, c.n_q_heads,
@@ -621,7 +626,7 @@ hipError_t launch_attention(const AttnCall& c, hipStream_t st) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (c.dtype == PIPESD_F32) {
-    const int threads = c.m * c.n_q_heads * (h / 8);
+    const int threads = c.m * c.n_q_heads * ((h + 7) / 8);
     attn_combine_kernel<<<(threads + 255) / 256, 256, 0, st>>>(c.part, c.m, c.n_q_heads, h, nsplit, c.out);
   } else {
     int max_m = 1;
@@ -633,7 +638,10 @@ hipError_t launch_attention(const AttnCall& c, hipStream_t st) {
   return hipGetLastError();
 }
 
-int attn_chunk_tokens(int dtype) { return dtype == PIPESD_F32 ? kAttnChunkMax : kAttnWgTokens; }
+int attn_chunk_tokens(int dtype, int head_dim) {
+  if (dtype != PIPESD_F32) return kAttnWgTokens;
+  return head_dim % 16 == 0 ? kAttnF32Split : kAttnChunkMax;
+}
 int attn_stream_plan(int n_q_heads, int n_kv_heads, int head_dim, AttnBatch& b, size_t* part_floats) {
   *part_floats = 0;
   if (b.n < 1 || b.n > kMaxPassClients || (head_dim != 128 && head_dim != 64)) return 0;

@@ -1,4 +1,4 @@
-// Row setup, the plain-ALU fp32 layer kernels, and KV bookkeeping kernels.
+// Row setup, the fp32 rotary step of head sizes the fused one does not take, and KV bookkeeping kernels.
 #include "common.h"
 
 namespace pipesd {
@@ -66,71 +66,8 @@ hipError_t launch_setup_rows(int dtype, const void* tok_emb, const PassTokens& t
 }
 
 // ---------------------------------------------------------------------------------------------
-// fp32 path
+// fp32 path, head_dim not a multiple of 16 (else the QKV product's epilogue does this)
 // ---------------------------------------------------------------------------------------------
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-
-// h = x * rsqrt(mean(x^2) + eps) * g, one workgroup per row
-__global__ void rmsnorm_rows_kernel(const float* __restrict__ x, const float* __restrict__ g, float eps, int d,
-                                    float* __restrict__ out) {
-  __shared__ float red[4];
-  const int r = blockIdx.x;
-  float s = 0.f;
-  for (int i = threadIdx.x; i < d; i += blockDim.x) {
-    const float v = x[(size_t)r * d + i];
-    s += v * v;
-  }
-  s = wave_sum(s);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-  __syncthreads();
-  const float tot = red[0] + red[1] + red[2] + red[3];
-  const float rstd = 1.0f / sqrtf(tot / (float)d + eps);
-  for (int i = threadIdx.x; i < d; i += blockDim.x) out[(size_t)r * d + i] = x[(size_t)r * d + i] * rstd * g[i];
-}
-
-hipError_t launch_rmsnorm_rows(const float* x, const float* gain, float eps, int m, int d, float* out, hipStream_t st) {
-  rmsnorm_rows_kernel<<<m, 256, 0, st>>>(x, gain, eps, d, out);
-  return hipGetLastError();
-}
-
-// out[r][n] (+)= sum_k act[r][k] * w[n][k]; one wave per output column, lanes stride over K
-__global__ void gemm_f32_kernel(const float* __restrict__ act, int lda, const float* __restrict__ w, int N, int K, int m,
-                                float* __restrict__ out, int ldo, int add_to_out) {
-  const int lane = threadIdx.x & 63;
-  const int n = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (n >= N) return;
-  float acc[kMaxRows];
-#pragma unroll
-  for (int r = 0; r < kMaxRows; ++r) acc[r] = 0.f;
-  for (int k = lane; k < K; k += 64) {
-    const float wv = w[(size_t)n * K + k];
-#pragma unroll
-    for (int r = 0; r < kMaxRows; ++r)
-      if (r < m) acc[r] = fmaf(act[(size_t)r * lda + k], wv, acc[r]);
-  }
-#pragma unroll
-  for (int r = 0; r < kMaxRows; ++r) {
-    if (r < m) {
-      const float v = wave_sum(acc[r]);
-      if (lane == 0) {
-        float* o = out + (size_t)r * ldo + n;
-        *o = add_to_out ? (*o + v) : v;
-      }
-    }
-  }
-}
-
-hipError_t launch_gemm_f32(const float* act, int lda, const float* w, int N, int K, int m, float* out, int ldo,
-                           int add_to_out, hipStream_t st) {
-  const int waves = 4;
-  gemm_f32_kernel<<<(N + waves - 1) / waves, waves * 64, 0, st>>>(act, lda, w, N, K, m, out, ldo, add_to_out);
-  return hipGetLastError();
-}
-
 // rotate q and k, store q to the query buffer and k, v to the paged cache (fp32 cache)
 __global__ void rope_append_f32_kernel(const float* __restrict__ qkv, int m, int start_pos, int layer, int n_q_heads,
                                        KvView kv, const float* __restrict__ rope_cs, float* __restrict__ qbuf) {
@@ -161,21 +98,6 @@ hipError_t launch_rope_append_f32(const float* qkv, int m, int start_pos, int la
                                   const float* rope_cs, float* qbuf, hipStream_t st) {
   dim3 grid(n_q_heads + 2 * kv.n_kv_heads, m);
   rope_append_f32_kernel<<<grid, 64, 0, st>>>(qkv, m, start_pos, layer, n_q_heads, kv, rope_cs, qbuf);
-  return hipGetLastError();
-}
-
-// act2 = silu(gate) * up with gu = [gate | up] per row
-__global__ void silu_mul_kernel(const float* __restrict__ gu, int d_ffn, float* __restrict__ act2) {
-  const int r = blockIdx.y;
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= d_ffn) return;
-  const float g = gu[(size_t)r * 2 * d_ffn + j], u = gu[(size_t)r * 2 * d_ffn + d_ffn + j];
-  act2[(size_t)r * d_ffn + j] = (g / (1.0f + expf(-g))) * u;
-}
-
-hipError_t launch_silu_mul(const float* gu, int m, int d_ffn, float* act2, hipStream_t st) {
-  dim3 grid((d_ffn + 255) / 256, m);
-  silu_mul_kernel<<<grid, 256, 0, st>>>(gu, d_ffn, act2);
   return hipGetLastError();
 }
 
