@@ -12,6 +12,7 @@ namespace pipesd {
 constexpr int kVThreads = 256;
 constexpr int kStatChunks = 64;   // softmax partials per row
 constexpr int kScanBlocks = 64;   // workgroups of the CDF scan
+constexpr int kHold = 8;          // values a thread holds in registers at once
 
 struct Uniforms {
   float u[kMaxRows];
@@ -51,15 +52,35 @@ __global__ __launch_bounds__(kVThreads) void softmax_stats_kernel(const float* _
   const int per = (V + kStatChunks - 1) / kStatChunks;
   const int lo = c * per, hi = min(V, lo + per);
   const float* zr = z + (size_t)row * V;
-  float mx = -INFINITY;
-  for (int i = lo + threadIdx.x; i < hi; i += kVThreads) mx = fmaxf(mx, zr[i]);
+  // A thread's values stay in registers between the two sweeps where they fit (any vocabulary up to
+  // 131072): the logits are read once, all of a thread's loads in flight together.  152 rows of
+  // 128256: 41 us with two sweeps over memory.
+  const bool held = per <= kHold * kVThreads;
+  float v[kHold], mx = -INFINITY;
+  if (held) {
+#pragma unroll
+    for (int j = 0; j < kHold; ++j) {
+      const int i = lo + (int)threadIdx.x + j * kVThreads;
+      v[j] = i < hi ? zr[i] : -INFINITY;
+    }
+#pragma unroll
+    for (int j = 0; j < kHold; ++j) mx = fmaxf(mx, v[j]);
+  } else {
+    for (int i = lo + threadIdx.x; i < hi; i += kVThreads) mx = fmaxf(mx, zr[i]);
+  }
   mx = wave_max(mx);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
   __syncthreads();
   mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
   __syncthreads();
   float s = 0.f;
-  for (int i = lo + threadIdx.x; i < hi; i += kVThreads) s += expf(zr[i] - mx);
+  if (held) {
+#pragma unroll
+    for (int j = 0; j < kHold; ++j)
+      if (lo + (int)threadIdx.x + j * kVThreads < hi) s += expf(v[j] - mx);
+  } else {
+    for (int i = lo + threadIdx.x; i < hi; i += kVThreads) s += expf(zr[i] - mx);
+  }
   s = wave_sumf(s);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
   __syncthreads();
@@ -89,43 +110,68 @@ __device__ __forceinline__ unsigned long long fixed_weight(float p, float q, boo
   return (unsigned long long)((double)w * 1099511627776.0);  // floor(w * 2^40), exact
 }
 
-__device__ __forceinline__ unsigned long long block_sum_u64(unsigned long long v, unsigned long long* red) {
+// sums of the lanes 0..own lane
+__device__ __forceinline__ unsigned long long wave_scan_u64(unsigned long long v) {
+  const int lane = threadIdx.x & 63;
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += shfl_u64(v, (threadIdx.x & 63) ^ o);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return red[0] + red[1] + red[2] + red[3];
+  for (int d = 1; d < 64; d <<= 1) {
+    const unsigned long long o = shfl_up_u64(v, d);
+    if (lane >= d) v += o;
+  }
+  return v;
 }
 
 // `stats` == nullptr: `p` holds probabilities.  Otherwise `p` holds logits and `stats` the (max,
 // sum of exp) chunk partials of softmax_stats_kernel: the probabilities are formed on the fly by the
 // very expressions softmax_write_kernel uses, so the decision is the one the two-step path takes.
 // (drafts[0..k-1] and un[0..k] may point into kernel arguments)
+//
+// Bound by a chain of dependent latencies, not by the 1 MB it reads at a vocabulary of 128256: the
+// rows' statistics, the tests, a sweep over one row, the arrival of the other workgroups, the draw.
+// Each link asks for all it needs at once, and the draw (find the chunk, then the token in it) is two
+// scans by the whole last workgroup.  With the draw walked by one wave, 64 tokens and one round trip
+// to memory at a time, the step took 41 us at that vocabulary and 18 us on given probabilities; now
+// 11 and 10.
 __device__ __forceinline__ void spec_accept_body(const float* __restrict__ p, const float* __restrict__ q,
                                                  const float* __restrict__ stats, int k, int V, const int32_t* drafts,
                                                  const float* un, unsigned long long* partial, unsigned* counter,
                                                  int32_t* __restrict__ result, int32_t* __restrict__ result_copy) {
-  __shared__ unsigned long long red[kVThreads / 64];
-  __shared__ int s_a, s_last;
+  constexpr int kWaves = kVThreads / 64;
+  __shared__ unsigned long long red[kWaves];
+  __shared__ int s_last;
   __shared__ float s_M[kMaxRows], s_S[kMaxRows];
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const bool from_logits = stats != nullptr;
   __shared__ int s_ok[kMaxRows];
+  // operands of the k tests (side by side: thread i has test i)
+  float test_p = 0.f, test_q = 0.f;
+  if (tid < k) {
+    const size_t at = (size_t)tid * V + drafts[tid];
+    test_p = p[at];
+    test_q = q[at];
+  }
   // Row statistics: one wave per row, lane j holding chunk j's (max, sum of exp); the row's max and
   // the rescaled sum are folded across the wave in a fixed butterfly order.  Every workgroup does
   // this for all k + 1 rows itself (one 512-byte load per row).
   static_assert(kStatChunks == 64, "one chunk partial per lane");
   if (from_logits) {
     const int sper = (V + kStatChunks - 1) / kStatChunks;
-    const int lane = tid & 63;
-    for (int row = tid >> 6; row <= k; row += kVThreads / 64) {
-      const bool have = lane * sper < V;
-      const float2 ms = have ? *(const float2*)(stats + ((size_t)row * kStatChunks + lane) * 2) : make_float2(-INFINITY, 0.f);
-      float M = ms.x;
+    const bool have = lane * sper < V;
+    constexpr int kRowsPerWave = kMaxRows / kWaves;
+    float2 ms[kRowsPerWave];
+#pragma unroll
+    for (int j = 0; j < kRowsPerWave; ++j) {
+      const int row = w + j * kWaves;
+      ms[j] = have && row <= k ? *(const float2*)(stats + ((size_t)row * kStatChunks + lane) * 2) : make_float2(-INFINITY, 0.f);
+    }
+#pragma unroll
+    for (int j = 0; j < kRowsPerWave; ++j) {
+      const int row = w + j * kWaves;
+      if (row > k) break;
+      float M = ms[j].x;
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o, 64));
-      float S = have ? ms.y * expf(ms.x - M) : 0.f;
+      float S = have ? ms[j].y * expf(ms[j].x - M) : 0.f;
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) S += __shfl_xor(S, o, 64);
       if (lane == 0) {
@@ -135,33 +181,43 @@ __device__ __forceinline__ void spec_accept_body(const float* __restrict__ p, co
     }
   }
   __syncthreads();
-  if (tid < k) {  // the k tests side by side
-    const int d = drafts[tid];
-    const float v = p[(size_t)tid * V + d];
-    s_ok[tid] = accept_test(from_logits ? expf(v - s_M[tid]) / s_S[tid] : v, q[(size_t)tid * V + d], un[tid]) ? 1 : 0;
-  }
+  if (tid < k)
+    s_ok[tid] = accept_test(from_logits ? expf(test_p - s_M[tid]) / s_S[tid] : test_p, test_q, un[tid]) ? 1 : 0;
   __syncthreads();
-  auto prob = [&](int row, int i) -> float {
-    const float v = p[(size_t)row * V + i];
-    return from_logits ? expf(v - s_M[row]) / s_S[row] : v;
-  };
-  if (tid == 0) {  // the tests count in order, up to the first failure
-    int a = 0;
-    while (a < k && s_ok[a]) ++a;
-    s_a = a;
-  }
-  __syncthreads();
-  const int a = s_a;
+  int a = 0;  // the tests count in order, up to the first failure
+  while (a < k && s_ok[a]) ++a;
   const bool residual = a < k;
+  const float* pr = p + (size_t)a * V;
   const float* qr = q + (size_t)(residual ? a : 0) * V;
+  const float row_M = from_logits ? s_M[a] : 0.f, row_S = from_logits ? s_S[a] : 1.f;
+  auto prob = [&](float v) -> float { return from_logits ? expf(v - row_M) / row_S : v; };
+  // weights of the tokens i0, i0 + step, .. (kHold of them; 0 from `end` on)
+  auto weights = [&](int i0, int step, int end, unsigned long long (&out)[kHold]) {
+    float pv[kHold], qv[kHold];
+#pragma unroll
+    for (int j = 0; j < kHold; ++j) {
+      const int i = min(i0 + j * step, V - 1);
+      pv[j] = pr[i];
+      qv[j] = residual ? qr[i] : 0.f;
+    }
+#pragma unroll
+    for (int j = 0; j < kHold; ++j) out[j] = i0 + j * step < end ? fixed_weight(prob(pv[j]), qv[j], residual) : 0ull;
+  };
 
   const int per = (V + kScanBlocks - 1) / kScanBlocks;
   const int lo = blockIdx.x * per, hi = min(V, lo + per);
-  unsigned long long s = 0;
-  for (int i = lo + tid; i < hi; i += kVThreads) s += fixed_weight(prob(a, i), residual ? qr[i] : 0.f, residual);
-  s = block_sum_u64(s, red);
+  unsigned long long s = 0, wt[kHold];
+  for (int base = lo; base < hi; base += kVThreads * kHold) {
+    weights(base + tid, kVThreads, hi, wt);
+#pragma unroll
+    for (int j = 0; j < kHold; ++j) s += wt[j];
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) s += shfl_u64(s, lane ^ o);
+  if (lane == 0) red[w] = s;
+  __syncthreads();
   if (tid == 0) {
-    partial[blockIdx.x] = s;
+    partial[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
     __threadfence();
     const unsigned prev = atomicAdd(counter, 1u);
     s_last = (prev == (unsigned)gridDim.x - 1);
@@ -169,59 +225,10 @@ __device__ __forceinline__ void spec_accept_body(const float* __restrict__ p, co
   __syncthreads();
   if (!s_last) return;
   __threadfence();
-  if (tid >= 64) return;  // the last workgroup's first wave finishes the draw
 
-  unsigned long long W = 0;
-  for (int b = 0; b < kScanBlocks; ++b) W += partial[b];
-  int next;
-  if (W == 0) {
-    // every weight truncated to zero: lowest-index maximum of the target row
-    float best = -INFINITY;
-    int bi = 0x7fffffff;
-    for (int i = tid; i < V; i += 64) {
-      const float v = prob(a, i);
-      if (v > best) { best = v; bi = i; }
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-      const float ob = __shfl_xor(best, o, 64);
-      const int oi = __shfl_xor(bi, o, 64);
-      if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
-    }
-    next = bi;
-  } else {
-    const unsigned long long ui = (unsigned long long)(un[k] * 16777216.0f);  // floor(u * 2^24)
-    const unsigned long long T = (__umul64hi(W, ui) << 40) | ((W * ui) >> 24);
-    // chunk whose running total first exceeds T
-    unsigned long long run = 0;
-    int b = 0;
-    for (; b < kScanBlocks - 1; ++b) {
-      const unsigned long long nb = run + partial[b];
-      if (nb > T) break;
-      run = nb;
-    }
-    const int clo = b * per, chi = min(V, clo + per);
-    next = chi - 1;
-    bool found = false;
-    for (int base = clo; base < chi && !found; base += 64) {
-      const int i = base + tid;
-      unsigned long long w = (i < chi) ? fixed_weight(prob(a, i), residual ? qr[i] : 0.f, residual) : 0ull;
-      unsigned long long inc = w;  // inclusive scan across the wave
-#pragma unroll
-      for (int d = 1; d < 64; d <<= 1) {
-        const unsigned long long o = shfl_up_u64(inc, d);
-        if (tid >= d) inc += o;
-      }
-      const bool hit = (run + inc) > T;
-      const unsigned long long m = __ballot(hit);
-      if (m != 0ull) {
-        next = base + __ffsll((long long)m) - 1;
-        found = true;
-      } else {
-        run += shfl_u64(inc, 63);
-      }
-    }
-  }
-  if (tid == 0) {
+  // the last workgroup to arrive finishes the draw: lane b of every wave has the sum of chunk b
+  static_assert(kScanBlocks == 64, "one chunk sum per lane");
+  auto decide = [&](int next) {
     result[0] = a;
     result[1] = next;
     if (result_copy != nullptr) {
@@ -229,6 +236,58 @@ __device__ __forceinline__ void spec_accept_body(const float* __restrict__ p, co
       result_copy[1] = next;
     }
     *counter = 0u;
+  };
+  const unsigned long long mine = partial[lane], upto = wave_scan_u64(mine), W = shfl_u64(upto, 63);
+  if (W == 0) {
+    // every weight truncated to zero: lowest-index maximum of the target row
+    if (tid >= 64) return;
+    float best = -INFINITY;
+    int bi = 0x7fffffff;
+    for (int i = tid; i < V; i += 64) {
+      const float v = prob(pr[i]);
+      if (v > best) { best = v; bi = i; }
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+      const float ob = __shfl_xor(best, o, 64);
+      const int oi = __shfl_xor(bi, o, 64);
+      if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
+    }
+    if (tid == 0) decide(bi);
+    return;
+  }
+  const unsigned long long ui = (unsigned long long)(un[k] * 16777216.0f);  // floor(u * 2^24)
+  const unsigned long long T = (__umul64hi(W, ui) << 40) | ((W * ui) >> 24);
+  // chunk whose running total first exceeds T (T < W: there is one)
+  const int b = min(__ffsll((long long)__ballot(upto > T)) - 1, kScanBlocks - 1);
+  unsigned long long run = shfl_u64(upto, b) - shfl_u64(mine, b);
+  const int clo = b * per, chi = min(V, clo + per);
+  for (int base = clo; base < chi; base += kVThreads * kHold) {
+    // thread t has the kHold tokens behind base + t * kHold
+    const int i0 = base + tid * kHold;
+    weights(i0, 1, chi, wt);
+    unsigned long long own = 0;
+#pragma unroll
+    for (int j = 0; j < kHold; ++j) own += wt[j];
+    const unsigned long long inc = wave_scan_u64(own);
+    __syncthreads();  // (red has been read)
+    if (lane == 63) red[w] = inc;
+    __syncthreads();
+    unsigned long long before = run + inc - own;
+#pragma unroll
+    for (int ww = 0; ww < kWaves; ++ww) {
+      if (ww < w) before += red[ww];
+      run += red[ww];
+    }
+    if (before <= T && before + own > T) {  // one thread of the workgroup
+      int j = 0;
+#pragma unroll
+      for (int jj = 0; jj < kHold - 1; ++jj) {
+        before += wt[jj];
+        if (before <= T) j = jj + 1;
+      }
+      decide(i0 + j);
+    }
+    if (run > T) return;  // (found: the same for all threads)
   }
 }
 
@@ -312,21 +371,26 @@ __global__ __launch_bounds__(kVThreads) void argmax_partial_kernel(const float* 
   }
 }
 
-__global__ void greedy_decide_kernel(const float* __restrict__ stats, int k, int V, RowTokens drafts,
-                                     int32_t* __restrict__ result, int32_t* __restrict__ result_copy) {
+// one wave per row, lane j holding chunk j's (max, index)
+constexpr int kDecideWaves = 16;
+__global__ __launch_bounds__(kDecideWaves * 64) void greedy_decide_kernel(const float* __restrict__ stats, int k, int V,
+                                                                          RowTokens drafts, int32_t* __restrict__ result,
+                                                                          int32_t* __restrict__ result_copy) {
   __shared__ int am[kMaxRows];
   const int per = (V + kStatChunks - 1) / kStatChunks;
-  if ((int)threadIdx.x <= k) {
-    const float* st = stats + (size_t)threadIdx.x * kStatChunks * 2;
-    float best = -INFINITY;
-    int bi = 0x7fffffff;
-    for (int j = 0; j < kStatChunks; ++j) {
-      if (j * per >= V) break;
-      const float v = st[j * 2];
-      const int idx = __float_as_int(st[j * 2 + 1]);
-      if (v > best || (v == best && idx < bi)) { best = v; bi = idx; }
+  const int lane = threadIdx.x & 63;
+  for (int row = threadIdx.x >> 6; row <= k; row += kDecideWaves) {
+    const bool have = lane * per < V;
+    const float2 st = have ? *(const float2*)(stats + ((size_t)row * kStatChunks + lane) * 2) : make_float2(-INFINITY, 0.f);
+    float best = st.x;
+    int bi = have ? __float_as_int(st.y) : 0x7fffffff;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      const float ob = __shfl_xor(best, o, 64);
+      const int oi = __shfl_xor(bi, o, 64);
+      if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
     }
-    am[threadIdx.x] = bi;
+    if (lane == 0) am[row] = bi;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -346,7 +410,7 @@ hipError_t launch_greedy_accept(const VerifyCall& c, hipStream_t st) {
   argmax_partial_kernel<<<grid, kVThreads, 0, st>>>(c.logits_or_p, c.V, c.row_stats);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  greedy_decide_kernel<<<1, 64, 0, st>>>(c.row_stats, c.k, c.V, c.drafts, c.result, c.result_copy);
+  greedy_decide_kernel<<<1, kDecideWaves * 64, 0, st>>>(c.row_stats, c.k, c.V, c.drafts, c.result, c.result_copy);
   return hipGetLastError();
 }
 
