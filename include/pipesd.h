@@ -110,8 +110,9 @@ int pipesd_kv_destroy(pipesd_kv *kv);
 int pipesd_seq_reset(pipesd_kv *kv, int32_t seq);
 
 /* Commit n more tokens (host array) to client `seq`: afterwards keys/values are cached for all
- * committed tokens but the last, which is pending.  Runs the same forward as a verify pass in row
- * blocks (128 rows; 32 on an fp32 model whose head_dim is no multiple of 16), without the LM head.  Returns after the work is enqueued on `stream`.
+ * committed tokens but the last, which is pending.  Runs the same forward as a verify pass,
+ * without the LM head, in passes of up to 2048 rows on a bf16 model and 128 on an fp32 one (32 if its
+ * head_dim is no multiple of 16).  Returns after the work is enqueued on `stream`.
  * ENOMEM if the pool cannot hold the new rows. */
 int pipesd_prefill(pipesd_model *model, pipesd_kv *kv, int32_t seq, const int32_t *tokens, int32_t n,
                    void *stream);
@@ -259,9 +260,9 @@ int pipesd_model_fused_launches(const pipesd_model *model, int64_t *n);
 
 /* GEMM kernel of bf16 passes of more than 64 rows (batched verification, prompt ingestion).  Two
  * kernels compute them: the narrow one of the single-client pass, run by groups of workgroups that
- * share the weights through a chiplet's L2, and a wide one that stages the activations of all rows
- * in LDS.  mode 0 (default): per product, whichever was measured faster for its shape; 1: always the
- * narrow kernel; 2: always the wide one.  Both accumulate every output in the same order and give
+ * share the weights through a chiplet's L2, and a wide one that brings tiles of both operands through
+ * LDS.  mode 0 (default): the wide one, which was measured faster for every shape; 1: the narrow kernel
+ * (prompts then run in passes of 128 rows); 2: as 0.  Both accumulate every output in the same order and give
  * bit-identical results, so the mode changes speed only.  PIPESD_EINVAL for another mode. */
 int pipesd_model_set_wide_gemm(pipesd_model *model, int32_t mode);
 

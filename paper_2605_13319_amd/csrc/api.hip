@@ -3,6 +3,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <new>
 #include <vector>
 
@@ -47,9 +48,10 @@ struct pipesd_model {
   unsigned* counters = nullptr;
   ActArena arena{};  // bf16 path: per-layer activation buffers (passes of up to 32 rows)
   int pass_act_tiles = 2;  // row tiles of the buffers of the pass being enqueued
-  ActArena arena_big{};  // bf16 path: one buffer of each kind, 16 row tiles (passes of several clients, up to 256 rows; 33..128 rows use 8 of them)
-  int wide_mode = 0;        // GEMM kernel of passes of more than 64 rows: 0 by shape, 1 narrow, 2 wide
-  void* wide_ws = nullptr;  // bf16 path: running sums of the K-split workgroups of passes of more than 64 rows
+  ActArena arena_big{};  // bf16 path: one buffer of each kind for passes of more than 32 rows, up to kMaxPromptRows
+  int wide_mode = 0;        // GEMM kernel of passes of more than 64 rows: 1 narrow, else wide
+  void* wide_ws = nullptr;  // bf16 path: running sums in passes of more than 64 rows
+  float* wide_rstd = nullptr;  // bf16 path: rstd of every row of such a pass
   size_t wide_ws_bytes = 0;
   RowMap* rowmap_dev = nullptr;  // bf16 path: per-row placement of a pass that holds several clients
   float* attn_part = nullptr;
@@ -239,7 +241,7 @@ static int build_device_model(pipesd_model* m, const pipesd_weights* w) {
   if ((rc = dev_alloc(m, (void**)&m->theta, th.size() * 8))) return rc;
   HIP_TRY(hipMemcpy(m->theta, th.data(), th.size() * 8, hipMemcpyHostToDevice));
 
-  const size_t RP = c.dtype == PIPESD_BF16 ? kMaxPassRows : f32_pass_rows(c);  // rows of the largest pass
+  const size_t RP = c.dtype == PIPESD_BF16 ? kMaxPromptRows : f32_pass_rows(c);  // rows of the largest pass
   if (c.dtype == PIPESD_F32) {
     if ((rc = dev_alloc(m, (void**)&m->xres, RP * d * 4))) return rc;
     if ((rc = dev_alloc(m, (void**)&m->qkv, RP * nqkv * 4))) return rc;
@@ -261,12 +263,14 @@ static int build_device_model(pipesd_model* m, const pipesd_weights* w) {
     const size_t arena_bytes = act_arena_layout(m->arena, L, d, qd, F, true, 2);
     if ((rc = dev_alloc(m, (void**)&m->arena.base, arena_bytes))) return rc;
     HIP_TRY(hipMemset(m->arena.base, 0, arena_bytes));
-    const size_t big_bytes = act_arena_layout(m->arena_big, L, d, qd, F, false, kMaxPassRows / 16);
+    const size_t big_bytes = act_arena_layout(m->arena_big, L, d, qd, F, false, kMaxPromptRows / 16);
     if ((rc = dev_alloc(m, (void**)&m->arena_big.base, big_bytes))) return rc;
     HIP_TRY(hipMemset(m->arena_big.base, 0, big_bytes));
     const int gemm_nk[5][2] = {{(int)nqkv, (int)d}, {(int)d, (int)qd}, {2 * (int)F, (int)d}, {(int)d, (int)F}, {(int)V, (int)d}};
-    for (const auto& nk : gemm_nk) m->wide_ws_bytes = std::max(m->wide_ws_bytes, gemm_wide_workspace_bytes(nk[0], nk[1]));  // (sized as if every product ran wide)
-    if (m->wide_ws_bytes && (rc = dev_alloc(m, &m->wide_ws, m->wide_ws_bytes))) return rc;
+    for (int i = 0; i < 5; ++i)  // (the last, the LM head, is no part of prompts)
+      m->wide_ws_bytes = std::max(m->wide_ws_bytes, gemm_wide_workspace_bytes(gemm_nk[i][0], gemm_nk[i][1], i < 4 ? kMaxPromptRows : kMaxPassRows));
+    if ((rc = dev_alloc(m, &m->wide_ws, m->wide_ws_bytes))) return rc;
+    if ((rc = dev_alloc(m, (void**)&m->wide_rstd, kMaxPromptRows * sizeof(float)))) return rc;
     if ((rc = dev_alloc(m, (void**)&m->step_clock, ((size_t)4 * L + 1) * 8))) return rc;
     if ((rc = dev_alloc(m, (void**)&m->rowmap_dev, sizeof(RowMap)))) return rc;
     if ((rc = dev_alloc(m, (void**)&m->attn_count, kAttnCounters * sizeof(unsigned)))) return rc;
@@ -314,6 +318,19 @@ extern "C" size_t pipesd_kv_block_bytes(const pipesd_model* model, int32_t block
   return (size_t)c.n_layers * 2 * c.n_kv_heads * c.head_dim * block_tokens * model->esz;
 }
 
+// the batch of a prompt's attention: its blocks of 128 rows, one "client" each
+static AttnBatch prompt_blocks(int rows, int start_pos) {
+  AttnBatch b{};
+  for (int r0 = 0; r0 < rows; r0 += kPromptBlockRows) {
+    AttnClient& ac = b.c[b.n++];
+    ac.row_off = r0;
+    ac.m = std::min(kPromptBlockRows, rows - r0);
+    ac.start_pos = start_pos + r0;
+  }
+  return b;
+}
+static_assert(kMaxPromptRows <= kMaxPassClients * kPromptBlockRows, "a prompt's blocks fit a batch");
+
 static int ensure_attn_scratch(pipesd_model* m, size_t floats);
 
 // Floats of attention partials the largest pass over a pool of `pool_tokens` cached tokens can need:
@@ -326,7 +343,15 @@ static size_t attn_scratch_bound(const pipesd_model* m, int64_t pool_tokens) {
   // (the streaming kernel splits no finer but rounds a head group's rows up to whole pairs of 16-row tiles)
   const int64_t rows = m->cfg.dtype == PIPESD_BF16 ? kMaxRows : f32_pass_rows(m->cfg);  // of one client
   const int64_t group_rows = (int64_t)(m->cfg.n_q_heads / m->cfg.n_kv_heads) * rows + 31;
-  return (size_t)splits * (size_t)(group_rows * m->cfg.n_kv_heads) * (m->cfg.head_dim + 4);
+  size_t floats = (size_t)splits * (size_t)(group_rows * m->cfg.n_kv_heads) * (m->cfg.head_dim + 4);
+  if (m->cfg.dtype == PIPESD_BF16) {  // and a prompt's last pass
+    const int rows = (int)std::min(pool_tokens, (int64_t)kMaxPromptRows);
+    AttnBatch b = prompt_blocks(rows, (int)(pool_tokens - rows));
+    size_t prompt_floats = 0;
+    if (attn_stream_plan(m->cfg.n_q_heads, m->cfg.n_kv_heads, m->cfg.head_dim, b, true, &prompt_floats))
+      floats = std::max(floats, prompt_floats);
+  }
+  return floats;
 }
 
 extern "C" int pipesd_kv_create(const pipesd_model* model, int32_t max_seqs, int32_t block_tokens, void* pool,
@@ -645,6 +670,7 @@ static GemmCall gemm_call(pipesd_model* m, const void* wp, int N, int K, int row
   c.rope_cs = m->rope_cs;
   c.wide_ws = m->wide_ws;
   c.wide_ws_bytes = m->wide_ws_bytes;
+  c.rstd = m->wide_rstd;
   c.wide_mode = m->wide_mode;
   c.gate = m->gate;
   return c;
@@ -669,15 +695,20 @@ static GemmF32Call gemm_f32_call(pipesd_model* m, const float* act, int lda, con
 }
 
 // The rows of one pass: one client's k + 1 rows, or (bf16) the rows of up to 16 clients one after
-// the other, at most 128 in all.
-constexpr int kPrefillRows = 128;  // rows per pass of prompt ingestion (bf16)
+// the other, at most 256 in all, or a piece of one client's prompt.
+// Rows per pass of prompt ingestion (bf16): the weights are read once per 2048 rows and every product
+// has enough rows to fill the device without a split of K; a prompt of 2048 tokens at the 8B shape takes
+// 54.7 ms, 103.9 in passes of 128 rows.  Passes of 128 rows remain for what larger ones do not do:
+// contexts the streaming attention declines, the narrow GEMM kernel, the all-layers kernel's model.
+constexpr int kPrefillRows = 128;
 struct PassClient {
   int32_t seq, rows, start_pos;
 };
 struct PassLayout {
   int n_clients = 0, rows = 0;
   PassClient client[kMaxPassClients];
-  PassTokens tok{};
+  PassTokens tok{};                      // tokens of the rows (up to kMaxPassRows)
+  const int32_t* prompt_tok = nullptr;   // or (one client): where they are on the host
 };
 constexpr int kPassRowsCap = 256;  // rows the batched call puts into one pass (<= kMaxPassRows)
 
@@ -688,8 +719,9 @@ static int run_pass(pipesd_model* m, pipesd_kv* kv, const PassLayout& pl, bool w
   const int rows = pl.rows;
   const bool bf = c.dtype == PIPESD_BF16;
   const bool single = pl.n_clients == 1;
-  if (pl.n_clients < 1 || pl.n_clients > kMaxPassClients || rows < 1 || rows > (bf ? kMaxPassRows : f32_pass_rows(c)) ||
-      (!bf && !single))
+  const bool prompt = bf && single && rows > kMaxRows;
+  if (pl.n_clients < 1 || pl.n_clients > kMaxPassClients || rows < 1 || (!bf && !single) ||
+      rows > (!bf ? f32_pass_rows(c) : prompt && !want_logits ? kMaxPromptRows : kMaxPassRows))
     return PIPESD_EINVAL;
   const int32_t seq = pl.client[0].seq;
   const int start_pos = pl.client[0].start_pos;
@@ -697,46 +729,66 @@ static int run_pass(pipesd_model* m, pipesd_kv* kv, const PassLayout& pl, bool w
   KvView view = view_of(kv, single ? seq : 0);
   const int chunk = attn_chunk_tokens(c.dtype, c.head_dim);
   const int nsplit = attn_nsplit(start_pos + rows, chunk);  // (one client)
+  // passes of few rows per client, and prompts: the streaming attention kernel with its own split of
+  // every context
+  const bool may_fuse = bf && single && m->fused_enabled && m->gate == nullptr;
   RowMap map{};
-  AttnBatch ab{};
-  ab.n = pl.n_clients;
-  size_t part_floats = 0;
-  for (int i = 0, r0 = 0; i < pl.n_clients; ++i) {
+  AttnBatch ab{}, ab_stream = prompt ? prompt_blocks(rows, start_pos) : AttnBatch{};
+  for (int i = 0, r0 = 0; !prompt && i < pl.n_clients; ++i) {
     const PassClient& pc = pl.client[i];
     const int32_t toff = single ? 0 : pc.seq * kv->n_blocks;
     for (int r = 0; r < pc.rows; ++r) {
       map.pos[r0 + r] = pc.start_pos + r;
       map.table_off[r0 + r] = toff;
     }
-    AttnClient& ac = ab.c[i];
+    AttnClient& ac = ab_stream.c[ab_stream.n++];
     ac.row_off = r0;
     ac.m = pc.rows;
     ac.start_pos = pc.start_pos;
     ac.table_off = toff;
-    ac.nsplit = attn_nsplit(pc.start_pos + pc.rows, chunk);
-    if (part_floats > (size_t)INT32_MAX) return PIPESD_ENOMEM;
-    ac.part_off = (int32_t)part_floats;
-    part_floats += (size_t)c.n_q_heads * pc.rows * ac.nsplit * (c.head_dim + 4);
     r0 += pc.rows;
+  }
+  size_t part_floats = 0, stream_floats = 0;
+  const int stream_tiles =
+      bf && !may_fuse ? attn_stream_plan(c.n_q_heads, c.n_kv_heads, c.head_dim, ab_stream, prompt, &stream_floats) : 0;
+  if (stream_tiles == 0) {  // the split kernels
+    ab.n = pl.n_clients;
+    for (int i = 0, r0 = 0; i < pl.n_clients; ++i) {
+      const PassClient& pc = pl.client[i];
+      AttnClient& ac = ab.c[i];
+      ac.row_off = r0;
+      ac.m = pc.rows;
+      ac.start_pos = pc.start_pos;
+      ac.table_off = single ? 0 : pc.seq * kv->n_blocks;
+      ac.nsplit = attn_nsplit(pc.start_pos + pc.rows, chunk);
+      if (part_floats > (size_t)INT32_MAX) return PIPESD_ENOMEM;
+      ac.part_off = (int32_t)part_floats;
+      part_floats += (size_t)c.n_q_heads * pc.rows * ac.nsplit * (c.head_dim + 4);
+      r0 += pc.rows;
+    }
   }
   // per-layer partial buffers only where the all-layers kernel may run (one client); otherwise one, reused
   const bool part_per_layer = bf && single && rows <= 16;
-  // passes of few rows per client: the streaming attention kernel with its own split of every context
-  AttnBatch ab_stream = ab;
-  size_t stream_floats = 0;
-  const bool may_fuse = bf && single && m->fused_enabled && m->gate == nullptr;
-  const int stream_tiles = bf && !may_fuse ? attn_stream_plan(c.n_q_heads, c.n_kv_heads, c.head_dim, ab_stream, &stream_floats) : 0;
-  int rc = ensure_attn_scratch(m, std::max(part_floats * (part_per_layer ? c.n_layers : 1), stream_tiles ? stream_floats : 0));
+  int rc = ensure_attn_scratch(m, stream_tiles ? stream_floats : part_floats * (part_per_layer ? c.n_layers : 1));
   if (rc) return rc;
   ActArena& ar = rows <= 2 * 16 ? m->arena : m->arena_big;
-  const int act_tiles = rows <= 2 * 16 ? 2 : rows <= 8 * 16 ? 8 : kMaxPassRows / 16;
+  const int act_tiles = rows <= 2 * 16 ? 2 : (rows + 127) / 128 * 8;
   m->pass_act_tiles = act_tiles;
   ar.part = m->attn_part;
   ar.part_stride = part_per_layer ? part_floats : 0;
   const RowMap* rows_dev = single ? nullptr : m->rowmap_dev;
-  HIP_TRY(launch_setup_rows(c.dtype, m->tok_emb, pl.tok, map, rows, d, c.head_dim, m->theta, bf ? ar.ra(0) : m->xres,
-                            m->rope_cs, bf ? m->attn_norm[0] : nullptr, bf ? ar.xa(0) : nullptr, act_tiles,
-                            bf ? ar.sa(0) : nullptr, ar.ssq_stride, single ? nullptr : m->rowmap_dev, st));
+  for (int r0 = 0; r0 < rows; r0 += kMaxPassRows) {  // (a launch carries the tokens and positions of up to 256 rows)
+    const int nr = std::min(kMaxPassRows, rows - r0);
+    PassTokens part;
+    if (pl.prompt_tok)
+      for (int r = 0; r < nr; ++r) {
+        part.tok[r] = pl.prompt_tok[r0 + r];
+        map.pos[r] = start_pos + r0 + r;
+      }
+    HIP_TRY(launch_setup_rows(c.dtype, m->tok_emb, pl.prompt_tok ? part : pl.tok, map, r0, nr, d, c.head_dim, m->theta,
+                              bf ? ar.ra(0) : m->xres, m->rope_cs, bf ? m->attn_norm[0] : nullptr, bf ? ar.xa(0) : nullptr,
+                              act_tiles, bf ? ar.sa(0) : nullptr, ar.ssq_stride, single ? nullptr : m->rowmap_dev, st));
+  }
   int norm_parts = 1;  // the row setup leaves one sum of squares per row, residual epilogues one per n-tile
   bool fused = false;
   if (bf && single && m->fused_enabled && m->gate == nullptr) {
@@ -883,8 +935,20 @@ static int run_rows(pipesd_model* m, pipesd_kv* kv, int32_t seq, const int32_t* 
   pl.n_clients = 1;
   pl.rows = rows;
   pl.client[0] = PassClient{seq, rows, start_pos};
-  for (int r = 0; r < rows; ++r) pl.tok.tok[r] = row_tokens[r];
+  pl.prompt_tok = row_tokens;
   return run_pass(m, kv, pl, want_logits, st);
+}
+
+// Rows of the next pass of a prompt of which `left` rows remain from position start_pos on.
+static int prompt_pass_rows(const pipesd_model* m, size_t left, int start_pos) {
+  const pipesd_config& c = m->cfg;
+  if (c.dtype != PIPESD_BF16) return (int)std::min(left, (size_t)f32_pass_rows(c));
+  const int rows = (int)std::min(left, (size_t)kMaxPromptRows);
+  if (rows <= kPrefillRows) return rows;
+  if (m->wide_mode == 1 || m->fused_enabled) return kPrefillRows;
+  AttnBatch b = prompt_blocks(rows, start_pos);
+  size_t floats = 0;
+  return attn_stream_plan(c.n_q_heads, c.n_kv_heads, c.head_dim, b, true, &floats) ? rows : kPrefillRows;
 }
 
 // The fused layer kernel raises a sticky flag if one of its device-wide barriers timed out.
@@ -920,10 +984,9 @@ extern "C" int pipesd_prefill(pipesd_model* model, pipesd_kv* kv, int32_t seq, c
   const int32_t cached_before = start;
   int rc = ensure_blocks(kv, seq, start + (int32_t)rows.size(), st);
   if (rc) return rc;
-  const size_t block = model->cfg.dtype == PIPESD_BF16 ? kPrefillRows : f32_pass_rows(model->cfg);  // rows per pass
-  for (size_t i = 0; i < rows.size(); i += block) {
-    const int nr = (int)((rows.size() - i < block) ? rows.size() - i : block);
-    rc = run_rows(model, kv, seq, rows.data() + i, nr, start + (int)i, false, st);
+  for (size_t i = 0, nr = 0; i < rows.size(); i += nr) {
+    nr = (size_t)prompt_pass_rows(model, rows.size() - i, start + (int)i);
+    rc = run_rows(model, kv, seq, rows.data() + i, (int)nr, start + (int)i, false, st);
     if (rc) {
       release_beyond(kv, s, cached_before);
       return rc;

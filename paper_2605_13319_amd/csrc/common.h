@@ -10,6 +10,8 @@ namespace pipesd {
 
 constexpr int kMaxRows = PIPESD_MAX_ROWS;  // rows of one client per pass (k + 1)
 constexpr int kMaxPassRows = 256;          // rows of all clients that share a pass (bf16)
+constexpr int kMaxPromptRows = 2048;       // rows of one client's prompt that share a pass (bf16)
+constexpr int kPromptBlockRows = 128;      // rows of a prompt that attend as one client of the pass
 constexpr int kBlockTokens = 16;           // tokens per KV block
 constexpr int kWave = 64;
 
@@ -76,12 +78,12 @@ __device__ __forceinline__ int64_t v_index(const KvView& kv, int layer, int pos,
 
 // ActPack: activations handed from one kernel to the next GEMM, already in the B-operand layout of
 // the 16x16x32 bf16 MFMA and split into a bf16 hi + lo pair.  For a consumer with K columns the
-// buffer is uint4[K/32][nt row tiles][hi, lo][64 entries] (nt = 2 for passes of up to 32 rows, 8 for
-// the largest passes of several clients): entry (c, g) of k-step ks holds columns ks*32 + g*8 .. +7
+// buffer is uint4[K/32][nt row tiles][hi, lo][64 entries] (nt = 2 for passes of up to 32 rows, a multiple
+// of 8 for larger ones): entry (c, g) of k-step ks holds columns ks*32 + g*8 .. +7
 // of row (row tile)*16 + c and is what MFMA lane g*16 + c consumes.  Within a 1 KB fragment:
 //  * nt = 2: entry c*4 + g.  A row's 64 bytes are contiguous, so a pass with m < 16 rows (the usual
 //    single-client pass) touches only the first m*64 bytes of each fragment;
-//  * nt = 8: entry g*16 + c, the consumer's lane order: full tiles are read with lane l taking
+//  * nt >= 8: entry g*16 + c, the consumer's lane order: full tiles are read with lane l taking
 //    entry l (fully coalesced, and a straight copy into LDS for the wide GEMM), and the 16 lanes of
 //    an epilogue that hold the same columns of 16 rows store 256 contiguous bytes.
 __device__ __forceinline__ size_t act_index(int kstep, int mt, int hl, int c, int g, int nt) {
@@ -113,7 +115,8 @@ struct PassTokens {
 // models also the packed, gained copy and the per-row sum of squares for the first fused norm
 // `map` gives every row's position; it is also copied to `map_dev` (if not null) for the kernels
 // that need it per row
-hipError_t launch_setup_rows(int dtype, const void* tok_emb, const PassTokens& toks, const RowMap& map, int m,
+// (rows row0 .. row0 + m - 1 of the pass; row0 a multiple of 16)
+hipError_t launch_setup_rows(int dtype, const void* tok_emb, const PassTokens& toks, const RowMap& map, int row0, int m,
                              int d_model, int head_dim, const double* theta, float* xres, float* rope_cs,
                              const float* gain, void* xpk, int act_tiles, float* ssq_out, int ssq_stride,
                              RowMap* map_dev, hipStream_t st);
@@ -147,11 +150,11 @@ struct GemmCall {
   int layer, start_pos, n_q_heads;
   const float* rope_cs;
   const RowMap* rows;  // device; nullptr: one client, row r at position start_pos + r, table kv.table
-  // passes of more than 64 rows: workspace for the running sums of K-split workgroups
-  // (gemm_wide_workspace_bytes; may be null when that is 0)
+  // passes of more than 64 rows: workspace for running sums (gemm_wide_workspace_bytes)
   void* wide_ws = nullptr;
   size_t wide_ws_bytes = 0;
-  int wide_mode = 0;  // 0: kernel chosen by shape, 1: narrow kernel, 2: wide kernel
+  float* rstd = nullptr;  // passes of more than 64 rows: kMaxPromptRows floats of scratch (products with a fused norm)
+  int wide_mode = 0;  // 1: narrow kernel whatever the rows (up to kMaxPassRows), else the wide one beyond 64 rows
   // optional: events that take the kernel's own start and end (no marker packets around it)
   hipEvent_t ev_start = nullptr, ev_stop = nullptr;
   // optional device word: the launch does nothing if it holds 0 (a round of a chain whose buffer
@@ -160,9 +163,9 @@ struct GemmCall {
 };
 hipError_t launch_gemm_bf16(const GemmCall& c, hipStream_t st);
 int device_cu_count();
-// bytes of GemmCall::wide_ws a product with N weight rows and K columns needs on this device when
-// it runs on the wide kernel (0 when that needs no workspace)
-size_t gemm_wide_workspace_bytes(int N, int K);
+// the most bytes of GemmCall::wide_ws a product with N weight rows and K columns asks for in passes of
+// up to max_rows rows
+size_t gemm_wide_workspace_bytes(int N, int K, int max_rows);
 
 // re-tile [rows][K] bf16 row-major (up to 3 stacked sources) into 16-row x 32-column matrix-core
 // fragments; PACK_HALVES makes tile rows 8..15 the partners (second source half / second half of
@@ -265,14 +268,14 @@ int attn_nsplit(int total_tokens, int chunk);
 constexpr int kAttnF32Split = 256;  // tokens per workgroup of the fp32 cache's kernel (head_dim a multiple of 16)
 int attn_chunk_tokens(int dtype, int head_dim);  // tokens per workgroup of the attention kernel for this cache
 hipError_t launch_attn_f32(const AttnCall& c, int nsplit, hipStream_t st);  // fp32 cache, head_dim a multiple of 16
-// Passes of at most kMaxRows rows per client, and prompt blocks of up to 128 rows alone in their
-// pass (bf16 cache), take the streaming kernel.  Fills span,
+// Passes of at most kMaxRows rows per client, and prompts, whose blocks of up to kPromptBlockRows rows
+// are the clients of the batch (`prompt`), take the streaming kernel (bf16 cache).  Fills span,
 // nsplit, part_off and count_off of every client of `b` (row_off, m, start_pos, table_off given) and
 // returns the query tiles per workgroup, or 0 if the pass does not fit (then the split kernels run);
 // *part_floats = size of the partial buffer the launch needs.  A client's split depends on its own
 // context only, so its results do not depend on who shares the pass.
 constexpr int kAttnCounters = kMaxPassClients * 512;
-int attn_stream_plan(int n_q_heads, int n_kv_heads, int head_dim, AttnBatch& b, size_t* part_floats);
+int attn_stream_plan(int n_q_heads, int n_kv_heads, int head_dim, AttnBatch& b, bool prompt, size_t* part_floats);
 hipError_t launch_attention(const AttnCall& c, hipStream_t st);
 
 // ---- vocabulary-wide decision ----

@@ -1,7 +1,7 @@
 // Device code of the skinny bf16 GEMM, shared by the per-GEMM kernel and the fused layer kernel.
 //
 // y[m][N] = act[m][K] * W[N][K]^T with few rows m (a client's k + 1 <= 32, or the rows of several
-// clients, up to 128; the QKV / O / SwiGLU-FFN / LM-head products of the target forward, Sec. 2.2).  The pass is bound by streaming W once from HBM, so
+// clients; the QKV / O / SwiGLU-FFN / LM-head products of the target forward, Sec. 2.2).  The pass is bound by streaming W once from HBM, so
 // everything is arranged around that stream:
 //  * W is re-tiled once, at model creation, into the order the matrix cores consume it: tile
 //    (n-tile of 16 weight rows, k-step of 32 columns) is 1 KB, lane l holding row l%16, columns
@@ -14,8 +14,8 @@
 //    matrix cores idle otherwise.
 //  * A pass of more than 16 rows is spread over GROUPS of workgroups that walk the same tiles, one
 //    per 16 rows, placed on the same chiplet: the weights cross the memory interface once and the
-//    other readers are served by the chiplet's L2.  (Beyond 64 rows the larger products go to the
-//    kernel of kernels_gemm_wide.hip, which stages all rows' activations in LDS instead.)
+//    other readers are served by the chiplet's L2.  (Beyond 64 rows the products go to the kernel of
+//    kernels_gemm_wide.hip, which brings both operands through LDS instead.)
 //  * K is cut into W * P slices of KSTEPS*32 columns; a team of W waves takes slices p*W + w,
 //    p = 0..P-1, one phase after the other, for a group of tg n-tiles, each wave keeping its running
 //    16x16 sums in its own LDS slots; after the last phase the team adds them in a fixed order.
@@ -70,8 +70,6 @@ struct GemmArgs {
 // filled in by launch_gemm_bf16
 constexpr int kWideMinRowTiles = 5;
 hipError_t launch_gemm_wide(const GemmCall& c, GemmArgs a, hipStream_t st);
-bool gemm_wide_preferred(int N, int K, int row_tiles);
-bool gemm_wide_supported(int N, int K, int act_tiles);  // the wide kernel can run this product on ActPack buffers of that many row tiles
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 

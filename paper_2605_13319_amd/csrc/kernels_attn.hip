@@ -141,7 +141,6 @@ constexpr int kStreamWgTokens = kStreamWaves * 32;  // tokens per workgroup and 
 constexpr int kStreamMaxSteps = 64;            // steps of a split (a lane per step holds its block-table entries)
 constexpr int kStreamMinSpan = 256;            // a client's context is cut into at most kStreamMaxSplits
 constexpr int kStreamMaxSplits = 16;           // splits of 256 * 2^j tokens, j as small as that allows
-constexpr int kStreamMaxRows = 128;            // rows of a client (a prompt block brings up to 128; a NAV pass at most kMaxRows)
 
 constexpr size_t stream_lds_floats(int hd) { return (size_t)kStreamWaves * 16 * (hd + 4) + 2 * kStreamWaves * 16; }
 template <int HD>
@@ -568,7 +567,7 @@ hipError_t launch_attention(const AttnCall& c, hipStream_t st) {
     }
     if (c.stream_tiles) {  // few rows per client: the streaming kernel (the batch was planned by attn_stream_plan)
       const int T = c.stream_tiles;
-      if ((h != 128 && h != 64) || max_m > kStreamMaxRows || (T != 1 && T != 2) || c.counters == nullptr) return hipErrorInvalidValue;
+      if ((h != 128 && h != 64) || max_m > kPromptBlockRows || (T != 1 && T != 2) || c.counters == nullptr) return hipErrorInvalidValue;
       for (int i = 0; i < b.n; ++i)  // (a lane per step holds the step's block-table entries)
         if (b.c[i].span < kStreamWgTokens || b.c[i].span > kStreamMaxSteps * kStreamWgTokens) return hipErrorInvalidValue;
       const int nz = ((group * max_m + 15) / 16 + T - 1) / T;
@@ -642,7 +641,7 @@ int attn_chunk_tokens(int dtype, int head_dim) {
   if (dtype != PIPESD_F32) return kAttnWgTokens;
   return head_dim % 16 == 0 ? kAttnF32Split : kAttnChunkMax;
 }
-int attn_stream_plan(int n_q_heads, int n_kv_heads, int head_dim, AttnBatch& b, size_t* part_floats) {
+int attn_stream_plan(int n_q_heads, int n_kv_heads, int head_dim, AttnBatch& b, bool prompt, size_t* part_floats) {
   *part_floats = 0;
   if (b.n < 1 || b.n > kMaxPassClients || (head_dim != 128 && head_dim != 64)) return 0;
   const int group = n_q_heads / n_kv_heads;
@@ -650,15 +649,16 @@ int attn_stream_plan(int n_q_heads, int n_kv_heads, int head_dim, AttnBatch& b, 
   long tasks = 0;  // (kv head, split, query tile) over all clients
   for (int i = 0; i < b.n; ++i) {
     AttnClient& cl = b.c[i];
-    if (cl.m > kStreamMaxRows || (cl.m > kMaxRows && b.n != 1)) return 0;
+    if (cl.m > (prompt ? kPromptBlockRows : kMaxRows)) return 0;
     max_m = std::max(max_m, (int)cl.m);
     const int total = cl.start_pos + cl.m;
     cl.span = kStreamMinSpan;
     if (cl.m <= kMaxRows) {
       while ((total + cl.span - 1) / cl.span > kStreamMaxSplits) cl.span *= 2;
     } else {
-      // a prompt block (alone in its pass): the query tiles alone give many workgroups, so the context
-      // is cut only as far as it takes to have about two workgroups per compute unit
+      // a prompt block: the query tiles alone give many workgroups, so the context is cut only as far as
+      // it takes for the block by itself to have about two workgroups per compute unit (by itself: its
+      // results do not depend on how many blocks of the prompt share the pass)
       const long groups = (long)n_kv_heads * (((group * cl.m + 15) / 16 + 1) / 2);
       const long fit = ((long)total + kStreamMaxSteps * kStreamWgTokens - 1) / (kStreamMaxSteps * kStreamWgTokens);
       const long want = std::max(fit, std::min((long)kStreamMaxSplits, 2L * device_cu_count() / groups));

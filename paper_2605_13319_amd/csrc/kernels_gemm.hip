@@ -3,6 +3,7 @@
 // device_gemm.h.
 #include <hip/hip_ext.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "device_gemm.h"
@@ -74,10 +75,10 @@ static void shape_for(int N, int K, int slots_cu, GemmPlan& p) {
 hipError_t launch_gemm_bf16(const GemmCall& c, hipStream_t st) {
   const int n_cu = device_cu_count();
   if (n_cu <= 0) return hipErrorUnknown;
-  if (c.m < 1 || c.m > kMaxPassRows || c.K % 512 != 0 || c.act_tiles * 16 < c.m) return hipErrorInvalidValue;
+  if (c.m < 1 || c.m > kMaxPromptRows || c.K % 512 != 0 || c.act_tiles * 16 < c.m) return hipErrorInvalidValue;
   const int row_tiles = (c.m + 15) / 16;
   GemmPlan p;
-  shape_for(c.N, c.K, n_cu / row_tiles, p);
+  shape_for(c.N, c.K, std::max(1, n_cu / row_tiles), p);
   if (row_tiles > 1) p.grid = (p.grid + 7) / 8 * 8 * row_tiles;  // groups are b, b + 8, ..: whole rounds of the 8 chiplets
   GemmArgs a{};
   a.wp = (const u32x4*)c.wp;
@@ -111,9 +112,8 @@ hipError_t launch_gemm_bf16(const GemmCall& c, hipStream_t st) {
   a.act_tiles = c.act_tiles;
   a.gate = c.gate;
   if (c.gate != nullptr && row_tiles >= kWideMinRowTiles) return hipErrorInvalidValue;  // the wide kernel has no gate
-  if (row_tiles >= kWideMinRowTiles && gemm_wide_supported(c.N, c.K, c.act_tiles) &&
-      (c.wide_mode == 2 || (c.wide_mode == 0 && gemm_wide_preferred(c.N, c.K, row_tiles))))
-    return launch_gemm_wide(c, a, st);
+  if (row_tiles >= kWideMinRowTiles && c.wide_mode != 1) return launch_gemm_wide(c, a, st);
+  if (c.m > kMaxPassRows) return hipErrorInvalidValue;
   const size_t lds = gemm_lds_floats(p.tg, p.W, 1, 1) * sizeof(float);
   const bool timed = c.ev_start != nullptr && c.ev_stop != nullptr;
   auto launch = [&](auto kernel) {

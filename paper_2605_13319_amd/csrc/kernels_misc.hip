@@ -8,19 +8,19 @@ namespace pipesd {
 // evaluated in fp64 and rounded once (rotary positions; the target forward of Sec. 2.2).
 // ---------------------------------------------------------------------------------------------
 template <typename T>
-__global__ void setup_rows_kernel(const T* __restrict__ emb, PassTokens toks, RowMap map, int m, int d, int half,
+__global__ void setup_rows_kernel(const T* __restrict__ emb, PassTokens toks, RowMap map, int row0, int m, int d, int half,
                                   const double* __restrict__ theta, float* __restrict__ xres,
                                   float* __restrict__ rope_cs, const float* __restrict__ gain, uint4* xpk,
                                   int act_tiles, float* __restrict__ ssq_out, int ssq_stride,
                                   RowMap* __restrict__ map_dev) {
   __shared__ float red[4];
-  const int r = blockIdx.x;
-  if (r >= m) return;
+  const int b = blockIdx.x, r = row0 + b;  // (tokens and positions are those of the launch's own rows)
+  if (b >= m) return;
   if (map_dev != nullptr && r == 0 && threadIdx.x < kMaxPassRows) {
     map_dev->pos[threadIdx.x] = map.pos[threadIdx.x];
     map_dev->table_off[threadIdx.x] = map.table_off[threadIdx.x];
   }
-  const size_t base = (size_t)toks.tok[r] * d;
+  const size_t base = (size_t)toks.tok[b] * d;
   float sq = 0.f;
   for (int j = threadIdx.x; j < d / 8; j += blockDim.x) {
     float v[8], y[8];
@@ -45,21 +45,21 @@ __global__ void setup_rows_kernel(const T* __restrict__ emb, PassTokens toks, Ro
     if (threadIdx.x == 0) ssq_out[(size_t)r * ssq_stride] = (red[0] + red[1]) + (red[2] + red[3]);
   }
   for (int i = threadIdx.x; i < half; i += blockDim.x) {
-    const double ang = (double)map.pos[r] * theta[i];
+    const double ang = (double)map.pos[b] * theta[i];
     rope_cs[((size_t)r * half + i) * 2 + 0] = (float)cos(ang);
     rope_cs[((size_t)r * half + i) * 2 + 1] = (float)sin(ang);
   }
 }
 
-hipError_t launch_setup_rows(int dtype, const void* tok_emb, const PassTokens& toks, const RowMap& map, int m,
+hipError_t launch_setup_rows(int dtype, const void* tok_emb, const PassTokens& toks, const RowMap& map, int row0, int m,
                              int d_model, int head_dim, const double* theta, float* xres, float* rope_cs,
                              const float* gain, void* xpk, int act_tiles, float* ssq_out, int ssq_stride,
                              RowMap* map_dev, hipStream_t st) {
   if (dtype == PIPESD_F32)
-    setup_rows_kernel<float><<<m, 256, 0, st>>>((const float*)tok_emb, toks, map, m, d_model, head_dim / 2, theta, xres,
+    setup_rows_kernel<float><<<m, 256, 0, st>>>((const float*)tok_emb, toks, map, row0, m, d_model, head_dim / 2, theta, xres,
                                                 rope_cs, nullptr, nullptr, 0, nullptr, 0, map_dev);
   else
-    setup_rows_kernel<uint16_t><<<m, 256, 0, st>>>((const uint16_t*)tok_emb, toks, map, m, d_model, head_dim / 2, theta,
+    setup_rows_kernel<uint16_t><<<m, 256, 0, st>>>((const uint16_t*)tok_emb, toks, map, row0, m, d_model, head_dim / 2, theta,
                                                    xres, rope_cs, gain, (uint4*)xpk, act_tiles, ssq_out, ssq_stride,
                                                    map_dev);
   return hipGetLastError();
