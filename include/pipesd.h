@@ -258,11 +258,12 @@ int pipesd_kv_read(const pipesd_model *model, const pipesd_kv *kv, int32_t seq, 
 int pipesd_model_set_fused(pipesd_model *model, int32_t on);
 int pipesd_model_fused_launches(const pipesd_model *model, int64_t *n);
 
-/* GEMM kernel of bf16 passes of more than 64 rows (batched verification, prompt ingestion).  Two
+/* GEMM kernel of bf16 passes of more than 32 rows (batched verification, prompt ingestion).  Two
  * kernels compute them: the narrow one of the single-client pass, run by groups of workgroups that
  * share the weights through a chiplet's L2, and a wide one that brings tiles of both operands through
- * LDS.  mode 0 (default): the wide one, which was measured faster for every shape; 1: the narrow kernel
- * (prompts then run in passes of 128 rows); 2: as 0.  Both accumulate every output in the same order and give
+ * LDS.  mode 0 (default): per product, whichever a model of their times (fitted to
+ * measurements) says is faster; 1: always the narrow kernel (prompts then run in passes of 128 rows);
+ * 2: always the wide one.  Both accumulate every output in the same order and give
  * bit-identical results, so the mode changes speed only.  PIPESD_EINVAL for another mode. */
 int pipesd_model_set_wide_gemm(pipesd_model *model, int32_t mode);
 

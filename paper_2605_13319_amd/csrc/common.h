@@ -150,11 +150,11 @@ struct GemmCall {
   int layer, start_pos, n_q_heads;
   const float* rope_cs;
   const RowMap* rows;  // device; nullptr: one client, row r at position start_pos + r, table kv.table
-  // passes of more than 64 rows: workspace for running sums (gemm_wide_workspace_bytes)
+  // passes of more than 32 rows: workspace for running sums (gemm_wide_workspace_bytes)
   void* wide_ws = nullptr;
   size_t wide_ws_bytes = 0;
-  float* rstd = nullptr;  // passes of more than 64 rows: kMaxPromptRows floats of scratch (products with a fused norm)
-  int wide_mode = 0;  // 1: narrow kernel whatever the rows (up to kMaxPassRows), else the wide one beyond 64 rows
+  float* rstd = nullptr;  // such passes: kMaxPromptRows floats of scratch (products with a fused norm)
+  int wide_mode = 0;  // beyond 32 rows: 0 kernel by shape, 1 narrow (up to kMaxPassRows), 2 wide
   // optional: events that take the kernel's own start and end (no marker packets around it)
   hipEvent_t ev_start = nullptr, ev_stop = nullptr;
   // optional device word: the launch does nothing if it holds 0 (a round of a chain whose buffer

@@ -14,7 +14,7 @@
 //    matrix cores idle otherwise.
 //  * A pass of more than 16 rows is spread over GROUPS of workgroups that walk the same tiles, one
 //    per 16 rows, placed on the same chiplet: the weights cross the memory interface once and the
-//    other readers are served by the chiplet's L2.  (Beyond 64 rows the products go to the kernel of
+//    other readers are served by the chiplet's L2.  (Beyond 32 rows most products go to the kernel of
 //    kernels_gemm_wide.hip, which brings both operands through LDS instead.)
 //  * K is cut into W * P slices of KSTEPS*32 columns; a team of W waves takes slices p*W + w,
 //    p = 0..P-1, one phase after the other, for a group of tg n-tiles, each wave keeping its running
@@ -66,10 +66,11 @@ struct GemmArgs {
   const int32_t* gate;    // optional: the launch does nothing if this device word holds 0
 };
 
-// passes of at least this many row tiles take the wide kernel (kernels_gemm_wide.hip); `a` comes
-// filled in by launch_gemm_bf16
-constexpr int kWideMinRowTiles = 5;
+// passes of at least this many row tiles can take the wide kernel (kernels_gemm_wide.hip; below, the
+// packed activations have the layout of few rows); `a` comes filled in by launch_gemm_bf16
+constexpr int kWideMinRowTiles = 3;
 hipError_t launch_gemm_wide(const GemmCall& c, GemmArgs a, hipStream_t st);
+double gemm_wide_us(const GemmCall& c);  // about how long it takes
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 

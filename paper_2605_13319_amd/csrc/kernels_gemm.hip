@@ -72,6 +72,16 @@ static void shape_for(int N, int K, int slots_cu, GemmPlan& p) {
   p.grid = groups < slots ? groups : slots;
 }
 
+// About how long this kernel takes: a start and an end, the weights once from memory, and the other row
+// tiles' reads of them from the L2s; phases cost another 15 %.  Measured at the 8B shape (microseconds at 1 /
+// 2 / 4 / 8 row tiles): QKV 14 / 17.5 / 20.7 / 30.6, O 11.4 / 13.7 / 16.9 / 25, gate/up 39 / 49 / 71 / 107.
+// (Beyond 8 row tiles the wide kernel runs whatever this says: groups of 10 or 12 workgroups per stream
+// took up to three times as long as groups of 8 or 16.)
+static double gemm_narrow_us(const GemmPlan& p, int row_tiles) {
+  const double mb = (double)p.N * p.K * 2e-6;
+  return (6.5 + mb / 6.9 + 0.05 * mb * (row_tiles - 1)) * (p.P > 1 ? 1.15 : 1.0);
+}
+
 hipError_t launch_gemm_bf16(const GemmCall& c, hipStream_t st) {
   const int n_cu = device_cu_count();
   if (n_cu <= 0) return hipErrorUnknown;
@@ -112,7 +122,9 @@ hipError_t launch_gemm_bf16(const GemmCall& c, hipStream_t st) {
   a.act_tiles = c.act_tiles;
   a.gate = c.gate;
   if (c.gate != nullptr && row_tiles >= kWideMinRowTiles) return hipErrorInvalidValue;  // the wide kernel has no gate
-  if (row_tiles >= kWideMinRowTiles && c.wide_mode != 1) return launch_gemm_wide(c, a, st);
+  if (row_tiles >= kWideMinRowTiles && c.wide_mode != 1 &&
+      (c.wide_mode == 2 || row_tiles > 8 || gemm_wide_us(c) < gemm_narrow_us(p, row_tiles)))
+    return launch_gemm_wide(c, a, st);
   if (c.m > kMaxPassRows) return hipErrorInvalidValue;
   const size_t lds = gemm_lds_floats(p.tg, p.W, 1, 1) * sizeof(float);
   const bool timed = c.ev_start != nullptr && c.ev_stop != nullptr;

@@ -1,4 +1,4 @@
-// GEMM for passes of more than 64 rows (batched verification of many clients, prompt ingestion).
+// GEMM for passes of more than 32 rows (batched verification of several clients, prompt ingestion).
 //
 // At this many rows the activations of a K slice no longer fit a wave's registers, and spreading the
 // rows over workgroups that re-read the weights from the L2 (the narrow kernel's way) moves many
@@ -288,29 +288,24 @@ __global__ __launch_bounds__(kWideWaves * 64) void gemm_wide_kernel(GemmArgs a, 
   }
 }
 
-// rstd of every row of the pass, in the narrow kernel's order: lane sums of the partial sums j = lane,
-// lane + 64, .., then the xor butterfly 32, 16, .., 1.  Eight rows per wave, all of whose partial sums
-// are requested before any is added.
-constexpr int kRstdRows = 8;
+// rstd of every row of the pass, one wave per row, in the narrow kernel's order: lane sums of the partial
+// sums j = lane, lane + 64, .., then the xor butterfly 32, 16, .., 1.  (Latency only: with eight rows per
+// wave, whose butterflies wait for each other, it took 7 us instead of 4.6.)
 __global__ __launch_bounds__(256) void wide_rstd_kernel(GemmArgs a, float* rstd) {
-  const int lane = threadIdx.x & 63, row0 = ((int)blockIdx.x * 4 + (int)(threadIdx.x >> 6)) * kRstdRows;
-  float v[kSsqPerLane][kRstdRows];
+  const int lane = threadIdx.x & 63, row = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6);
+  if (row >= a.m) return;
+  float v[kSsqPerLane];
 #pragma unroll
-  for (int j4 = 0; j4 < kSsqPerLane; ++j4)
-#pragma unroll
-    for (int i = 0; i < kRstdRows; ++i) {
-      const int row = row0 + i, j = lane + 64 * j4;
-      v[j4][i] = (row < a.m && j < a.ssq_parts) ? a.ssq_in[(size_t)row * a.ssq_stride + j] : 0.f;
-    }
-#pragma unroll
-  for (int i = 0; i < kRstdRows; ++i) {
-    float t = v[0][i];
-#pragma unroll
-    for (int j4 = 1; j4 < kSsqPerLane; ++j4) t += v[j4][i];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
-    if (lane == 0 && row0 + i < a.m) rstd[row0 + i] = 1.0f / sqrtf(t / (float)a.K + a.eps);
+  for (int j4 = 0; j4 < kSsqPerLane; ++j4) {
+    const int j = lane + 64 * j4;
+    v[j4] = j < a.ssq_parts ? a.ssq_in[(size_t)row * a.ssq_stride + j] : 0.f;
   }
+  float t = v[0];
+#pragma unroll
+  for (int j4 = 1; j4 < kSsqPerLane; ++j4) t += v[j4];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+  if (lane == 0) rstd[row] = 1.0f / sqrtf(t / (float)a.K + a.eps);
 }
 
 // split mode, second half: add the W running sums of every 16 x 16 tile in the order w = 0..W-1 and
@@ -326,12 +321,20 @@ __global__ __launch_bounds__(256) void gemm_wide_finish_kernel(GemmArgs a, WideA
 #pragma unroll
   for (int ww = 0; ww < kWideMaxRoles; ++ww)
     if (ww < a.W) pv[ww] = x.ws[(((size_t)ww * a.ntiles + t) * x.row_tiles + rt) * 64 + lane];
+  // (the residual epilogue's operands travel with the sums; clamped, so that nothing waits at a branch)
+  f32x4 pre_res = zero, pre_gain = zero;
+  const bool resid = a.epi == EPI_RESID;
+  if (resid) {
+    const int col = t * 16 + (lane >> 4) * 4;
+    pre_res = *(const f32x4*)(a.res_in + (size_t)min(row, a.m - 1) * a.ldo + col);
+    pre_gain = *(const f32x4*)(a.gain_next + col);
+  }
   const float rstd = (x.rstd != nullptr && row < a.m) ? x.rstd[row] : 1.0f;
   f32x4 v = zero;
 #pragma unroll
   for (int ww = 0; ww < kWideMaxRoles; ++ww)
     if (ww < a.W) v += pv[ww];
-  epilogue_quad<false>(a, t, row, lane, v, rstd, false, zero, zero);
+  epilogue_quad<false>(a, t, row, lane, v, rstd, resid, pre_res, pre_gain);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -349,6 +352,7 @@ struct WidePlan {
   int ct, rt;  // n-tiles per workgroup: 16 (2 x 4 waves of rt x 4 tiles) or 8 (4 x 2 waves); row tiles per wave
   bool whole;
   int block_tiles, nrb;
+  double us;
 };
 constexpr size_t kWideSplitBytes = (size_t)128 << 20;  // the most that split products' running sums may take
 
@@ -363,26 +367,40 @@ static WidePlan wide_plan(int N, int K, int row_tiles, int n_cu, size_t ws_bytes
   wide_roles(K, W, P);
   const int ntiles = (N + 15) / 16;
   WidePlan best{};
-  double best_us = 0.0;
   for (const int ct : {16, 8})
-    for (int rt = ct == 16 ? 4 : 3; rt >= (ct == 16 ? 2 : 1); --rt)
+    for (int rt = ct == 16 ? 2 : 1; rt <= (ct == 16 ? 4 : 3); ++rt)  // (of equals the smallest that holds the block)
       for (const bool whole : {true, false}) {
         const int tiles = (ct == 16 ? 2 : 4) * rt;
-        WidePlan p{ct, rt, whole, 0, (row_tiles + tiles - 1) / tiles};
+        WidePlan p{ct, rt, whole, 0, (row_tiles + tiles - 1) / tiles, 0.0};
         p.block_tiles = (row_tiles + p.nrb - 1) / p.nrb;  // (spread evenly)
         p.nrb = (row_tiles + p.block_tiles - 1) / p.block_tiles;
         const size_t ws = (size_t)ntiles * row_tiles * 1024 * (whole ? (P > 1 ? 1 : 0) : W);
         if (ws > (whole ? ws_bytes : std::min(ws_bytes, kWideSplitBytes))) continue;
         const int wgs = (ntiles + ct - 1) / ct * p.nrb * (whole ? 1 : W), steps = 16 * P * (whole ? W : 1);
-        double us = 3.0 + (double)((wgs + n_cu - 1) / n_cu) * (6.0 + steps * (0.08 + 0.0056 * ct * p.block_tiles));
+        // (the smallest tiles leave room for a second workgroup on a compute unit, which pays where the
+        // weights are few enough to come from the caches: QKV of the 8B shape at 333 rows 47 against 54 us,
+        // but gate/up at 128 rows 83 against 73)
+        const bool two = ct == 8 && rt == 1 && (size_t)N * K * 2 <= ((size_t)64 << 20) && wgs > n_cu;
+        const int slots = two ? 2 * n_cu : n_cu;
+        double us = 3.0 + (double)((wgs + slots - 1) / slots) *
+                              (6.0 + steps * (0.08 + 0.0056 * ct * p.block_tiles) * (two ? 1.45 : 1.0));
         us = std::max(us, 3.0 + (double)ntiles * 16 * K * 2 / 5e6);
         if (!whole) us += 4.0 + (double)ws / 2.1e6;
-        if (best.ct == 0 || us < best_us) {
-          best = p;
-          best_us = us;
-        }
+        p.us = us;
+        if (best.ct == 0 || us < best.us) best = p;
       }
   return best;
+}
+
+// The kernel that computes rstd in front of a product with a norm takes 5 more.  Small products (QKV, O)
+// stay on the narrow kernel longer than large ones.  8 layers and the LM head, microseconds per pass, all
+// narrow / all wide / by these two models: 8B 40 rows 1959 / 1409 / 1344, 80 rows 2585 / 1756 / 1727, 128 rows
+// 2912 / 2121 / 2095; 1B 48 rows 710 / 803 / 704, 80 rows 824 / 822 / 780; 13B 48 rows 2174 / 2022 / 1964.
+double gemm_wide_us(const GemmCall& c) {
+  const int n_cu = device_cu_count();
+  if (n_cu <= 0) return 0.0;
+  const WidePlan p = wide_plan(c.N, c.K, (c.m + 15) / 16, n_cu, c.wide_ws ? c.wide_ws_bytes : 0);
+  return p.us + (c.ssq_in != nullptr ? 5.0 : 0.0);
 }
 
 // largest workspace any product with N weight rows and K columns asks for at up to max_rows rows
@@ -424,7 +442,7 @@ hipError_t launch_gemm_wide(const GemmCall& c, GemmArgs a, hipStream_t st) {
   const hipEvent_t e1 = timed ? c.ev_stop : nullptr;
   if (a.ssq_in != nullptr) {
     if (c.rstd == nullptr) return hipErrorInvalidValue;
-    const dim3 rgrid((c.m + 4 * kRstdRows - 1) / (4 * kRstdRows));
+    const dim3 rgrid((c.m + 3) / 4);
     if (timed)
       hipExtLaunchKernelGGL(wide_rstd_kernel, rgrid, dim3(256), 0, st, e0, nullptr, 0, a, c.rstd);
     else

@@ -224,7 +224,7 @@ class Model:
             pass
 
     def set_wide_gemm(self, mode: int) -> None:
-        """GEMM kernel of passes of more than 64 rows: 0 or 2 wide, 1 narrow (same results)."""
+        """GEMM kernel of passes of more than 32 rows: 0 by shape, 1 narrow, 2 wide (same results)."""
         _check(_lib.pipesd_model_set_wide_gemm(self.handle, int(mode)), "pipesd_model_set_wide_gemm")
 
     def set_fused(self, on: bool) -> None:

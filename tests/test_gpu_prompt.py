@@ -12,22 +12,22 @@ SHAPES = [I.ModelShape("prompt-512", 2, 512, 8, 2, 64, 1536, 300), I.ModelShape(
           I.ModelShape("prompt-2048", 2, 2048, 16, 4, 128, 7168, 300), I.ModelShape("prompt-4096", 2, 4096, 32, 8, 128, 14336, 300)]
 
 
-# rows of the first pass (tokens - 1): one past the narrow kernel's range, a full and a ragged last row
+# rows of the first pass (tokens - 1): three and four row tiles (by product narrow or wide), five, a full and a ragged last row
 # block, one row in the last 16, and (2049 and more tokens) a second pass of one row and of a few hundred
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: s.name)
 def test_long_passes_equal_short_ones(shape):
     from paper_2605_13319_amd import nav
     model = nav.Model(shape, I.make_weights(shape, 61))
-    for tokens in (66, 97, 129, 130, 146, 258, 334, 690, 2049, 2050, 2381):
+    for tokens in (34, 50, 65, 66, 97, 129, 130, 146, 258, 334, 690, 2049, 2050, 2381):
         toks = I.make_tokens(tokens, shape.vocab, 62 + tokens)
         pools = []
-        for mode in (1, 0):
+        for mode in (1, 0, 2):
             model.set_wide_gemm(mode)
             kv = nav.KVCache(model, max_seqs=1, n_blocks=(tokens + 15) // 16 + 1)
             kv.prefill(0, toks)
             pools.append(kv.pool.clone())
         print(shape.name, tokens, flush=True)
-        assert bool((pools[0] == pools[1]).all()), f"{tokens} tokens: the caches differ"
+        assert bool((pools[0] == pools[1]).all()) and bool((pools[0] == pools[2]).all()), f"{tokens} tokens: the caches differ"
 
 
 def test_a_turn_behind_a_cached_context_equals_one_prompt():
