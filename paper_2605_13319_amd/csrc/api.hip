@@ -49,8 +49,8 @@ struct pipesd_model {
   ActArena arena{};  // bf16 path: per-layer activation buffers (passes of up to 32 rows)
   int pass_act_tiles = 2;  // row tiles of the buffers of the pass being enqueued
   ActArena arena_big{};  // bf16 path: one buffer of each kind for passes of more than 32 rows, up to kMaxPromptRows
-  int wide_mode = 0;        // GEMM kernel of passes of more than 64 rows: 1 narrow, else wide
-  void* wide_ws = nullptr;  // bf16 path: running sums in passes of more than 64 rows
+  int wide_mode = 0;        // GEMM kernel of passes of more than 32 rows: 0 by shape, 1 narrow, 2 wide
+  void* wide_ws = nullptr;  // bf16 path: running sums in passes of more than 32 rows
   float* wide_rstd = nullptr;  // bf16 path: rstd of every row of such a pass
   size_t wide_ws_bytes = 0;
   RowMap* rowmap_dev = nullptr;  // bf16 path: per-row placement of a pass that holds several clients
@@ -850,6 +850,7 @@ static int run_pass(pipesd_model* m, pipesd_kv* kv, const PassLayout& pl, bool w
         HIP_TRY(launch_gemm_f32(g, st));
         if (!rope) HIP_TRY(launch_rope_append_f32(m->qkv, rows, start_pos, l, c.n_q_heads, view, m->rope_cs, m->qbuf, st));
       }
+      if (l + 1 == c.n_layers && !want_logits) break;  // (as below)
       {
         ProfScope ps(m, PIPESD_PROF_ATTN, st);
         HIP_TRY(launch_attention(at, st));
@@ -879,6 +880,7 @@ static int run_pass(pipesd_model* m, pipesd_kv* kv, const PassLayout& pl, bool w
         g.n_q_heads = c.n_q_heads;
         HIP_TRY(launch_gemm_bf16(g, st));
       }
+      if (l + 1 == c.n_layers && !want_logits) break;  // nothing reads what the last layer of a prompt leaves but its keys and values
       {
         ProfScope ps(m, PIPESD_PROF_ATTN, st);
         HIP_TRY(launch_attention(at, st));
