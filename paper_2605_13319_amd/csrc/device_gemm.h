@@ -178,6 +178,29 @@ __device__ __forceinline__ void chunk_mfma(u32x4 (&af)[KSTEPS], const u32x4 (&bh
   }
 }
 
+// The same for a wave that takes one tile through several K slices (phases): fragment ks of the next
+// slice's activations, both halves, is requested along with that of its weights.
+template <int KSTEPS, bool NT, bool HAS_NEXT, int KS = 0>
+__device__ __forceinline__ void chunk_mfma_phase(u32x4 (&af)[KSTEPS], u32x4 (&bhi)[KSTEPS], u32x4 (&blo)[KSTEPS], f32x4& acc,
+                                                 const u32x4* nxt, const u32x4* nact, int act_step, int act_half) {
+  if constexpr (KS < KSTEPS) {
+    constexpr int YOUNGER = 3 * (HAS_NEXT ? KSTEPS - 1 : KSTEPS - 1 - KS);
+    static_assert(YOUNGER < 64, "the wait counter has six bits");
+    asm volatile("s_waitcnt vmcnt(%3)" : "+v"(af[KS]), "+v"(bhi[KS]), "+v"(blo[KS]) : "n"(YOUNGER));
+    const bf16x8 av = as_bf16x8(af[KS]);
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, as_bf16x8(bhi[KS]), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, as_bf16x8(blo[KS]), acc, 0, 0, 0);
+    if constexpr (HAS_NEXT) {
+      af[KS] = stream_load<NT>(nxt + KS * 64);
+      bhi[KS] = act_load(nact + KS * act_step);
+      blo[KS] = act_load(nact + KS * act_step + act_half);
+    }
+    chunk_mfma_phase<KSTEPS, NT, HAS_NEXT, KS + 1>(af, bhi, blo, acc, nxt, nact, act_step, act_half);
+  } else {
+    asm volatile("s_nop 15\n\ts_nop 7" : "+v"(acc));  // (as in chunk_mfma)
+  }
+}
+
 __device__ __forceinline__ f32x4 shfl4(f32x4 v, int src) {
   return f32x4{__shfl(v[0], src, 64), __shfl(v[1], src, 64), __shfl(v[2], src, 64), __shfl(v[3], src, 64)};
 }
@@ -345,7 +368,9 @@ __host__ __device__ inline size_t gemm_lds_floats(int tg, int W, int MT, int tea
 // in-flight first chunk (gemm_prefetch), the epilogue and the phase count are read from `a`.
 // Otherwise (one kernel per kind of product) the body requests the first chunk itself, P1 says at
 // compile time that a.P == 1, and the sums of squares are read iff the epilogue is not the residual one.
-template <int MT, int KSTEPS, bool CO, bool NT = true, int EPI = kEpiAny, bool P1 = false>
+// ONE (MT = 1, several phases): no team has more than one tile, and the activation fragments of the
+// next phase are requested while the current one is multiplied.
+template <int MT, int KSTEPS, bool CO, bool NT = true, int EPI = kEpiAny, bool P1 = false, bool ONE = false>
 __device__ __forceinline__ void gemm_body(const GemmArgs& a, const TeamPos& tp, int teams_per_wg, int nwaves_wg,
                                           float* lds, u32x4 (&af)[KSTEPS]) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -366,6 +391,12 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, const TeamPos& tp, 
       for (int mt = 0; mt < MT; ++mt)
         if (tp.row_base + mt * 16 + bc < a.m)
           b[mt][ks] = act_load(a.actp + act_index(slice * KSTEPS + ks, mt + (tp.row_base >> 4), hl, bc, bg, a.act_tiles));
+  };
+  // (ONE: no branch around the loads; the lanes whose row is not part of the pass read its last row)
+  const int act_step = (int)(act_index(1, 0, 0, 0, 0, a.act_tiles) - act_index(0, 0, 0, 0, 0, a.act_tiles));
+  const int act_half = (int)(act_index(0, 0, 1, 0, 0, a.act_tiles) - act_index(0, 0, 0, 0, 0, a.act_tiles));
+  auto act_ptr = [&](int slice) {
+    return a.actp + act_index(slice * KSTEPS, tp.row_base >> 4, 0, min(bc, a.m - 1 - tp.row_base), bg, a.act_tiles);
   };
   auto await_act = [&]() {
 #pragma unroll
@@ -486,7 +517,16 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, const TeamPos& tp, 
     // which only a padded grid has, requests the last group's chunk and never uses it.
     constexpr bool NORM = EPI != EPI_RESID;
     const int g0 = min(tp.team, ngroups - 1);
-    {
+    if constexpr (ONE) {
+      const u32x4* first = gemm_chunk_ptr<KSTEPS>(a, lane, tp.wt, g0, 0);
+      const u32x4* act = act_ptr(tp.wt);
+#pragma unroll
+      for (int ks = 0; ks < KSTEPS; ++ks) {
+        af[ks] = stream_load<NT>(first + ks * 64);
+        bhi[0][ks] = act_load(act + ks * act_step);
+        blo[0][ks] = act_load(act + ks * act_step + act_half);
+      }
+    } else {
       const u32x4* first = gemm_chunk_ptr<KSTEPS>(a, lane, tp.wt, g0 * a.tg, 0);
 #pragma unroll
       for (int ks = 0; ks < KSTEPS; ++ks) af[ks] = stream_load<NT>(first + ks * 64);
@@ -524,7 +564,22 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, const TeamPos& tp, 
     const int nt_g = on ? min(a.tg, a.ntiles - t0) : 0;
     const int e_first = tp.wt * 64 + lane;
     const bool pre = it == 0 && have_pre;
-    if (on) {
+    if constexpr (ONE) {
+      // (a workgroup beyond the last tile multiplies the last tile again and stores nothing)
+      const int tile = min(tp.team, ngroups - 1);
+      f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
+      auto phase = [&](int p, auto has_next) {
+        constexpr bool NEXT = decltype(has_next)::value;
+        const int pn = NEXT ? p + 1 : p;
+        f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+        chunk_mfma_phase<KSTEPS, NT, NEXT>(af, bhi[0], blo[0], acc, gemm_chunk_ptr<KSTEPS>(a, lane, tp.wt, tile, pn),
+                                           act_ptr(pn * a.W + tp.wt), act_step, act_half);
+        sum += acc;
+      };
+      for (int p = 0; p + 1 < a.P; ++p) phase(p, std::true_type{});
+      phase(a.P - 1, std::false_type{});
+      red[(size_t)tp.wt * 64 + lane] = sum;
+    } else if (on) {
       const int nphase = (EPI != kEpiAny && P1) ? 1 : a.P;
       for (int p = 0; p < nphase; ++p) {
         if ((EPI == kEpiAny || !P1) && a.P > 1) {

@@ -12,8 +12,9 @@ namespace pipesd {
 
 // EPI (the projection's epilogue) is a template parameter: every projection of a layer is a kernel
 // of its own name, with only its own epilogue's code and registers.
-// and P1 says that every wave has a single K slice (no phases).
-template <int KSTEPS, bool NT, int EPI, bool P1>
+// P1 says that every wave has a single K slice (no phases); ONE that there are phases and that no team
+// has more than one tile.
+template <int KSTEPS, bool NT, int EPI, bool P1, bool ONE = false>
 __global__ __launch_bounds__(512) void gemm_bf16_kernel(GemmArgs a) {
   extern __shared__ float lds[];
   if (a.gate != nullptr && *a.gate == 0) return;  // (uniform: a round of a chain that does not run)
@@ -26,7 +27,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_kernel(GemmArgs a) {
   TeamPos tp{(b / (8 * rt)) * 8 + (b & 7), (int)gridDim.x / rt, w, 0, true};
   tp.row_base = ((b >> 3) % rt) * 16;
   u32x4 af[KSTEPS];
-  gemm_body<1, KSTEPS, false, NT, EPI, P1>(a, tp, 1, a.W, lds, af);
+  gemm_body<1, KSTEPS, false, NT, EPI, P1, ONE>(a, tp, 1, a.W, lds, af);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -143,9 +144,17 @@ hipError_t launch_gemm_bf16(const GemmCall& c, hipStream_t st) {
       default: launch(gemm_bf16_kernel<16, NT, EPI_QKV, P1>); break;
     }
   };
+  // Down projections: several K slices per wave and a tile for every team.  Awaiting a slice's
+  // activations by themselves then drains the weight stream once per tile, so the next slice's travel
+  // with its weights instead.  9 rows: 27.1 -> 25.2 us at the 8B shape (117 MB, 4 slices), 14.5 -> 14.6
+  // at the 1B shape (34 MB, 2 slices), 5 rows there 13.1 -> 12.9.  With two tiles per team (17 rows and
+  // more at the 8B shape) the same took 43 us against 36: 21 registers spill.
+  const bool single_tile = c.epi == EPI_RESID && p.tg == 1 && p.ntiles <= p.grid / row_tiles;
   auto launch_nt = [&](auto nt) {
     if (p.P == 1)
       launch_p(nt, std::true_type{});
+    else if (single_tile)
+      launch(gemm_bf16_kernel<16, decltype(nt)::value, EPI_RESID, false, true>);
     else
       launch_p(nt, std::false_type{});
   };
