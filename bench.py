@@ -287,7 +287,7 @@ def prefill(args, np, torch, I, nav):
         "steps": args.steps, "warmup": args.warmup, "ms_per_step": total / len(times) * 1e3, "higher_is_better": True,
         "scaling": "weak", "vs_baseline": None, "dtype": "bf16" if shape.dtype != I.DTYPE_F32 else "f32", "data": "synthetic",
         "config": {"workload": f"{shape.name}: ingestion of a {n}-token prompt into an empty sequence, passes of up to "
-                               f"128 rows, paged KV (16-token blocks)"},
+                               f"{2048 if shape.dtype != I.DTYPE_F32 else 128} rows, paged KV (16-token blocks)"},
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
                      "frac": achieved / MFMA_BF16_PEAK_TFLOPS, "traffic": None,
                      "kernel": "all kernels of the call; algorithmic flop (each product counted once, not per bf16 half)"},

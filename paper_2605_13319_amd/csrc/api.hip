@@ -698,7 +698,7 @@ static GemmF32Call gemm_f32_call(pipesd_model* m, const float* act, int lda, con
 // the other, at most 256 in all, or a piece of one client's prompt.
 // Rows per pass of prompt ingestion (bf16): the weights are read once per 2048 rows and every product
 // has enough rows to fill the device without a split of K; a prompt of 2048 tokens at the 8B shape takes
-// 54.7 ms, 103.9 in passes of 128 rows.  Passes of 128 rows remain for what larger ones do not do:
+// 53.4 ms, 103.9 in passes of 128 rows.  Passes of 128 rows remain for what larger ones do not do:
 // contexts the streaming attention declines, the narrow GEMM kernel, the all-layers kernel's model.
 constexpr int kPrefillRows = 128;
 struct PassClient {

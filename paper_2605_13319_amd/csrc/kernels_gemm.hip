@@ -147,7 +147,7 @@ hipError_t launch_gemm_bf16(const GemmCall& c, hipStream_t st) {
   // Down projections: several K slices per wave and a tile for every team.  Awaiting a slice's
   // activations by themselves then drains the weight stream once per tile, so the next slice's travel
   // with its weights instead.  9 rows: 27.1 -> 25.2 us at the 8B shape (117 MB, 4 slices), 14.5 -> 14.6
-  // at the 1B shape (34 MB, 2 slices), 5 rows there 13.1 -> 12.9.  With two tiles per team (17 rows and
+  // at the 1B shape (34 MB, 2 slices).  With two tiles per team (17 rows and
   // more at the 8B shape) the same took 43 us against 36: 21 registers spill.
   const bool single_tile = c.epi == EPI_RESID && p.tg == 1 && p.ntiles <= p.grid / row_tiles;
   auto launch_nt = [&](auto nt) {
