@@ -122,8 +122,8 @@ __device__ __forceinline__ unsigned long long wave_scan_u64(unsigned long long v
 }
 
 // `stats` == nullptr: `p` holds probabilities.  Otherwise `p` holds logits and `stats` the (max,
-// sum of exp) chunk partials of softmax_stats_kernel: the probabilities are formed on the fly by the
-// very expressions softmax_write_kernel uses, so the decision is the one the two-step path takes.
+// sum of exp) chunk partials of softmax_stats_kernel: the probabilities expf(z - M) / S are formed here,
+// where they are used, and nowhere else.
 // (drafts[0..k-1] and un[0..k] may point into kernel arguments)
 //
 // Bound by a chain of dependent latencies, not by the 1 MB it reads at a vocabulary of 128256: the
@@ -138,7 +138,7 @@ __device__ __forceinline__ void spec_accept_body(const float* __restrict__ p, co
                                                  int32_t* __restrict__ result, int32_t* __restrict__ result_copy) {
   constexpr int kWaves = kVThreads / 64;
   __shared__ unsigned long long red[kWaves];
-  __shared__ int s_last;
+  __shared__ int s_last, s_next;
   __shared__ float s_M[kMaxRows], s_S[kMaxRows];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const bool from_logits = stats != nullptr;
@@ -257,10 +257,17 @@ __device__ __forceinline__ void spec_accept_body(const float* __restrict__ p, co
   }
   const unsigned long long ui = (unsigned long long)(un[k] * 16777216.0f);  // floor(u * 2^24)
   const unsigned long long T = (__umul64hi(W, ui) << 40) | ((W * ui) >> 24);
-  // chunk whose running total first exceeds T (T < W: there is one)
-  const int b = min(__ffsll((long long)__ballot(upto > T)) - 1, kScanBlocks - 1);
+  // chunk whose running total first exceeds T (T < W: there is one, lane 63's total being W)
+  const int above = __ffsll((long long)__ballot(upto > T)), b = above > 0 ? above - 1 : kScanBlocks - 1;
   unsigned long long run = shfl_u64(upto, b) - shfl_u64(mine, b);
   const int clo = b * per, chi = min(V, clo + per);
+  // The smallest token of the chunk whose running sum exceeds T (the last one if none does): every
+  // thread looks through its own tokens, a wave's first finder takes part in the minimum.  Thread 0
+  // reports it, so that a result is written and the counter cleared whatever the sums are.  (The sums
+  // between the tokens count, not only those between the threads: weights of distributions with masses
+  // beyond 2^24 wrap.)
+  constexpr int kNone = 0x7fffffff;
+  if (tid == 0) s_next = kNone;
   for (int base = clo; base < chi; base += kVThreads * kHold) {
     // thread t has the kHold tokens behind base + t * kHold
     const int i0 = base + tid * kHold;
@@ -269,26 +276,27 @@ __device__ __forceinline__ void spec_accept_body(const float* __restrict__ p, co
 #pragma unroll
     for (int j = 0; j < kHold; ++j) own += wt[j];
     const unsigned long long inc = wave_scan_u64(own);
-    __syncthreads();  // (red has been read)
+    __syncthreads();  // (red has been read, s_next is set)
     if (lane == 63) red[w] = inc;
     __syncthreads();
-    unsigned long long before = run + inc - own;
+    unsigned long long at = run + inc - own;  // sum in front of the thread's first token
 #pragma unroll
     for (int ww = 0; ww < kWaves; ++ww) {
-      if (ww < w) before += red[ww];
+      if (ww < w) at += red[ww];
       run += red[ww];
     }
-    if (before <= T && before + own > T) {  // one thread of the workgroup
-      int j = 0;
+    int found = kNone;
 #pragma unroll
-      for (int jj = 0; jj < kHold - 1; ++jj) {
-        before += wt[jj];
-        if (before <= T) j = jj + 1;
-      }
-      decide(i0 + j);
+    for (int j = 0; j < kHold; ++j) {
+      at += wt[j];
+      if (at > T) found = min(found, i0 + j);
     }
-    if (run > T) return;  // (found: the same for all threads)
+    const int finder = __ffsll((long long)__ballot(found != kNone));
+    if (finder == lane + 1) atomicMin(&s_next, found);
+    __syncthreads();
+    if (s_next != kNone) break;
   }
+  if (tid == 0) decide(min(s_next, chi - 1));
 }
 
 __global__ __launch_bounds__(kVThreads) void spec_accept_kernel(const float* __restrict__ p, const float* __restrict__ q,

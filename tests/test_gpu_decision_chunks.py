@@ -22,3 +22,39 @@ def test_decision_at_the_ends_of_its_chunks(vocab, k):
         for first in (0.0, 1 - 2.0 ** -24):
             u = np.array([0.0] * (k - 1) + [first, last], dtype=np.float32)
             assert nav.spec_accept(pd, qd, d, u) == oracle_accept(p, q, d, u)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("first", [0, 8, 13])
+def test_draw_takes_the_smallest_token_above_the_threshold(first):
+    """The drawn token is the smallest whose running 64-bit sum exceeds the threshold, also where the
+    sum comes back below it further on (four weights of 2^62 add up to 0): all inside the first of the
+    64 chunks (16 tokens), in one thread's eight tokens, in the second thread's, and across two threads
+    and the chunk's end.  Twice in a row: the first call leaves its scratch as it found it."""
+    import torch
+    from paper_2605_13319_amd import nav
+    vocab, k = 1024, 1
+    p = np.zeros((k + 1, vocab), dtype=np.float32)
+    p[0, 5] = 0.5
+    p[1, 0] = 0.25 if first else 0.0
+    p[1, first:min(first + 4, 16)] = 2.0 ** 22
+    if first < 13:
+        p[1, first + 4] = 1.0
+    else:
+        p[1, 900] = 2.0 ** 22 + 0.5
+    q = np.full((k, vocab), 1.0 / vocab, dtype=np.float32)
+    u = np.array([0.0, 0.5], dtype=np.float32)
+    w = [int(float(x) * 2.0 ** 40) for x in p[1]]
+    T = ((sum(w) % 2 ** 64) * 2 ** 23) >> 24
+    run, want = 0, None
+    for j, x in enumerate(w):
+        run = (run + x) % 2 ** 64
+        if want is None and run > T:
+            want = j
+    assert want == first
+    pd, qd = torch.from_numpy(p).cuda(), torch.from_numpy(q).cuda()
+    result = torch.zeros(2, dtype=torch.int32, device="cuda")
+    for _ in range(2):
+        assert nav.spec_accept(pd, qd, [5], u) == (1, want)
+        nav.spec_accept_static(pd, qd, [5], u, result)
+        assert result.tolist() == [1, want]
