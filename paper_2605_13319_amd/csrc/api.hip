@@ -318,40 +318,14 @@ extern "C" size_t pipesd_kv_block_bytes(const pipesd_model* model, int32_t block
   return (size_t)c.n_layers * 2 * c.n_kv_heads * c.head_dim * block_tokens * model->esz;
 }
 
-// the batch of a prompt's attention: its blocks of 128 rows, one "client" each
-static AttnBatch prompt_blocks(int rows, int start_pos) {
-  AttnBatch b{};
-  for (int r0 = 0; r0 < rows; r0 += kPromptBlockRows) {
-    AttnClient& ac = b.c[b.n++];
-    ac.row_off = r0;
-    ac.m = std::min(kPromptBlockRows, rows - r0);
-    ac.start_pos = start_pos + r0;
-  }
-  return b;
-}
-static_assert(kMaxPromptRows <= kMaxPassClients * kPromptBlockRows, "a prompt's blocks fit a batch");
-
 static int ensure_attn_scratch(pipesd_model* m, size_t floats);
 
-// Floats of attention partials the largest pass over a pool of `pool_tokens` cached tokens can need:
-// a client brings at most kMaxRows rows (a prompt block of an fp32 model up to 128) and ceil(context / chunk) splits, the contexts of the
-// clients of a pass add up to at most the pool, and a pass holds at most kMaxPassClients clients.
+// partials no pass over a pool of `pool_tokens` cached tokens exceeds (with the exceptions stated there)
 static size_t attn_scratch_bound(const pipesd_model* m, int64_t pool_tokens) {
-  const int chunk = attn_chunk_tokens(m->cfg.dtype, m->cfg.head_dim);
-  const int64_t clients = m->cfg.dtype == PIPESD_BF16 ? kMaxPassClients : 1;
-  const int64_t splits = pool_tokens / chunk + clients;
-  // (the streaming kernel splits no finer but rounds a head group's rows up to whole pairs of 16-row tiles)
-  const int64_t rows = m->cfg.dtype == PIPESD_BF16 ? kMaxRows : f32_pass_rows(m->cfg);  // of one client
-  const int64_t group_rows = (int64_t)(m->cfg.n_q_heads / m->cfg.n_kv_heads) * rows + 31;
-  size_t floats = (size_t)splits * (size_t)(group_rows * m->cfg.n_kv_heads) * (m->cfg.head_dim + 4);
-  if (m->cfg.dtype == PIPESD_BF16) {  // and a prompt's last pass
-    const int rows = (int)std::min(pool_tokens, (int64_t)kMaxPromptRows);
-    AttnBatch b = prompt_blocks(rows, (int)(pool_tokens - rows));
-    size_t prompt_floats = 0;
-    if (attn_stream_plan(m->cfg.n_q_heads, m->cfg.n_kv_heads, m->cfg.head_dim, b, true, &prompt_floats))
-      floats = std::max(floats, prompt_floats);
-  }
-  return floats;
+  const pipesd_config& c = m->cfg;
+  const bool bf = c.dtype == PIPESD_BF16;
+  return attn_scratch_floats(c.n_q_heads, c.n_kv_heads, c.head_dim, device_cu_count(), bf ? kMaxPassClients : 1,
+                             bf ? kMaxRows : f32_pass_rows(c), attn_chunk_tokens(c.dtype, c.head_dim), bf, pool_tokens);
 }
 
 extern "C" int pipesd_kv_create(const pipesd_model* model, int32_t max_seqs, int32_t block_tokens, void* pool,
@@ -750,7 +724,7 @@ static int run_pass(pipesd_model* m, pipesd_kv* kv, const PassLayout& pl, bool w
   }
   size_t part_floats = 0, stream_floats = 0;
   const int stream_tiles =
-      bf && !may_fuse ? attn_stream_plan(c.n_q_heads, c.n_kv_heads, c.head_dim, ab_stream, prompt, &stream_floats) : 0;
+      bf && !may_fuse ? attn_stream_plan(c.n_q_heads, c.n_kv_heads, c.head_dim, device_cu_count(), ab_stream, prompt, &stream_floats) : 0;
   if (stream_tiles == 0) {  // the split kernels
     ab.n = pl.n_clients;
     for (int i = 0, r0 = 0; i < pl.n_clients; ++i) {
@@ -767,8 +741,8 @@ static int run_pass(pipesd_model* m, pipesd_kv* kv, const PassLayout& pl, bool w
       r0 += pc.rows;
     }
   }
-  // per-layer partial buffers only where the all-layers kernel may run (one client); otherwise one, reused
-  const bool part_per_layer = bf && single && rows <= 16;
+  // per-layer partial buffers only where the all-layers kernel may run; otherwise one, reused
+  const bool part_per_layer = may_fuse && rows <= 16;
   int rc = ensure_attn_scratch(m, stream_tiles ? stream_floats : part_floats * (part_per_layer ? c.n_layers : 1));
   if (rc) return rc;
   ActArena& ar = rows <= 2 * 16 ? m->arena : m->arena_big;
@@ -950,7 +924,7 @@ static int prompt_pass_rows(const pipesd_model* m, size_t left, int start_pos) {
   if (m->wide_mode == 1 || m->fused_enabled) return kPrefillRows;
   AttnBatch b = prompt_blocks(rows, start_pos);
   size_t floats = 0;
-  return attn_stream_plan(c.n_q_heads, c.n_kv_heads, c.head_dim, b, true, &floats) ? rows : kPrefillRows;
+  return attn_stream_plan(c.n_q_heads, c.n_kv_heads, c.head_dim, device_cu_count(), b, true, &floats) ? rows : kPrefillRows;
 }
 
 // The fused layer kernel raises a sticky flag if one of its device-wide barriers timed out.

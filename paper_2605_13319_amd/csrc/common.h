@@ -4,14 +4,10 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include "../../include/pipesd.h"
+#include "attn_plan.h"
 
 namespace pipesd {
 
-constexpr int kMaxRows = PIPESD_MAX_ROWS;  // rows of one client per pass (k + 1)
-constexpr int kMaxPassRows = 256;          // rows of all clients that share a pass (bf16)
-constexpr int kMaxPromptRows = 2048;       // rows of one client's prompt that share a pass (bf16)
-constexpr int kPromptBlockRows = 128;      // rows of a prompt that attend as one client of the pass
 constexpr int kBlockTokens = 16;           // tokens per KV block
 constexpr int kWave = 64;
 
@@ -52,17 +48,6 @@ struct KvView {
 struct RowMap {
   int32_t pos[kMaxPassRows];        // position of the row in its client's sequence
   int32_t table_off[kMaxPassRows];  // entries from KvView::table to the client's block table
-};
-constexpr int kMaxPassClients = 16;  // clients whose rows share one pass (each has at least 2 rows)
-struct AttnClient {
-  int32_t row_off, m, start_pos;  // the client's rows in the pass; position of its first row
-  int32_t table_off;              // entries from KvView::table to the client's block table
-  int32_t nsplit, part_off;       // splits of its context; floats from the partial buffer's start to the client's partials
-  int32_t span, count_off;        // streaming kernel: tokens per split, the client's first arrival counter
-};
-struct AttnBatch {
-  int32_t n;
-  AttnClient c[kMaxPassClients];
 };
 
 __device__ __forceinline__ int64_t k_index(const KvView& kv, int layer, int pos, int kvh, int e) {
@@ -268,14 +253,6 @@ int attn_nsplit(int total_tokens, int chunk);
 constexpr int kAttnF32Split = 256;  // tokens per workgroup of the fp32 cache's kernel (head_dim a multiple of 16)
 int attn_chunk_tokens(int dtype, int head_dim);  // tokens per workgroup of the attention kernel for this cache
 hipError_t launch_attn_f32(const AttnCall& c, int nsplit, hipStream_t st);  // fp32 cache, head_dim a multiple of 16
-// Passes of at most kMaxRows rows per client, and prompts, whose blocks of up to kPromptBlockRows rows
-// are the clients of the batch (`prompt`), take the streaming kernel (bf16 cache).  Fills span,
-// nsplit, part_off and count_off of every client of `b` (row_off, m, start_pos, table_off given) and
-// returns the query tiles per workgroup, or 0 if the pass does not fit (then the split kernels run);
-// *part_floats = size of the partial buffer the launch needs.  A client's split depends on its own
-// context only, so its results do not depend on who shares the pass.
-constexpr int kAttnCounters = kMaxPassClients * 512;
-int attn_stream_plan(int n_q_heads, int n_kv_heads, int head_dim, AttnBatch& b, bool prompt, size_t* part_floats);
 hipError_t launch_attention(const AttnCall& c, hipStream_t st);
 
 // ---- vocabulary-wide decision ----

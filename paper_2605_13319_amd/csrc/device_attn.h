@@ -16,7 +16,6 @@
 
 namespace pipesd {
 
-constexpr int kPartPad = 4;  // a partial row is [head_dim values, max, sum, 2 unused] so that rows stay 16-byte aligned
 constexpr int kAttnWaves = 8;
 constexpr int kAttnWgTokens = kAttnWaves * 32;
 

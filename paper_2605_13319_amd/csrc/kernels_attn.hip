@@ -135,13 +135,6 @@ __global__ __launch_bounds__(kAttnWaves * 64) void attn_mfma_kernel(const float*
 // [split] block a whole number of 128-byte lines, so no cache line holds partials of two groups:
 // the merging workgroup reads lines nobody on its compute unit has touched during this kernel,
 // after every writer has drained its write-through stores and then incremented the counter.
-constexpr int kStreamWaves = 4;                // waves per workgroup: one per SIMD, so that two workgroups in different
-                                               // phases (waiting for keys and values / multiplying) share a compute unit
-constexpr int kStreamWgTokens = kStreamWaves * 32;  // tokens per workgroup and step
-constexpr int kStreamMaxSteps = 64;            // steps of a split (a lane per step holds its block-table entries)
-constexpr int kStreamMinSpan = 256;            // a client's context is cut into at most kStreamMaxSplits
-constexpr int kStreamMaxSplits = 16;           // splits of 256 * 2^j tokens, j as small as that allows
-
 constexpr size_t stream_lds_floats(int hd) { return (size_t)kStreamWaves * 16 * (hd + 4) + 2 * kStreamWaves * 16; }
 template <int HD>
 constexpr size_t stream_lds_bytes(int T) {
@@ -640,51 +633,6 @@ hipError_t launch_attention(const AttnCall& c, hipStream_t st) {
 int attn_chunk_tokens(int dtype, int head_dim) {
   if (dtype != PIPESD_F32) return kAttnWgTokens;
   return head_dim % 16 == 0 ? kAttnF32Split : kAttnChunkMax;
-}
-int attn_stream_plan(int n_q_heads, int n_kv_heads, int head_dim, AttnBatch& b, bool prompt, size_t* part_floats) {
-  *part_floats = 0;
-  if (b.n < 1 || b.n > kMaxPassClients || (head_dim != 128 && head_dim != 64)) return 0;
-  const int group = n_q_heads / n_kv_heads;
-  int max_m = 1;
-  long tasks = 0;  // (kv head, split, query tile) over all clients
-  for (int i = 0; i < b.n; ++i) {
-    AttnClient& cl = b.c[i];
-    if (cl.m > (prompt ? kPromptBlockRows : kMaxRows)) return 0;
-    max_m = std::max(max_m, (int)cl.m);
-    const int total = cl.start_pos + cl.m;
-    cl.span = kStreamMinSpan;
-    if (cl.m <= kMaxRows) {
-      while ((total + cl.span - 1) / cl.span > kStreamMaxSplits) cl.span *= 2;
-    } else {
-      // a prompt block: the query tiles alone give many workgroups, so the context is cut only as far as
-      // it takes for the block by itself to have about two workgroups per compute unit (by itself: its
-      // results do not depend on how many blocks of the prompt share the pass)
-      const long groups = (long)n_kv_heads * (((group * cl.m + 15) / 16 + 1) / 2);
-      const long fit = ((long)total + kStreamMaxSteps * kStreamWgTokens - 1) / (kStreamMaxSteps * kStreamWgTokens);
-      const long want = std::max(fit, std::min((long)kStreamMaxSplits, 2L * device_cu_count() / groups));
-      const int steps = (total + kStreamMinSpan - 1) / kStreamMinSpan;
-      cl.span = (int)((steps + want - 1) / want) * kStreamMinSpan;
-    }
-    cl.nsplit = (total + cl.span - 1) / cl.span;
-    if (cl.span > kStreamMaxSteps * kStreamWgTokens || cl.nsplit > kStreamMaxSplits) return 0;  // (contexts beyond 131072 tokens)
-    tasks += (long)n_kv_heads * cl.nsplit * ((group * cl.m + 15) / 16);
-  }
-  // two tiles per workgroup (keys and values read once for both) where a head group has exactly
-  // two, or where single tiles would be more workgroups than two rounds of the device
-  const int max_qt = (group * max_m + 15) / 16;
-  const int T = (max_qt == 2 || tasks > 2L * device_cu_count()) ? 2 : 1;
-  const int nz = (max_qt + T - 1) / T;
-  if ((long)n_kv_heads * nz > kAttnCounters / kMaxPassClients) return 0;
-  size_t floats = 0;
-  for (int i = 0; i < b.n; ++i) {
-    AttnClient& cl = b.c[i];
-    if (floats > (size_t)INT32_MAX) return 0;
-    cl.part_off = (int32_t)floats;
-    cl.count_off = i * (kAttnCounters / kMaxPassClients);
-    floats += (size_t)n_kv_heads * nz * cl.nsplit * T * 16 * (head_dim + kPartPad);
-  }
-  *part_floats = floats;
-  return T;
 }
 
 }  // namespace pipesd

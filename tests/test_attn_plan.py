@@ -1,0 +1,84 @@
+"""The attention scratch that a cache pool is given at its creation holds the partials of every pass over
+it: the planner of the streaming attention swept over rows, starts and pool sizes on the host."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2605_13319_amd", "csrc")
+
+SWEEP = r"""
+#include <stdio.h>
+#include <stdlib.h>
+#include "attn_plan.h"
+using namespace pipesd;
+static long checked = 0;
+static bool check(int nq, int nkv, int hd, int n_cu, AttnBatch b, bool prompt, long pool, const char* what) {
+  size_t need = 0;
+  const int T = attn_stream_plan(nq, nkv, hd, n_cu, b, prompt, &need);
+  if (T == 0) return true;  // (declined: the split kernels)
+  const size_t have = attn_scratch_floats(nq, nkv, hd, n_cu, kMaxPassClients, kMaxRows, 256, true, pool);
+  // the kernel's layout: client after client, [kv head][own tile groups][split][T][16][head_dim + pad]
+  size_t end = 0;
+  for (int i = 0; i < b.n; ++i) {
+    const AttnClient& c = b.c[i];
+    if ((size_t)c.part_off != end || (end * 4) % 128) { printf("%s: client %d at %d, not %zu\n", what, i, c.part_off, end); return false; }
+    end += (size_t)nkv * ((((nq / nkv) * c.m + 15) / 16 + T - 1) / T) * c.nsplit * T * 16 * (hd + 4);
+  }
+  ++checked;
+  if (end <= need && need <= have) return true;
+  printf("%s: heads %d/%d x %d, pool %ld: used %zu, planned %zu, there %zu (first client: %d rows behind %d, n = %d)\n", what, nq, nkv, hd,
+         pool, end, need, have, b.c[0].m, b.c[0].start_pos, b.n);
+  return false;
+}
+int main(int argc, char** argv) {
+  const int nq = atoi(argv[1]), nkv = atoi(argv[2]), hd = atoi(argv[3]), n_cu = atoi(argv[4]);
+  unsigned seed = 12345;
+  auto rnd = [&](long n) { seed = seed * 1664525u + 1013904223u; return (long)((seed >> 8) % (unsigned long)n); };
+  for (long pool : {16L, 112L, 1024L, 2048L, 2064L, 4096L, 10000L, 33008L, 131072L, 262144L}) {
+    for (long rows = 33; rows <= 2048 && rows <= pool; ++rows)
+      for (int s = 0; s < 5; ++s) {
+        const long room = pool - rows, start = s == 0 ? 0 : s == 1 ? room : s == 2 ? room / 2 : rnd(room + 1);
+        if (!check(nq, nkv, hd, n_cu, prompt_blocks((int)rows, (int)start), true, pool, "prompt")) return 1;
+      }
+    for (int t = 0; t < 2000; ++t) {  // rounds of 1 .. 16 clients whose blocks of 16 tokens share the pool
+      AttnBatch b{};
+      long left = pool / 16, rows = 0;
+      const int n = 1 + (int)rnd(16);
+      for (int i = 0; i < n && left > 0; ++i) {
+        const long m = 1 + rnd(32), most = left - (n - 1 - i) > 0 ? left - (n - 1 - i) : 1;
+        const long blocks = i == n - 1 ? left : 1 + rnd(most);
+        if (blocks * 16 < m || rows + m > kMaxPassRows) continue;
+        AttnClient& c = b.c[b.n++];
+        c.row_off = (int)rows;
+        c.m = (int)m;
+        c.start_pos = (int)(blocks * 16 - m);
+        rows += m;
+        left -= blocks;
+      }
+      if (b.n > 0 && !check(nq, nkv, hd, n_cu, b, false, pool, "round")) return 1;
+    }
+  }
+  printf("%ld plans\n", checked);
+  return checked > 10000 ? 0 : 1;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def sweep(tmp_path_factory):
+    cxx = shutil.which("g++") or shutil.which("clang++") or "/opt/rocm/llvm/bin/clang++"
+    d = tmp_path_factory.mktemp("plan")
+    (d / "sweep.cpp").write_text(SWEEP)
+    subprocess.run([cxx, "-std=c++17", "-O2", "-Wall", "-Werror", "-I", CSRC, "-o", str(d / "sweep"), str(d / "sweep.cpp")], check=True)
+    return str(d / "sweep")
+
+
+# head groups of 1, 4, 8, 16 and 128 heads, both head sizes; the largest number of heads the kernel takes
+@pytest.mark.parametrize("heads", [(32, 8, 128), (32, 8, 64), (40, 40, 128), (8, 2, 64), (16, 1, 128), (64, 8, 64), (128, 128, 64),
+                                   (128, 8, 64), (128, 1, 64)])
+@pytest.mark.parametrize("n_cu", [256, 64])
+def test_scratch_of_a_pool_holds_every_pass(sweep, heads, n_cu):
+    r = subprocess.run([sweep, *map(str, heads), str(n_cu)], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout
