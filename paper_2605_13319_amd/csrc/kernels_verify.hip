@@ -136,7 +136,7 @@ __device__ __forceinline__ void spec_accept_body(const float* __restrict__ p, co
                                                  const float* __restrict__ stats, int k, int V, const int32_t* drafts,
                                                  const float* un, unsigned long long* partial, unsigned* counter,
                                                  int32_t* __restrict__ result, int32_t* __restrict__ result_copy) {
-  constexpr int kWaves = kVThreads / 64;
+  constexpr int kWaves = kVThreads / 64, kNone = 0x7fffffff;
   __shared__ unsigned long long red[kWaves];
   __shared__ int s_last, s_next;
   __shared__ float s_M[kMaxRows], s_S[kMaxRows];
@@ -217,6 +217,7 @@ __device__ __forceinline__ void spec_accept_body(const float* __restrict__ p, co
   if (lane == 0) red[w] = s;
   __syncthreads();
   if (tid == 0) {
+    s_next = kNone;
     partial[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
     __threadfence();
     const unsigned prev = atomicAdd(counter, 1u);
@@ -266,8 +267,6 @@ __device__ __forceinline__ void spec_accept_body(const float* __restrict__ p, co
   // reports it, so that a result is written and the counter cleared whatever the sums are.  (The sums
   // between the tokens count, not only those between the threads: weights of distributions with masses
   // beyond 2^24 wrap.)
-  constexpr int kNone = 0x7fffffff;
-  if (tid == 0) s_next = kNone;
   for (int base = clo; base < chi; base += kVThreads * kHold) {
     // thread t has the kHold tokens behind base + t * kHold
     const int i0 = base + tid * kHold;
@@ -276,8 +275,7 @@ __device__ __forceinline__ void spec_accept_body(const float* __restrict__ p, co
 #pragma unroll
     for (int j = 0; j < kHold; ++j) own += wt[j];
     const unsigned long long inc = wave_scan_u64(own);
-    __syncthreads();  // (red has been read, s_next is set)
-    if (lane == 63) red[w] = inc;
+    if (lane == 63) red[w] = inc;  // (everybody has read what was there: a barrier lies behind each read)
     __syncthreads();
     unsigned long long at = run + inc - own;  // sum in front of the thread's first token
 #pragma unroll
