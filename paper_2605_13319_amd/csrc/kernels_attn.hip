@@ -6,9 +6,11 @@
 // (max, sum, o); a second kernel merges the splits in a fixed order, so results do not depend on
 // scheduling.
 #include <algorithm>
+#include <type_traits>
 
 #include "device_attn.h"
 #include "device_dma.h"
+#include "lds_limit.h"
 
 namespace pipesd {
 
@@ -564,27 +566,20 @@ hipError_t launch_attention(const AttnCall& c, hipStream_t st) {
       for (int i = 0; i < b.n; ++i)  // (a lane per step holds the step's block-table entries)
         if (b.c[i].span < kStreamWgTokens || b.c[i].span > kStreamMaxSteps * kStreamWgTokens) return hipErrorInvalidValue;
       const int nz = ((group * max_m + 15) / 16 + T - 1) / T;
-      static bool stream_lds_allowed = false;
-      if (!stream_lds_allowed) {
-        const hipFuncAttribute attr = hipFuncAttributeMaxDynamicSharedMemorySize;
-        hipError_t e = hipFuncSetAttribute((const void*)attn_stream_kernel<128, 1>, attr, (int)stream_lds_bytes<128>(1));
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)attn_stream_kernel<128, 2>, attr, (int)stream_lds_bytes<128>(2));
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)attn_stream_kernel<64, 1>, attr, (int)stream_lds_bytes<64>(1));
-        if (e == hipSuccess) e = hipFuncSetAttribute((const void*)attn_stream_kernel<64, 2>, attr, (int)stream_lds_bytes<64>(2));
-        if (e != hipSuccess) return e;
-        stream_lds_allowed = true;
-      }
       const dim3 grid(c.kv.n_kv_heads, splits, nz), block(kStreamWaves * 64);
-      uint4* outp = (uint4*)c.outp;
-      if (h == 128 && T == 2)
-        attn_stream_kernel<128, 2><<<grid, block, stream_lds_bytes<128>(2), st>>>(c.q, c.kv, c.layer, c.n_q_heads, b, c.part, outp, c.act_tiles, c.gate, c.counters);
-      else if (h == 128)
-        attn_stream_kernel<128, 1><<<grid, block, stream_lds_bytes<128>(1), st>>>(c.q, c.kv, c.layer, c.n_q_heads, b, c.part, outp, c.act_tiles, c.gate, c.counters);
-      else if (T == 2)
-        attn_stream_kernel<64, 2><<<grid, block, stream_lds_bytes<64>(2), st>>>(c.q, c.kv, c.layer, c.n_q_heads, b, c.part, outp, c.act_tiles, c.gate, c.counters);
-      else
-        attn_stream_kernel<64, 1><<<grid, block, stream_lds_bytes<64>(1), st>>>(c.q, c.kv, c.layer, c.n_q_heads, b, c.part, outp, c.act_tiles, c.gate, c.counters);
-      return hipGetLastError();
+      auto go = [&](auto hd, auto t) -> hipError_t {
+        constexpr int HD = decltype(hd)::value, TT = decltype(t)::value;
+        static std::atomic<uint64_t> lds_allowed;
+        constexpr size_t lds = stream_lds_bytes<HD>(TT);
+        const hipError_t e = allow_lds(lds_allowed, (const void*)attn_stream_kernel<HD, TT>, lds);
+        if (e != hipSuccess) return e;
+        attn_stream_kernel<HD, TT><<<grid, block, lds, st>>>(c.q, c.kv, c.layer, c.n_q_heads, b, c.part, (uint4*)c.outp, c.act_tiles,
+                                                             c.gate, c.counters);
+        return hipGetLastError();
+      };
+      using std::integral_constant;
+      if (h == 128) return T == 2 ? go(integral_constant<int, 128>{}, integral_constant<int, 2>{}) : go(integral_constant<int, 128>{}, integral_constant<int, 1>{});
+      return T == 2 ? go(integral_constant<int, 64>{}, integral_constant<int, 2>{}) : go(integral_constant<int, 64>{}, integral_constant<int, 1>{});
     }
     // more tasks than the device holds at once (two workgroups per compute unit): a workgroup walks
     // several query tiles with its keys and values in registers, as many as still leave about two
@@ -594,26 +589,21 @@ hipError_t launch_attention(const AttnCall& c, hipStream_t st) {
     dim3 grid(c.kv.n_kv_heads, splits, (max_qt + qpw - 1) / qpw);
     if (h != 128 && h != 64) return hipErrorInvalidValue;
     const size_t lds = attn_lds_floats(h) * sizeof(float);
-    static bool lds_allowed = false;  // more than 64 KB of dynamic LDS has to be asked for once per kernel
-    if (!lds_allowed) {
-      const int b128 = (int)(attn_lds_floats(128) * sizeof(float)), b64 = (int)(attn_lds_floats(64) * sizeof(float));
-      const hipFuncAttribute attr = hipFuncAttributeMaxDynamicSharedMemorySize;
-      hipError_t e = hipFuncSetAttribute((const void*)attn_mfma_kernel<128, false>, attr, b128);
-      if (e == hipSuccess) e = hipFuncSetAttribute((const void*)attn_mfma_kernel<128, true>, attr, b128);
-      if (e == hipSuccess) e = hipFuncSetAttribute((const void*)attn_mfma_kernel<64, false>, attr, b64);
-      if (e == hipSuccess) e = hipFuncSetAttribute((const void*)attn_mfma_kernel<64, true>, attr, b64);
-      if (e != hipSuccess) return e;
-      lds_allowed = true;
-    }
     const dim3 block(kAttnWaves * 64);
-    if (h == 128 && qpw > 1)
-      attn_mfma_kernel<128, true><<<grid, block, lds, st>>>(c.q, c.kv, c.layer, c.n_q_heads, b, c.part, qpw, c.gate);
-    else if (h == 128)
-      attn_mfma_kernel<128, false><<<grid, block, lds, st>>>(c.q, c.kv, c.layer, c.n_q_heads, b, c.part, qpw, c.gate);
-    else if (qpw > 1)
-      attn_mfma_kernel<64, true><<<grid, block, lds, st>>>(c.q, c.kv, c.layer, c.n_q_heads, b, c.part, qpw, c.gate);
-    else
-      attn_mfma_kernel<64, false><<<grid, block, lds, st>>>(c.q, c.kv, c.layer, c.n_q_heads, b, c.part, qpw, c.gate);
+    auto go = [&](auto hd, auto multi) -> hipError_t {
+      constexpr int HD = decltype(hd)::value;
+      constexpr bool MULTI = decltype(multi)::value;
+      static std::atomic<uint64_t> lds_allowed;
+      const hipError_t ea = allow_lds(lds_allowed, (const void*)attn_mfma_kernel<HD, MULTI>, lds);
+      if (ea != hipSuccess) return ea;
+      attn_mfma_kernel<HD, MULTI><<<grid, block, lds, st>>>(c.q, c.kv, c.layer, c.n_q_heads, b, c.part, qpw, c.gate);
+      return hipSuccess;
+    };
+    using std::integral_constant;
+    hipError_t el;
+    if (h == 128) el = qpw > 1 ? go(integral_constant<int, 128>{}, std::true_type{}) : go(integral_constant<int, 128>{}, std::false_type{});
+    else el = qpw > 1 ? go(integral_constant<int, 64>{}, std::true_type{}) : go(integral_constant<int, 64>{}, std::false_type{});
+    if (el != hipSuccess) return el;
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

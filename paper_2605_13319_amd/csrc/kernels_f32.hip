@@ -8,6 +8,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "lds_limit.h"
 
 namespace pipesd {
 
@@ -342,12 +343,9 @@ __global__ __launch_bounds__(kF32Waves * 64) void attn_f32_kernel(const float* _
 template <int HT>
 static hipError_t launch_attn_f32_ht(const AttnCall& c, int nsplit, hipStream_t st) {
   constexpr size_t lds = ((size_t)kF32Waves * 16 * (HT * 16 + 4) + 2 * kF32Waves * 16) * sizeof(float);
-  static bool lds_allowed = false;  // more than 64 KB of dynamic LDS has to be asked for once per kernel
-  if (!lds_allowed) {
-    const hipError_t e = hipFuncSetAttribute((const void*)attn_f32_kernel<HT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    lds_allowed = true;
-  }
+  static std::atomic<uint64_t> lds_allowed;
+  const hipError_t e = allow_lds(lds_allowed, (const void*)attn_f32_kernel<HT>, lds);
+  if (e != hipSuccess) return e;
   const int group = c.n_q_heads / c.kv.n_kv_heads;
   const dim3 grid(c.kv.n_kv_heads, nsplit, (group * c.m + 15) / 16);
   attn_f32_kernel<HT><<<grid, kF32Waves * 64, lds, st>>>(c.q, c.kv, c.layer, c.m, c.start_pos, c.n_q_heads, nsplit, c.part, c.out);

@@ -46,6 +46,7 @@
 
 #include "device_dma.h"
 #include "device_gemm.h"
+#include "lds_limit.h"
 
 namespace pipesd {
 
@@ -415,13 +416,9 @@ template <int WM, int WN, int RT, bool WHOLE, bool P1>
 static hipError_t launch_wide_kernel(const GemmArgs& a, const WideArgs& x, int grid, bool timed, hipEvent_t e0,
                                      hipEvent_t e1, hipStream_t st) {
   constexpr size_t lds = wide_lds_bytes(WM, WN, RT);
-  static bool attr_set = false;  // more than 64 KB of dynamic LDS has to be allowed once per kernel
-  if (!attr_set) {
-    const hipError_t e = hipFuncSetAttribute((const void*)gemm_wide_kernel<WM, WN, RT, WHOLE, P1>,
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
+  static std::atomic<uint64_t> lds_allowed;
+  const hipError_t e = allow_lds(lds_allowed, (const void*)gemm_wide_kernel<WM, WN, RT, WHOLE, P1>, lds);
+  if (e != hipSuccess) return e;
   // start of the first kernel of the product, end of the last
   if (timed)
     hipExtLaunchKernelGGL((gemm_wide_kernel<WM, WN, RT, WHOLE, P1>), dim3(grid), dim3(kWideWaves * 64), (uint32_t)lds, st, e0,

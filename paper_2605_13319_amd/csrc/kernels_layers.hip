@@ -16,7 +16,10 @@
 // The barrier is a monotone counter per group of workgroups plus one top counter; a waiter gives up
 // after a bounded number of polls, raises an error flag and every workgroup leaves the kernel, so a
 // lost workgroup can never hang the device.
+#include <algorithm>
+
 #include "device_attn.h"
+#include "lds_limit.h"
 
 namespace pipesd {
 
@@ -304,17 +307,12 @@ hipError_t launch_layers(const LayersCall& c, hipStream_t st) {
   hipError_t e = hipMemsetAsync(c.bar, 0, (1 + kBarGroups) * 32 * sizeof(unsigned), st);  // counters; the flag is sticky
   if (e != hipSuccess) return e;
   void* args[] = {&a};
-  static bool lds_allowed = false;  // more than 64 KB of dynamic LDS has to be asked for once per kernel
-  if (!lds_allowed) {
-    const int cap = (int)(attn_lds_floats(128) * sizeof(float)) > 64 * 1024 ? (int)(attn_lds_floats(128) * sizeof(float)) : 64 * 1024;
-    e = hipFuncSetAttribute((const void*)layers_kernel<128>, hipFuncAttributeMaxDynamicSharedMemorySize, cap);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)layers_kernel<64>, hipFuncAttributeMaxDynamicSharedMemorySize, cap);
-    if (e != hipSuccess) return e;
-    lds_allowed = true;
-  }
-  if (c.head_dim == 128)
-    return hipLaunchCooperativeKernel((const void*)layers_kernel<128>, dim3(grid), dim3(512), args, lds, st);
-  return hipLaunchCooperativeKernel((const void*)layers_kernel<64>, dim3(grid), dim3(512), args, lds, st);
+  static std::atomic<uint64_t> lds_allowed[2];
+  const bool wide = c.head_dim == 128;
+  const void* kernel = wide ? (const void*)layers_kernel<128> : (const void*)layers_kernel<64>;
+  e = allow_lds(lds_allowed[wide], kernel, std::max(attn_lds_floats(128) * sizeof(float), (size_t)64 * 1024));
+  if (e != hipSuccess) return e;
+  return hipLaunchCooperativeKernel(kernel, dim3(grid), dim3(512), args, lds, st);
 }
 
 }  // namespace pipesd
