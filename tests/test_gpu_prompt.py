@@ -49,3 +49,88 @@ def test_a_turn_behind_a_cached_context_equals_one_prompt():
     a, b = p[:, :, :full], p[:, :, full + 1:2 * full + 1]
     assert float((a - b).abs().max()) <= 2.0 ** -7 * float(a.abs().max())
     assert float((a != b).float().mean()) < 0.02
+
+
+# tokens cached first (behind them a block of 128 rows takes 8 or 16 splits of the context), and tokens of
+# the call itself: a full block and a row, a ragged last block of a few rows (cut finer than the others),
+# a longer ragged one, and a second pass of one row
+@pytest.mark.parametrize("shape", SHAPES[:3], ids=lambda s: s.name)
+@pytest.mark.parametrize("cached", [4500, 9001])
+def test_long_passes_behind_a_cached_context_equal_short_ones(shape, cached):
+    from paper_2605_13319_amd import nav
+    model = nav.Model(shape, I.make_weights(shape, 61))
+    first = I.make_tokens(cached, shape.vocab, 71)
+    for tokens in (129, 270, 700, 2049):  # (as many rows: the pending token and all but the last)
+        toks = I.make_tokens(tokens, shape.vocab, 72 + tokens)
+        pools = []
+        for mode in (1, 0, 2):
+            model.set_wide_gemm(mode)
+            kv = nav.KVCache(model, max_seqs=1, n_blocks=(cached + tokens + 15) // 16 + 1)
+            kv.prefill(0, first)
+            kv.prefill(0, toks)
+            pools.append(kv.pool.clone())
+        print(shape.name, cached, tokens, flush=True)
+        assert bool((pools[0] == pools[1]).all()) and bool((pools[0] == pools[2]).all()), f"{tokens} tokens: the caches differ"
+
+
+def test_context_beyond_the_streaming_attention():
+    """Behind 131072 tokens prompts run in passes of 128 rows and every pass on the split kernels.  One
+    layer, so that the keys and values of all tokens follow from their embeddings, and weights large
+    enough for peaked attention (the logits without it are far off): logits of passes of 1, 16 and 17
+    rows against 64 bits, the bound that of a bf16 model's logits."""
+    import torch
+    from paper_2605_13319_amd import nav
+    shape = I.ModelShape("far", 1, 512, 8, 1, 64, 512, 300)
+    w = I.make_weights(shape, 95, std=0.08)
+    n = 131072 + 200
+    toks = I.make_tokens(n, shape.vocab, 96)
+    extra = I.make_tokens(16, shape.vocab, 97)
+    model = nav.Model(shape, w)
+    kv = nav.KVCache(model, max_seqs=1, n_blocks=(n + 16 + 15) // 16 + 1)
+    kv.prefill(0, toks[:n - 150])
+    kv.prefill(0, toks[n - 150:])
+
+    def wide(a):
+        t = torch.from_numpy(a.view("int16")).cuda().view(torch.bfloat16) if a.dtype.itemsize == 2 else torch.from_numpy(a).cuda()
+        return t.double()
+
+    h, g = shape.head_dim, shape.n_q_heads
+    text = torch.tensor(list(toks) + list(extra), device="cuda")
+    x = wide(w["tok_emb"])[text]
+    theta = shape.rope_base ** (-2.0 * torch.arange(h // 2, dtype=torch.float64, device="cuda") / h)
+    ang = torch.arange(len(text), device="cuda").double()[:, None] * theta
+    cos, sin = torch.cos(ang), torch.sin(ang)
+
+    def norm(v, gain):
+        return v * torch.rsqrt(v.square().mean(-1, keepdim=True) + shape.rms_eps) * wide(gain)
+
+    def rotate(v, c, s):
+        a, b = v[..., : h // 2], v[..., h // 2:]
+        return torch.cat([a * c - b * s, b * c + a * s], dim=-1)
+
+    y = norm(x, w["attn_norm"][0])
+    keys = rotate(y @ wide(w["wk"][0]).t().contiguous(), cos, sin).bfloat16().double()
+    vals = (y @ wide(w["wv"][0]).t().contiguous()).bfloat16().double()
+    rows = slice(n - 1, n + 16)
+    q = rotate((y[rows] @ wide(w["wq"][0]).t().contiguous()).view(17, g, h), cos[rows][:, None], sin[rows][:, None])
+    sc = (q.reshape(17 * g, h) @ keys.t().contiguous()).view(17, g, -1) / h ** 0.5
+    later = torch.arange(n + 16, device="cuda")[None, :] > torch.arange(n - 1, n + 16, device="cuda")[:, None]
+    p = torch.softmax(sc.masked_fill(later[:, None, :], float("-inf")), dim=-1)
+    o = (p.view(17 * g, -1) @ vals).view(17, g * h)
+
+    def logits(attended):
+        z = x[rows] + attended @ wide(w["wo"][0]).t().contiguous()
+        f = norm(z, w["ffn_norm"][0])
+        f = torch.nn.functional.silu(f @ wide(w["w_gate"][0]).t().contiguous()) * (f @ wide(w["w_up"][0]).t().contiguous())
+        z = z + f @ wide(w["w_down"][0]).t().contiguous()
+        return (norm(z, w["final_norm"]) @ wide(w["lm_head"]).t().contiguous()).cpu().numpy()
+
+    ref = logits(o)
+    assert abs(ref - logits(0.0 * o)).max(axis=1).min() > 0.2
+    got = {}
+    for m in (1, 16, 17):
+        got[m] = kv.forward_logits(0, extra[:m - 1])
+        err = float(abs(got[m] - ref[:m]).max())
+        print(f"{m} rows behind {n} tokens: err {err:.2e}", flush=True)
+        assert err <= 2e-2
+    assert (got[1] == got[17][:1]).all() and (got[16] == got[17][:16]).all()
