@@ -81,7 +81,12 @@ typedef struct pipesd_kv pipesd_kv;
 
 /* Target model handle (Sec. 4.2: the cloud keeps one target model for all clients, Appendix I).
  * The weights are re-tiled into library-owned device memory in the order the matrix cores read
- * them, synchronously: when the call returns the caller may free its own copies.
+ * them, synchronously: when the call returns the caller may free its own copies.  Beside the weights a
+ * bf16 handle holds, whether such passes come or not, what its largest passes need: activations of a
+ * prompt pass of 2048 rows, 8192 * (4 d_model + 2 n_q_heads * head_dim + d_ffn) bytes (320 MB at d_model
+ * 4096, 32 heads of 128, d_ffn 14336); running sums of products, up to 128 MB or, if more, 2048 fp32 rows
+ * of the widest product of more than 4096 columns (226 MB at 27648 x 5120); logits of 256 rows; and 5 MB
+ * per layer of that shape.
  * weights == NULL creates a shape-only handle without device memory (for planning KV pools and
  * exercising the bookkeeping without a GPU); compute calls on it return PIPESD_ESTATE.
  * EINVAL: null cfg/out, non-positive sizes, n_q_heads not a multiple of n_kv_heads, odd head_dim,

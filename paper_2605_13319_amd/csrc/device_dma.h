@@ -21,4 +21,10 @@ __device__ __forceinline__ void lds_dma16(const void* src_lane, void* dst_wave) 
   asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src_lane), "{m0}"(lds_addr) : "memory");
 }
 
+// The same with the source as a scalar base and a per-lane offset, and the destination as the wave's byte
+// address in LDS: for copies whose offsets stay and whose bases move on.
+__device__ __forceinline__ void lds_dma16(const char* base, unsigned lane_off, unsigned lds_addr) {
+  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane_off), "s"(base), "{m0}"(lds_addr) : "memory");
+}
+
 }  // namespace pipesd

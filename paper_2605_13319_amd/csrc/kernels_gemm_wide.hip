@@ -24,9 +24,10 @@
 // What bounds it: the matrix cores' rate in a loop of this form, 1.5 PFLOP/s of issued bf16 products
 // (hi and lo halves counted; measured with the same operand reads, barriers and copies but nothing
 // else; a large library product of this device reaches 1.5 - 1.6), and for passes of few row tiles the
-// weights' way from memory.  Issued rates: 2048 rows 1.3 PFLOP/s (gate/up of the 8B shape 734 us; 128
-// rows at a time with one row tile x four n-tiles per wave it took 16 x 74), 152 rows 0.87 (80 us,
-// before 107), 68 rows 3.7 TB/s of weights (64 us; with the weights held in the caches 49).
+// weights' way from memory.  Issued rates: 2048 rows 1.24 - 1.36 PFLOP/s (gate/up of the 8B shape 708 -
+// 778 us in several sessions, the matrix cores busy in 67 % of the cycles; 128 rows at a time with one row
+// tile x four n-tiles per wave it took 16 x 83), 152 rows 0.91 (83 us, before 108), 68 rows 3.6 TB/s of
+// weights (65 us, before 78; with the weights held in the caches 49).
 //
 // Results are bit-identical to the narrow kernel's, row by row: K is cut into the same W * P slices
 // of 512 columns, every slice is accumulated from zero in the same k-step order (hi half, then lo
@@ -82,11 +83,6 @@ __device__ __forceinline__ void wide_dispatch_count(int n, F& f) {
   }
 }
 
-// a 1 KB fragment from base + voff (per lane) to LDS at lds_addr (wave-uniform; lane i's 16 bytes at + 16 i)
-__device__ __forceinline__ void wide_request(const char* base, unsigned voff, unsigned lds_addr) {
-  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(base), "{m0}"(lds_addr) : "memory");
-}
-
 template <int WM, int WN, int RT, bool WHOLE, bool P1>
 __global__ __launch_bounds__(kWideWaves * 64) void gemm_wide_kernel(GemmArgs a, WideArgs x) {
   static_assert(WM * WN == kWideWaves, "eight waves");
@@ -133,7 +129,7 @@ __global__ __launch_bounds__(kWideWaves * 64) void gemm_wide_kernel(GemmArgs a, 
   const unsigned lds0 = (unsigned)(unsigned long long)(__attribute__((address_space(3))) char*)ring;
   auto request_one = [&](int buf, int i) {  // this wave's i-th fragment of the next k-step, into the ring at byte offset buf
     const int f = i < NW_ ? w + kWideWaves * i : CT + min(w + kWideWaves * (i - NW_), 2 * TILES - 1);
-    wide_request(i < NW_ ? wbase : abase, voff[i], lds0 + (unsigned)(buf + f * 1024));
+    lds_dma16(i < NW_ ? wbase : abase, voff[i], lds0 + (unsigned)(buf + f * 1024));  // (a 1 KB fragment)
   };
   // the requests have covered a slice: move to the next slice of the walk (slice p*W + w follows
   // (p-1)*W + w; role w + 1 follows role w); past the end of the walk, to the last slice again
@@ -378,9 +374,14 @@ static WidePlan wide_plan(int N, int K, int row_tiles, int n_cu, size_t ws_bytes
         const size_t ws = (size_t)ntiles * row_tiles * 1024 * (whole ? (P > 1 ? 1 : 0) : W);
         if (ws > (whole ? ws_bytes : std::min(ws_bytes, kWideSplitBytes))) continue;
         const int wgs = (ntiles + ct - 1) / ct * p.nrb * (whole ? 1 : W), steps = 16 * P * (whole ? W : 1);
-        // (the smallest tiles leave room for a second workgroup on a compute unit, which pays where the
-        // weights are few enough to come from the caches: QKV of the 8B shape at 333 rows 47 against 54 us,
-        // but gate/up at 128 rows 83 against 73)
+        // The smallest tiles leave room for a second workgroup on a compute unit.  Beyond 64 MB of weights
+        // that does not pay (8B gate/up at 128 rows 83 against 73 us); up to there it depends, and 1.45
+        // times the time of one stands for both outcomes.  Microseconds, with / without: 1B QKV at 660 / 760 /
+        // 1300 rows 33.5 / 34.9, 35.6 / 38.9, 40.5 / 43.7; 1B O at 1030 / 2048 rows 33.5 / 35.2, 46.1 / 45.5;
+        // 8B QKV at 330 / 370 / 400 / 600 / 2048 rows 54.7 / 56.5, 56.9 / 62.5, 61.2 / 56.7, 69.1 / 62.8, 197 / 188;
+        // 8B O at 520 / 800 / 1025 rows 59.4 / 55.7, 69.4 / 62.0, 78.8 / 68.3; 1B down at 1030 / 1300 rows 113 / 123,
+        // 141 / 137.  Neither side of it is faster in every call (a limit of 16 MB: 8B prompts of 400 and more
+        // tokens up to 3 % faster, 8B of 333 and 1B of 1030 tokens 1 and 4 % slower).
         const bool two = ct == 8 && rt == 1 && (size_t)N * K * 2 <= ((size_t)64 << 20) && wgs > n_cu;
         const int slots = two ? 2 * n_cu : n_cu;
         double us = 3.0 + (double)((wgs + slots - 1) / slots) *
