@@ -1531,9 +1531,7 @@ extern "C" int pipesd_spec_accept_static(const float* p, const float* q, const i
   vc.scan_partial = (unsigned long long*)sp;  // 64 x 8 bytes
   vc.counter = (unsigned*)(sp + 1024);
   vc.result = result_dev;
-  // the counter must start at zero whatever the call before left (a fill kernel, not a memset node:
-  // the caller may be recording a graph)
-  HIP_TRY(launch_clear_words(vc.counter, 1, st));
+  // (the counter is zero from the load of the module on and wraps to zero in every call)
   HIP_TRY(launch_spec_accept(vc, st));
   return PIPESD_OK;
 }

@@ -318,7 +318,5 @@ hipError_t launch_set_table(int32_t* table, int first, const int32_t* entries, i
 // token equal to `guess`.
 hipError_t launch_chain_step(int32_t* result, int32_t* result_copy, int k, int guess, const int32_t* alive_in,
                              int32_t* alive_out, hipStream_t st);
-// words[0..n-1] = 0 by a small kernel (usable where a memset node is not: under graph capture)
-hipError_t launch_clear_words(unsigned* words, int n, hipStream_t st);
 
 }  // namespace pipesd

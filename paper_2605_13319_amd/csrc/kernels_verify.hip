@@ -129,9 +129,11 @@ __device__ __forceinline__ unsigned long long wave_scan_u64(unsigned long long v
 // Bound by a chain of dependent latencies, not by the 1 MB it reads at a vocabulary of 128256: the
 // rows' statistics, the tests, a sweep over one row, the arrival of the other workgroups, the draw.
 // Each link asks for all it needs at once, and the draw (find the chunk, then the token in it) is two
-// scans by the whole last workgroup.  With the draw walked by one wave, 64 tokens and one round trip
-// to memory at a time, the step took 41 us at that vocabulary and 18 us on given probabilities; now
-// 11 and 10.
+// scans by the whole last workgroup.  The chunk sums reach it written through and read past the
+// caches, without fences (a device-scope fence writes the whole L2 back), every wave makes the tests for
+// itself, and the arrival counter wraps to zero by itself, so that no launch has to clear it in front:
+// 9.7 -> 7.8 us on given probabilities at that vocabulary and 8 drafts, and 1.4 for the clearing launch
+// (a call of the static entry point among others 14.4 -> 11.1, now the host's share).
 __device__ __forceinline__ void spec_accept_body(const float* __restrict__ p, const float* __restrict__ q,
                                                  const float* __restrict__ stats, int k, int V, const int32_t* drafts,
                                                  const float* un, unsigned long long* partial, unsigned* counter,
@@ -142,13 +144,14 @@ __device__ __forceinline__ void spec_accept_body(const float* __restrict__ p, co
   __shared__ float s_M[kMaxRows], s_S[kMaxRows];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const bool from_logits = stats != nullptr;
-  __shared__ int s_ok[kMaxRows];
-  // operands of the k tests (side by side: thread i has test i)
-  float test_p = 0.f, test_q = 0.f;
-  if (tid < k) {
-    const size_t at = (size_t)tid * V + drafts[tid];
+  // operands of the k tests, side by side: lane i of every wave has test i
+  static_assert(kMaxRows <= 64, "a lane per test");
+  float test_p = 0.f, test_q = 0.f, test_u = 0.f;
+  if (lane < k) {
+    const size_t at = (size_t)lane * V + drafts[lane];
     test_p = p[at];
     test_q = q[at];
+    test_u = un[lane];
   }
   // Row statistics: one wave per row, lane j holding chunk j's (max, sum of exp); the row's max and
   // the rescaled sum are folded across the wave in a fixed butterfly order.  Every workgroup does
@@ -179,13 +182,12 @@ __device__ __forceinline__ void spec_accept_body(const float* __restrict__ p, co
         s_S[row] = S;
       }
     }
+    __syncthreads();
   }
-  __syncthreads();
-  if (tid < k)
-    s_ok[tid] = accept_test(from_logits ? expf(test_p - s_M[tid]) / s_S[tid] : test_p, test_q, un[tid]) ? 1 : 0;
-  __syncthreads();
-  int a = 0;  // the tests count in order, up to the first failure
-  while (a < k && s_ok[a]) ++a;
+  bool fails = false;
+  if (lane < k) fails = !accept_test(from_logits ? expf(test_p - s_M[lane]) / s_S[lane] : test_p, test_q, test_u);
+  const unsigned long long failed = __ballot(fails);  // the tests count in order, up to the first failure
+  const int a = failed != 0 ? __ffsll((long long)failed) - 1 : k;
   const bool residual = a < k;
   const float* pr = p + (size_t)a * V;
   const float* qr = q + (size_t)(residual ? a : 0) * V;
@@ -218,14 +220,14 @@ __device__ __forceinline__ void spec_accept_body(const float* __restrict__ p, co
   __syncthreads();
   if (tid == 0) {
     s_next = kNone;
-    partial[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
-    __threadfence();
-    const unsigned prev = atomicAdd(counter, 1u);
-    s_last = (prev == (unsigned)gridDim.x - 1);
+    // written through to memory, acknowledged, then counted in.  (The counter wraps: it is zero again once
+    // all workgroups of a launch have arrived, whatever they find.)
+    __hip_atomic_store(&partial[blockIdx.x], red[0] + red[1] + red[2] + red[3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    s_last = atomicInc(counter, (unsigned)kScanBlocks - 1u) == (unsigned)kScanBlocks - 1u;
   }
   __syncthreads();
   if (!s_last) return;
-  __threadfence();
 
   // the last workgroup to arrive finishes the draw: lane b of every wave has the sum of chunk b
   static_assert(kScanBlocks == 64, "one chunk sum per lane");
@@ -236,9 +238,9 @@ __device__ __forceinline__ void spec_accept_body(const float* __restrict__ p, co
       result_copy[0] = a;
       result_copy[1] = next;
     }
-    *counter = 0u;
   };
-  const unsigned long long mine = partial[lane], upto = wave_scan_u64(mine), W = shfl_u64(upto, 63);
+  const unsigned long long mine = __hip_atomic_load(&partial[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const unsigned long long upto = wave_scan_u64(mine), W = shfl_u64(upto, 63);
   if (W == 0) {
     // every weight truncated to zero: lowest-index maximum of the target row
     if (tid >= 64) return;
@@ -264,7 +266,7 @@ __device__ __forceinline__ void spec_accept_body(const float* __restrict__ p, co
   const int clo = b * per, chi = min(V, clo + per);
   // The smallest token of the chunk whose running sum exceeds T (the last one if none does): every
   // thread looks through its own tokens, a wave's first finder takes part in the minimum.  Thread 0
-  // reports it, so that a result is written and the counter cleared whatever the sums are.  (The sums
+  // reports it, so that a result is written whatever the sums are.  (The sums
   // between the tokens count, not only those between the threads: weights of distributions with masses
   // beyond 2^24 wrap.)
   for (int base = clo; base < chi; base += kVThreads * kHold) {
