@@ -143,20 +143,17 @@ constexpr size_t stream_lds_bytes(int T) {
   return stream_lds_floats(HD) * sizeof(float) + (size_t)T * (HD / 32) * 2 * 64 * 16 + 16;
 }
 
+// (split: numbered over all clients of the batch; z: group of T tiles)
 template <int HD, int T>
-__global__ __launch_bounds__(kStreamWaves * 64, 2) void attn_stream_kernel(const float* q, KvView kv, int layer, int n_q_heads,
-                                                                      AttnBatch batch, float* part, uint4* outp,
-                                                                      int act_tiles, const int32_t* gate,
-                                                                      unsigned* counters) {
-  extern __shared__ float lds[];
-  if (gate != nullptr && *gate == 0) return;  // (uniform: a round of a chain that does not run)
+__device__ __forceinline__ void attn_stream_body(const float* q, const KvView& kv, int layer, int n_q_heads, const AttnBatch& batch,
+                                                 float* part, uint4* outp, int act_tiles, unsigned* counters, int kvh, int split,
+                                                 int z, float* lds) {
   constexpr int KSQ = HD / 32, HT = HD / 16, ROW = HD + 4;
-  const int kvh = blockIdx.x;
-  int ci = 0, split = blockIdx.y;
+  int ci = 0;
   while (ci + 1 < batch.n && split >= batch.c[ci].nsplit) split -= batch.c[ci++].nsplit;
   const AttnClient cl = batch.c[ci];
   const int group = n_q_heads / kv.n_kv_heads, m = cl.m, R = group * m;
-  const int nqt = (R + 15) / 16, qt0 = (int)blockIdx.z * T;
+  const int nqt = (R + 15) / 16, qt0 = z * T;
   if (split >= cl.nsplit || qt0 >= nqt) return;  // whole workgroup
   float(*o_lds)[16][ROW] = (float(*)[16][ROW])lds;
   float(*m_lds)[16] = (float(*)[16])(lds + (size_t)kStreamWaves * 16 * ROW);
@@ -426,7 +423,7 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void attn_stream_kernel(const
   constexpr int TPR = HD / 8;
   const int mr = tid / TPR, e0 = (tid % TPR) * 8;
   const int nz = (nqt + T - 1) / T;
-  float* gpart = part + cl.part_off + (size_t)(kvh * nz + (int)blockIdx.z) * cl.nsplit * (T * 16 * ROW);
+  float* gpart = part + cl.part_off + (size_t)(kvh * nz + z) * cl.nsplit * (T * 16 * ROW);
 #pragma unroll
   for (int t = 0; t < T; ++t) {
     if (qt0 + t >= nqt) break;
@@ -473,7 +470,7 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void attn_stream_kernel(const
   // ---- count in; the last of the client's splits to arrive merges them ----
   Xwg<true>::drain();  // this thread's partial stores have been acknowledged
   __syncthreads();
-  unsigned* counter = counters + cl.count_off + kvh * nz + (int)blockIdx.z;
+  unsigned* counter = counters + cl.count_off + kvh * nz + z;
   if (tid == 0) {
     const unsigned prev = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int last = prev == (unsigned)cl.nsplit - 1u;
@@ -491,6 +488,397 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void attn_stream_kernel(const
     attn_merge_rows([&](int sp) { return gpart + ((size_t)(sp * T + t) * 16 + mr) * ROW; }, cl.nsplit, HD, e0, acc);
     store_act8x<false>((u32x4*)outp, cl.row_off + r2, head2 * HD + e0, acc, act_tiles);
   }
+}
+
+template <int HD, int T>
+__global__ __launch_bounds__(kStreamWaves * 64, 2) void attn_stream_kernel(const float* q, KvView kv, int layer, int n_q_heads,
+                                                                      AttnBatch batch, float* part, uint4* outp,
+                                                                      int act_tiles, const int32_t* gate,
+                                                                      unsigned* counters) {
+  extern __shared__ float lds[];
+  if (gate != nullptr && *gate == 0) return;  // (uniform: a round of a chain that does not run)
+  attn_stream_body<HD, T>(q, kv, layer, n_q_heads, batch, part, outp, act_tiles, counters, (int)blockIdx.x, (int)blockIdx.y,
+                          (int)blockIdx.z, lds);
+}
+
+// ------------------------------------------------------------------------------------------------
+// bf16 cache, prompt blocks of more than kMaxRows rows
+// ------------------------------------------------------------------------------------------------
+// Workgroup (kv head, four query tiles, split of a block's context) of four waves, a query tile each.  All waves
+// walk the same tokens, 32 per step: a step's keys and values are copied from memory into LDS once for all
+// tiles, two steps ahead, into a ring of three steps, one barrier per step; a wave keeps its queries, its
+// running (max, sum) and its outputs in registers and merges with no other wave.  Keys and values are read from
+// LDS without bank conflicts.
+//
+// What bounds it: instruction issue.  A step is 34 products and about 80 vector instructions per wave, and with two
+// waves of a SIMD at it a product keeps the vector instructions out for about 8 cycles (32 products and 128 multiply-adds
+// take 620 and 603 cycles by themselves, 882 on two waves of a SIMD); three waves per SIMD overlap what can
+// be.  Scores go into the exponential by one fused multiply-add (base 2, the scale folded in), the row sums are products
+// with ones, and the lanes of a row agree on a new maximum, and rescale the outputs, only in steps that bring one.
+// A maximum that only moves once a score exceeds it by 2^8 is faster (73 us where this took 84), but the largest weight of a
+// row is then no exact 1, and its 16 bits (hi + lo) cost precision: error to 64 bits 2.8e-6 instead of 2.6e-6
+// (queries of N(0, 4^2)); with the weights cut into three bf16 exactly it took 89.
+//
+// 8B shape, per layer: 2047 rows 241 -> 81 us, 333 rows behind 1000 tokens 69 -> 38.  The kernel before (the streaming one) gave
+// every (kv head, split, two tiles) a workgroup whose four waves took other tokens each: up to four steps between
+// copies of the queries and a merge of the waves.  Two tiles per wave (half the reads of keys and values, half the
+// workgroups, two waves per SIMD) took 91 where one took 78.
+//
+// A row's result depends on its block's rows and context only.  Partials take the space the streaming kernel's
+// layout with `T` tiles per group gives a tile, their maxima in base 2.
+constexpr int kPromptRing = 3;  // steps in LDS
+template <int HD>
+constexpr size_t prompt_lds_bytes() { return (size_t)kPromptRing * (HD / 8) * 1024 + 16; }
+
+// combine x with the lanes 16 and 32 away
+template <class F>
+__device__ __forceinline__ float across_groups(float x, F f) {
+  typedef __attribute__((ext_vector_type(2))) unsigned u2;
+  const unsigned a = __float_as_uint(x);
+  const u2 p = __builtin_bit_cast(u2, __builtin_amdgcn_permlane16_swap(a, a, false, false));
+  const unsigned b = __float_as_uint(f(__uint_as_float(p.x), __uint_as_float(p.y)));
+  const u2 r = __builtin_bit_cast(u2, __builtin_amdgcn_permlane32_swap(b, b, false, false));
+  return f(__uint_as_float(r.x), __uint_as_float(r.y));
+}
+
+// (y: four tiles, of ny; split: numbered over all blocks of the batch)
+template <int HD>
+__device__ __forceinline__ void attn_prompt_body(const float* q, const KvView& kv, int layer, int n_q_heads, const AttnBatch& batch,
+                                                 int T, float* part, uint4* outp, int act_tiles, unsigned* counters, int kvh,
+                                                 int y, int ny, int split, float* lds) {
+  constexpr int KSQ = HD / 32, HT = HD / 16, ROW = HD + 4;
+  constexpr int NI = HD / 8, NPW = NI / kStreamWaves;  // 1 KB copies of a step (keys, then values), per wave
+  constexpr int kBuf = NI * 1024, kRing = kPromptRing * kBuf;
+  int ci = 0;
+  while (ci + 1 < batch.n && split >= batch.c[ci].nsplit) split -= batch.c[ci++].nsplit;
+  const AttnClient cl = batch.c[ci];
+  const int group = n_q_heads / kv.n_kv_heads, m = cl.m, R = group * m;
+  const int nqt = (R + 15) / 16, qt0 = y * kStreamWaves;
+  if (split >= cl.nsplit || qt0 >= nqt) return;  // whole workgroup
+  char* ring = (char*)lds;
+  int* last_lds = (int*)(ring + kRing);
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int c = lane & 15, g = lane >> 4;
+  const int total = cl.start_pos + m;
+  const int span0 = split * cl.span, span1 = min(total, span0 + cl.span);
+  const int nsteps = (span1 - span0 + kPromptStep - 1) / kPromptStep;
+  const uint16_t* pool = (const uint16_t*)kv.pool;
+  const int32_t* table = kv.table + cl.table_off;
+  const float kscale = 1.44269504088896341f / sqrtf((float)HD);  // scores -> exponents of two
+  const float m_rinv = __builtin_amdgcn_rcpf((float)m);
+  const int qd = n_q_heads * HD;
+
+  // ---- copies ----
+  // k index g*8 + e of the value products is token g*8 + e of the step, so row a of key operand tt is token
+  // (a / 4)*8 + tt*4 + a % 4: a lane's eight scores are then eight tokens in order, as the values have them.  The
+  // copies keep memory's order but for a swap of 16-byte pieces inside a token's (a pair of value halves') row,
+  // piece ^ key_swap(token), so that the reads of the operands meet no bank twice.  Wave w copies its part of
+  // block w / 2 of a step; lane L holds that block's table entry of step 64 n + L.
+  constexpr int PIECES = HD / 8, TPC = 64 / PIECES;  // 16-byte pieces of a token's keys, tokens of a copy
+  auto key_swap = [](int blk, int tok) { return ((tok & 3) | ((tok >> 3) & 1) << 2 | ((blk ^ (tok >> 2)) & 1) << 3) & (PIECES - 1); };
+  const int blk_w = w >> 1, half_w = w & 1;
+  int step_blk = 0;
+  auto look_up = [&](int it) {
+    const int tb = span0 + (it + lane) * kPromptStep + blk_w * kBlockTokens;
+    step_blk = table[tb < total ? tb / kBlockTokens : 0];
+  };
+  look_up(0);
+
+  // ---- this wave's tile: rows, queries (hi and lo operands), first and last position ----
+  const int tile = qt0 + w, rr0 = tile * 16, rr1 = min(rr0 + 15, R - 1);
+  int pos_min = cl.start_pos, pos_max = -1;  // (no such tile: no token to see)
+  if (tile < nqt) {
+    const int h0 = div_small(rr0, m_rinv), h1 = div_small(rr1, m_rinv);
+    pos_min = cl.start_pos + (h0 == h1 ? rr0 - h0 * m : 0);
+    pos_max = cl.start_pos + (h0 == h1 ? rr1 - h1 * m : m - 1);
+  }
+  const int rr = rr0 + c;  // rows beyond the head group read row 0 of the group (their results are dropped)
+  const bool live = rr < R;
+  const int gq = live ? div_small(rr, m_rinv) : 0, r = live ? rr - gq * m : 0;
+  const int pos_q = cl.start_pos + r;
+  au32x4 qr[KSQ][2];
+  {
+    const uint16_t* q16 = (const uint16_t*)q + (size_t)(cl.row_off + r) * 2 * qd + (kvh * group + gq) * HD + g * 8;
+#pragma unroll
+    for (int s = 0; s < KSQ; ++s)
+#pragma unroll
+      for (int hl = 0; hl < 2; ++hl) qr[s][hl] = *(const au32x4*)(q16 + hl * qd + s * 32);
+  }
+
+  unsigned koff[NPW / 2];
+#pragma unroll
+  for (int i = 0; i < NPW / 2; ++i) {
+    const int tok = (half_w * (NPW / 2) + i) * TPC + lane / PIECES;
+    koff[i] = (unsigned)(tok * HD * 2 + ((lane % PIECES) ^ key_swap(blk_w, tok)) * 16);
+  }
+  const unsigned voff = (unsigned)(half_w * (NPW / 2) * 1024 + (lane >> 1) * 32 + ((lane & 1) ^ (((lane >> 3) ^ (lane >> 4)) & 1)) * 16);
+  const unsigned lds0 = (unsigned)(unsigned long long)(__attribute__((address_space(3))) char*)ring;
+  auto request = [&](int it, int buf) {
+    const char* base = (const char*)(pool + (int64_t)layer * kv.layer_stride +
+                                     (int64_t)__builtin_amdgcn_readlane(step_blk, it & 63) * kv.block_elems + (int64_t)kvh * kBlockTokens * HD);
+    const char* vbase = base + kv.v_offset * 2;
+    const unsigned dst = lds0 + (unsigned)(buf + (blk_w * KSQ + half_w * (NPW / 2)) * 1024);
+#pragma unroll
+    for (int i = 0; i < NPW / 2; ++i) {
+      lds_dma16(base, koff[i], dst + i * 1024);
+      lds_dma16(vbase + i * 1024, voff, dst + (2 * KSQ + i) * 1024);
+    }
+  };
+  asm volatile("" : "+v"(step_blk));  // (awaited here; the queries are still on their way)
+  request(0, 0);
+  request(min(1, nsteps - 1), kBuf);
+  // (the queries: a wait for them inside the loop would be one for the copies, in every step)
+  bf16x8 qf[KSQ][2];
+#pragma unroll
+  for (int s = 0; s < KSQ; ++s)
+#pragma unroll
+    for (int hl = 0; hl < 2; ++hl) {
+      asm volatile("" : "+v"(qr[s][hl]));
+      qf[s][hl] = __builtin_bit_cast(bf16x8, qr[s][hl]);
+    }
+
+  // running maximum of query row c: as a score, in base 2, and that or 0.  A lane looks at its own eight scores; the
+  // lanes of a row agree on a new maximum only where one has found a larger score.
+  float lim = -INFINITY, m_run = -INFINITY, m_ref = 0.f;
+  const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 oacc[HT];
+  // sum of the row's weights (four times), by a product with ones: of the weights as the products have them, hi + lo
+  f32x4 lacc = zero;
+  const bf16x8 ones = __builtin_bit_cast(bf16x8, au32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
+#pragma unroll
+  for (int j = 0; j < HT; ++j) oacc[j] = zero;
+  auto rescale = [&](float mx) {
+    mx = across_groups(mx, [](float a, float b) { return fmaxf(a, b); });
+    const bool up = mx > lim;
+    const float m_new = up ? mx * kscale : m_run;
+    const float alpha = up ? __builtin_amdgcn_exp2f(m_run - m_new) : 1.0f;  // (0 for the first tokens a row sees)
+    m_run = m_new;
+    lim = up ? mx : lim;
+    m_ref = m_new == -INFINITY ? 0.f : m_new;  // (a row that has seen no token yet: all weights 0)
+    lacc *= alpha;
+#pragma unroll
+    for (int j = 0; j < HT; ++j) oacc[j] *= alpha;
+  };
+
+  // operands from LDS: byte offsets in a step's buffer
+  int kat[KSQ];
+  {
+    const int blk = c >> 3, tok = ((c >> 2) & 1) * 8 + (c & 3);
+#pragma unroll
+    for (int s = 0; s < KSQ; ++s) kat[s] = (blk * kBlockTokens + tok) * HD * 2 + ((s * 4 + g) ^ key_swap(blk, tok)) * 16;
+  }
+  const int vat = 2 * KSQ * 1024 + (g >> 1) * HD * kBlockTokens * 2 + c * kBlockTokens * 2 + ((g & 1) ^ (((c >> 2) ^ (c >> 3)) & 1)) * 16;
+  // (operand 1's tokens are four rows further; with 16 pieces their swap differs by 8 pieces, which is operand 0's of s ^ 2)
+  auto key = [&](const char* b, int tt, int s) { return *(const bf16x8*)(b + kat[tt == 1 && PIECES == 16 ? s ^ 2 : s] + tt * 4 * HD * 2); };
+  auto value = [&](const char* b, int j) { return *(const au32x4*)(b + vat + j * 16 * kBlockTokens * 2); };
+
+  // one step.  (The order is spelled out: left to itself the compiler reads the operands one by one, each right
+  // before its products.)  edge: not every row sees all 32 tokens, or some are beyond the cached ones.
+  auto step = [&](const char* b, int tok0, auto edge, auto request_next) {
+    constexpr bool EDGE = decltype(edge)::value;
+    bf16x8 kf[2][KSQ];
+    au32x4 vr[HT];
+#pragma unroll
+    for (int s = 0; s < KSQ; ++s)
+#pragma unroll
+      for (int tt = 0; tt < 2; ++tt) kf[tt][s] = key(b, tt, s);
+    __builtin_amdgcn_sched_barrier(0);
+    request_next();
+    __builtin_amdgcn_sched_barrier(0);
+    f32x4 sa[2];
+#pragma unroll
+    for (int s = 0; s < KSQ; ++s) {
+#pragma unroll
+      for (int hl = 0; hl < 2; ++hl)
+#pragma unroll
+        for (int tt = 0; tt < 2; ++tt)
+          sa[tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[tt][s], qf[s][hl], s == 0 && hl == 0 ? zero : sa[tt], 0, 0, 0);
+      if (!EDGE && s == KSQ / 2 - 1) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < HT; ++j) vr[j] = value(b, j);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    float sc[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      sc[i] = sa[i >> 2][i & 3];
+      if constexpr (EDGE) sc[i] = tok0 + g * 8 + i > pos_q ? -INFINITY : sc[i];
+    }
+    float mx = sc[0];
+#pragma unroll
+    for (int i = 1; i < 8; ++i) mx = fmaxf(mx, sc[i]);
+    if (__builtin_amdgcn_ballot_w64(mx > lim) != 0) rescale(mx);
+    float pv[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) pv[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[i], kscale, -m_ref));
+    bf16x8 phi, plo;
+    split_hi_lo8(pv, phi, plo);
+    if constexpr (EDGE) {
+#pragma unroll
+      for (int j = 0; j < HT; ++j) vr[j] = value(b, j);  // (read no earlier: registers)
+      // values of tokens at or beyond `total` read as zero (their weights are exact zeros, but what the cache
+      // holds there need not be a number)
+      const int nvalid = total - (tok0 + g * 8);
+      unsigned keep[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) keep[i] = (2 * i < nvalid ? 0xffffu : 0u) | (2 * i + 1 < nvalid ? 0xffff0000u : 0u);
+#pragma unroll
+      for (int j = 0; j < HT; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) vr[j][i] &= keep[i];
+    }
+#pragma unroll
+    for (int j = 0; j < HT; ++j) oacc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vr[j]), phi, oacc[j], 0, 0, 0);
+    lacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, phi, lacc, 0, 0, 0);
+#pragma unroll
+    for (int j = 0; j < HT; ++j) oacc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vr[j]), plo, oacc[j], 0, 0, 0);
+    lacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, plo, lacc, 0, 0, 0);
+    // (the compiler pads no wait states behind products whose results are read in another basic block)
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 15\n\ts_nop 1" ::: "memory");
+  };
+
+  // steps the tile sees in full
+  const int see = min(pos_min + 1, span1) - span0;
+  const int nfull = tile < nqt && see > 0 ? min(nsteps, see / kPromptStep) : 0;
+  int rd = 0, it = 0;
+  auto open_step = [&] {
+    // the step has landed for every wave, and nobody reads the step before any more: its buffer takes the step after the next
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NPW) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  auto request_next = [&] {
+    const int nx = min(it + 2, nsteps - 1);
+    if ((nx & 63) == 0) {
+      look_up(nx);
+      asm volatile("" : "+v"(step_blk));  // (awaited here: at the join the compiler would wait in every step, for the copies as well)
+    }
+    request(nx, rd == 0 ? 2 * kBuf : rd - kBuf);
+    rd = rd == kRing - kBuf ? 0 : rd + kBuf;
+  };
+#pragma unroll 1
+  for (; it < nfull; ++it) {
+    open_step();
+    step(ring + rd, 0, std::false_type{}, request_next);
+  }
+  const int nseen = pos_max < span0 ? 0 : min(nsteps, (pos_max - span0) / kPromptStep + 1);
+#pragma unroll 1
+  for (; it < nseen; ++it) {
+    open_step();
+    step(ring + rd, span0 + it * kPromptStep, std::true_type{}, request_next);
+  }
+#pragma unroll 1
+  for (; it < nsteps; ++it) {  // (other waves' tiles see more)
+    open_step();
+    request_next();
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (copies asked for past the end land before the LDS is given back)
+
+  // ---- rows whose context is one split are finished; others leave a partial, and the workgroup whose split
+  // arrives last merges them: its own outputs are still in its registers, the others' come from memory.  (With the
+  // merge spread over all threads of the workgroup, every split read: 14 us for two splits of a block, 6 this way.)
+  const size_t split_floats = (size_t)T * 16 * ROW;
+  float l_row = lacc[0];
+  // the tile's partial: [element j*16 + g*4 .. + 3][lane], whole kilobytes, then (max, sum) of its 16 rows
+  float* tpart = part + cl.part_off + (size_t)(kvh * ((nqt + T - 1) / T) + tile / T) * cl.nsplit * split_floats + (size_t)(tile % T) * 16 * ROW;
+  if (cl.nsplit > 1) {
+    if (tile < nqt) {
+      float* dst = tpart + split * split_floats;
+#pragma unroll
+      for (int j = 0; j < HT; ++j) Xwg<true>::st4f(dst + (j * 64 + lane) * 4, oacc[j]);
+      if (g == 0) Xwg<true>::st4f(dst + (HT * 64 + c) * 4, f32x4{m_run, l_row, 0.f, 0.f});
+    }
+    Xwg<true>::drain();  // this thread's partial stores have been acknowledged
+    __syncthreads();
+    unsigned* counter = counters + cl.count_off + kvh * ny + y;
+    if (tid == 0) {
+      const unsigned prev = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int last = prev == (unsigned)cl.nsplit - 1u;
+      if (last) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ready for the next launch
+      *last_lds = last;
+    }
+    __syncthreads();
+    if (*last_lds == 0) return;
+    if (tile < nqt) {
+      struct Part {
+        f32x4 o[HT], ml;
+      };
+      auto fetch = [&](Part& p, int s) {
+        const f32x4* ps = (const f32x4*)(tpart + (size_t)s * split_floats);
+        p.ml = ps[HT * 64 + c];
+#pragma unroll
+        for (int j = 0; j < HT; ++j) p.o[j] = ps[j * 64 + lane];
+      };
+      Part p;
+      fetch(p, 0);
+      float M = m_run;
+      for (int s0 = 0; s0 < cl.nsplit; s0 += 4) {
+        float ms[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ms[i] = tpart[(size_t)min(s0 + i, cl.nsplit - 1) * split_floats + (HT * 64 + c) * 4];
+        M = fmaxf(fmaxf(M, fmaxf(ms[0], ms[1])), fmaxf(ms[2], ms[3]));
+      }
+      f32x4 o[HT];
+#pragma unroll
+      for (int j = 0; j < HT; ++j) o[j] = zero;
+      float L = 0.f;
+      auto add = [&](const f32x4 (&os)[HT], float m_s, float l_s) {
+        const float wgt = __builtin_amdgcn_exp2f(m_s - M);
+        L += l_s * wgt;
+#pragma unroll
+        for (int j = 0; j < HT; ++j) o[j] += os[j] * wgt;
+      };
+      for (int s = 0; s < cl.nsplit; ++s) {  // in index order, whoever came last
+        Part nx;
+        fetch(nx, min(s + 1, cl.nsplit - 1));
+        if (s == split) add(oacc, m_run, l_row);
+        else add(p.o, p.ml[0], p.ml[1]);
+        p = nx;
+      }
+#pragma unroll
+      for (int j = 0; j < HT; ++j) oacc[j] = o[j];
+      l_row = L;
+    }
+  }
+  if (tile >= nqt) return;
+  const float inv = 1.0f / l_row;  // (the quotients are cut to 16 bits)
+#pragma unroll
+  for (int j = 0; j < HT; ++j) {
+    const f32x4 y = oacc[j] * inv, y2 = shfl4(y, lane + 16);  // (elements + 4 .. + 7 of the 8)
+    const float y8[8] = {y[0], y[1], y[2], y[3], y2[0], y2[1], y2[2], y2[3]};
+    if (live && (g & 1) == 0) store_act8x<false>((u32x4*)outp, cl.row_off + r, (kvh * group + gq) * HD + j * 16 + g * 4, y8, act_tiles);
+  }
+}
+
+// (the last blocks have the longest contexts: their workgroups start first)
+template <int HD>
+__global__ __launch_bounds__(kStreamWaves * 64, 3) void attn_prompt_kernel(const float* q, KvView kv, int layer, int n_q_heads,
+                                                                           AttnBatch batch, int T, float* part, uint4* outp,
+                                                                           int act_tiles, unsigned* counters) {
+  extern __shared__ float lds[];
+  attn_prompt_body<HD>(q, kv, layer, n_q_heads, batch, T, part, outp, act_tiles, counters, (int)blockIdx.x, (int)blockIdx.y,
+                       (int)gridDim.y, (int)(gridDim.z - 1 - blockIdx.z), lds);
+}
+
+// A prompt whose last block the streaming kernel takes: both in one launch, side by side (150 rows behind 700
+// tokens at the 8B shape, a layer: 265 us before the prompt kernel, 269 with two launches, 253 in one).
+// Workgroups 0 .. ny * splits - 1 of a KV head are the prompt blocks', the others the last block's.
+template <int HD>
+__global__ __launch_bounds__(kStreamWaves * 64, 2) void attn_prompt_mixed_kernel(const float* q, KvView kv, int layer, int n_q_heads,
+                                                                                 AttnBatch blocks, int ny, int splits, AttnBatch few,
+                                                                                 int few_splits, float* part, uint4* outp,
+                                                                                 int act_tiles, unsigned* counters) {
+  extern __shared__ float lds[];
+  const int i = (int)blockIdx.y, n = ny * splits;
+  if (i < n)
+    attn_prompt_body<HD>(q, kv, layer, n_q_heads, blocks, 1, part, outp, act_tiles, counters, (int)blockIdx.x, i % ny, ny,
+                         splits - 1 - i / ny, lds);
+  else
+    attn_stream_body<HD, 1>(q, kv, layer, n_q_heads, few, part, outp, act_tiles, counters, (int)blockIdx.x, (i - n) % few_splits,
+                            (i - n) / few_splits, lds);
 }
 
 // grid = (threads of the largest client / 64, clients)
@@ -560,24 +948,58 @@ hipError_t launch_attention(const AttnCall& c, hipStream_t st) {
       max_m = b.c[i].m > max_m ? b.c[i].m : max_m;
       tasks += (long)c.kv.n_kv_heads * b.c[i].nsplit * ((group * b.c[i].m + 15) / 16);
     }
-    if (c.stream_tiles) {  // few rows per client: the streaming kernel (the batch was planned by attn_stream_plan)
+    if (c.stream_tiles) {  // the streaming kernels (the batch was planned by attn_stream_plan)
       const int T = c.stream_tiles;
       if ((h != 128 && h != 64) || max_m > kPromptBlockRows || (T != 1 && T != 2) || c.counters == nullptr) return hipErrorInvalidValue;
-      for (int i = 0; i < b.n; ++i)  // (a lane per step holds the step's block-table entries)
-        if (b.c[i].span < kStreamWgTokens || b.c[i].span > kStreamMaxSteps * kStreamWgTokens) return hipErrorInvalidValue;
-      const int nz = ((group * max_m + 15) / 16 + T - 1) / T;
-      const dim3 grid(c.kv.n_kv_heads, splits, nz), block(kStreamWaves * 64);
+      // prompt blocks, and what the streaming kernel takes of them (the last block of a prompt may be of few rows)
+      AttnBatch few{}, blocks{};
+      int few_m = 1, few_splits = 0, blocks_m = 1, block_splits = 0;
+      for (int i = 0; i < b.n; ++i) {
+        const AttnClient& cl = b.c[i];
+        if (!attn_few_rows(group, c.kv.n_kv_heads, cl.m, cl.start_pos + cl.m)) {
+          if (cl.span < kPromptStep || cl.span % kPromptStep != 0) return hipErrorInvalidValue;
+          blocks.c[blocks.n++] = cl;
+          blocks_m = std::max(blocks_m, (int)cl.m);
+          block_splits += cl.nsplit;
+        } else {
+          // (a lane per step holds the step's block-table entries)
+          if (cl.span < kStreamWgTokens || cl.span > kStreamMaxSteps * kStreamWgTokens) return hipErrorInvalidValue;
+          few.c[few.n++] = cl;
+          few_m = std::max(few_m, (int)cl.m);
+          few_splits += cl.nsplit;
+        }
+      }
+      using std::integral_constant;
+      if (blocks.n > 0) {
+        if (c.gate != nullptr) return hipErrorInvalidValue;
+        const int ny = (attn_query_tiles(group, blocks_m) + kStreamWaves - 1) / kStreamWaves, nf = attn_query_tiles(group, few_m) * few_splits;
+        if (few.n > 0 && T != 1) return hipErrorInvalidValue;
+        auto go = [&](auto hd) -> hipError_t {
+          constexpr int HD = decltype(hd)::value;
+          constexpr size_t lds = prompt_lds_bytes<HD>(), lds_mixed = std::max(lds, stream_lds_bytes<HD>(1));
+          static_assert(lds_mixed <= 64 * 1024, "no limit to raise");
+          if (few.n == 0)
+            attn_prompt_kernel<HD><<<dim3(c.kv.n_kv_heads, ny, block_splits), kStreamWaves * 64, lds, st>>>(
+                c.q, c.kv, c.layer, c.n_q_heads, blocks, T, c.part, (uint4*)c.outp, c.act_tiles, c.counters);
+          else
+            attn_prompt_mixed_kernel<HD><<<dim3(c.kv.n_kv_heads, ny * block_splits + nf), kStreamWaves * 64, lds_mixed, st>>>(
+                c.q, c.kv, c.layer, c.n_q_heads, blocks, ny, block_splits, few, few_splits, c.part, (uint4*)c.outp, c.act_tiles, c.counters);
+          return hipGetLastError();
+        };
+        return h == 128 ? go(integral_constant<int, 128>{}) : go(integral_constant<int, 64>{});
+      }
+      const int nz = (attn_query_tiles(group, few_m) + T - 1) / T;
+      const dim3 grid(c.kv.n_kv_heads, few_splits, nz), block(kStreamWaves * 64);
       auto go = [&](auto hd, auto t) -> hipError_t {
         constexpr int HD = decltype(hd)::value, TT = decltype(t)::value;
         static std::atomic<uint64_t> lds_allowed;
         constexpr size_t lds = stream_lds_bytes<HD>(TT);
         const hipError_t e = allow_lds(lds_allowed, (const void*)attn_stream_kernel<HD, TT>, lds);
         if (e != hipSuccess) return e;
-        attn_stream_kernel<HD, TT><<<grid, block, lds, st>>>(c.q, c.kv, c.layer, c.n_q_heads, b, c.part, (uint4*)c.outp, c.act_tiles,
+        attn_stream_kernel<HD, TT><<<grid, block, lds, st>>>(c.q, c.kv, c.layer, c.n_q_heads, few, c.part, (uint4*)c.outp, c.act_tiles,
                                                              c.gate, c.counters);
         return hipGetLastError();
       };
-      using std::integral_constant;
       if (h == 128) return T == 2 ? go(integral_constant<int, 128>{}, integral_constant<int, 2>{}) : go(integral_constant<int, 128>{}, integral_constant<int, 1>{});
       return T == 2 ? go(integral_constant<int, 64>{}, integral_constant<int, 2>{}) : go(integral_constant<int, 64>{}, integral_constant<int, 1>{});
     }
