@@ -26,8 +26,6 @@ constexpr int kStreamMaxSteps = 64;            // steps of a split (a lane per s
 constexpr int kStreamMinSpan = 256;            // a client's context is cut into at most kStreamMaxSplits
 constexpr int kStreamMaxSplits = 16;           // splits of 256 * 2^j tokens, j as small as that allows
 constexpr int kPromptStep = 32;                // prompt kernel: tokens per step
-constexpr int kPromptMinSpan = 256;            // a block's context is cut into spans of at least this many
-constexpr int kPromptFewTiles = 128, kPromptFewTokens = 2048;  // blocks the streaming kernel keeps: fewer tiles, up to as many tokens
 constexpr int kAttnCounters = kMaxPassClients * 512;  // arrival counters
 
 struct AttnClient {
@@ -39,6 +37,9 @@ struct AttnClient {
 struct AttnBatch {
   int32_t n;
   AttnClient c[kMaxPassClients];
+};
+struct PromptShares {
+  int32_t n[kMaxPassClients];  // workgroups that share a client's spans
 };
 
 // the batch of a prompt's attention: its blocks of 128 rows, one "client" each
@@ -56,31 +57,19 @@ static_assert(kMaxPromptRows <= kMaxPassClients * kPromptBlockRows, "a prompt's 
 
 inline int attn_query_tiles(int group, int m) { return (group * m + 15) / 16; }  // of the rows that share a KV head
 
-// Rows of one client, or a block of a prompt, that the streaming kernel takes: as many as a round can have, and
-// blocks that would leave the prompt kernel with few workgroups of many steps: fewer than 128 query tiles (32
-// workgroups) behind up to 2048 tokens, or less than a full block at a context of 128 tokens, which the streaming
-// kernel's four waves see in one step.  8B shape, microseconds on the streaming / the prompt kernel: 48 rows behind 1,
-// 128, 300 and 900 tokens 5.7 / 6.8, 8.2 / 9.4, 11.2 / 13.2, 14.6 / 18.0; 128 rows behind 1, 128, 300 and 900 6.2 / 7.7,
-// 15.0 / 11.0, 15.5 / 15.0, 27 / 28; 300 rows behind 1, 64 and 900 16 / 13, 22 / 15, 48 / 36.  (Both kinds of a prompt's blocks
-// share a launch.)
-inline bool attn_few_rows(int group, int n_kv_heads, int m, int64_t total) {
-  return m <= kMaxRows || (m < kPromptBlockRows && total <= kPromptBlockRows) ||
-         (total <= kPromptFewTokens && n_kv_heads * attn_query_tiles(group, m) < kPromptFewTiles);
-}
-
-// Splits wanted of another block at a context of `total` tokens: by the block alone (its results do not depend on
-// how many blocks of the prompt share the pass), spans of 2048 tokens for a full block, of 8 per row for a
-// last one, and no more than leave a workgroup per pair of tiles two of a compute unit (the partials' memory).  A
-// split costs its partials' way through memory and their merge, about 6 us: 2047 rows at the 8B shape 85 us with spans
-// of 2048 tokens, 101 with 1024, 124 with 512; 128 rows behind 2900 tokens 41, 36, 38.
+// Splits wanted of a prompt block of m rows (33 .. 128) at a context of `total` tokens.  The query tiles
+// alone give many workgroups, so the context is cut only as far as it takes for the block by itself to
+// have about two workgroups per compute unit (by itself: its results do not depend on how many blocks
+// of the prompt share the pass), and as far as a split's largest number of steps asks for.
 inline long prompt_block_splits(int group, int n_kv_heads, int m, int64_t total, int n_cu) {
-  const long span = m == kPromptBlockRows ? 2048 : std::max(kPromptMinSpan, 8 * m);
-  const long most = 2L * n_cu / (n_kv_heads * ((attn_query_tiles(group, m) + 1) / 2));
-  return std::max(1L, std::min({(long)kStreamMaxSplits, most, (long)((total + span - 1) / span)}));
+  const long groups = (long)n_kv_heads * ((attn_query_tiles(group, m) + 1) / 2);
+  const long fit = (long)((total + kStreamMaxSteps * kStreamWgTokens - 1) / (kStreamMaxSteps * kStreamWgTokens));
+  return std::max(fit, std::min((long)kStreamMaxSplits, 2L * n_cu / groups));
 }
 
 // Passes of at most kMaxRows rows per client, and prompts, whose blocks of up to kPromptBlockRows rows
-// are the clients of the batch (`prompt`), take the streaming kernel (bf16 cache).  Fills span,
+// are the clients of the batch (`prompt`), take the streaming kernel (bf16 cache), or the prompt kernel with the
+// same spans and the same results (attn_prompt_shares).  Fills span,
 // nsplit, part_off and count_off of every client of `b` (row_off, m, start_pos, table_off given) and
 // returns the query tiles per workgroup, or 0 if the pass does not fit (then the split kernels run);
 // *part_floats = size of the partial buffer the launch needs.  A client's split depends on its own
@@ -92,35 +81,32 @@ inline int attn_stream_plan(int n_q_heads, int n_kv_heads, int head_dim, int n_c
   const int group = n_q_heads / n_kv_heads;
   int max_m = 1;
   long tasks = 0;  // (kv head, split, query tile) over all clients
-  bool blocks = false;
   for (int i = 0; i < b.n; ++i) {
     AttnClient& cl = b.c[i];
     if (cl.m > (prompt ? kPromptBlockRows : kMaxRows)) return 0;
     max_m = std::max(max_m, (int)cl.m);
     const int total = cl.start_pos + cl.m;
     cl.span = kStreamMinSpan;
-    if (attn_few_rows(group, n_kv_heads, cl.m, total)) {
+    if (cl.m <= kMaxRows) {
       while ((total + cl.span - 1) / cl.span > kStreamMaxSplits) cl.span *= 2;
     } else {
-      blocks = true;
       const long want = prompt_block_splits(group, n_kv_heads, cl.m, total, n_cu);
-      cl.span = (int)((total + want * kPromptStep - 1) / (want * kPromptStep)) * kPromptStep;
+      const int steps = (total + kStreamMinSpan - 1) / kStreamMinSpan;
+      cl.span = (int)((steps + want - 1) / want) * kStreamMinSpan;
     }
     cl.nsplit = (total + cl.span - 1) / cl.span;
-    if (total > kStreamMaxSplits * kStreamMaxSteps * kStreamWgTokens) return 0;  // (contexts beyond 131072 tokens)
+    if (cl.span > kStreamMaxSteps * kStreamWgTokens || cl.nsplit > kStreamMaxSplits) return 0;  // (contexts beyond 131072 tokens)
     tasks += (long)n_kv_heads * cl.nsplit * attn_query_tiles(group, cl.m);
   }
   // two tiles per workgroup (keys and values read once for both) where a head group has exactly
   // two, or where single tiles would be more workgroups than two rounds of the device
-  // (one where a prompt's last block shares a launch with blocks of the prompt kernel)
   const int max_qt = attn_query_tiles(group, max_m);
-  const int T = !blocks && (max_qt == 2 || tasks > 2L * n_cu) ? 2 : 1;
+  const int T = (max_qt == 2 || tasks > 2L * n_cu) ? 2 : 1;
+  if ((long)n_kv_heads * ((max_qt + T - 1) / T) > kAttnCounters / kMaxPassClients) return 0;
   size_t floats = 0;
   for (int i = 0; i < b.n; ++i) {
     AttnClient& cl = b.c[i];
     if (floats > (size_t)INT32_MAX) return 0;
-    const int qt = attn_query_tiles(group, cl.m), per_wg = attn_few_rows(group, n_kv_heads, cl.m, cl.start_pos + cl.m) ? T : kStreamWaves;
-    if ((long)n_kv_heads * ((qt + per_wg - 1) / per_wg) > kAttnCounters / kMaxPassClients) return 0;
     cl.part_off = (int32_t)floats;
     cl.count_off = i * (kAttnCounters / kMaxPassClients);
     const int nz = (attn_query_tiles(group, cl.m) + T - 1) / T;  // (the client's own tiles: the kernel's layout)
@@ -130,12 +116,44 @@ inline int attn_stream_plan(int n_q_heads, int n_kv_heads, int head_dim, int n_c
   return T;
 }
 
+// Which kernel takes a planned pass: 0 for the streaming kernel, else the prompt kernel, with `shares`->n[i] workgroups for
+// (a KV head's four query tiles of) client i, each with spans of its own, and their sum returned.  Either way every
+// row gets the same bits: the rule is about time.  The prompt kernel's workgroups are long (a wave walks all tokens of
+// its spans), so it needs many of them: from 96 groups of four tiles on it is never slower, from 64 on in contexts of 256
+// to 2048 tokens.  Microseconds per layer, streaming / prompt kernel.  8B shape: 128 rows (64 groups) behind 1, 300, 900, 1900 and
+// 6000 tokens 199 / 204, 210 / 209, 220 / 215, 222 / 217, 242 / 243, 129 rows behind 6000 280 / 294; 200 rows (104) behind 1, 900
+// and 6000 254 / 254, 289 / 270, 335 / 330; 333 rows behind 900 420 / 407; 2048 rows 1741 / 1642.  1B shape: 128 rows behind
+// 1 and 900 87 / 90, 101 / 97; 333 behind 900 175 / 166; 2048 675 / 622.  13B shape: 129 rows (120) behind 1, 900 and 6000 344 / 346,
+// 372 / 362, 434 / 431; 2048 3149 / 3047.  The work is cut into about twice as many shares as the device holds workgroups (two per
+// compute unit), none below 8 steps: 2047 rows at the 8B shape 117 us with one share per slot, 113 with two, 120 with four.
+inline int attn_prompt_shares(int group, int n_kv_heads, int n_cu, const AttnBatch& b, PromptShares* shares) {
+  int max_m = 0, most = 0;
+  long groups = 0, work = 0;  // groups of four tiles; steps of all of them
+  auto steps_of = [](const AttnClient& cl) { return (cl.start_pos + cl.m + kPromptStep - 1) / kPromptStep; };
+  for (int i = 0; i < b.n; ++i) {
+    const long g4 = (long)n_kv_heads * ((attn_query_tiles(group, b.c[i].m) + kStreamWaves - 1) / kStreamWaves);
+    max_m = std::max(max_m, (int)b.c[i].m);
+    most = std::max(most, (int)(b.c[i].start_pos + b.c[i].m));
+    groups += g4;
+    work += g4 * steps_of(b.c[i]);
+  }
+  if (max_m <= kMaxRows) return 0;  // (rounds of clients, prompts of a few rows)
+  if (groups < 64 || (groups < 96 && (most < 256 || most > 2048 + kPromptBlockRows))) return 0;
+  const long share_steps = std::max(8L, work / (4L * n_cu));
+  int sum = 0;
+  for (int i = 0; i < b.n; ++i) {
+    shares->n[i] = (int)std::min((long)b.c[i].nsplit, (steps_of(b.c[i]) + share_steps - 1) / share_steps);
+    sum += shares->n[i];
+  }
+  return sum;
+}
+
 // Floats of attention partials that no pass over a pool of `pool_tokens` cached tokens exceeds, but for
 // the ones named below.
 //  * NAV passes: up to `clients` clients of up to `rows` rows, contexts of at most the pool together, split
 //    no finer than `chunk` tokens, a head group's rows rounded up to whole pairs of 16-row tiles.  (An
 //    fp32 model's prompt blocks are such passes, of one client.)
-//  * Prompts of a bf16 model on the prompt and streaming kernels: up to 16 blocks, all of 128 rows but the last, which
+//  * Prompts of a bf16 model on the streaming kernel: up to 16 blocks, all of 128 rows but the last, which
 //    is cut finer the fewer rows it has: the worst number of rows is looked for.
 // Not covered: prompt passes the streaming plan declines (a context beyond 131072 tokens, more than 128
 // query heads) and the partials per layer of the all-layers kernel.  They would make every pool pay for
@@ -148,10 +166,7 @@ inline size_t attn_scratch_floats(int n_q_heads, int n_kv_heads, int head_dim, i
   if (!stream_prompts) return nav;
   const int64_t steps = (pool_tokens + kStreamMinSpan - 1) / kStreamMinSpan;
   auto block_rows = [&](int m) {  // (rows, padded) x splits of a block of m rows behind the longest context
-    // (behind the longest context, or behind the longest at which the streaming kernel takes as many rows)
-    const long want = m <= kMaxRows ? kStreamMaxSplits
-                                    : std::max(prompt_block_splits(group, n_kv_heads, m, pool_tokens, n_cu),
-                                               n_kv_heads * attn_query_tiles(group, m) < kPromptFewTiles ? (long)(kPromptFewTokens / kStreamMinSpan) : 1L);
+    const long want = m <= kMaxRows ? kStreamMaxSplits : prompt_block_splits(group, n_kv_heads, m, pool_tokens, n_cu);
     const int64_t splits = std::min((int64_t)std::min(want, (long)kStreamMaxSplits), steps);
     return (size_t)splits * ((attn_query_tiles(group, m) + 1) / 2 * 2) * 16;
   };

@@ -115,8 +115,8 @@ __global__ __launch_bounds__(kAttnWaves * 64) void attn_mfma_kernel(const float*
 }
 
 // ------------------------------------------------------------------------------------------------
-// bf16 cache, passes of few rows per client (the NAV pass itself) and prompt blocks: one workgroup
-// walks a whole split of the context
+// bf16 cache, passes of few rows per client (the NAV pass itself) and prompt passes of few blocks
+// (attn_prompt_shares): one workgroup walks a whole split of the context
 // ------------------------------------------------------------------------------------------------
 // Workgroup (kv head, split of a client's context, T query tiles) of four waves: wave w takes tokens
 // span0 + it*128 + w*32 .. + 31 in step it and keeps a running (max, sum, O) per query tile in
@@ -143,17 +143,20 @@ constexpr size_t stream_lds_bytes(int T) {
   return stream_lds_floats(HD) * sizeof(float) + (size_t)T * (HD / 32) * 2 * 64 * 16 + 16;
 }
 
-// (split: numbered over all clients of the batch; z: group of T tiles)
 template <int HD, int T>
-__device__ __forceinline__ void attn_stream_body(const float* q, const KvView& kv, int layer, int n_q_heads, const AttnBatch& batch,
-                                                 float* part, uint4* outp, int act_tiles, unsigned* counters, int kvh, int split,
-                                                 int z, float* lds) {
+__global__ __launch_bounds__(kStreamWaves * 64, 2) void attn_stream_kernel(const float* q, KvView kv, int layer, int n_q_heads,
+                                                                      AttnBatch batch, float* part, uint4* outp,
+                                                                      int act_tiles, const int32_t* gate,
+                                                                      unsigned* counters) {
+  extern __shared__ float lds[];
+  if (gate != nullptr && *gate == 0) return;  // (uniform: a round of a chain that does not run)
   constexpr int KSQ = HD / 32, HT = HD / 16, ROW = HD + 4;
-  int ci = 0;
+  const int kvh = blockIdx.x;
+  int ci = 0, split = blockIdx.y;
   while (ci + 1 < batch.n && split >= batch.c[ci].nsplit) split -= batch.c[ci++].nsplit;
   const AttnClient cl = batch.c[ci];
   const int group = n_q_heads / kv.n_kv_heads, m = cl.m, R = group * m;
-  const int nqt = (R + 15) / 16, qt0 = z * T;
+  const int nqt = (R + 15) / 16, qt0 = (int)blockIdx.z * T;
   if (split >= cl.nsplit || qt0 >= nqt) return;  // whole workgroup
   float(*o_lds)[16][ROW] = (float(*)[16][ROW])lds;
   float(*m_lds)[16] = (float(*)[16])(lds + (size_t)kStreamWaves * 16 * ROW);
@@ -423,7 +426,7 @@ __device__ __forceinline__ void attn_stream_body(const float* q, const KvView& k
   constexpr int TPR = HD / 8;
   const int mr = tid / TPR, e0 = (tid % TPR) * 8;
   const int nz = (nqt + T - 1) / T;
-  float* gpart = part + cl.part_off + (size_t)(kvh * nz + z) * cl.nsplit * (T * 16 * ROW);
+  float* gpart = part + cl.part_off + (size_t)(kvh * nz + (int)blockIdx.z) * cl.nsplit * (T * 16 * ROW);
 #pragma unroll
   for (int t = 0; t < T; ++t) {
     if (qt0 + t >= nqt) break;
@@ -470,7 +473,7 @@ __device__ __forceinline__ void attn_stream_body(const float* q, const KvView& k
   // ---- count in; the last of the client's splits to arrive merges them ----
   Xwg<true>::drain();  // this thread's partial stores have been acknowledged
   __syncthreads();
-  unsigned* counter = counters + cl.count_off + kvh * nz + z;
+  unsigned* counter = counters + cl.count_off + kvh * nz + (int)blockIdx.z;
   if (tid == 0) {
     const unsigned prev = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int last = prev == (unsigned)cl.nsplit - 1u;
@@ -490,47 +493,35 @@ __device__ __forceinline__ void attn_stream_body(const float* q, const KvView& k
   }
 }
 
-template <int HD, int T>
-__global__ __launch_bounds__(kStreamWaves * 64, 2) void attn_stream_kernel(const float* q, KvView kv, int layer, int n_q_heads,
-                                                                      AttnBatch batch, float* part, uint4* outp,
-                                                                      int act_tiles, const int32_t* gate,
-                                                                      unsigned* counters) {
-  extern __shared__ float lds[];
-  if (gate != nullptr && *gate == 0) return;  // (uniform: a round of a chain that does not run)
-  attn_stream_body<HD, T>(q, kv, layer, n_q_heads, batch, part, outp, act_tiles, counters, (int)blockIdx.x, (int)blockIdx.y,
-                          (int)blockIdx.z, lds);
-}
-
 // ------------------------------------------------------------------------------------------------
-// bf16 cache, prompt blocks of more than kMaxRows rows
+// bf16 cache, passes of many prompt rows
 // ------------------------------------------------------------------------------------------------
-// Workgroup (kv head, four query tiles, split of a block's context) of four waves, a query tile each.  All waves
-// walk the same tokens, 32 per step: a step's keys and values are copied from memory into LDS once for all
-// tiles, two steps ahead, into a ring of three steps, one barrier per step; a wave keeps its queries, its
-// running (max, sum) and its outputs in registers and merges with no other wave.  Keys and values are read from
-// LDS without bank conflicts.
+// The streaming kernel's results, bit for bit, with keys and values shared by four query tiles: workgroup (kv head,
+// four query tiles, share of a block's spans) of four waves, a query tile each.  All waves walk the same tokens,
+// 32 per step: a step's keys and values are copied from memory into LDS once for all tiles, two steps
+// ahead, into a ring of three steps, one barrier per step.  What the streaming kernel gives its wave w (tokens
+// it*128 + w*32 .. + 31 of every step of a span) is here every fourth step, so a wave keeps four running
+// (max, sum, O), one per wave of the streaming kernel, merges them in the same order at the end of a span and leaves the
+// span's partial in the scratch.  A workgroup that has all spans of its block merges them by itself, every wave its own;
+// if several share them, partials are written through and the last to arrive merges, as in the streaming kernel.
 //
-// What bounds it: instruction issue.  A step is 34 products and about 80 vector instructions per wave, and with two
-// waves of a SIMD at it a product keeps the vector instructions out for about 8 cycles (32 products and 128 multiply-adds
-// take 620 and 603 cycles by themselves, 882 on two waves of a SIMD); three waves per SIMD overlap what can
-// be.  Scores go into the exponential by one fused multiply-add (base 2, the scale folded in), the row sums are products
-// with ones, and the lanes of a row agree on a new maximum, and rescale the outputs, only in steps that bring one.
-// A maximum that only moves once a score exceeds it by 2^8 is faster (73 us where this took 84), but the largest weight of a
-// row is then no exact 1, and its 16 bits (hi + lo) cost precision: error to 64 bits 2.8e-6 instead of 2.6e-6
-// (queries of N(0, 4^2)); with the weights cut into three bf16 exactly it took 89.
+// Every product, sum and rounding is the streaming kernel's own, in its order (the order of tokens inside an operand
+// too); products with weights that are all zero and rescaling of zeros or by 1 are left out, which changes no bit of a
+// finite result.  So which of the two kernels a pass takes, and into how many shares it is cut, is a matter of time alone
+// (attn_prompt_shares), and a row's keys and values do not depend on what other rows its prompt was fed with.
 //
-// 8B shape, per layer: 2047 rows 241 -> 81 us, 333 rows behind 1000 tokens 69 -> 38.  The kernel before (the streaming one) gave
-// every (kv head, split, two tiles) a workgroup whose four waves took other tokens each: up to four steps between
-// copies of the queries and a merge of the waves.  Two tiles per wave (half the reads of keys and values, half the
-// workgroups, two waves per SIMD) took 91 where one took 78.
-//
-// A row's result depends on its block's rows and context only.  Partials take the space the streaming kernel's
-// layout with `T` tiles per group gives a tile, their maxima in base 2.
+// 8B shape, per layer, streaming / this kernel: 2047 rows 241 / 113 us, 333 rows behind 1000 tokens 69 / 39.  Bound by what a step
+// waits for, with few waves to cover it: four states take 254 registers, so two waves share a SIMD (1.6 on average),
+// each going from scores over a maximum, exponentials and cuts to 16 bits to the values' products.  Of
+// the cycles the vector units issue in 47 %, the matrix cores work in 26 %, LDS is read in 33 %, 39 % of those bank conflicts: a
+// lane needs 8 bytes of either block's values, and 16 lanes of such reads meet half of the banks.  Sums grouped otherwise
+// (one state per wave, spans of 2048 tokens, a step's tokens in another order: three waves per SIMD) took 81 us for the 2047
+// rows, but moved cached keys and values by a bf16 step here and there, and with them drawn tokens.
 constexpr int kPromptRing = 3;  // steps in LDS
 template <int HD>
 constexpr size_t prompt_lds_bytes() { return (size_t)kPromptRing * (HD / 8) * 1024 + 16; }
 
-// combine x with the lanes 16 and 32 away
+// combine x with the lanes 16 and 32 away, in the order of two exchanges by xor (f is commutative)
 template <class F>
 __device__ __forceinline__ float across_groups(float x, F f) {
   typedef __attribute__((ext_vector_type(2))) unsigned u2;
@@ -541,48 +532,52 @@ __device__ __forceinline__ float across_groups(float x, F f) {
   return f(__uint_as_float(r.x), __uint_as_float(r.y));
 }
 
-// (y: four tiles, of ny; split: numbered over all blocks of the batch)
+// (grid: kv heads, groups of four tiles of the largest block, shares of all blocks; the last blocks have the longest
+// contexts: their workgroups start first)
 template <int HD>
-__device__ __forceinline__ void attn_prompt_body(const float* q, const KvView& kv, int layer, int n_q_heads, const AttnBatch& batch,
-                                                 int T, float* part, uint4* outp, int act_tiles, unsigned* counters, int kvh,
-                                                 int y, int ny, int split, float* lds) {
+__global__ __launch_bounds__(kStreamWaves * 64, 2) void attn_prompt_kernel(const float* q, KvView kv, int layer, int n_q_heads,
+                                                                           AttnBatch batch, PromptShares shares, float* part,
+                                                                           uint4* outp, int act_tiles, unsigned* counters) {
+// (a product and a sum make one operation exactly where they do in the streaming kernel: spelled out)
+#pragma clang fp contract(off)
+  extern __shared__ float lds[];
   constexpr int KSQ = HD / 32, HT = HD / 16, ROW = HD + 4;
   constexpr int NI = HD / 8, NPW = NI / kStreamWaves;  // 1 KB copies of a step (keys, then values), per wave
   constexpr int kBuf = NI * 1024, kRing = kPromptRing * kBuf;
-  int ci = 0;
-  while (ci + 1 < batch.n && split >= batch.c[ci].nsplit) split -= batch.c[ci++].nsplit;
+  const int kvh = blockIdx.x;
+  int ci = 0, share = (int)(gridDim.z - 1 - blockIdx.z);
+  while (share >= shares.n[ci]) share -= shares.n[ci++];
   const AttnClient cl = batch.c[ci];
+  const int n_shares = shares.n[ci];
   const int group = n_q_heads / kv.n_kv_heads, m = cl.m, R = group * m;
-  const int nqt = (R + 15) / 16, qt0 = y * kStreamWaves;
-  if (split >= cl.nsplit || qt0 >= nqt) return;  // whole workgroup
+  const int nqt = (R + 15) / 16, qt0 = (int)blockIdx.y * kStreamWaves;
+  if (qt0 >= nqt) return;  // whole workgroup
   char* ring = (char*)lds;
-  int* last_lds = (int*)(ring + kRing);
   const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int c = lane & 15, g = lane >> 4;
   const int total = cl.start_pos + m;
-  const int span0 = split * cl.span, span1 = min(total, span0 + cl.span);
-  const int nsteps = (span1 - span0 + kPromptStep - 1) / kPromptStep;
+  // this workgroup's spans, and the steps (of the whole context) they end with
+  const int sp0 = share * cl.nsplit / n_shares, sp1 = (share + 1) * cl.nsplit / n_shares, span_steps = cl.span / kPromptStep;
+  const int nsteps = min((total + kPromptStep - 1) / kPromptStep, sp1 * span_steps);
   const uint16_t* pool = (const uint16_t*)kv.pool;
   const int32_t* table = kv.table + cl.table_off;
-  const float kscale = 1.44269504088896341f / sqrtf((float)HD);  // scores -> exponents of two
+  const float scale = 1.0f / sqrtf((float)HD);
   const float m_rinv = __builtin_amdgcn_rcpf((float)m);
   const int qd = n_q_heads * HD;
 
-  // ---- copies ----
-  // k index g*8 + e of the value products is token g*8 + e of the step, so row a of key operand tt is token
-  // (a / 4)*8 + tt*4 + a % 4: a lane's eight scores are then eight tokens in order, as the values have them.  The
-  // copies keep memory's order but for a swap of 16-byte pieces inside a token's (a pair of value halves') row,
-  // piece ^ key_swap(token), so that the reads of the operands meet no bank twice.  Wave w copies its part of
-  // block w / 2 of a step; lane L holds that block's table entry of step 64 n + L.
+  // ---- copies: in memory's order but for a swap of 16-byte pieces inside a token's keys (a pair of value halves), so
+  // that the reads of the operands meet no bank twice.  Wave w copies half w % 2 of block w / 2 of a step; lane L
+  // holds that block's table entry of step 64 n + L. ----
   constexpr int PIECES = HD / 8, TPC = 64 / PIECES;  // 16-byte pieces of a token's keys, tokens of a copy
-  auto key_swap = [](int blk, int tok) { return ((tok & 3) | ((tok >> 3) & 1) << 2 | ((blk ^ (tok >> 2)) & 1) << 3) & (PIECES - 1); };
+  auto key_swap = [](int tok) { return PIECES == 16 ? tok : (tok >> 1) & (PIECES - 1); };
   const int blk_w = w >> 1, half_w = w & 1;
   int step_blk = 0;
   auto look_up = [&](int it) {
-    const int tb = span0 + (it + lane) * kPromptStep + blk_w * kBlockTokens;
+    const int tb = (it + lane) * kPromptStep + blk_w * kBlockTokens;
     step_blk = table[tb < total ? tb / kBlockTokens : 0];
   };
-  look_up(0);
+  int it = sp0 * span_steps;
+  look_up(it & ~63);
 
   // ---- this wave's tile: rows, queries (hi and lo operands), first and last position ----
   const int tile = qt0 + w, rr0 = tile * 16, rr1 = min(rr0 + 15, R - 1);
@@ -609,24 +604,24 @@ __device__ __forceinline__ void attn_prompt_body(const float* q, const KvView& k
 #pragma unroll
   for (int i = 0; i < NPW / 2; ++i) {
     const int tok = (half_w * (NPW / 2) + i) * TPC + lane / PIECES;
-    koff[i] = (unsigned)(tok * HD * 2 + ((lane % PIECES) ^ key_swap(blk_w, tok)) * 16);
+    koff[i] = (unsigned)(tok * HD * 2 + ((lane % PIECES) ^ key_swap(tok)) * 16);
   }
-  const unsigned voff = (unsigned)(half_w * (NPW / 2) * 1024 + (lane >> 1) * 32 + ((lane & 1) ^ (((lane >> 3) ^ (lane >> 4)) & 1)) * 16);
+  const unsigned voff = (unsigned)((lane >> 1) * 32 + ((lane & 1) ^ ((lane >> 4) & 1) ^ (lane >> 5)) * 16);
   const unsigned lds0 = (unsigned)(unsigned long long)(__attribute__((address_space(3))) char*)ring;
   auto request = [&](int it, int buf) {
     const char* base = (const char*)(pool + (int64_t)layer * kv.layer_stride +
                                      (int64_t)__builtin_amdgcn_readlane(step_blk, it & 63) * kv.block_elems + (int64_t)kvh * kBlockTokens * HD);
-    const char* vbase = base + kv.v_offset * 2;
-    const unsigned dst = lds0 + (unsigned)(buf + (blk_w * KSQ + half_w * (NPW / 2)) * 1024);
+    const char* vbase = base + kv.v_offset * 2 + half_w * (NPW / 2) * 1024;
+    const unsigned dst = lds0 + (unsigned)buf;
 #pragma unroll
     for (int i = 0; i < NPW / 2; ++i) {
-      lds_dma16(base, koff[i], dst + i * 1024);
-      lds_dma16(vbase + i * 1024, voff, dst + (2 * KSQ + i) * 1024);
+      lds_dma16(base, koff[i], dst + (blk_w * KSQ + half_w * (NPW / 2) + i) * 1024);
+      lds_dma16(vbase + i * 1024, voff, dst + (2 * KSQ + (half_w * (NPW / 2) + i) * 2 + blk_w) * 1024);
     }
   };
   asm volatile("" : "+v"(step_blk));  // (awaited here; the queries are still on their way)
-  request(0, 0);
-  request(min(1, nsteps - 1), kBuf);
+  request(it, 0);
+  request(min(it + 1, nsteps - 1), kBuf);
   // (the queries: a wait for them inside the loop would be one for the copies, in every step)
   bf16x8 qf[KSQ][2];
 #pragma unroll
@@ -637,44 +632,32 @@ __device__ __forceinline__ void attn_prompt_body(const float* q, const KvView& k
       qf[s][hl] = __builtin_bit_cast(bf16x8, qr[s][hl]);
     }
 
-  // running maximum of query row c: as a score, in base 2, and that or 0.  A lane looks at its own eight scores; the
-  // lanes of a row agree on a new maximum only where one has found a larger score.
-  float lim = -INFINITY, m_run = -INFINITY, m_ref = 0.f;
-  const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
-  f32x4 oacc[HT];
-  // sum of the row's weights (four times), by a product with ones: of the weights as the products have them, hi + lo
-  f32x4 lacc = zero;
-  const bf16x8 ones = __builtin_bit_cast(bf16x8, au32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
-#pragma unroll
-  for (int j = 0; j < HT; ++j) oacc[j] = zero;
-  auto rescale = [&](float mx) {
-    mx = across_groups(mx, [](float a, float b) { return fmaxf(a, b); });
-    const bool up = mx > lim;
-    const float m_new = up ? mx * kscale : m_run;
-    const float alpha = up ? __builtin_amdgcn_exp2f(m_run - m_new) : 1.0f;  // (0 for the first tokens a row sees)
-    m_run = m_new;
-    lim = up ? mx : lim;
-    m_ref = m_new == -INFINITY ? 0.f : m_new;  // (a row that has seen no token yet: all weights 0)
-    lacc *= alpha;
-#pragma unroll
-    for (int j = 0; j < HT; ++j) oacc[j] *= alpha;
+  // operands from LDS: byte offsets in a step's buffer
+  const int kat = c * HD * 2 + (g ^ key_swap(c)) * 16;  // (pieces 4 s + g of a token: the same with bits flipped)
+  // (values: kilobytes of 32 elements' rows, of one block and of the other; element row e has its halves swapped if bits 3
+  // and 4 of e differ.  Both blocks' parts of an operand are read by one instruction: rows e and e + 16 swapped alike
+  // would have the compiler pair those instead, and copy registers behind.)
+  const int vat = 2 * KSQ * 1024 + c * kBlockTokens * 2 + (g & 1) * 8;
+  const int vat0 = vat + ((g >> 1) ^ (c >> 3)) * 16, vat1 = vat + 512 + ((g >> 1) ^ (c >> 3) ^ 1) * 16;
+  auto key = [&](int b, int tt, int s) { return *(const bf16x8*)(ring + ((b + kat) ^ (s * 64)) + tt * KSQ * 1024); };
+  auto value = [&](int b, int j) {
+    const char* p = ring + (b + ((j & 1) ? vat1 : vat0)) + (j >> 1) * 2048;
+    const au32x2 lo = *(const au32x2*)p, hi = *(const au32x2*)(p + 1024);
+    return au32x4{lo.x, lo.y, hi.x, hi.y};
   };
 
-  // operands from LDS: byte offsets in a step's buffer
-  int kat[KSQ];
-  {
-    const int blk = c >> 3, tok = ((c >> 2) & 1) * 8 + (c & 3);
-#pragma unroll
-    for (int s = 0; s < KSQ; ++s) kat[s] = (blk * kBlockTokens + tok) * HD * 2 + ((s * 4 + g) ^ key_swap(blk, tok)) * 16;
-  }
-  const int vat = 2 * KSQ * 1024 + (g >> 1) * HD * kBlockTokens * 2 + c * kBlockTokens * 2 + ((g & 1) ^ (((c >> 2) ^ (c >> 3)) & 1)) * 16;
-  // (operand 1's tokens are four rows further; with 16 pieces their swap differs by 8 pieces, which is operand 0's of s ^ 2)
-  auto key = [&](const char* b, int tt, int s) { return *(const bf16x8*)(b + kat[tt == 1 && PIECES == 16 ? s ^ 2 : s] + tt * 4 * HD * 2); };
-  auto value = [&](const char* b, int j) { return *(const au32x4*)(b + vat + j * 16 * kBlockTokens * 2); };
+  // the running state of query row c over the tokens of one wave of the streaming kernel
+  struct State {
+    f32x4 o[HT];
+    float m, l;
+  };
+  const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
+  State st[kStreamWaves];
 
-  // one step.  (The order is spelled out: left to itself the compiler reads the operands one by one, each right
-  // before its products.)  edge: not every row sees all 32 tokens, or some are beyond the cached ones.
-  auto step = [&](const char* b, int tok0, auto edge, auto request_next) {
+  // One step.  (The order is spelled out: left to itself the compiler reads the operands one by one, each right
+  // before its products.)  edge: not every row sees all 32 tokens, or some are beyond the cached ones.  The lanes of a
+  // row agree on a new maximum, and rescale, only in steps that bring one.  first: the state is still empty.
+  auto step = [&](State& x, int b, int tok0, bool first, auto edge, auto request_next) {
     constexpr bool EDGE = decltype(edge)::value;
     bf16x8 kf[2][KSQ];
     au32x4 vr[HT];
@@ -703,16 +686,31 @@ __device__ __forceinline__ void attn_prompt_body(const float* q, const KvView& k
     float sc[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      sc[i] = sa[i >> 2][i & 3];
-      if constexpr (EDGE) sc[i] = tok0 + g * 8 + i > pos_q ? -INFINITY : sc[i];
+      sc[i] = sa[i >> 2][i & 3] * scale;
+      if constexpr (EDGE) sc[i] = tok0 + (i >> 2) * 16 + g * 4 + (i & 3) > pos_q ? -INFINITY : sc[i];
     }
     float mx = sc[0];
 #pragma unroll
     for (int i = 1; i < 8; ++i) mx = fmaxf(mx, sc[i]);
-    if (__builtin_amdgcn_ballot_w64(mx > lim) != 0) rescale(mx);
-    float pv[8];
+    float alpha = 1.0f;
+    if (__builtin_amdgcn_ballot_w64(mx > x.m) != 0) {
+      const float m_new = fmaxf(across_groups(mx, [](float a, float b) { return fmaxf(a, b); }), x.m);
+      alpha = attn_exp(x.m - (m_new == -INFINITY ? 0.f : m_new));  // (0 for the first tokens a row sees)
+      x.m = m_new;
+      if (!first) {  // (uniform)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) pv[i] = __builtin_amdgcn_exp2f(__builtin_fmaf(sc[i], kscale, -m_ref));
+        for (int j = 0; j < HT; ++j) x.o[j] *= alpha;
+      }
+    }
+    const float m_ref = x.m == -INFINITY ? 0.f : x.m;  // a row that has seen no token yet: all weights 0
+    float pv[8], l_step = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      pv[i] = attn_exp(sc[i] - m_ref);
+      l_step += pv[i];
+    }
+    l_step = across_groups(l_step, [](float a, float b) { return a + b; });
+    x.l = __builtin_fmaf(x.l, alpha, l_step);
     bf16x8 phi, plo;
     split_hi_lo8(pv, phi, plo);
     if constexpr (EDGE) {
@@ -720,33 +718,29 @@ __device__ __forceinline__ void attn_prompt_body(const float* q, const KvView& k
       for (int j = 0; j < HT; ++j) vr[j] = value(b, j);  // (read no earlier: registers)
       // values of tokens at or beyond `total` read as zero (their weights are exact zeros, but what the cache
       // holds there need not be a number)
-      const int nvalid = total - (tok0 + g * 8);
       unsigned keep[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) keep[i] = (2 * i < nvalid ? 0xffffu : 0u) | (2 * i + 1 < nvalid ? 0xffff0000u : 0u);
+      for (int i = 0; i < 4; ++i) {
+        const int nvalid = total - (tok0 + (i >> 1) * 16 + g * 4 + (i & 1) * 2);
+        keep[i] = (nvalid > 0 ? 0xffffu : 0u) | (nvalid > 1 ? 0xffff0000u : 0u);
+      }
 #pragma unroll
       for (int j = 0; j < HT; ++j)
 #pragma unroll
         for (int i = 0; i < 4; ++i) vr[j][i] &= keep[i];
     }
 #pragma unroll
-    for (int j = 0; j < HT; ++j) oacc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vr[j]), phi, oacc[j], 0, 0, 0);
-    lacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, phi, lacc, 0, 0, 0);
+    for (int j = 0; j < HT; ++j) x.o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vr[j]), phi, x.o[j], 0, 0, 0);
 #pragma unroll
-    for (int j = 0; j < HT; ++j) oacc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vr[j]), plo, oacc[j], 0, 0, 0);
-    lacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, plo, lacc, 0, 0, 0);
-    // (the compiler pads no wait states behind products whose results are read in another basic block)
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_nop 15\n\ts_nop 1" ::: "memory");
+    for (int j = 0; j < HT; ++j) x.o[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vr[j]), plo, x.o[j], 0, 0, 0);
   };
 
-  // steps the tile sees in full
-  const int see = min(pos_min + 1, span1) - span0;
-  const int nfull = tile < nqt && see > 0 ? min(nsteps, see / kPromptStep) : 0;
-  int rd = 0, it = 0;
+  const int nfull = tile < nqt ? (pos_min + 1) / kPromptStep : 0;  // steps the tile sees in full
+  const int nseen = tile < nqt ? pos_max / kPromptStep + 1 : 0;    // steps it sees anything of
+  int rd = 0;
   auto open_step = [&] {
-    // the step has landed for every wave, and nobody reads the step before any more: its buffer takes the step after the next
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(NPW) : "memory");
+    // the step has landed for every wave, and every wave has read the step before: its buffer takes the step after the next
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(NPW) : "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   };
@@ -759,126 +753,142 @@ __device__ __forceinline__ void attn_prompt_body(const float* q, const KvView& k
     request(nx, rd == 0 ? 2 * kBuf : rd - kBuf);
     rd = rd == kRing - kBuf ? 0 : rd + kBuf;
   };
+  // the tile's partials: [span][element j*16 + g*4 .. + 3][lane], whole kilobytes, then (max, sum) of its 16 rows
+  f32x4* tpart = (f32x4*)(part + cl.part_off + (size_t)(kvh * nqt + tile) * cl.nsplit * (16 * ROW));
+  // (a workgroup that has all spans keeps the last one's)
+  const int sp_kept = n_shares == 1 ? cl.nsplit - 1 : -1;
+  f32x4 o[HT];
+  float L = 0.f, M = 0.f;
 #pragma unroll 1
-  for (; it < nfull; ++it) {
-    open_step();
-    step(ring + rd, 0, std::false_type{}, request_next);
-  }
-  const int nseen = pos_max < span0 ? 0 : min(nsteps, (pos_max - span0) / kPromptStep + 1);
-#pragma unroll 1
-  for (; it < nseen; ++it) {
-    open_step();
-    step(ring + rd, span0 + it * kPromptStep, std::true_type{}, request_next);
-  }
-#pragma unroll 1
-  for (; it < nsteps; ++it) {  // (other waves' tiles see more)
-    open_step();
-    request_next();
-  }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (copies asked for past the end land before the LDS is given back)
-
-  // ---- rows whose context is one split are finished; others leave a partial, and the workgroup whose split
-  // arrives last merges them: its own outputs are still in its registers, the others' come from memory.  (With the
-  // merge spread over all threads of the workgroup, every split read: 14 us for two splits of a block, 6 this way.)
-  const size_t split_floats = (size_t)T * 16 * ROW;
-  float l_row = lacc[0];
-  // the tile's partial: [element j*16 + g*4 .. + 3][lane], whole kilobytes, then (max, sum) of its 16 rows
-  float* tpart = part + cl.part_off + (size_t)(kvh * ((nqt + T - 1) / T) + tile / T) * cl.nsplit * split_floats + (size_t)(tile % T) * 16 * ROW;
-  if (cl.nsplit > 1) {
-    if (tile < nqt) {
-      float* dst = tpart + split * split_floats;
+  for (int sp = sp0; sp < sp1; ++sp) {
 #pragma unroll
-      for (int j = 0; j < HT; ++j) Xwg<true>::st4f(dst + (j * 64 + lane) * 4, oacc[j]);
-      if (g == 0) Xwg<true>::st4f(dst + (HT * 64 + c) * 4, f32x4{m_run, l_row, 0.f, 0.f});
+    for (int ww = 0; ww < kStreamWaves; ++ww) {
+      st[ww].m = -INFINITY;
+      st[ww].l = 0.f;
+#pragma unroll
+      for (int j = 0; j < HT; ++j) st[ww].o[j] = zero;
     }
-    Xwg<true>::drain();  // this thread's partial stores have been acknowledged
+    const int begin = it, end = min(nsteps, (sp + 1) * span_steps);
+#pragma unroll 1
+    while (it + kStreamWaves <= min(end, nfull)) {
+#pragma unroll
+      for (int ww = 0; ww < kStreamWaves; ++ww) {
+        open_step();
+        step(st[ww], rd, 0, it < begin + kStreamWaves, std::false_type{}, request_next);
+        ++it;
+      }
+    }
+#pragma unroll 1
+    while (it < end) {
+#pragma unroll
+      for (int ww = 0; ww < kStreamWaves; ++ww) {
+        if (it >= end) break;
+        open_step();
+        if (it < nseen) step(st[ww], rd, it * kPromptStep, it < begin + kStreamWaves, std::true_type{}, request_next);
+        else request_next();  // (other waves' tiles see more)
+        ++it;
+      }
+    }
+    // (The last products may have been issued in another basic block, where the compiler pads too few
+    // wait states for the reads of their results below: spell them out.)
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 15\n\ts_nop 7" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    M = st[0].m;
+#pragma unroll
+    for (int ww = 1; ww < kStreamWaves; ++ww) M = fmaxf(M, st[ww].m);
+    const float M_ref = M == -INFINITY ? 0.f : M;
+    L = 0.f;
+#pragma unroll
+    for (int j = 0; j < HT; ++j) o[j] = zero;
+#pragma unroll
+    for (int ww = 0; ww < kStreamWaves; ++ww) {
+      const float sw = attn_exp(st[ww].m - M_ref);
+      L = __builtin_fmaf(st[ww].l, sw, L);
+#pragma unroll
+      for (int j = 0; j < HT; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[j][i] = __builtin_fmaf(st[ww].o[j][i], sw, o[j][i]);
+    }
+    if (sp != sp_kept && tile < nqt) {
+      f32x4* dst = tpart + sp * (4 * ROW);
+      const f32x4 ml = f32x4{M, L, 0.f, 0.f};  // (the four lanes of a row write the same)
+      if (n_shares > 1) {  // written through to memory: another workgroup may merge
+#pragma unroll
+        for (int j = 0; j < HT; ++j) Xwg<true>::st4f((float*)(dst + j * 64 + lane), o[j]);
+        Xwg<true>::st4f((float*)(dst + HT * 64 + c), ml);
+      } else {
+#pragma unroll
+        for (int j = 0; j < HT; ++j) dst[j * 64 + lane] = o[j];
+        dst[HT * 64 + c] = ml;
+      }
+    }
+  }
+  // copies asked for past the end land before the LDS is given back; this thread's partial stores have been acknowledged
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if (n_shares > 1) {  // count in; the last of the block's workgroups to arrive merges
     __syncthreads();
-    unsigned* counter = counters + cl.count_off + kvh * ny + y;
+    int* last_lds = (int*)(ring + kRing);
     if (tid == 0) {
+      unsigned* counter = counters + cl.count_off + kvh * (int)gridDim.y + (int)blockIdx.y;
       const unsigned prev = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const int last = prev == (unsigned)cl.nsplit - 1u;
+      const int last = prev == (unsigned)n_shares - 1u;
       if (last) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // ready for the next launch
       *last_lds = last;
     }
     __syncthreads();
     if (*last_lds == 0) return;
-    if (tile < nqt) {
-      struct Part {
-        f32x4 o[HT], ml;
-      };
-      auto fetch = [&](Part& p, int s) {
-        const f32x4* ps = (const f32x4*)(tpart + (size_t)s * split_floats);
-        p.ml = ps[HT * 64 + c];
-#pragma unroll
-        for (int j = 0; j < HT; ++j) p.o[j] = ps[j * 64 + lane];
-      };
-      Part p;
-      fetch(p, 0);
-      float M = m_run;
-      for (int s0 = 0; s0 < cl.nsplit; s0 += 4) {
-        float ms[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) ms[i] = tpart[(size_t)min(s0 + i, cl.nsplit - 1) * split_floats + (HT * 64 + c) * 4];
-        M = fmaxf(fmaxf(M, fmaxf(ms[0], ms[1])), fmaxf(ms[2], ms[3]));
-      }
-      f32x4 o[HT];
-#pragma unroll
-      for (int j = 0; j < HT; ++j) o[j] = zero;
-      float L = 0.f;
-      auto add = [&](const f32x4 (&os)[HT], float m_s, float l_s) {
-        const float wgt = __builtin_amdgcn_exp2f(m_s - M);
-        L += l_s * wgt;
-#pragma unroll
-        for (int j = 0; j < HT; ++j) o[j] += os[j] * wgt;
-      };
-      for (int s = 0; s < cl.nsplit; ++s) {  // in index order, whoever came last
-        Part nx;
-        fetch(nx, min(s + 1, cl.nsplit - 1));
-        if (s == split) add(oacc, m_run, l_row);
-        else add(p.o, p.ml[0], p.ml[1]);
-        p = nx;
-      }
-#pragma unroll
-      for (int j = 0; j < HT; ++j) oacc[j] = o[j];
-      l_row = L;
-    }
   }
   if (tile >= nqt) return;
-  const float inv = 1.0f / l_row;  // (the quotients are cut to 16 bits)
+
+  // ---- the spans' partials, as attn_merge_rows takes them ----
+  if (cl.nsplit > 1) {
+    constexpr int BATCH = 9;
+    auto max_of = [&](int s) { return s == sp_kept ? M : tpart[s * (4 * ROW) + HT * 64 + c][0]; };
+    float top = -INFINITY, sum = 0.f;
+    f32x4 acc[HT];
+#pragma unroll
+    for (int j = 0; j < HT; ++j) acc[j] = zero;
+    for (int s0 = 0; s0 < cl.nsplit; s0 += BATCH) {
+      const int s1 = min(cl.nsplit, s0 + BATCH);
+      float bm = top;
+      for (int s = s0; s < s1; ++s) bm = fmaxf(bm, max_of(s));
+      const float so = top == -INFINITY ? 0.f : attn_exp(top - bm);
+      for (int s = s0; s < s1; ++s) {
+        const f32x4* ps = tpart + s * (4 * ROW);
+        f32x4 os[HT];
+        float m_s = M, l_s = L;
+        if (s == sp_kept) {
+#pragma unroll
+          for (int j = 0; j < HT; ++j) os[j] = o[j];
+        } else {
+          const f32x4 ml = ps[HT * 64 + c];
+          m_s = ml[0];
+          l_s = ml[1];
+#pragma unroll
+          for (int j = 0; j < HT; ++j) os[j] = ps[j * 64 + lane];
+        }
+        const float wgt = m_s != -INFINITY ? attn_exp(m_s - bm) : 0.f;
+        // (the first of a batch: the product is rounded, the rescaling is part of the sum)
+        auto take = [&](float a, float v) { return s == s0 ? __builtin_fmaf(a, so, v * wgt) : __builtin_fmaf(v, wgt, a); };
+        sum = take(sum, l_s);
+#pragma unroll
+        for (int j = 0; j < HT; ++j)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) acc[j][i] = take(acc[j][i], os[j][i]);
+      }
+      top = bm;
+    }
+    L = sum;
+#pragma unroll
+    for (int j = 0; j < HT; ++j) o[j] = acc[j];
+  }
 #pragma unroll
   for (int j = 0; j < HT; ++j) {
-    const f32x4 y = oacc[j] * inv, y2 = shfl4(y, lane + 16);  // (elements + 4 .. + 7 of the 8)
+    const f32x4 y = f32x4{o[j][0] / L, o[j][1] / L, o[j][2] / L, o[j][3] / L}, y2 = shfl4(y, lane + 16);  // (elements + 4 .. + 7 of the 8)
     const float y8[8] = {y[0], y[1], y[2], y[3], y2[0], y2[1], y2[2], y2[3]};
     if (live && (g & 1) == 0) store_act8x<false>((u32x4*)outp, cl.row_off + r, (kvh * group + gq) * HD + j * 16 + g * 4, y8, act_tiles);
   }
-}
-
-// (the last blocks have the longest contexts: their workgroups start first)
-template <int HD>
-__global__ __launch_bounds__(kStreamWaves * 64, 3) void attn_prompt_kernel(const float* q, KvView kv, int layer, int n_q_heads,
-                                                                           AttnBatch batch, int T, float* part, uint4* outp,
-                                                                           int act_tiles, unsigned* counters) {
-  extern __shared__ float lds[];
-  attn_prompt_body<HD>(q, kv, layer, n_q_heads, batch, T, part, outp, act_tiles, counters, (int)blockIdx.x, (int)blockIdx.y,
-                       (int)gridDim.y, (int)(gridDim.z - 1 - blockIdx.z), lds);
-}
-
-// A prompt whose last block the streaming kernel takes: both in one launch, side by side (150 rows behind 700
-// tokens at the 8B shape, a layer: 265 us before the prompt kernel, 269 with two launches, 253 in one).
-// Workgroups 0 .. ny * splits - 1 of a KV head are the prompt blocks', the others the last block's.
-template <int HD>
-__global__ __launch_bounds__(kStreamWaves * 64, 2) void attn_prompt_mixed_kernel(const float* q, KvView kv, int layer, int n_q_heads,
-                                                                                 AttnBatch blocks, int ny, int splits, AttnBatch few,
-                                                                                 int few_splits, float* part, uint4* outp,
-                                                                                 int act_tiles, unsigned* counters) {
-  extern __shared__ float lds[];
-  const int i = (int)blockIdx.y, n = ny * splits;
-  if (i < n)
-    attn_prompt_body<HD>(q, kv, layer, n_q_heads, blocks, 1, part, outp, act_tiles, counters, (int)blockIdx.x, i % ny, ny,
-                         splits - 1 - i / ny, lds);
-  else
-    attn_stream_body<HD, 1>(q, kv, layer, n_q_heads, few, part, outp, act_tiles, counters, (int)blockIdx.x, (i - n) % few_splits,
-                            (i - n) / few_splits, lds);
 }
 
 // grid = (threads of the largest client / 64, clients)
@@ -948,55 +958,34 @@ hipError_t launch_attention(const AttnCall& c, hipStream_t st) {
       max_m = b.c[i].m > max_m ? b.c[i].m : max_m;
       tasks += (long)c.kv.n_kv_heads * b.c[i].nsplit * ((group * b.c[i].m + 15) / 16);
     }
-    if (c.stream_tiles) {  // the streaming kernels (the batch was planned by attn_stream_plan)
+    if (c.stream_tiles) {  // few rows per client: the streaming kernel (the batch was planned by attn_stream_plan)
       const int T = c.stream_tiles;
       if ((h != 128 && h != 64) || max_m > kPromptBlockRows || (T != 1 && T != 2) || c.counters == nullptr) return hipErrorInvalidValue;
-      // prompt blocks, and what the streaming kernel takes of them (the last block of a prompt may be of few rows)
-      AttnBatch few{}, blocks{};
-      int few_m = 1, few_splits = 0, blocks_m = 1, block_splits = 0;
-      for (int i = 0; i < b.n; ++i) {
-        const AttnClient& cl = b.c[i];
-        if (!attn_few_rows(group, c.kv.n_kv_heads, cl.m, cl.start_pos + cl.m)) {
-          if (cl.span < kPromptStep || cl.span % kPromptStep != 0) return hipErrorInvalidValue;
-          blocks.c[blocks.n++] = cl;
-          blocks_m = std::max(blocks_m, (int)cl.m);
-          block_splits += cl.nsplit;
-        } else {
-          // (a lane per step holds the step's block-table entries)
-          if (cl.span < kStreamWgTokens || cl.span > kStreamMaxSteps * kStreamWgTokens) return hipErrorInvalidValue;
-          few.c[few.n++] = cl;
-          few_m = std::max(few_m, (int)cl.m);
-          few_splits += cl.nsplit;
-        }
-      }
+      for (int i = 0; i < b.n; ++i)  // (a lane per step holds the step's block-table entries)
+        if (b.c[i].span < kStreamWgTokens || b.c[i].span > kStreamMaxSteps * kStreamWgTokens) return hipErrorInvalidValue;
       using std::integral_constant;
-      if (blocks.n > 0) {
+      PromptShares shares;
+      if (const int n = attn_prompt_shares(group, c.kv.n_kv_heads, device_cu_count(), b, &shares)) {
         if (c.gate != nullptr) return hipErrorInvalidValue;
-        const int ny = (attn_query_tiles(group, blocks_m) + kStreamWaves - 1) / kStreamWaves, nf = attn_query_tiles(group, few_m) * few_splits;
-        if (few.n > 0 && T != 1) return hipErrorInvalidValue;
+        const dim3 grid(c.kv.n_kv_heads, (attn_query_tiles(group, max_m) + kStreamWaves - 1) / kStreamWaves, n);
         auto go = [&](auto hd) -> hipError_t {
           constexpr int HD = decltype(hd)::value;
-          constexpr size_t lds = prompt_lds_bytes<HD>(), lds_mixed = std::max(lds, stream_lds_bytes<HD>(1));
-          static_assert(lds_mixed <= 64 * 1024, "no limit to raise");
-          if (few.n == 0)
-            attn_prompt_kernel<HD><<<dim3(c.kv.n_kv_heads, ny, block_splits), kStreamWaves * 64, lds, st>>>(
-                c.q, c.kv, c.layer, c.n_q_heads, blocks, T, c.part, (uint4*)c.outp, c.act_tiles, c.counters);
-          else
-            attn_prompt_mixed_kernel<HD><<<dim3(c.kv.n_kv_heads, ny * block_splits + nf), kStreamWaves * 64, lds_mixed, st>>>(
-                c.q, c.kv, c.layer, c.n_q_heads, blocks, ny, block_splits, few, few_splits, c.part, (uint4*)c.outp, c.act_tiles, c.counters);
+          static_assert(prompt_lds_bytes<HD>() <= 64 * 1024, "no limit to raise");
+          attn_prompt_kernel<HD><<<grid, kStreamWaves * 64, prompt_lds_bytes<HD>(), st>>>(
+              c.q, c.kv, c.layer, c.n_q_heads, b, shares, c.part, (uint4*)c.outp, c.act_tiles, c.counters);
           return hipGetLastError();
         };
         return h == 128 ? go(integral_constant<int, 128>{}) : go(integral_constant<int, 64>{});
       }
-      const int nz = (attn_query_tiles(group, few_m) + T - 1) / T;
-      const dim3 grid(c.kv.n_kv_heads, few_splits, nz), block(kStreamWaves * 64);
+      const int nz = ((group * max_m + 15) / 16 + T - 1) / T;
+      const dim3 grid(c.kv.n_kv_heads, splits, nz), block(kStreamWaves * 64);
       auto go = [&](auto hd, auto t) -> hipError_t {
         constexpr int HD = decltype(hd)::value, TT = decltype(t)::value;
         static std::atomic<uint64_t> lds_allowed;
         constexpr size_t lds = stream_lds_bytes<HD>(TT);
         const hipError_t e = allow_lds(lds_allowed, (const void*)attn_stream_kernel<HD, TT>, lds);
         if (e != hipSuccess) return e;
-        attn_stream_kernel<HD, TT><<<grid, block, lds, st>>>(c.q, c.kv, c.layer, c.n_q_heads, few, c.part, (uint4*)c.outp, c.act_tiles,
+        attn_stream_kernel<HD, TT><<<grid, block, lds, st>>>(c.q, c.kv, c.layer, c.n_q_heads, b, c.part, (uint4*)c.outp, c.act_tiles,
                                                              c.gate, c.counters);
         return hipGetLastError();
       };

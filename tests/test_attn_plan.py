@@ -82,3 +82,86 @@ def sweep(tmp_path_factory):
 def test_scratch_of_a_pool_holds_every_pass(sweep, heads, n_cu):
     r = subprocess.run([sweep, *map(str, heads), str(n_cu)], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout
+
+
+ROUTES = r"""
+#include <stdio.h>
+#include <stdlib.h>
+#include "attn_plan.h"
+using namespace pipesd;
+// a prompt pass per line of arguments (rows, first position): 0 / 1 (prompt kernel), then per block rows:spans:tokens per span:workgroups
+int main(int argc, char** argv) {
+  const int nq = atoi(argv[1]), nkv = atoi(argv[2]), hd = atoi(argv[3]);
+  for (int i = 4; i + 1 < argc; i += 2) {
+    AttnBatch b = prompt_blocks(atoi(argv[i]), atoi(argv[i + 1]));
+    size_t floats = 0;
+    PromptShares s{};
+    if (attn_stream_plan(nq, nkv, hd, 256, b, true, &floats) == 0) return 1;
+    const int n = attn_prompt_shares(nq / nkv, nkv, 256, b, &s);
+    int sum = 0;
+    printf("%d", n > 0);
+    for (int j = 0; j < b.n; ++j) {
+      printf(" %d:%d:%d:%d", b.c[j].m, b.c[j].nsplit, b.c[j].span, n > 0 ? s.n[j] : 0);
+      sum += s.n[j];
+      if (n > 0 && (s.n[j] < 1 || s.n[j] > b.c[j].nsplit || b.c[j].span % (4 * kPromptStep) != 0)) return 2;
+    }
+    if (n > 0 && sum != n) return 3;
+    printf("\n");
+  }
+  return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def routes(tmp_path_factory):
+    cxx = shutil.which("g++") or shutil.which("clang++") or "/opt/rocm/llvm/bin/clang++"
+    d = tmp_path_factory.mktemp("routes")
+    (d / "routes.cpp").write_text(ROUTES)
+    subprocess.run([cxx, "-std=c++17", "-O2", "-Wall", "-Werror", "-I", CSRC, "-o", str(d / "routes"), str(d / "routes.cpp")], check=True)
+
+    def run(shape, passes):
+        """Per (rows, first position): whether the prompt kernel takes it, and its blocks (rows, spans, tokens per span, workgroups)."""
+        r = subprocess.run([str(d / "routes"), str(shape.n_q_heads), str(shape.n_kv_heads), str(shape.head_dim),
+                            *[str(v) for p in passes for v in p]], capture_output=True, text=True, check=True)
+        lines = [ln.split() for ln in r.stdout.splitlines()]
+        return [(ln[0] == "1", [tuple(map(int, blk.split(":"))) for blk in ln[1:]]) for ln in lines]
+
+    return run
+
+
+def test_the_gpu_cases_of_prompt_attention_take_the_kernels_they_are_meant_for(routes):
+    from tests import test_gpu_prompt_attention as t
+
+    def passes(cached, sizes):  # (rows, first position) of the calls
+        got, length = [], cached
+        for n in sizes:
+            got.append((n - (1 if length == 0 else 0), max(0, length - 1)))
+            length += n
+        return got
+
+    for shape in t.BIG:
+        for tokens in t.SHORT + [257, 300]:
+            assert routes(shape, passes(0, [tokens]))[0][0], (shape.name, tokens)
+            assert not any(p for p, _ in routes(shape, passes(0, t.in_blocks(0, tokens, 32))))
+    for shape in t.SHAPES:
+        assert [r[0] for r in routes(shape, [(rows, 0) for rows in (128, 215, 299, 2048)])] == [False, False, True, True]
+    seen = {"spans of a lone workgroup": 0, "spans of several": 0, "most spans": 0, "longest walk": 0, "span": 0, "ragged": 0}
+    for shape in t.SMALL:
+        for cached, tokens in t.LONG:
+            first_pass = min(tokens, 2048 + (cached == 0))
+            taken, blocks = routes(shape, passes(cached, [first_pass]))[0]
+            assert taken, (shape.name, cached, tokens)
+            assert not any(p for p, _ in routes(shape, passes(cached, t.in_blocks(cached, tokens, 128))))
+            for rows, spans, span, workgroups in blocks:
+                if workgroups == 1:
+                    seen["spans of a lone workgroup"] = max(seen["spans of a lone workgroup"], spans)
+                elif workgroups < spans:
+                    seen["spans of several"] = max(seen["spans of several"], spans)
+                seen["most spans"] = max(seen["most spans"], spans)
+                seen["longest walk"] = max(seen["longest walk"], spans * span // (32 * workgroups))
+                seen["span"] = max(seen["span"], span)
+                seen["ragged"] += rows % 128 != 0
+    assert seen["spans of a lone workgroup"] >= 3 and seen["spans of several"] >= 4 and seen["most spans"] >= 10, seen
+    assert seen["longest walk"] > 64 and seen["span"] > 256 and seen["ragged"] > 0, seen
+    print(seen)
