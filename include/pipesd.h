@@ -216,8 +216,8 @@ int pipesd_spec_accept(const float *p, const float *q, const int32_t *draft_toke
  * Limits: 1 <= k <= PIPESD_STATIC_MAX_K, 1 <= vocab <= PIPESD_STATIC_MAX_VOCAB; beyond them the call
  * returns PIPESD_EINVAL and pipesd_last_hip_error() says which limit.  Every call on a GPU uses that
  * GPU's one scratch array: calls that overlap on one GPU (two streams, two threads) race; calls on
- * one stream are ordered and safe.  The arrival counter is cleared by a small kernel at the start
- * of every call, so a graph that records this call records no memset node. */
+ * one stream are ordered and safe.  A call is one kernel: its arrival counter wraps to zero by itself,
+ * so a graph that records this call records no memset node. */
 enum { PIPESD_STATIC_MAX_K = PIPESD_MAX_ROWS - 1, PIPESD_STATIC_MAX_VOCAB = 1 << 22 };
 int pipesd_spec_accept_static(const float *p, const float *q, const int32_t *draft_tokens, int32_t k,
                               int32_t vocab, const float *uniforms, int32_t *result_dev, void *stream);
