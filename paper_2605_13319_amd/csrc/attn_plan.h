@@ -116,16 +116,17 @@ inline int attn_stream_plan(int n_q_heads, int n_kv_heads, int head_dim, int n_c
   return T;
 }
 
-// Which kernel takes a planned pass: 0 for the streaming kernel, else the prompt kernel, with `shares`->n[i] workgroups for
-// (a KV head's four query tiles of) client i, each with spans of its own, and their sum returned.  Either way every
-// row gets the same bits: the rule is about time.  The prompt kernel's workgroups are long (a wave walks all tokens of
-// its spans), so it needs many of them: from 96 groups of four tiles on it is never slower, from 64 on in contexts of 256
-// to 2048 tokens.  Microseconds per layer, streaming / prompt kernel.  8B shape: 128 rows (64 groups) behind 1, 300, 900, 1900 and
-// 6000 tokens 199 / 204, 210 / 209, 220 / 215, 222 / 217, 242 / 243, 129 rows behind 6000 280 / 294; 200 rows (104) behind 1, 900
-// and 6000 254 / 254, 289 / 270, 335 / 330; 333 rows behind 900 420 / 407; 2048 rows 1741 / 1642.  1B shape: 128 rows behind
-// 1 and 900 87 / 90, 101 / 97; 333 behind 900 175 / 166; 2048 675 / 622.  13B shape: 129 rows (120) behind 1, 900 and 6000 344 / 346,
-// 372 / 362, 434 / 431; 2048 3149 / 3047.  The work is cut into about twice as many shares as the device holds workgroups (two per
-// compute unit), none below 8 steps: 2047 rows at the 8B shape 117 us with one share per slot, 113 with two, 120 with four.
+// Which kernel takes a planned pass: 0 for the streaming kernel, else the prompt kernel, with `shares`->n[i] workgroups
+// for (a KV head's four query tiles of) client i, each with spans of its own, and their sum returned.  Either way
+// every row gets the same bits: the rule is about time.  The prompt kernel's workgroups are long (a wave walks all
+// tokens of its spans), so it needs many of them: from 96 groups of four tiles on it is nowhere slower by more than
+// 2 %, from 64 on in contexts of 256 to 2048 tokens.  Microseconds per layer, streaming / prompt kernel.  8B shape:
+// 128 rows (64 groups) behind 1, 300, 900, 1900 and 6000 tokens 199 / 204, 210 / 209, 220 / 215, 222 / 217, 242 / 243,
+// 129 rows behind 6000 280 / 294; 200 rows (104) behind 1, 900 and 6000 254 / 254, 289 / 270, 335 / 330; 333 rows
+// behind 900 420 / 407; 2048 rows 1741 / 1642.  1B shape: 128 rows behind 1 and 900 87 / 90, 101 / 97; 333 behind 900
+// 175 / 166; 2048 675 / 622.  13B shape: 129 rows (120) behind 1, 900 and 6000 344 / 346, 372 / 362, 434 / 431; 2048
+// 3149 / 3047.  The work is cut into about twice as many shares as the device holds workgroups (two per compute
+// unit), none below 8 steps: 2047 rows at the 8B shape 117 us with one share per slot, 113 with two, 120 with four.
 inline int attn_prompt_shares(int group, int n_kv_heads, int n_cu, const AttnBatch& b, PromptShares* shares) {
   int max_m = 0, most = 0;
   long groups = 0, work = 0;  // groups of four tiles; steps of all of them

@@ -508,9 +508,9 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void attn_stream_kernel(const
 // Every product, sum and rounding is the streaming kernel's own, in its order (the order of tokens inside an operand
 // too); products with weights that are all zero and rescaling of zeros or by 1 are left out, which changes no bit of a
 // finite result.  So which of the two kernels a pass takes, and into how many shares it is cut, is a matter of time alone
-// (attn_prompt_shares), and a row's keys and values do not depend on what other rows its prompt was fed with.
+// (attn_prompt_shares): a row's result depends on its block's rows and context only.
 //
-// 8B shape, per layer, streaming / this kernel: 2047 rows 241 / 113 us, 333 rows behind 1000 tokens 69 / 39.  Bound by what a step
+// 8B shape, per layer, streaming / this kernel: 2047 rows 241 / 113 to 117 us, 333 rows behind 1000 tokens 69 / 39.  Bound by what a step
 // waits for, with few waves to cover it: four states take 254 registers, so two waves share a SIMD (1.6 on average),
 // each going from scores over a maximum, exponentials and cuts to 16 bits to the values' products.  Of
 // the cycles the vector units issue in 47 %, the matrix cores work in 26 %, LDS is read in 33 %, 39 % of those bank conflicts: a
