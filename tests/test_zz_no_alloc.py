@@ -53,3 +53,37 @@ def test_static_scratch_limits_are_errors():
     with pytest.raises(nav.PipesdError) as e:  # a draft token outside the vocabulary
         nav.spec_accept_static(tp, tq, np.array([1, 64], np.int32), u, out)
     assert e.value.status == nav.EINVAL
+
+
+def test_static_decision_recorded_in_a_graph_leaves_its_counter_at_zero():
+    """Replays of one recorded call on changing probabilities, eager calls of another size between them: nothing but
+    the kernel's own wrapping counter stands between one decision and the next, whichever way each ends (a rejection,
+    all drafts accepted, no weight at all)."""
+    import torch
+    from paper_2605_13319_amd import nav
+    V, k = 32003, 6
+    p, q, d, u = _case(V, k, 21)
+    tp, tq = torch.from_numpy(p).cuda(), torch.from_numpy(q).cuda()
+    out = torch.zeros(2, dtype=torch.int32, device="cuda")
+    p2, q2, d2, u2 = _case(517, 2, 22)
+    tp2, tq2 = torch.from_numpy(p2).cuda(), torch.from_numpy(q2).cuda()
+    out2 = torch.zeros(2, dtype=torch.int32, device="cuda")
+    nav.spec_accept_static(tp, tq, d, u, out)  # (the scratch's address is looked up outside the recording)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        nav.spec_accept_static(tp, tq, d, u, out)
+    nothing = np.zeros_like(p)
+    rounds = [(p, q), (p, p[:k].copy()), (nothing, q), _case(V, k, 23)[:2], (p, q)]
+    for i, (pi, qi) in enumerate(rounds):
+        print("replay", i, flush=True)
+        tp.copy_(torch.from_numpy(pi))
+        tq.copy_(torch.from_numpy(qi))
+        out.fill_(-7)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert tuple(int(x) for x in out.cpu()) == oracle_accept(pi, qi, d, u)
+        out2.fill_(-7)
+        nav.spec_accept_static(tp2, tq2, d2, u2, out2)
+        torch.cuda.synchronize()
+        assert tuple(int(x) for x in out2.cpu()) == oracle_accept(p2, q2, d2, u2)
