@@ -118,35 +118,52 @@ inline int attn_stream_plan(int n_q_heads, int n_kv_heads, int head_dim, int n_c
 
 // Which kernel takes a planned pass: 0 for the streaming kernel, else the prompt kernel, with `shares`->n[i] workgroups
 // for (a KV head's four query tiles of) client i, each with spans of its own, and their sum returned.  Either way
-// every row gets the same bits: the rule is about time.  The prompt kernel's workgroups are long (a wave walks all
-// tokens of its spans), so it needs many of them: from 96 groups of four tiles on it is nowhere slower by more than
-// 2 %, from 64 on in contexts of 256 to 2048 tokens.  Microseconds per layer, streaming / prompt kernel.  8B shape:
-// 128 rows (64 groups) behind 1, 300, 900, 1900 and 6000 tokens 199 / 204, 210 / 209, 220 / 215, 222 / 217, 242 / 243,
-// 129 rows behind 6000 280 / 294; 200 rows (104) behind 1, 900 and 6000 254 / 254, 289 / 270, 335 / 330; 333 rows
-// behind 900 420 / 407; 2048 rows 1741 / 1642.  1B shape: 128 rows behind 1 and 900 87 / 90, 101 / 97; 333 behind 900
-// 175 / 166; 2048 675 / 622.  13B shape: 129 rows (120) behind 1, 900 and 6000 344 / 346, 372 / 362, 434 / 431; 2048
-// 3149 / 3047.  The work is cut into about twice as many shares as the device holds workgroups (two per compute
-// unit), none below 8 steps: 2047 rows at the 8B shape 117 us with one share per slot, 113 with two, 120 with four.
-inline int attn_prompt_shares(int group, int n_kv_heads, int n_cu, const AttnBatch& b, PromptShares* shares) {
+// every row gets the same bits: the rule is about time.  The work is cut into about twice as many shares as the device
+// holds workgroups (two per compute unit), none below 8 steps: 2047 rows at the 8B shape 117 us with one share per slot,
+// 113 with two, 120 with four.
+//
+// The prompt kernel's workgroups are long (a wave walks all tokens of its spans), so it needs many of them, and
+// its time goes by groups of four tiles, whether a last one is full or not.  Both kernels were timed at 14 shapes (1B, 8B and 13B;
+// 16 to 128 query heads, 2 to 64 KV heads, either head size), 33 to 900 rows behind 0 to 7000 tokens.  Of 2995 passes that the rule
+// below gives to the prompt kernel 4 are slower by more than 2.5 % of the call (48 heads of 64 on 8 KV heads, 270 and 290 rows
+// behind 4000 to 7000 tokens: 3 to 12 %).  It also keeps passes back that would gain, at the three models none more than
+// 5 %.  Changes of a layer's attention, streaming -> prompt kernel, on the two sides of its lines:
+//  * workgroups up to half a compute unit each: 16 heads of 128, 200 rows behind 300 tokens (128 workgroups) + 3.7 us, 289
+//    rows (96) + 4.6; 8B shape, 128 rows behind 300 (128) - 1.2, 129 rows (144) - 5.3;
+//  * contexts of one span, one each: 64 heads of 64, 127 to 240 rows alone (128 to 240) + 1.7 to 2.6, 256 rows (256) + 1.0,
+//    heads of 128, 128 heads (256) 0 to - 3;
+//  * walks of 32 and more steps, one and five eighths each, and 96 groups: 64 heads of 64 on 4 KV heads, 129 rows behind 3000 (292
+//    workgroups, 56 steps) + 9.4, 48 heads of 128, 129 behind 1900 (256, 32) + 7.2, 1B shape, 150 behind 5000 (432, 48, 80 groups)
+//    + 10.8; 8B shape, 200 rows behind 3000 (536, 32) - 7.2, 256 behind 6000 (512, 56) - 25;
+//  * head size 64, groups of less than 84 % tiles: 64 KV heads, 129 rows behind 900 and 6000 (75 %) + 6.9 and + 10.7.
+inline int attn_prompt_shares(int group, int n_kv_heads, int head_dim, int n_cu, const AttnBatch& b, PromptShares* shares) {
   int max_m = 0, most = 0;
-  long groups = 0, work = 0;  // groups of four tiles; steps of all of them
+  long tiles = 0, groups = 0, work = 0;  // query tiles; groups of four of them; steps of all groups
   auto steps_of = [](const AttnClient& cl) { return (cl.start_pos + cl.m + kPromptStep - 1) / kPromptStep; };
+  auto groups_of = [&](const AttnClient& cl) { return (long)n_kv_heads * ((attn_query_tiles(group, cl.m) + kStreamWaves - 1) / kStreamWaves); };
   for (int i = 0; i < b.n; ++i) {
-    const long g4 = (long)n_kv_heads * ((attn_query_tiles(group, b.c[i].m) + kStreamWaves - 1) / kStreamWaves);
     max_m = std::max(max_m, (int)b.c[i].m);
     most = std::max(most, (int)(b.c[i].start_pos + b.c[i].m));
-    groups += g4;
-    work += g4 * steps_of(b.c[i]);
+    tiles += (long)n_kv_heads * attn_query_tiles(group, b.c[i].m);
+    groups += groups_of(b.c[i]);
+    work += groups_of(b.c[i]) * steps_of(b.c[i]);
   }
   if (max_m <= kMaxRows) return 0;  // (rounds of clients, prompts of a few rows)
-  if (groups < 64 || (groups < 96 && (most < 256 || most > 2048 + kPromptBlockRows))) return 0;
+  if (groups < 64 || (head_dim == 64 && 25 * tiles < 84 * groups)) return 0;
   const long share_steps = std::max(8L, work / (4L * n_cu));
-  int sum = 0;
+  long sum = 0, workgroups = 0, walk = 0;  // walk: the most steps of a workgroup
   for (int i = 0; i < b.n; ++i) {
-    shares->n[i] = (int)std::min((long)b.c[i].nsplit, (steps_of(b.c[i]) + share_steps - 1) / share_steps);
-    sum += shares->n[i];
+    const AttnClient& cl = b.c[i];
+    const long n = std::min((long)cl.nsplit, (steps_of(cl) + share_steps - 1) / share_steps);
+    shares->n[i] = (int)n;
+    sum += n;
+    workgroups += groups_of(cl) * n;
+    walk = std::max(walk, std::min((long)steps_of(cl), (cl.nsplit + n - 1) / n * (cl.span / kPromptStep)));
   }
-  return sum;
+  const long eighths = 8 * workgroups / n_cu;  // of a workgroup per compute unit
+  if (2 * workgroups <= n_cu || (most <= kStreamMinSpan && eighths < 8)) return 0;
+  if (walk >= 32 && (groups < 96 || eighths < 13)) return 0;
+  return (int)sum;
 }
 
 // Floats of attention partials that no pass over a pool of `pool_tokens` cached tokens exceeds, but for

@@ -965,7 +965,7 @@ hipError_t launch_attention(const AttnCall& c, hipStream_t st) {
         if (b.c[i].span < kStreamWgTokens || b.c[i].span > kStreamMaxSteps * kStreamWgTokens) return hipErrorInvalidValue;
       using std::integral_constant;
       PromptShares shares;
-      if (const int n = attn_prompt_shares(group, c.kv.n_kv_heads, device_cu_count(), b, &shares)) {
+      if (const int n = attn_prompt_shares(group, c.kv.n_kv_heads, h, device_cu_count(), b, &shares)) {
         if (c.gate != nullptr) return hipErrorInvalidValue;
         const dim3 grid(c.kv.n_kv_heads, (attn_query_tiles(group, max_m) + kStreamWaves - 1) / kStreamWaves, n);
         auto go = [&](auto hd) -> hipError_t {

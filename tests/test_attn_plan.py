@@ -97,7 +97,7 @@ int main(int argc, char** argv) {
     size_t floats = 0;
     PromptShares s{};
     if (attn_stream_plan(nq, nkv, hd, 256, b, true, &floats) == 0) return 1;
-    const int n = attn_prompt_shares(nq / nkv, nkv, 256, b, &s);
+    const int n = attn_prompt_shares(nq / nkv, nkv, hd, 256, b, &s);
     int sum = 0;
     printf("%d", n > 0);
     for (int j = 0; j < b.n; ++j) {
@@ -145,7 +145,7 @@ def test_the_gpu_cases_of_prompt_attention_take_the_kernels_they_are_meant_for(r
             assert routes(shape, passes(0, [tokens]))[0][0], (shape.name, tokens)
             assert not any(p for p, _ in routes(shape, passes(0, t.in_blocks(0, tokens, 32))))
     for shape in t.SHAPES:
-        assert [r[0] for r in routes(shape, [(rows, 0) for rows in (128, 215, 299, 2048)])] == [False, False, True, True]
+        assert [r[0] for r in routes(shape, [(rows, 0) for rows in (128, 215, 299, 2048)])] == [False, False, shape.head_dim == 128, True]
     seen = {"spans of a lone workgroup": 0, "spans of several": 0, "most spans": 0, "longest walk": 0, "span": 0, "ragged": 0}
     for shape in t.SMALL:
         for cached, tokens in t.LONG:
@@ -165,3 +165,19 @@ def test_the_gpu_cases_of_prompt_attention_take_the_kernels_they_are_meant_for(r
     assert seen["spans of a lone workgroup"] >= 3 and seen["spans of several"] >= 4 and seen["most spans"] >= 10, seen
     assert seen["longest walk"] > 64 and seen["span"] > 256 and seen["ragged"] > 0, seen
     print(seen)
+
+
+def test_prompt_attention_goes_where_it_was_measured_faster(routes):
+    """Passes on both sides of the rule's lines: (query heads, KV heads, head size), (rows, first position), and whether the prompt
+    kernel, the faster one there, takes them."""
+    from paper_2605_13319_amd import inputs as I
+    cases = [((32, 8, 128), (2047, 0), True), ((32, 8, 128), (333, 999), True), ((32, 8, 128), (128, 0), False),
+             ((32, 8, 128), (129, 299), True), ((32, 8, 128), (128, 299), False),  # workgroups: half a compute unit each
+             ((32, 8, 128), (255, 0), False), ((128, 16, 128), (128, 0), True),    # contexts of one span
+             ((64, 4, 64), (129, 2999), False), ((48, 8, 128), (129, 1899), False), ((128, 8, 64), (129, 1899), False),  # long walks
+             ((64, 8, 128), (97, 5999), False), ((32, 8, 64), (150, 4999), False), ((32, 8, 128), (200, 2999), True), ((32, 8, 128), (256, 5999), True),
+             ((32, 8, 64), (256, 5999), True), ((40, 40, 128), (200, 5999), True),
+             ((64, 64, 64), (129, 899), False), ((64, 64, 64), (129, 5999), False), ((64, 64, 64), (256, 899), True)]  # groups not full
+    for (n_q, n_kv, hd), where, prompt in cases:
+        shape = I.ModelShape("route", 2, 512, n_q, n_kv, hd, 512, 300)
+        assert routes(shape, [where])[0][0] == prompt, (n_q, n_kv, hd, where)
