@@ -103,8 +103,8 @@ size_t pipesd_kv_block_bytes(const pipesd_model *model, int32_t block_tokens);
  * (16) tokens; per layer the keys of a block are [kv_head][token][head_dim] and the values
  * [kv_head][head_dim][token].  pool == NULL gives bookkeeping only (see pipesd_model_create).
  * With a pool, the model's scratch for attention partials is sized here for the largest pass this
- * pool admits (about 1 MB per 256 pool tokens for 32 query heads of 128, and no less than a prompt
- * pass of 2048 rows takes, about 200 MB there), so that no verify call and no prompt allocates.  What
+ * pool admits (for 32 query heads of 128 on 8 KV heads 1.6 MB per 256 pool tokens, and no less than a prompt
+ * pass over the pool takes, 207 MB from 2048 pool tokens on), so that no verify call and no prompt allocates.  What
  * grows it later, synchronising the device, are prompt passes that reach beyond 131072 tokens of
  * context or belong to a model of more than 128 query heads, and the all-layers kernel
  * (pipesd_model_set_fused).

@@ -566,7 +566,7 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void attn_prompt_kernel(const
   const int qd = n_q_heads * HD;
 
   // ---- copies: in memory's order but for a swap of 16-byte pieces inside a token's keys (a pair of value halves), so
-  // that the reads of the operands meet no bank twice.  Wave w copies half w % 2 of block w / 2 of a step; lane L
+  // that the reads of keys meet no bank twice (those of values, 8 bytes a lane, meet half of them).  Wave w copies half w % 2 of block w / 2 of a step; lane L
   // holds that block's table entry of step 64 n + L. ----
   constexpr int PIECES = HD / 8, TPC = 64 / PIECES;  // 16-byte pieces of a token's keys, tokens of a copy
   auto key_swap = [](int tok) { return PIECES == 16 ? tok : (tok >> 1) & (PIECES - 1); };

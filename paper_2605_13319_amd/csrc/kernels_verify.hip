@@ -133,7 +133,7 @@ __device__ __forceinline__ unsigned long long wave_scan_u64(unsigned long long v
 // caches, without fences (a device-scope fence writes the whole L2 back), every wave makes the tests for
 // itself, and the arrival counter wraps to zero by itself, so that no launch has to clear it in front:
 // 9.7 -> 7.8 us on given probabilities at that vocabulary and 8 drafts, and 1.4 for the clearing launch
-// (a call of the static entry point among others 14.4 -> 11.1, now the host's share).
+// (a call of the static entry point among others 14.0 to 14.7 -> 11.3 to 11.5, now the host's share).
 __device__ __forceinline__ void spec_accept_body(const float* __restrict__ p, const float* __restrict__ q,
                                                  const float* __restrict__ stats, int k, int V, const int32_t* drafts,
                                                  const float* un, unsigned long long* partial, unsigned* counter,
