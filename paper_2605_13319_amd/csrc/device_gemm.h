@@ -209,14 +209,23 @@ __device__ __forceinline__ f32x4 shfl4(f32x4 v, int src) {
 // activation row `row` with weight rows gg*4 .. gg*4+3 of tile t.  Partner rows (i, i+8) sit 32 lanes
 // apart and the two halves of an 8-column group 16 lanes apart, so pairs are joined by shuffles.
 // Every lane of the wave must call this (rows beyond the pass only skip the stores).
-// RESID: `pre` says that pre_res / pre_gain already hold this quad's residual and gain values.
+// RESID: `pre` says that `p` holds the quad's residual and gain values (resid_pre).
 // EPI: the epilogue as a compile-time constant (the per-projection kernels: only that epilogue's code
 // and registers are in the kernel), or kEpiAny to pick by a.epi at run time (kernels that run several
 // kinds of products).
 constexpr int kEpiAny = -1;
+struct ResidPre {
+  f32x4 res, gain;
+};
+// loaded without a branch: the indices of tiles and rows beyond the product's are clamped, and what is read for
+// them is never used
+__device__ __forceinline__ ResidPre resid_pre(const GemmArgs& a, int t, int row, int lane) {
+  const int col = min(t, a.ntiles - 1) * 16 + (lane >> 4) * 4;
+  return ResidPre{*(const f32x4*)(a.res_in + (size_t)min(row, a.m - 1) * a.ldo + col), *(const f32x4*)(a.gain_next + col)};
+}
 template <bool CO, int EPI = kEpiAny>
-__device__ __forceinline__ void epilogue_quad(const GemmArgs& a, int t, int row, int lane, f32x4 v, float rstd,
-                                              bool pre, f32x4 pre_res, f32x4 pre_gain) {
+__device__ __forceinline__ void epilogue_quad(const GemmArgs& a, int t, int row, int lane, f32x4 v, float rstd, bool pre,
+                                              const ResidPre& p) {
   const int gg = lane >> 4;
   const bool live = row < a.m;
   switch (EPI == kEpiAny ? a.epi : EPI) {
@@ -236,13 +245,13 @@ __device__ __forceinline__ void epilogue_quad(const GemmArgs& a, int t, int row,
       const size_t at = (size_t)row * a.ldo + t * 16 + gg * 4;
       f32x4 x = f32x4{0.f, 0.f, 0.f, 0.f};
       if (live) {
-        x = (pre ? pre_res : *(const f32x4*)(a.res_in + at)) + v;
+        x = (pre ? p.res : *(const f32x4*)(a.res_in + at)) + v;
         Xwg<CO>::st4f(a.out + at, x);
       }
       float sq = x[0] * x[0] + x[1] * x[1] + x[2] * x[2] + x[3] * x[3];
       sq += __shfl_xor(sq, 16, 64);
       sq += __shfl_xor(sq, 32, 64);
-      const f32x4 gn = pre ? pre_gain : *(const f32x4*)(a.gain_next + t * 16 + gg * 4);
+      const f32x4 gn = pre ? p.gain : *(const f32x4*)(a.gain_next + t * 16 + gg * 4);
       const f32x4 y = x * gn;
       const f32x4 hi4 = shfl4(y, lane + 16);  // columns +4..+7 of the 8-column group
       if (live && (gg & 1) == 0) {
@@ -480,7 +489,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, const TeamPos& tp, 
     }
   };
   // residual epilogue: residual and gain values of the first quad this lane will finish
-  f32x4 pre_res = f32x4{0.f, 0.f, 0.f, 0.f}, pre_gain = pre_res;
+  ResidPre pre_ops{};
   bool have_pre = false;
   typedef std::integral_constant<int, 0> none_younger;
   if constexpr (EPI == kEpiAny) {
@@ -490,8 +499,8 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, const TeamPos& tp, 
       if (e_first < min(a.tg, a.ntiles - t0) * MT * 64) {
         const int tt = e_first / (MT * 64), rem = e_first % (MT * 64), l = rem & 63;
         const int row = tp.row_base + (rem >> 6) * 16 + (l & 15), col = (t0 + tt) * 16 + (l >> 4) * 4;
-        if (row < a.m) pre_res = *(const f32x4*)(a.res_in + (size_t)row * a.ldo + col);
-        pre_gain = *(const f32x4*)(a.gain_next + col);
+        if (row < a.m) pre_ops.res = *(const f32x4*)(a.res_in + (size_t)row * a.ldo + col);
+        pre_ops.gain = *(const f32x4*)(a.gain_next + col);
         have_pre = true;
       }
     }
@@ -538,9 +547,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, const TeamPos& tp, 
       const int t0 = g0 * a.tg, nq = min(a.tg, a.ntiles - t0) * MT * 64, e_first = tp.wt * 64 + lane;
       const int e = min(e_first, nq - 1);
       const int tt = e / (MT * 64), rem = e % (MT * 64), l = rem & 63;
-      const int row = min(tp.row_base + (rem >> 6) * 16 + (l & 15), a.m - 1), col = (t0 + tt) * 16 + (l >> 4) * 4;
-      pre_res = *(const f32x4*)(a.res_in + (size_t)row * a.ldo + col);
-      pre_gain = *(const f32x4*)(a.gain_next + col);
+      pre_ops = resid_pre(a, t0 + tt, tp.row_base + (rem >> 6) * 16 + (l & 15), l);
       have_pre = working && e_first < nq;
     }
     if constexpr (P1) {
@@ -618,7 +625,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, const TeamPos& tp, 
         for (int ww = 0; ww < a.W; ++ww) v += red[((size_t)(tt * a.W + ww) * MT + mt) * 64 + l];
         const int lrow = mt * 16 + (l & 15), row = tp.row_base + lrow;
         const float rstd = (a.ssq_in != nullptr && row < a.m) ? rstd_lds[lrow] : 1.0f;
-        epilogue_quad<CO, EPI>(a, t0 + tt, row, l, v, rstd, pre && e == e_first, pre_res, pre_gain);
+        epilogue_quad<CO, EPI>(a, t0 + tt, row, l, v, rstd, pre && e == e_first, pre_ops);
       }
     }
     __syncthreads();  // red is free again

@@ -179,7 +179,7 @@ __global__ __launch_bounds__(kWideWaves * 64) void gemm_wide_kernel(GemmArgs a, 
 
   int rd = 0, wr = kRing - kBuf;  // k-step being read, and the one to be requested into (byte offsets in the ring)
   // where the role totals of a walk with phases wait
-  f32x4* tot = x.ws + ((size_t)(cg * CT + wn * 4) * x.row_tiles + rt0) * 64 + lane;
+  auto tot = [&](int t, int r) { return x.ws + ((size_t)t * x.row_tiles + rt0 + r * WM + wm) * 64 + lane; };
   auto walk = [&](auto lrc) {
     constexpr int LR = decltype(lrc)::value;
     constexpr int NR = 4 + 2 * LR;  // operand reads of a k-step: weights, then (row tile, half)
@@ -240,14 +240,18 @@ __global__ __launch_bounds__(kWideWaves * 64) void gemm_wide_kernel(GemmArgs a, 
         if (++p == a.P) {
           p = 0;
           if constexpr (WHOLE) {  // a role is complete: into the total (nobody else touches these)
+            // (an n-tile's totals asked for before its first store: behind a store each would wait by itself)
 #pragma unroll
             for (int n = 0; n < 4; ++n) {
-              if (cg * CT + wn * 4 + n < a.ntiles) {
+              const int t = cg * CT + wn * 4 + n;
+              if (t < a.ntiles) {
+                f32x4 old[LR > 0 ? LR : 1];
+#pragma unroll
+                for (int r = 0; r < LR; ++r) old[r] = wj == 0 ? zero : *tot(t, r);
 #pragma unroll
                 for (int r = 0; r < LR; ++r) {
-                  f32x4* t = tot + ((size_t)n * x.row_tiles + r * WM + wm) * 64;
-                  sum[n][r] = (wj == 0 ? zero : *t) + sum[n][r];
-                  if (wj + 1 < a.W) *t = sum[n][r];
+                  sum[n][r] = old[r] + sum[n][r];
+                  if (wj + 1 < a.W) *tot(t, r) = sum[n][r];
                 }
               }
             }
@@ -265,21 +269,37 @@ __global__ __launch_bounds__(kWideWaves * 64) void gemm_wide_kernel(GemmArgs a, 
   }
   // the requests past the end of the walk must have landed before the workgroup gives its LDS back
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if constexpr (WHOLE) {
+    // What the epilogue reads is asked for before its first store: behind the stores of an earlier tile every
+    // load would wait by itself.
+    const int t0 = cg * CT + wn * 4;
+    const int c = lane & 15;
+    float rstd[RT];
 #pragma unroll
-  for (int n = 0; n < 4; ++n) {
-    const int t = cg * CT + wn * 4 + n;
+    for (int r = 0; r < RT; ++r) rstd[r] = x.rstd != nullptr ? x.rstd[min((rt0 + r * WM + wm) * 16 + c, a.m - 1)] : 1.0f;
+    const bool resid = a.epi == EPI_RESID;
 #pragma unroll
-    for (int r = 0; r < RT; ++r) {
-      const int lt = r * WM + wm, rt = rt0 + lt;
-      if (t < a.ntiles && lt < live) {
-        if constexpr (WHOLE) {
-          const int row = rt * 16 + (lane & 15);
-          float rstd = 1.0f;
-          if (x.rstd != nullptr && row < a.m) rstd = x.rstd[row];
-          epilogue_quad<false>(a, t, row, lane, sum[n][r], rstd, false, zero, zero);
-        } else {
-          x.ws[(((size_t)role * a.ntiles + t) * x.row_tiles + rt) * 64 + lane] = sum[n][r];
-        }
+    for (int n = 0; n < 4; ++n) {  // (an n-tile at a time: registers)
+      ResidPre pre[RT];
+      if (resid) {
+#pragma unroll
+        for (int r = 0; r < RT; ++r) pre[r] = resid_pre(a, t0 + n, (rt0 + r * WM + wm) * 16 + c, lane);
+      }
+#pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        const int lt = r * WM + wm;
+        if (t0 + n < a.ntiles && lt < live)
+          epilogue_quad<false>(a, t0 + n, (rt0 + lt) * 16 + c, lane, sum[n][r], rstd[r], resid, pre[r]);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+      const int t = cg * CT + wn * 4 + n;
+#pragma unroll
+      for (int r = 0; r < RT; ++r) {
+        const int lt = r * WM + wm, rt = rt0 + lt;
+        if (t < a.ntiles && lt < live) x.ws[(((size_t)role * a.ntiles + t) * x.row_tiles + rt) * 64 + lane] = sum[n][r];
       }
     }
   }
@@ -307,6 +327,7 @@ __global__ __launch_bounds__(256) void wide_rstd_kernel(GemmArgs a, float* rstd)
 
 // split mode, second half: add the W running sums of every 16 x 16 tile in the order w = 0..W-1 and
 // finish it.  Workgroup (4 n-tiles, row tile), one tile per wave; all W sums are requested at once.
+template <int EPI>
 __global__ __launch_bounds__(256) void gemm_wide_finish_kernel(GemmArgs a, WideArgs x) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int rt = (int)blockIdx.y;
@@ -316,22 +337,16 @@ __global__ __launch_bounds__(256) void gemm_wide_finish_kernel(GemmArgs a, WideA
   const int row = rt * 16 + (lane & 15);
   f32x4 pv[kWideMaxRoles];
 #pragma unroll
-  for (int ww = 0; ww < kWideMaxRoles; ++ww)
-    if (ww < a.W) pv[ww] = x.ws[(((size_t)ww * a.ntiles + t) * x.row_tiles + rt) * 64 + lane];
-  // (the residual epilogue's operands travel with the sums; clamped, so that nothing waits at a branch)
-  f32x4 pre_res = zero, pre_gain = zero;
-  const bool resid = a.epi == EPI_RESID;
-  if (resid) {
-    const int col = t * 16 + (lane >> 4) * 4;
-    pre_res = *(const f32x4*)(a.res_in + (size_t)min(row, a.m - 1) * a.ldo + col);
-    pre_gain = *(const f32x4*)(a.gain_next + col);
-  }
-  const float rstd = (x.rstd != nullptr && row < a.m) ? x.rstd[row] : 1.0f;
+  for (int ww = 0; ww < kWideMaxRoles; ++ww) pv[ww] = x.ws[(((size_t)min(ww, a.W - 1) * a.ntiles + t) * x.row_tiles + rt) * 64 + lane];
+  // (the residual epilogue's operands travel with the sums)
+  ResidPre pre{};
+  constexpr bool resid = EPI == EPI_RESID;
+  if constexpr (resid) pre = resid_pre(a, t, row, lane);
+  const float rstd = x.rstd != nullptr ? x.rstd[min(row, a.m - 1)] : 1.0f;
   f32x4 v = zero;
 #pragma unroll
-  for (int ww = 0; ww < kWideMaxRoles; ++ww)
-    if (ww < a.W) v += pv[ww];
-  epilogue_quad<false>(a, t, row, lane, v, rstd, resid, pre_res, pre_gain);
+  for (int ww = 0; ww < kWideMaxRoles; ++ww) v = ww < a.W ? v + pv[ww] : v;
+  epilogue_quad<false, EPI>(a, t, row, lane, v, rstd, resid, pre);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -475,10 +490,18 @@ hipError_t launch_gemm_wide(const GemmCall& c, GemmArgs a, hipStream_t st) {
   else if (p.ct == 8 && p.rt == 1) e = go(integral_constant<int, 4>{}, integral_constant<int, 2>{}, integral_constant<int, 1>{});
   if (e != hipSuccess || p.whole) return e;
   const dim3 fgrid((a.ntiles + 3) / 4, x.row_tiles);
-  if (timed)
-    hipExtLaunchKernelGGL(gemm_wide_finish_kernel, fgrid, dim3(256), 0, st, nullptr, e1, 0, a, x);
-  else
-    gemm_wide_finish_kernel<<<fgrid, 256, 0, st>>>(a, x);
+  auto finish = [&](auto kernel) {
+    if (timed)
+      hipExtLaunchKernelGGL(kernel, fgrid, dim3(256), 0, st, nullptr, e1, 0, a, x);
+    else
+      kernel<<<fgrid, 256, 0, st>>>(a, x);
+  };
+  switch (a.epi) {
+    case EPI_STORE: finish(gemm_wide_finish_kernel<EPI_STORE>); break;
+    case EPI_RESID: finish(gemm_wide_finish_kernel<EPI_RESID>); break;
+    case EPI_SWIGLU: finish(gemm_wide_finish_kernel<EPI_SWIGLU>); break;
+    default: finish(gemm_wide_finish_kernel<EPI_QKV>); break;
+  }
   return hipGetLastError();
 }
 
