@@ -73,14 +73,17 @@ static void shape_for(int N, int K, int slots_cu, GemmPlan& p) {
   p.grid = groups < slots ? groups : slots;
 }
 
-// About how long this kernel takes: a start and an end, the weights once from memory, and the other row
-// tiles' reads of them from the L2s; phases cost another 15 %.  Measured at the 8B shape (microseconds at 1 /
-// 2 / 4 / 8 row tiles): QKV 14 / 17.5 / 20.7 / 30.6, O 11.4 / 13.7 / 16.9 / 25, gate/up 39 / 49 / 71 / 107.
+// About how long this kernel takes in groups of row_tiles workgroups: a start and an end, and what a compute unit
+// reads of the weights, at 52 to 62 GB/s; phases cost another 15 %.  Within 15 % of the measured times of most products of the 1B,
+// 8B and 13B shapes at 33 to 128 rows.  8B QKV, microseconds, narrow / wide with its rstd kernel: 48 rows 18.3 / 23.8, 64
+// 20.1 / 26.0, 80 24.6 / 25.2, 112 30.7 / 28.7; 8B gate/up 48 rows 71 / 52; 1B gate/up 64 rows 26 / 28, 80 30 / 27.
 // (Beyond 8 row tiles the wide kernel runs whatever this says: groups of 10 or 12 workgroups per stream
 // took up to three times as long as groups of 8 or 16.)
-static double gemm_narrow_us(const GemmPlan& p, int row_tiles) {
-  const double mb = (double)p.N * p.K * 2e-6;
-  return (6.5 + mb / 6.9 + 0.05 * mb * (row_tiles - 1)) * (p.P > 1 ? 1.15 : 1.0);
+static double gemm_narrow_us(const GemmPlan& p, int row_tiles, int n_cu) {
+  const int groups = (p.ntiles + p.tg - 1) / p.tg, streams = p.grid / row_tiles;  // (the grid of whole groups)
+  const double mb = (double)((groups + streams - 1) / streams) * p.tg * p.K * 32e-6 * std::max(1.0, (double)p.grid / n_cu);
+  const double mbs = row_tiles <= 3 ? 0.052 : row_tiles <= 5 ? 0.057 : 0.062;
+  return (6.5 + mb / mbs) * (p.P > 1 ? 1.15 : 1.0);
 }
 
 hipError_t launch_gemm_bf16(const GemmCall& c, hipStream_t st) {
@@ -89,8 +92,11 @@ hipError_t launch_gemm_bf16(const GemmCall& c, hipStream_t st) {
   if (c.m < 1 || c.m > kMaxPromptRows || c.K % 512 != 0 || c.act_tiles * 16 < c.m) return hipErrorInvalidValue;
   const int row_tiles = (c.m + 15) / 16;
   GemmPlan p;
-  shape_for(c.N, c.K, std::max(1, n_cu / row_tiles), p);
-  if (row_tiles > 1) p.grid = (p.grid + 7) / 8 * 8 * row_tiles;  // groups are b, b + 8, ..: whole rounds of the 8 chiplets
+  // Groups of workgroups are b, b + 8, ..: whole rounds of the 8 chiplets, and no more of them than the device holds at
+  // once (40 groups of 7 on 256 compute units, 36 rounded up, took 53 us for 8B QKV, 32 groups take 31; 96 rows of 8B gate/up in
+  // 48 groups of 6 185 us, in 40 102).
+  shape_for(c.N, c.K, row_tiles == 1 ? n_cu : std::max(8, n_cu / row_tiles / 8 * 8), p);
+  if (row_tiles > 1) p.grid = (p.grid + 7) / 8 * 8 * row_tiles;
   GemmArgs a{};
   a.wp = (const u32x4*)c.wp;
   a.actp = (const u32x4*)c.actp;
@@ -124,7 +130,7 @@ hipError_t launch_gemm_bf16(const GemmCall& c, hipStream_t st) {
   a.gate = c.gate;
   if (c.gate != nullptr && row_tiles >= kWideMinRowTiles) return hipErrorInvalidValue;  // the wide kernel has no gate
   if (row_tiles >= kWideMinRowTiles && c.wide_mode != 1 &&
-      (c.wide_mode == 2 || row_tiles > 8 || gemm_wide_us(c) < gemm_narrow_us(p, row_tiles)))
+      (c.wide_mode == 2 || row_tiles > 8 || gemm_wide_us(c) < gemm_narrow_us(p, row_tiles, n_cu)))
     return launch_gemm_wide(c, a, st);
   if (c.m > kMaxPassRows) return hipErrorInvalidValue;
   const size_t lds = gemm_lds_floats(p.tg, p.W, 1, 1) * sizeof(float);

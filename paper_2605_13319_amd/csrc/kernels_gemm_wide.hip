@@ -368,56 +368,64 @@ struct WidePlan {
 };
 constexpr size_t kWideSplitBytes = (size_t)128 << 20;  // the most that split products' running sums may take
 
-// Shape of a product by a model of its time.  Measured (microseconds; 8B and 13B projections at 68 .. 2048
-// rows, the model within about 15 %): a workgroup needs 0.08 + 0.0056 per 16 x 16 output tile for a k-step
-// and about 6 around its walk, one workgroup runs per compute unit, the weights come at 5 TB/s at best,
-// and the second kernel of a split product takes 4 plus the running sums at 2.1 TB/s.  So few rows take
-// narrow tiles or a split of K, many rows 128 x 256 outputs per workgroup, and what decides in between
-// is how full the last round of workgroups is.
+// Shapes of the kernel, and what a k-step of a workgroup takes (microseconds): `step`, and `tile` for each of its 16 x 16
+// output tiles; `tbs`: the rate its weights come at from memory when nothing else holds it up (TB/s).
+struct WideShape {
+  int ct, rt;
+  double step, tile, tbs;
+};
+constexpr WideShape kWideShapes[] = {{16, 2, 0.39, 0.0010, 4.2}, {16, 3, 0.44, 0.0016, 4.0}, {16, 4, 0.37, 0.0030, 5.0},
+                                     {8, 1, 0.21, 0.0008, 4.8},  {8, 2, 0.28, 0.0022, 4.4},  {8, 3, 0.30, 0.0034, 4.3}};
+
+// Shape of a product by a model of its time.  A workgroup takes 2.4 us and its k-steps, and 2.5 for every role
+// whose total it keeps in memory; one workgroup runs per compute unit (a last round that is not full is up to 30 %
+// shorter), of the smallest shape two, in 1.84 times the time of one; 5.4 lie around it all, and the second
+// kernel of a split product takes its running sums at 4.2 TB/s.  So few rows take narrow tiles or a split of K, many
+// rows 128 x 256 outputs per workgroup, and what decides in between is how full the last round of workgroups is.
+//
+// The figures are a fit to 3000 timed products (the five of the 1B, 8B and 13B shapes, 33 to 2047 rows, every shape, whole and
+// split): the shape they choose takes 0.3 % longer than the fastest one in the mean and 11 % at most.  Before,
+// with constants from when the second kernel ran at 2.1 TB/s, 4.4 % and 56 %.  Microseconds, that choice / this one: 1B
+// down 700 rows 89.8 (8 x 1, whole) / 57.4 (16 x 3, split); 13B O 256 and 512 rows 57.9 / 38.3 and 98.0 / 69.6 (8 x 1, whole / 16 x 4,
+// split); 13B QKV 48 rows 62.5 / 48.0 (8 x 1, whole / split); 8B O 700 rows 66.2 / 50.4 (8 x 1 / 8 x 2); 8B head 96 rows 279 / 237
+// (16 x 2 / 16 x 3).
 static WidePlan wide_plan(int N, int K, int row_tiles, int n_cu, size_t ws_bytes) {
   int W, P;
   wide_roles(K, W, P);
   const int ntiles = (N + 15) / 16;
   WidePlan best{};
-  for (const int ct : {16, 8})
-    for (int rt = ct == 16 ? 2 : 1; rt <= (ct == 16 ? 4 : 3); ++rt)  // (of equals the smallest that holds the block)
-      for (const bool whole : {true, false}) {
-        const int tiles = (ct == 16 ? 2 : 4) * rt;
-        WidePlan p{ct, rt, whole, 0, (row_tiles + tiles - 1) / tiles, 0.0};
-        p.block_tiles = (row_tiles + p.nrb - 1) / p.nrb;  // (spread evenly)
-        p.nrb = (row_tiles + p.block_tiles - 1) / p.block_tiles;
-        const size_t ws = (size_t)ntiles * row_tiles * 1024 * (whole ? (P > 1 ? 1 : 0) : W);
-        if (ws > (whole ? ws_bytes : std::min(ws_bytes, kWideSplitBytes))) continue;
-        const int wgs = (ntiles + ct - 1) / ct * p.nrb * (whole ? 1 : W), steps = 16 * P * (whole ? W : 1);
-        // The smallest tiles leave room for a second workgroup on a compute unit.  Beyond 64 MB of weights
-        // that does not pay (8B gate/up at 128 rows 83 against 73 us); up to there it depends, and 1.45
-        // times the time of one stands for both outcomes.  Microseconds, with / without: 1B QKV at 660 / 760 /
-        // 1300 rows 33.5 / 34.9, 35.6 / 38.9, 40.5 / 43.7; 1B O at 1030 / 2048 rows 33.5 / 35.2, 46.1 / 45.5;
-        // 8B QKV at 330 / 370 / 400 / 600 / 2048 rows 54.7 / 56.5, 56.9 / 62.5, 61.2 / 56.7, 69.1 / 62.8, 197 / 188;
-        // 8B O at 520 / 800 / 1025 rows 59.4 / 55.7, 69.4 / 62.0, 78.8 / 68.3; 1B down at 1030 / 1300 rows 113 / 123,
-        // 141 / 137.  Neither side of it is faster in every call (a limit of 16 MB: 8B prompts of 400 and more
-        // tokens up to 3 % faster, 8B of 333 and 1B of 1030 tokens 1 and 4 % slower).
-        const bool two = ct == 8 && rt == 1 && (size_t)N * K * 2 <= ((size_t)64 << 20) && wgs > n_cu;
-        const int slots = two ? 2 * n_cu : n_cu;
-        double us = 3.0 + (double)((wgs + slots - 1) / slots) *
-                              (6.0 + steps * (0.08 + 0.0056 * ct * p.block_tiles) * (two ? 1.45 : 1.0));
-        us = std::max(us, 3.0 + (double)ntiles * 16 * K * 2 / 5e6);
-        if (!whole) us += 4.0 + (double)ws / 2.1e6;
-        p.us = us;
-        if (best.ct == 0 || us < best.us) best = p;
+  for (const WideShape& sh : kWideShapes)
+    for (const bool whole : {true, false}) {
+      const int tiles = (sh.ct == 16 ? 2 : 4) * sh.rt;
+      WidePlan p{sh.ct, sh.rt, whole, 0, (row_tiles + tiles - 1) / tiles, 0.0};
+      p.block_tiles = (row_tiles + p.nrb - 1) / p.nrb;  // (spread evenly)
+      p.nrb = (row_tiles + p.block_tiles - 1) / p.block_tiles;
+      const size_t ws = (size_t)ntiles * row_tiles * 1024 * (whole ? (P > 1 ? 1 : 0) : W);
+      if (ws > (whole ? ws_bytes : std::min(ws_bytes, kWideSplitBytes))) continue;
+      const int wgs = (ntiles + sh.ct - 1) / sh.ct * p.nrb * (whole ? 1 : W), steps = 16 * P * (whole ? W : 1);
+      const double one = 2.4 + steps * (sh.step + sh.tile * sh.ct * p.block_tiles) + (whole && P > 1 ? 2.5 * W : 0.0);
+      double us;
+      if (sh.ct == 8 && sh.rt == 1) {
+        const int left = wgs % (2 * n_cu);
+        us = one * (1.84 * (wgs / (2 * n_cu)) + (left == 0 ? 0.0 : left <= n_cu ? 1.0 : 1.84));
+      } else {
+        const int left = wgs % n_cu;
+        us = one * (wgs / n_cu + (left == 0 ? 0.0 : 0.7 + 0.3 * left / n_cu));
       }
+      us = 5.4 + std::max(us, (double)ntiles * 16 * K * 2e-6 / sh.tbs);
+      if (!whole) us += (double)ws / 4.2e6;
+      p.us = us;
+      if (best.ct == 0 || us < best.us) best = p;
+    }
   return best;
 }
 
-// The kernel that computes rstd in front of a product with a norm takes 5 more.  Small products (QKV, O)
-// stay on the narrow kernel longer than large ones.  8 layers and the LM head, microseconds per pass, all
-// narrow / all wide / by these two models: 8B 40 rows 1959 / 1409 / 1344, 80 rows 2585 / 1756 / 1727, 128 rows
-// 2912 / 2121 / 2095; 1B 48 rows 710 / 803 / 704, 80 rows 824 / 822 / 780; 13B 48 rows 2174 / 2022 / 1964.
+// (The kernel that computes rstd in front of a product with a norm takes 3.5 more.)
 double gemm_wide_us(const GemmCall& c) {
   const int n_cu = device_cu_count();
   if (n_cu <= 0) return 0.0;
   const WidePlan p = wide_plan(c.N, c.K, (c.m + 15) / 16, n_cu, c.wide_ws ? c.wide_ws_bytes : 0);
-  return p.us + (c.ssq_in != nullptr ? 5.0 : 0.0);
+  return p.us + (c.ssq_in != nullptr ? 3.5 : 0.0);
 }
 
 // largest workspace any product with N weight rows and K columns asks for at up to max_rows rows

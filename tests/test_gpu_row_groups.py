@@ -1,0 +1,27 @@
+"""Passes of three to eight row tiles, whose products the narrow kernel spreads over groups of as many workgroups: as
+many groups as the device holds at once, whole rounds of the chiplets, and more tiles than groups.  The caches are those
+of the wide kernel, whose shapes change over the same rows, bit for bit."""
+import pytest
+
+from paper_2605_13319_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+# four waves per workgroup (two workgroups per compute unit), eight, and phases with five
+SHAPES = [I.ModelShape("groups-2048", 2, 2048, 16, 4, 128, 4096, 300), I.ModelShape("groups-4096", 2, 4096, 32, 8, 128, 4096, 300),
+          I.ModelShape("groups-5120", 2, 5120, 40, 40, 128, 2560, 300)]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: s.name)
+def test_groups_of_three_to_eight_row_tiles(shape):
+    from paper_2605_13319_amd import nav
+    model = nav.Model(shape, I.make_weights(shape, 71))
+    for rows in (33, 64, 79, 96, 97, 112, 113, 128):
+        toks = I.make_tokens(rows + 1, shape.vocab, 72 + rows)
+        pools = []
+        for mode in (1, 2, 0):
+            model.set_wide_gemm(mode)
+            kv = nav.KVCache(model, max_seqs=1, n_blocks=rows // 16 + 2)
+            kv.prefill(0, toks)
+            pools.append(kv.pool.clone())
+        assert bool((pools[0] == pools[1]).all()) and bool((pools[0] == pools[2]).all()), f"{rows} rows: the caches differ"
