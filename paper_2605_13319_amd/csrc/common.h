@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "attn_plan.h"
+#include "device_lanes.h"
 
 namespace pipesd {
 

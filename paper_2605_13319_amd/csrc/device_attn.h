@@ -159,8 +159,7 @@ __device__ __forceinline__ void attn_task(const float* q, const KvView& kv, int 
   float m_run = sc[0];
 #pragma unroll
   for (int i = 1; i < 8; ++i) m_run = fmaxf(m_run, sc[i]);
-  m_run = fmaxf(m_run, __shfl_xor(m_run, 16, 64));
-  m_run = fmaxf(m_run, __shfl_xor(m_run, 32, 64));
+  m_run = fold_groups(m_run, LaneMax{});
   const float m_ref = (m_run == -INFINITY) ? 0.f : m_run;  // a row that sees none of the tokens: all weights 0
   float pv[8], l_run = 0.f;
 #pragma unroll
@@ -168,8 +167,7 @@ __device__ __forceinline__ void attn_task(const float* q, const KvView& kv, int 
     pv[i] = attn_exp(sc[i] - m_ref);
     l_run += pv[i];
   }
-  l_run += __shfl_xor(l_run, 16, 64);
-  l_run += __shfl_xor(l_run, 32, 64);
+  l_run = fold_groups(l_run, LaneAdd{});
   bf16x8 phi, plo;
   split_hi_lo8(pv, phi, plo);
 #pragma unroll

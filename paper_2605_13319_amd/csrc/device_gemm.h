@@ -201,13 +201,12 @@ __device__ __forceinline__ void chunk_mfma_phase(u32x4 (&af)[KSTEPS], u32x4 (&bh
   }
 }
 
-__device__ __forceinline__ f32x4 shfl4(f32x4 v, int src) {
-  return f32x4{__shfl(v[0], src, 64), __shfl(v[1], src, 64), __shfl(v[2], src, 64), __shfl(v[3], src, 64)};
-}
+__device__ __forceinline__ f32x4 from16(f32x4 v) { return f32x4{from16(v[0]), from16(v[1]), from16(v[2]), from16(v[3])}; }
+__device__ __forceinline__ f32x4 from32(f32x4 v) { return f32x4{from32(v[0]), from32(v[1]), from32(v[2]), from32(v[3])}; }
 
 // Finish one n-tile with a whole wave: lane (gg = lane/16, cc = lane%16) holds the dot products of
 // activation row `row` with weight rows gg*4 .. gg*4+3 of tile t.  Partner rows (i, i+8) sit 32 lanes
-// apart and the two halves of an 8-column group 16 lanes apart, so pairs are joined by shuffles.
+// apart and the two halves of an 8-column group 16 lanes apart, so pairs are joined across lanes.
 // Every lane of the wave must call this (rows beyond the pass only skip the stores).
 // RESID: `pre` says that `p` holds the quad's residual and gain values (resid_pre).
 // EPI: the epilogue as a compile-time constant (the per-projection kernels: only that epilogue's code
@@ -249,11 +248,10 @@ __device__ __forceinline__ void epilogue_quad(const GemmArgs& a, int t, int row,
         Xwg<CO>::st4f(a.out + at, x);
       }
       float sq = x[0] * x[0] + x[1] * x[1] + x[2] * x[2] + x[3] * x[3];
-      sq += __shfl_xor(sq, 16, 64);
-      sq += __shfl_xor(sq, 32, 64);
+      sq = fold_groups(sq, LaneAdd{});
       const f32x4 gn = pre ? p.gain : *(const f32x4*)(a.gain_next + t * 16 + gg * 4);
       const f32x4 y = x * gn;
-      const f32x4 hi4 = shfl4(y, lane + 16);  // columns +4..+7 of the 8-column group
+      const f32x4 hi4 = from16(y);  // columns +4..+7 of the 8-column group
       if (live && (gg & 1) == 0) {
         const float y8[8] = {y[0], y[1], y[2], y[3], hi4[0], hi4[1], hi4[2], hi4[3]};
         store_act8x<CO>(a.outp, row, t * 16 + gg * 4, y8, a.act_tiles);
@@ -262,14 +260,14 @@ __device__ __forceinline__ void epilogue_quad(const GemmArgs& a, int t, int row,
       break;
     }
     case EPI_SWIGLU: {
-      const f32x4 up = shfl4(v, lane + 32);
+      const f32x4 up = from32(v);
       f32x4 y;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const float gt = v[i] * rstd;
         y[i] = (gt / (1.0f + expf(-gt))) * (up[i] * rstd);
       }
-      const f32x4 hi4 = shfl4(y, lane + 16);
+      const f32x4 hi4 = from16(y);
       if (live && gg == 0) {
         const float y8[8] = {y[0], y[1], y[2], y[3], hi4[0], hi4[1], hi4[2], hi4[3]};
         store_act8x<CO>(a.outp, row, t * 8, y8, a.act_tiles);
@@ -277,7 +275,7 @@ __device__ __forceinline__ void epilogue_quad(const GemmArgs& a, int t, int row,
       break;
     }
     case EPI_QKV: {
-      const f32x4 x1 = shfl4(v, lane + 32);
+      const f32x4 x1 = from32(v);
       if (!live || gg >= 2) break;
       const int h = a.kv.head_dim, half = h >> 1, hpt = h >> 4;
       const int hd = t / hpt, i0 = (t % hpt) * 8 + gg * 4;
@@ -379,7 +377,9 @@ __host__ __device__ inline size_t gemm_lds_floats(int tg, int W, int MT, int tea
 // compile time that a.P == 1, and the sums of squares are read iff the epilogue is not the residual one.
 // ONE (MT = 1, several phases): no team has more than one tile, and the activation fragments of the
 // next phase are requested while the current one is multiplied.
-template <int MT, int KSTEPS, bool CO, bool NT = true, int EPI = kEpiAny, bool P1 = false, bool ONE = false>
+// NR, NL: rows whose sums of squares a wave takes at a time, partial sums per lane and row.
+template <int MT, int KSTEPS, bool CO, bool NT = true, int EPI = kEpiAny, bool P1 = false, bool ONE = false, int NR = 2,
+          int NL = kSsqPerLane>
 __device__ __forceinline__ void gemm_body(const GemmArgs& a, const TeamPos& tp, int teams_per_wg, int nwaves_wg,
                                           float* lds, u32x4 (&af)[KSTEPS]) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -417,20 +417,20 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, const TeamPos& tp, 
       }
   };
   // Fused norm: rstd per row from the producer's partial sums of squares, added in index order.  A
-  // wave takes two rows at a time, up to kSsqPerLane partial sums per lane and row (the host checks
-  // ssq_parts <= 64 * kSsqPerLane).  Everything the GEMM needs from the step before it is requested
+  // wave takes NR rows at a time, up to NL partial sums per lane and row (the host checks
+  // ssq_parts <= 64 * NL).  Everything the GEMM needs from the step before it is requested
   // in one go so that it arrives within one memory latency: the sums, the first quad's residual and
   // gain values (residual epilogue), the activation fragments.  Request and wait of the hand-issued
   // loads stay on one straight code path: a join of two paths would let the compiler copy registers
   // whose data is still on its way.
   const bool working = tp.active && tp.team < ngroups;
   const bool norm = a.ssq_in != nullptr;
-  float part[2][kSsqPerLane];
+  float part[NR][NL];
   auto ssq_request = [&](int row0) {
 #pragma unroll
-    for (int r2 = 0; r2 < 2; ++r2)
+    for (int r2 = 0; r2 < NR; ++r2)
 #pragma unroll
-      for (int j4 = 0; j4 < kSsqPerLane; ++j4) {
+      for (int j4 = 0; j4 < NL; ++j4) {
         const int row = row0 + r2 * nwaves_wg, j = lane + 64 * j4;
         part[r2][j4] = 0.f;
         // ("+v": the load lands in the very register that holds the zero of the lanes that skip it)
@@ -442,18 +442,17 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, const TeamPos& tp, 
   // `younger` = a constant number of hand-issued loads requested after the sums (they may stay in flight)
   auto ssq_finish = [&](int row0, auto younger) {
 #pragma unroll
-    for (int r2 = 0; r2 < 2; ++r2)
+    for (int r2 = 0; r2 < NR; ++r2)
 #pragma unroll
-      for (int j4 = 0; j4 < kSsqPerLane; ++j4)
+      for (int j4 = 0; j4 < NL; ++j4)
         asm volatile("s_waitcnt vmcnt(%1)" : "+v"(part[r2][j4]) : "n"(decltype(younger)::value));
 #pragma unroll
-    for (int r2 = 0; r2 < 2; ++r2) {
+    for (int r2 = 0; r2 < NR; ++r2) {
       const int row = row0 + r2 * nwaves_wg;
       float q = part[r2][0];
 #pragma unroll
-      for (int j4 = 1; j4 < kSsqPerLane; ++j4) q += part[r2][j4];
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o, 64);
+      for (int j4 = 1; j4 < NL; ++j4) q += part[r2][j4];
+      q = fold_wave(q, LaneAdd{});
       if (norm && lane == 0 && row < MT * 16) rstd_lds[row] = 1.0f / sqrtf(q / (float)a.K + a.eps);
     }
   };
@@ -464,27 +463,26 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, const TeamPos& tp, 
   // is still on its way (seen once; the ISA lint flags it).
   auto ssq_request_u = [&](int row0) {
 #pragma unroll
-    for (int r2 = 0; r2 < 2; ++r2)
+    for (int r2 = 0; r2 < NR; ++r2)
 #pragma unroll
-      for (int j4 = 0; j4 < kSsqPerLane; ++j4) {
+      for (int j4 = 0; j4 < NL; ++j4) {
         const int row = min(tp.row_base + row0 + r2 * nwaves_wg, a.m - 1), j = min(lane + 64 * j4, a.ssq_parts - 1);
         asm volatile("global_load_dword %0, %1, off" : "=v"(part[r2][j4]) : "v"(a.ssq_in + (size_t)row * a.ssq_stride + j));
       }
   };
   auto ssq_finish_u = [&](int row0) {
 #pragma unroll
-    for (int r2 = 0; r2 < 2; ++r2)
+    for (int r2 = 0; r2 < NR; ++r2)
 #pragma unroll
-      for (int j4 = 0; j4 < kSsqPerLane; ++j4) asm volatile("s_waitcnt vmcnt(0)" : "+v"(part[r2][j4]));
+      for (int j4 = 0; j4 < NL; ++j4) asm volatile("s_waitcnt vmcnt(0)" : "+v"(part[r2][j4]));
 #pragma unroll
-    for (int r2 = 0; r2 < 2; ++r2) {
+    for (int r2 = 0; r2 < NR; ++r2) {
       const int row = row0 + r2 * nwaves_wg;
       const bool live = row < MT * 16 && tp.row_base + row < a.m;
       float q = (live && lane < a.ssq_parts) ? part[r2][0] : 0.f;
 #pragma unroll
-      for (int j4 = 1; j4 < kSsqPerLane; ++j4) q += (live && lane + 64 * j4 < a.ssq_parts) ? part[r2][j4] : 0.f;
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o, 64);
+      for (int j4 = 1; j4 < NL; ++j4) q += (live && lane + 64 * j4 < a.ssq_parts) ? part[r2][j4] : 0.f;
+      q = fold_wave(q, LaneAdd{});
       if (lane == 0 && row < MT * 16) rstd_lds[row] = 1.0f / sqrtf(q / (float)a.K + a.eps);
     }
   };
@@ -512,7 +510,7 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, const TeamPos& tp, 
     }
     ssq_finish(w, none_younger{});
     if (norm)
-      for (int row0 = w + 2 * nwaves_wg; row0 < MT * 16; row0 += 2 * nwaves_wg) {
+      for (int row0 = w + NR * nwaves_wg; row0 < MT * 16; row0 += NR * nwaves_wg) {
         ssq_request(row0);
         ssq_finish(row0, none_younger{});
       }
@@ -557,8 +555,8 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, const TeamPos& tp, 
     if constexpr (P1) await_act();
     if constexpr (NORM) {
       ssq_finish_u(w);
-      if (tp.row_base + 2 * nwaves_wg < a.m)  // (few waves and many rows: the remaining rows)
-        for (int row0 = w + 2 * nwaves_wg; row0 < MT * 16; row0 += 2 * nwaves_wg) {
+      if (tp.row_base + NR * nwaves_wg < a.m)  // (few waves and many rows: the remaining rows)
+        for (int row0 = w + NR * nwaves_wg; row0 < MT * 16; row0 += NR * nwaves_wg) {
           ssq_request_u(row0);
           ssq_finish_u(row0);
         }

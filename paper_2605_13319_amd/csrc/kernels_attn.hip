@@ -354,8 +354,7 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void attn_stream_kernel(const
       float m_new = sc[0];
 #pragma unroll
       for (int i = 1; i < 8; ++i) m_new = fmaxf(m_new, sc[i]);
-      m_new = fmaxf(m_new, __shfl_xor(m_new, 16, 64));
-      m_new = fmaxf(m_new, __shfl_xor(m_new, 32, 64));
+      m_new = fold_groups(m_new, LaneMax{});
       m_new = fmaxf(m_new, m_run[t]);
       const float m_ref = (m_new == -INFINITY) ? 0.f : m_new;  // a row that has seen no token yet: all weights 0
       const float alpha = attn_exp(m_run[t] - m_ref);          // e^-inf = 0 for the first tokens a row sees
@@ -365,8 +364,7 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void attn_stream_kernel(const
         pv[i] = attn_exp(sc[i] - m_ref);
         l_step += pv[i];
       }
-      l_step += __shfl_xor(l_step, 16, 64);
-      l_step += __shfl_xor(l_step, 32, 64);
+      l_step = fold_groups(l_step, LaneAdd{});
       l_run[t] = l_run[t] * alpha + l_step;
       m_run[t] = m_new;
       bf16x8 phi, plo;
@@ -520,17 +518,6 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void attn_stream_kernel(const
 constexpr int kPromptRing = 3;  // steps in LDS
 template <int HD>
 constexpr size_t prompt_lds_bytes() { return (size_t)kPromptRing * (HD / 8) * 1024 + 16; }
-
-// combine x with the lanes 16 and 32 away, in the order of two exchanges by xor (f is commutative)
-template <class F>
-__device__ __forceinline__ float across_groups(float x, F f) {
-  typedef __attribute__((ext_vector_type(2))) unsigned u2;
-  const unsigned a = __float_as_uint(x);
-  const u2 p = __builtin_bit_cast(u2, __builtin_amdgcn_permlane16_swap(a, a, false, false));
-  const unsigned b = __float_as_uint(f(__uint_as_float(p.x), __uint_as_float(p.y)));
-  const u2 r = __builtin_bit_cast(u2, __builtin_amdgcn_permlane32_swap(b, b, false, false));
-  return f(__uint_as_float(r.x), __uint_as_float(r.y));
-}
 
 // (grid: kv heads, groups of four tiles of the largest block, shares of all blocks; the last blocks have the longest
 // contexts: their workgroups start first)
@@ -694,7 +681,7 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void attn_prompt_kernel(const
     for (int i = 1; i < 8; ++i) mx = fmaxf(mx, sc[i]);
     float alpha = 1.0f;
     if (__builtin_amdgcn_ballot_w64(mx > x.m) != 0) {
-      const float m_new = fmaxf(across_groups(mx, [](float a, float b) { return fmaxf(a, b); }), x.m);
+      const float m_new = fmaxf(fold_groups(mx, LaneMax{}), x.m);
       alpha = attn_exp(x.m - (m_new == -INFINITY ? 0.f : m_new));  // (0 for the first tokens a row sees)
       x.m = m_new;
       if (!first) {  // (uniform)
@@ -709,7 +696,7 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void attn_prompt_kernel(const
       pv[i] = attn_exp(sc[i] - m_ref);
       l_step += pv[i];
     }
-    l_step = across_groups(l_step, [](float a, float b) { return a + b; });
+    l_step = fold_groups(l_step, LaneAdd{});
     x.l = __builtin_fmaf(x.l, alpha, l_step);
     bf16x8 phi, plo;
     split_hi_lo8(pv, phi, plo);
@@ -885,7 +872,7 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void attn_prompt_kernel(const
   }
 #pragma unroll
   for (int j = 0; j < HT; ++j) {
-    const f32x4 y = f32x4{o[j][0] / L, o[j][1] / L, o[j][2] / L, o[j][3] / L}, y2 = shfl4(y, lane + 16);  // (elements + 4 .. + 7 of the 8)
+    const f32x4 y = f32x4{o[j][0] / L, o[j][1] / L, o[j][2] / L, o[j][3] / L}, y2 = from16(y);  // (elements + 4 .. + 7 of the 8)
     const float y8[8] = {y[0], y[1], y[2], y[3], y2[0], y2[1], y2[2], y2[3]};
     if (live && (g & 1) == 0) store_act8x<false>((u32x4*)outp, cl.row_off + r, (kvh * group + gq) * HD + j * 16 + g * 4, y8, act_tiles);
   }

@@ -117,8 +117,7 @@ __global__ __launch_bounds__(kF32Waves * 64) void gemm_f32_kernel(GemmF32Call a)
                        ((acc[rt][4] + acc[rt][5]) + (acc[rt][6] + acc[rt][7]));
     if (norm) {
       float q = (sq[rt][0] + sq[rt][1]) + (sq[rt][2] + sq[rt][3]);
-      q += __shfl_xor(q, 16, 64);
-      q += __shfl_xor(q, 32, 64);
+      q = fold_groups(q, LaneAdd{});
       if (g == 0) sqs[w][rt][c] = q;
     }
   }
@@ -142,7 +141,7 @@ __global__ __launch_bounds__(kF32Waves * 64) void gemm_f32_kernel(GemmF32Call a)
   } else if constexpr (EPI == EPI_SWIGLU) {
     f32x4 up;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) up[i] = __shfl(v[i], lane + 32, 64);
+    for (int i = 0; i < 4; ++i) up[i] = from32(v[i]);
     const int j0 = t * 8 + (g & 1) * 4, F = a.N / 2;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -150,7 +149,7 @@ __global__ __launch_bounds__(kF32Waves * 64) void gemm_f32_kernel(GemmF32Call a)
   } else {
     f32x4 pt;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) pt[i] = __shfl(v[i], lane + 32, 64);
+    for (int i = 0; i < 4; ++i) pt[i] = from32(v[i]);
     if (!live || g >= 2) return;
     const int h = a.kv.head_dim, half = h / 2, hpt = h / 16;
     const int hd = t / hpt, i0 = (t % hpt) * 8 + g * 4;
@@ -277,8 +276,7 @@ __global__ __launch_bounds__(kF32Waves * 64) void attn_f32_kernel(const float* _
       mx = fmaxf(mx, sc[s][i]);
     }
   }
-  mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-  mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+  mx = fold_groups(mx, LaneMax{});
   const float ref = mx == -INFINITY ? 0.f : mx;  // (a row that sees none of this wave's tokens)
   float l = 0.f;
   f32x4 osum[kF32AttnSteps][HT];
@@ -301,8 +299,7 @@ __global__ __launch_bounds__(kF32Waves * 64) void attn_f32_kernel(const float* _
       }
     }
   }
-  l += __shfl_xor(l, 16, 64);
-  l += __shfl_xor(l, 32, 64);
+  l = fold_groups(l, LaneAdd{});
 #pragma unroll
   for (int s = 0; s < kF32AttnSteps; ++s)
 #pragma unroll

@@ -14,7 +14,8 @@ namespace pipesd {
 // of its own name, with only its own epilogue's code and registers.
 // P1 says that every wave has a single K slice (no phases); ONE that there are phases and that no team
 // has more than one tile.
-template <int KSTEPS, bool NT, int EPI, bool P1, bool ONE = false>
+// NR, NL: see gemm_body.
+template <int KSTEPS, bool NT, int EPI, bool P1, bool ONE = false, int NR = 2, int NL = kSsqPerLane>
 __global__ __launch_bounds__(512) void gemm_bf16_kernel(GemmArgs a) {
   extern __shared__ float lds[];
   if (a.gate != nullptr && *a.gate == 0) return;  // (uniform: a round of a chain that does not run)
@@ -27,7 +28,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_kernel(GemmArgs a) {
   TeamPos tp{(b / (8 * rt)) * 8 + (b & 7), (int)gridDim.x / rt, w, 0, true};
   tp.row_base = ((b >> 3) % rt) * 16;
   u32x4 af[KSTEPS];
-  gemm_body<1, KSTEPS, false, NT, EPI, P1, ONE>(a, tp, 1, a.W, lds, af);
+  gemm_body<1, KSTEPS, false, NT, EPI, P1, ONE, NR, NL>(a, tp, 1, a.W, lds, af);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -141,13 +142,30 @@ hipError_t launch_gemm_bf16(const GemmCall& c, hipStream_t st) {
     else
       kernel<<<p.grid, p.W * 64, lds, st>>>(a);
   };
+  // Few waves and narrow models (K = 2048: 4 waves, 128 partial sums per row): the sums of squares of all rows in one go,
+  // 2 loads a row.  With 2 rows a wave and 8 loads a row, rows 8 and up are a second go, a memory latency more in
+  // front of everything (1B shape, 9 rows, this and the additions across lanes on the vector unit: QKV 9.3 -> 8.2 us, gate/up
+  // 16.8 -> 16.0, head 25.4 -> 24.7), but for up to 8 rows four would only be more to add (5 rows: gate/up 15.0 -> 15.9).
+  // Eight waves have all rows in one go as it is (8B QKV with 4 loads a row 14.3 -> 14.6).
+  auto launch_norm = [&](auto nt, auto epi, auto p1) {
+    constexpr bool NT = decltype(nt)::value, P1 = decltype(p1)::value;
+    constexpr int EPI = decltype(epi)::value;
+    if constexpr (P1) {
+      if (p.W < 8 && c.ssq_parts <= 2 * 64) {
+        if (c.m <= 2 * p.W) return launch(gemm_bf16_kernel<16, NT, EPI, true, false, 2, 2>);
+        return launch(gemm_bf16_kernel<16, NT, EPI, true, false, 4, 2>);
+      }
+    }
+    launch(gemm_bf16_kernel<16, NT, EPI, P1>);
+  };
   auto launch_p = [&](auto nt, auto p1) {
     constexpr bool NT = decltype(nt)::value, P1 = decltype(p1)::value;
+    using std::integral_constant;
     switch (c.epi) {
-      case EPI_STORE: launch(gemm_bf16_kernel<16, NT, EPI_STORE, P1>); break;
+      case EPI_STORE: launch_norm(nt, integral_constant<int, EPI_STORE>{}, p1); break;
       case EPI_RESID: launch(gemm_bf16_kernel<16, NT, EPI_RESID, P1>); break;
-      case EPI_SWIGLU: launch(gemm_bf16_kernel<16, NT, EPI_SWIGLU, P1>); break;
-      default: launch(gemm_bf16_kernel<16, NT, EPI_QKV, P1>); break;
+      case EPI_SWIGLU: launch_norm(nt, integral_constant<int, EPI_SWIGLU>{}, p1); break;
+      default: launch_norm(nt, integral_constant<int, EPI_QKV>{}, p1); break;
     }
   };
   // Down projections: several K slices per wave and a tile for every team.  Awaiting a slice's

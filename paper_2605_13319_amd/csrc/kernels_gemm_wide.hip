@@ -320,8 +320,7 @@ __global__ __launch_bounds__(256) void wide_rstd_kernel(GemmArgs a, float* rstd)
   float t = v[0];
 #pragma unroll
   for (int j4 = 1; j4 < kSsqPerLane; ++j4) t += v[j4];
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) t += __shfl_xor(t, o, 64);
+  t = fold_wave(t, LaneAdd{});
   if (lane == 0) rstd[row] = 1.0f / sqrtf(t / (float)a.K + a.eps);
 }
 

@@ -38,8 +38,7 @@ __global__ void setup_rows_kernel(const T* __restrict__ emb, PassTokens toks, Ro
   }
   for (int i = (d / 8) * 8 + threadIdx.x; i < d; i += blockDim.x) xres[(size_t)r * d + i] = load_elem(emb, base + i);
   if (ssq_out != nullptr) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) sq += __shfl_xor(sq, o, 64);
+    sq = fold_wave(sq, LaneAdd{});
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sq;
     __syncthreads();
     if (threadIdx.x == 0) ssq_out[(size_t)r * ssq_stride] = (red[0] + red[1]) + (red[2] + red[3]);

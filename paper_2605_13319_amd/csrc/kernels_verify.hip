@@ -18,29 +18,12 @@ struct Uniforms {
   float u[kMaxRows];
 };
 
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
-__device__ __forceinline__ float wave_sumf(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
 __device__ __forceinline__ unsigned long long shfl_u64(unsigned long long v, int src) {
   unsigned lo = (unsigned)v, hi = (unsigned)(v >> 32);
   lo = __shfl(lo, src, 64);
   hi = __shfl(hi, src, 64);
   return ((unsigned long long)hi << 32) | lo;
 }
-__device__ __forceinline__ unsigned long long shfl_up_u64(unsigned long long v, int d) {
-  unsigned lo = (unsigned)v, hi = (unsigned)(v >> 32);
-  lo = __shfl_up(lo, d, 64);
-  hi = __shfl_up(hi, d, 64);
-  return ((unsigned long long)hi << 32) | lo;
-}
-
 // ------------------------------------------------------------------------------------------
 // softmax: per (row, chunk) max and sum of exp; p = exp(z - M) / S with M, S merged from the chunk
 // partials in index order is formed where it is used (spec_accept_kernel), never written out
@@ -68,7 +51,7 @@ __global__ __launch_bounds__(kVThreads) void softmax_stats_kernel(const float* _
   } else {
     for (int i = lo + threadIdx.x; i < hi; i += kVThreads) mx = fmaxf(mx, zr[i]);
   }
-  mx = wave_max(mx);
+  mx = fold_wave(mx, LaneMax{});
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
   __syncthreads();
   mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
@@ -81,7 +64,7 @@ __global__ __launch_bounds__(kVThreads) void softmax_stats_kernel(const float* _
   } else {
     for (int i = lo + threadIdx.x; i < hi; i += kVThreads) s += expf(zr[i] - mx);
   }
-  s = wave_sumf(s);
+  s = fold_wave(s, LaneAdd{});
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -108,17 +91,6 @@ __device__ __forceinline__ bool accept_test(float p, float q, float u) {
 __device__ __forceinline__ unsigned long long fixed_weight(float p, float q, bool residual) {
   const float w = residual ? fmaxf(0.0f, p - q) : p;
   return (unsigned long long)((double)w * 1099511627776.0);  // floor(w * 2^40), exact
-}
-
-// sums of the lanes 0..own lane
-__device__ __forceinline__ unsigned long long wave_scan_u64(unsigned long long v) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const unsigned long long o = shfl_up_u64(v, d);
-    if (lane >= d) v += o;
-  }
-  return v;
 }
 
 // `stats` == nullptr: `p` holds probabilities.  Otherwise `p` holds logits and `stats` the (max,
@@ -171,12 +143,8 @@ __device__ __forceinline__ void spec_accept_body(const float* __restrict__ p, co
     for (int j = 0; j < kRowsPerWave; ++j) {
       const int row = w + j * kWaves;
       if (row > k) break;
-      float M = ms[j].x;
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) M = fmaxf(M, __shfl_xor(M, o, 64));
-      float S = have ? ms[j].y * expf(ms[j].x - M) : 0.f;
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) S += __shfl_xor(S, o, 64);
+      const float M = fold_wave(ms[j].x, LaneMax{});
+      const float S = fold_wave(have ? ms[j].y * expf(ms[j].x - M) : 0.f, LaneAdd{});
       if (lane == 0) {
         s_M[row] = M;
         s_S[row] = S;
@@ -214,8 +182,7 @@ __device__ __forceinline__ void spec_accept_body(const float* __restrict__ p, co
 #pragma unroll
     for (int j = 0; j < kHold; ++j) s += wt[j];
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) s += shfl_u64(s, lane ^ o);
+  s = sum_wave(s);
   if (lane == 0) red[w] = s;
   __syncthreads();
   if (tid == 0) {
@@ -240,7 +207,7 @@ __device__ __forceinline__ void spec_accept_body(const float* __restrict__ p, co
     }
   };
   const unsigned long long mine = __hip_atomic_load(&partial[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  const unsigned long long upto = wave_scan_u64(mine), W = shfl_u64(upto, 63);
+  const unsigned long long upto = scan_wave(mine), W = shfl_u64(upto, 63);
   if (W == 0) {
     // every weight truncated to zero: lowest-index maximum of the target row
     if (tid >= 64) return;
@@ -276,7 +243,7 @@ __device__ __forceinline__ void spec_accept_body(const float* __restrict__ p, co
     unsigned long long own = 0;
 #pragma unroll
     for (int j = 0; j < kHold; ++j) own += wt[j];
-    const unsigned long long inc = wave_scan_u64(own);
+    const unsigned long long inc = scan_wave(own);
     if (lane == 63) red[w] = inc;  // (everybody has read what was there: a barrier lies behind each read)
     __syncthreads();
     unsigned long long at = run + inc - own;  // sum in front of the thread's first token
