@@ -51,15 +51,20 @@ struct RowMap {
   int32_t table_off[kMaxPassRows];  // entries from KvView::table to the client's block table
 };
 
-__device__ __forceinline__ int64_t k_index(const KvView& kv, int layer, int pos, int kvh, int e) {
-  const int blk = kv.table[pos / kBlockTokens];
+// (blk: the sequence's cache block that holds `pos`)
+__device__ __forceinline__ int64_t k_index(const KvView& kv, int layer, int blk, int pos, int kvh, int e) {
   return (int64_t)layer * kv.layer_stride + (int64_t)blk * kv.block_elems +
          ((int64_t)kvh * kBlockTokens + (pos % kBlockTokens)) * kv.head_dim + e;
 }
-__device__ __forceinline__ int64_t v_index(const KvView& kv, int layer, int pos, int kvh, int e) {
-  const int blk = kv.table[pos / kBlockTokens];
+__device__ __forceinline__ int64_t v_index(const KvView& kv, int layer, int blk, int pos, int kvh, int e) {
   return (int64_t)layer * kv.layer_stride + kv.v_offset + (int64_t)blk * kv.block_elems +
          ((int64_t)kvh * kv.head_dim + e) * kBlockTokens + (pos % kBlockTokens);
+}
+__device__ __forceinline__ int64_t k_index(const KvView& kv, int layer, int pos, int kvh, int e) {
+  return k_index(kv, layer, kv.table[pos / kBlockTokens], pos, kvh, e);
+}
+__device__ __forceinline__ int64_t v_index(const KvView& kv, int layer, int pos, int kvh, int e) {
+  return v_index(kv, layer, kv.table[pos / kBlockTokens], pos, kvh, e);
 }
 
 // ActPack: activations handed from one kernel to the next GEMM, already in the B-operand layout of

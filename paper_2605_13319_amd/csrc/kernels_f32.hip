@@ -82,6 +82,21 @@ __global__ __launch_bounds__(kF32Waves * 64) void gemm_f32_kernel(GemmF32Call a)
     for (int j = 0; j < 8; ++j) acc[rt][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     sq[rt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
+  // What the epilogue reads besides the sums is asked for with the first operands (wave rt finishes row tile rt; the
+  // others read its rows again): behind the sums it would be one more round trip to memory.
+  const int erow = min(row0 + min(w, RT - 1) * 16 + c, a.m - 1);
+  f32x4 pre[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+  int blk = 0;
+  if constexpr (EPI == EPI_RESID) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) pre[0][i] = a.out[(size_t)erow * a.ldo + min(t * 16 + g * 4 + i, a.N - 1)];
+  } else if constexpr (EPI == EPI_QKV) {
+    const int h = a.kv.head_dim, hpt = h / 16;
+    const float* cs = a.rope_cs + ((size_t)erow * (h / 2) + (t % hpt) * 8 + (g & 1) * 4) * 2;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) pre[i >> 2][i & 3] = cs[i];
+    blk = a.kv.table[(a.start_pos + erow) / kBlockTokens];
+  }
   for (int k0 = w * 16; k0 < a.K; k0 += kF32Waves * 16 * kAheadF32) {
     f32x4 wf[kAheadF32], gf[kAheadF32], xf[RT][kAheadF32];
 #pragma unroll
@@ -93,7 +108,8 @@ __global__ __launch_bounds__(kF32Waves * 64) void gemm_f32_kernel(GemmF32Call a)
       gf[u] = norm ? load_cols<VEC>(a.gain, k, a.K) : f32x4{1.f, 1.f, 1.f, 1.f};
     }
 #pragma unroll
-    for (int u = 0; u < kAheadF32; ++u)
+    for (int u = 0; u < kAheadF32; ++u) {
+      if (k0 + u * kF32Waves * 16 >= a.K) break;  // (uniform: nothing but zeros from here on)
 #pragma unroll
       for (int rt = 0; rt < RT; ++rt) {
         const f32x4 x = xf[rt][u], y = x * gf[u];
@@ -104,13 +120,15 @@ __global__ __launch_bounds__(kF32Waves * 64) void gemm_f32_kernel(GemmF32Call a)
           s = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[u][j], y[j], s, 0, 0, 0);
         }
       }
+    }
   }
   // (The last products may have been issued in another basic block, where the compiler pads no wait
   // states for the stores below: spell them out.)
+  asm volatile("s_nop 15\n\ts_nop 7" ::: "memory");
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
-    for (int j = 0; j < 8; ++j) asm volatile("s_nop 15\n\ts_nop 7" : "+v"(acc[rt][j]));
+    for (int j = 0; j < 8; ++j) asm volatile("" : "+v"(acc[rt][j]));
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
     red[w][rt][lane] = ((acc[rt][0] + acc[rt][1]) + (acc[rt][2] + acc[rt][3])) +
@@ -137,7 +155,7 @@ __global__ __launch_bounds__(kF32Waves * 64) void gemm_f32_kernel(GemmF32Call a)
     float* o = a.out + (size_t)row * a.ldo + t * 16 + g * 4;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      if (live && t * 16 + g * 4 + i < a.N) o[i] = EPI == EPI_RESID ? o[i] + v[i] : v[i];
+      if (live && t * 16 + g * 4 + i < a.N) o[i] = EPI == EPI_RESID ? pre[0][i] + v[i] : v[i];
   } else if constexpr (EPI == EPI_SWIGLU) {
     f32x4 up;
 #pragma unroll
@@ -155,11 +173,11 @@ __global__ __launch_bounds__(kF32Waves * 64) void gemm_f32_kernel(GemmF32Call a)
     const int hd = t / hpt, i0 = (t % hpt) * 8 + g * 4;
     f32x4 r0 = v, r1 = pt;
     if (hd < a.n_q_heads + a.kv.n_kv_heads) {
-      const float* cs = a.rope_cs + ((size_t)row * half + i0) * 2;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        r0[i] = v[i] * cs[2 * i] - pt[i] * cs[2 * i + 1];
-        r1[i] = pt[i] * cs[2 * i] + v[i] * cs[2 * i + 1];
+        const float cs = pre[i >> 1][2 * (i & 1)], sn = pre[i >> 1][2 * (i & 1) + 1];
+        r0[i] = v[i] * cs - pt[i] * sn;
+        r1[i] = pt[i] * cs + v[i] * sn;
       }
     }
     float* kvp = (float*)a.kv.pool;
@@ -169,11 +187,11 @@ __global__ __launch_bounds__(kF32Waves * 64) void gemm_f32_kernel(GemmF32Call a)
       *(f32x4*)o = r0;
       *(f32x4*)(o + half) = r1;
     } else if (hd < a.n_q_heads + a.kv.n_kv_heads) {
-      float* o = kvp + k_index(a.kv, a.layer, pos, hd - a.n_q_heads, i0);
+      float* o = kvp + k_index(a.kv, a.layer, blk, pos, hd - a.n_q_heads, i0);
       *(f32x4*)o = r0;
       *(f32x4*)(o + half) = r1;
     } else {
-      float* o = kvp + v_index(a.kv, a.layer, pos, hd - a.n_q_heads - a.kv.n_kv_heads, i0);
+      float* o = kvp + v_index(a.kv, a.layer, blk, pos, hd - a.n_q_heads - a.kv.n_kv_heads, i0);
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         o[(size_t)i * kBlockTokens] = r0[i];
