@@ -598,8 +598,9 @@ static KvView view_of(const pipesd_kv* kv, int32_t seq) {
   return v;
 }
 
-// make sure the sequence owns blocks for `rows` cached rows and the device table shows them
-static int ensure_blocks(pipesd_kv* kv, int32_t seq, int32_t rows, hipStream_t st) {
+// make sure the sequence owns blocks for `rows` cached rows and the device table shows them (few new entries are left
+// to `update`, if there is one: the pass that is about to be enqueued writes them)
+static int ensure_blocks(pipesd_kv* kv, int32_t seq, int32_t rows, TableUpdate* update, hipStream_t st) {
   SeqState& s = kv->seqs[seq];
   const int32_t need = blocks_for(rows);
   const int32_t have = (int32_t)s.blocks.size();
@@ -610,7 +611,16 @@ static int ensure_blocks(pipesd_kv* kv, int32_t seq, int32_t rows, hipStream_t s
   }
   if (kv->table_dev && s.table_synced < (int32_t)s.blocks.size()) {
     const int32_t first = s.table_synced, n = (int32_t)s.blocks.size() - first;
-    HIP_TRY(launch_set_table(kv->table_dev + (size_t)seq * kv->n_blocks, first, s.blocks.data() + first, n, st));
+    constexpr int32_t room = sizeof(TableUpdate::v) / sizeof(int32_t);
+    if (update && update->n + n <= room && (int64_t)kv->max_seqs * kv->n_blocks <= INT32_MAX) {
+      update->table = kv->table_dev;
+      for (int32_t i = 0; i < n; ++i) {
+        update->at[update->n] = seq * kv->n_blocks + first + i;
+        update->v[update->n++] = s.blocks[first + i];
+      }
+    } else {
+      HIP_TRY(launch_set_table(kv->table_dev + (size_t)seq * kv->n_blocks, first, s.blocks.data() + first, n, st));
+    }
     s.table_synced = (int32_t)s.blocks.size();
   }
   return PIPESD_OK;
@@ -684,6 +694,7 @@ struct PassLayout {
   PassClient client[kMaxPassClients];
   PassTokens tok{};                      // tokens of the rows (up to kMaxPassRows)
   const int32_t* prompt_tok = nullptr;   // or (one client): where they are on the host
+  TableUpdate update;                    // block-table entries that the pass writes first
 };
 constexpr int kPassRowsCap = 256;  // rows the batched call puts into one pass (<= kMaxPassRows)
 
@@ -762,7 +773,7 @@ static int run_pass(pipesd_model* m, pipesd_kv* kv, const PassLayout& pl, bool w
       }
     HIP_TRY(launch_setup_rows(c.dtype, m->tok_emb, pl.prompt_tok ? part : pl.tok, map, r0, nr, d, c.head_dim, m->theta,
                               bf ? ar.ra(0) : m->xres, m->rope_cs, bf ? m->attn_norm[0] : nullptr, bf ? ar.xa(0) : nullptr,
-                              act_tiles, bf ? ar.sa(0) : nullptr, ar.ssq_stride, single ? nullptr : m->rowmap_dev, st));
+                              act_tiles, bf ? ar.sa(0) : nullptr, ar.ssq_stride, single ? nullptr : m->rowmap_dev, r0 == 0 ? pl.update : TableUpdate{}, st));
   }
   int norm_parts = 1;  // the row setup leaves one sum of squares per row, residual epilogues one per n-tile
   bool fused = false;
@@ -907,8 +918,9 @@ static int run_pass(pipesd_model* m, pipesd_kv* kv, const PassLayout& pl, bool w
 }
 
 static int run_rows(pipesd_model* m, pipesd_kv* kv, int32_t seq, const int32_t* row_tokens, int rows, int start_pos,
-                    bool want_logits, hipStream_t st) {
+                    bool want_logits, const TableUpdate& update, hipStream_t st) {
   PassLayout pl;
+  pl.update = update;
   pl.n_clients = 1;
   pl.rows = rows;
   pl.client[0] = PassClient{seq, rows, start_pos};
@@ -959,11 +971,12 @@ extern "C" int pipesd_prefill(pipesd_model* model, pipesd_kv* kv, int32_t seq, c
   rows.insert(rows.end(), tokens, tokens + n - 1);
   const int32_t start = lp > 0 ? lp - 1 : 0;
   const int32_t cached_before = start;
-  int rc = ensure_blocks(kv, seq, start + (int32_t)rows.size(), st);
+  TableUpdate update;
+  int rc = ensure_blocks(kv, seq, start + (int32_t)rows.size(), rows.empty() ? nullptr : &update, st);
   if (rc) return rc;
   for (size_t i = 0, nr = 0; i < rows.size(); i += nr) {
     nr = (size_t)prompt_pass_rows(model, rows.size() - i, start + (int)i);
-    rc = run_rows(model, kv, seq, rows.data() + i, (int)nr, start + (int)i, false, st);
+    rc = run_rows(model, kv, seq, rows.data() + i, (int)nr, start + (int)i, false, i == 0 ? update : TableUpdate{}, st);
     if (rc) {
       release_beyond(kv, s, cached_before);
       return rc;
@@ -980,9 +993,10 @@ static int verify_common(pipesd_model* model, pipesd_kv* kv, int32_t seq, const 
   int32_t rows[kMaxRows];
   rows[0] = s.text.back();
   for (int32_t i = 0; i < k; ++i) rows[i + 1] = extra[i];
-  int rc = ensure_blocks(kv, seq, lp + k, st);
+  TableUpdate update;
+  int rc = ensure_blocks(kv, seq, lp + k, &update, st);
   if (rc) return rc;
-  rc = run_rows(model, kv, seq, rows, k + 1, lp - 1, true, st);
+  rc = run_rows(model, kv, seq, rows, k + 1, lp - 1, true, update, st);
   if (rc) release_beyond(kv, s, lp - 1);
   *start_out = lp - 1;
   return rc;
@@ -1266,7 +1280,7 @@ extern "C" int pipesd_nav_verify_chain(pipesd_model* model, pipesd_kv* kv, int32
     // booking a round gives back the blocks beyond the rows it kept, those of later rounds included;
     // a later round that ran kept all rows before it, so its own blocks are reserved again (the free
     // list hands back the very blocks it was given last)
-    rc = ensure_blocks(kv, seq, (int32_t)s.text.size() + k_per_round[r], st);
+    rc = ensure_blocks(kv, seq, (int32_t)s.text.size() + k_per_round[r], nullptr, st);
     if (rc == PIPESD_OK)
       rc = commit_verify(model, kv, seq, tokens_concat + tok_off[r], k_per_round[r], model->result_host + 4 + 2 * r,
                          accepted_len + r, next_token + r);
@@ -1339,7 +1353,7 @@ extern "C" int pipesd_nav_verify_batch(pipesd_model* model, pipesd_kv* kv, int32
     }
     int rc = PIPESD_OK;
     for (int32_t i = first; i < last && rc == PIPESD_OK; ++i)
-      rc = ensure_blocks(kv, seq_ids[i], (int32_t)kv->seqs[seq_ids[i]].text.size() + k_per_seq[i], st);
+      rc = ensure_blocks(kv, seq_ids[i], (int32_t)kv->seqs[seq_ids[i]].text.size() + k_per_seq[i], &pl.update, st);
     if (rc == PIPESD_OK) rc = run_pass(model, kv, pl, true, st);
     // The clients that use the sampling rule are decided, and their caches trimmed, by one launch
     // each for the whole pass (bf16, two or more such clients); token-matching clients, and passes

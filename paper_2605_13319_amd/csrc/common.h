@@ -101,6 +101,13 @@ struct RowTokens {
 struct PassTokens {
   int32_t tok[kMaxPassRows];
 };
+// Entries of the sequences' block tables that a pass brings up to date: the row setup, its first launch, writes them
+// (nobody reads the tables before the launch behind it).  A launch of their own is 1.4 us on the device and 5 on the host.
+struct TableUpdate {
+  int32_t* table = nullptr;  // all sequences' tables
+  int32_t n = 0;
+  int32_t at[32], v[32];     // table[at[i]] = v[i]
+};
 
 // embedding gather into the fp32 residual stream + rotary cos/sin of the m positions; for bf16
 // models also the packed, gained copy and the per-row sum of squares for the first fused norm
@@ -110,7 +117,7 @@ struct PassTokens {
 hipError_t launch_setup_rows(int dtype, const void* tok_emb, const PassTokens& toks, const RowMap& map, int row0, int m,
                              int d_model, int head_dim, const double* theta, float* xres, float* rope_cs,
                              const float* gain, void* xpk, int act_tiles, float* ssq_out, int ssq_stride,
-                             RowMap* map_dev, hipStream_t st);
+                             RowMap* map_dev, const TableUpdate& update, hipStream_t st);
 
 // ---- bf16 path: skinny GEMM on the matrix cores over re-tiled weights ----
 enum GemmEpilogue { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_QKV = 3 };

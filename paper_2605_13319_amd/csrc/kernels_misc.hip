@@ -12,7 +12,7 @@ __global__ void setup_rows_kernel(const T* __restrict__ emb, PassTokens toks, Ro
                                   const double* __restrict__ theta, float* __restrict__ xres,
                                   float* __restrict__ rope_cs, const float* __restrict__ gain, uint4* xpk,
                                   int act_tiles, float* __restrict__ ssq_out, int ssq_stride,
-                                  RowMap* __restrict__ map_dev) {
+                                  RowMap* __restrict__ map_dev, TableUpdate update) {
   __shared__ float red[4];
   const int b = blockIdx.x, r = row0 + b;  // (tokens and positions are those of the launch's own rows)
   if (b >= m) return;
@@ -20,6 +20,7 @@ __global__ void setup_rows_kernel(const T* __restrict__ emb, PassTokens toks, Ro
     map_dev->pos[threadIdx.x] = map.pos[threadIdx.x];
     map_dev->table_off[threadIdx.x] = map.table_off[threadIdx.x];
   }
+  if (b == 0 && (int)threadIdx.x < update.n) update.table[update.at[threadIdx.x]] = update.v[threadIdx.x];
   const size_t base = (size_t)toks.tok[b] * d;
   float sq = 0.f;
   for (int j = threadIdx.x; j < d / 8; j += blockDim.x) {
@@ -53,14 +54,14 @@ __global__ void setup_rows_kernel(const T* __restrict__ emb, PassTokens toks, Ro
 hipError_t launch_setup_rows(int dtype, const void* tok_emb, const PassTokens& toks, const RowMap& map, int row0, int m,
                              int d_model, int head_dim, const double* theta, float* xres, float* rope_cs,
                              const float* gain, void* xpk, int act_tiles, float* ssq_out, int ssq_stride,
-                             RowMap* map_dev, hipStream_t st) {
+                             RowMap* map_dev, const TableUpdate& update, hipStream_t st) {
   if (dtype == PIPESD_F32)
     setup_rows_kernel<float><<<m, 256, 0, st>>>((const float*)tok_emb, toks, map, row0, m, d_model, head_dim / 2, theta, xres,
-                                                rope_cs, nullptr, nullptr, 0, nullptr, 0, map_dev);
+                                                rope_cs, nullptr, nullptr, 0, nullptr, 0, map_dev, update);
   else
     setup_rows_kernel<uint16_t><<<m, 256, 0, st>>>((const uint16_t*)tok_emb, toks, map, row0, m, d_model, head_dim / 2, theta,
                                                    xres, rope_cs, gain, (uint4*)xpk, act_tiles, ssq_out, ssq_stride,
-                                                   map_dev);
+                                                   map_dev, update);
   return hipGetLastError();
 }
 
@@ -164,19 +165,20 @@ hipError_t launch_kv_trim_batch(int dtype, const KvView& kv, int n_layers, const
   return hipGetLastError();
 }
 
+constexpr int kTableEntries = 128;  // per launch (a prompt of 2048 tokens in one)
 struct TableEntries {
-  int32_t v[16];
+  int32_t v[kTableEntries];
 };
 __global__ void set_table_kernel(int32_t* table, int first, TableEntries e, int n) {
   if ((int)threadIdx.x < n) table[first + threadIdx.x] = e.v[threadIdx.x];
 }
 
 hipError_t launch_set_table(int32_t* table, int first, const int32_t* entries, int n, hipStream_t st) {
-  for (int i = 0; i < n; i += 16) {
+  for (int i = 0; i < n; i += kTableEntries) {
     TableEntries e;
-    const int c = (n - i < 16) ? (n - i) : 16;
-    for (int j = 0; j < 16; ++j) e.v[j] = j < c ? entries[i + j] : 0;
-    set_table_kernel<<<1, 64, 0, st>>>(table, first + i, e, c);
+    const int c = (n - i < kTableEntries) ? (n - i) : kTableEntries;
+    for (int j = 0; j < kTableEntries; ++j) e.v[j] = j < c ? entries[i + j] : 0;
+    set_table_kernel<<<1, kTableEntries, 0, st>>>(table, first + i, e, c);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
   }

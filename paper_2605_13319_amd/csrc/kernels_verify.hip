@@ -104,8 +104,9 @@ __device__ __forceinline__ unsigned long long fixed_weight(float p, float q, boo
 // scans by the whole last workgroup.  The chunk sums reach it written through and read past the
 // caches, without fences (a device-scope fence writes the whole L2 back), every wave makes the tests for
 // itself, and the arrival counter wraps to zero by itself, so that no launch has to clear it in front:
-// 9.7 -> 7.8 us on given probabilities at that vocabulary and 8 drafts, and 1.4 for the clearing launch
-// (a call of the static entry point among others 14.0 to 14.7 -> 11.3 to 11.5, now the host's share).
+// 9.7 -> 7.8 us on given probabilities at that vocabulary and 8 drafts, and 1.4 for the clearing launch.  With its sums and
+// scans on the vector unit (device_lanes.h) calls of the static entry point follow each other every 6.9 us, which is now the
+// kernel's time; the host takes 6.2 (11.3, its own, before its arguments and its stream came without detours).
 __device__ __forceinline__ void spec_accept_body(const float* __restrict__ p, const float* __restrict__ q,
                                                  const float* __restrict__ stats, int k, int V, const int32_t* drafts,
                                                  const float* un, unsigned long long* partial, unsigned* counter,
