@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+from array import array
 from typing import Dict, Optional, Sequence
 
 import numpy as np
@@ -117,7 +118,37 @@ def _ptr(a: Optional[np.ndarray], typ):
     return None if a is None else a.ctypes.data_as(typ)
 
 
+def _ints(a):
+    """(int32 values as an argument for the library, their number).  A list of Python integers goes straight into a C
+    array (1 us, by way of numpy 3); whatever that does not take, numpy converts or refuses."""
+    if type(a) is list and a:
+        try:
+            buf = array("i", a)
+            return (C.c_int32 * len(buf)).from_buffer(buf), len(buf)
+        except (TypeError, OverflowError):
+            pass
+    v = _i32(a)
+    return _ptr(v, _i32p), len(v)
+
+
+def _floats(a):
+    """The same for float32 values; None stays None."""
+    if type(a) is list and a and type(a[0]) is float:
+        try:
+            buf = array("f", a)
+            return (C.c_float * len(buf)).from_buffer(buf)
+        except (TypeError, OverflowError):
+            pass
+    return None if a is None else _ptr(_f32(a), _f32p)
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
+    """The current stream's handle (0.5 us; 2.8 through a Stream object)."""
+    if _raw_stream is not None and torch.cuda.is_initialized():
+        return _raw_stream(torch.cuda.current_device())
     return int(torch.cuda.current_stream().cuda_stream)
 
 
@@ -297,15 +328,13 @@ class KVCache:
         _check(_lib.pipesd_seq_reset(self.handle, seq), "pipesd_seq_reset")
 
     def prefill(self, seq: int, tokens: Sequence[int]) -> None:
-        t = _i32(tokens)
-        _check(_lib.pipesd_prefill(self.model.handle, self.handle, seq, _ptr(t, _i32p), len(t), _stream()),
-               "pipesd_prefill")
+        t, n = _ints(tokens)
+        _check(_lib.pipesd_prefill(self.model.handle, self.handle, seq, t, n, _stream()), "pipesd_prefill")
 
     def nav_verify(self, seq: int, drafts: Sequence[int], draft_probs=None, uniforms=None,
                    prefix_len: Optional[int] = None):
         """draft_probs: torch CUDA float32 tensor [k][V], or numpy (uploaded), or None (token matching)."""
-        d = _i32(drafts)
-        k = len(d)
+        d, k = _ints(drafts)
         qptr, keep = None, None
         if draft_probs is not None:
             if isinstance(draft_probs, np.ndarray):
@@ -314,20 +343,19 @@ class KVCache:
                 keep = draft_probs.contiguous()
             assert keep.dtype == torch.float32 and keep.numel() == k * self.model.shape.vocab
             qptr = keep.data_ptr()
-        u = None if uniforms is None else _f32(uniforms)
+        u = _floats(uniforms)
         if prefix_len is None:
             prefix_len = self.length(seq)
         a, n = C.c_int32(-1), C.c_int32(-1)
-        _check(_lib.pipesd_nav_verify(self.model.handle, self.handle, seq, prefix_len, _ptr(d, _i32p), k, qptr,
-                                      _ptr(u, _f32p), C.byref(a), C.byref(n), _stream()), "pipesd_nav_verify")
+        _check(_lib.pipesd_nav_verify(self.model.handle, self.handle, seq, prefix_len, d, k, qptr, u, C.byref(a),
+                                      C.byref(n), _stream()), "pipesd_nav_verify")
         return a.value, n.value
 
     def nav_verify_begin(self, seq: int, drafts: Sequence[int], draft_probs=None, uniforms=None,
                          prefix_len: Optional[int] = None) -> None:
         """First half of nav_verify: enqueues the pass and returns without waiting.  The draft
         distributions are kept alive until nav_verify_end."""
-        d = _i32(drafts)
-        k = len(d)
+        d, k = _ints(drafts)
         qptr, keep = None, None
         if draft_probs is not None:
             if isinstance(draft_probs, np.ndarray):
@@ -336,11 +364,11 @@ class KVCache:
                 keep = draft_probs.contiguous()
             assert keep.dtype == torch.float32 and keep.numel() == k * self.model.shape.vocab
             qptr = keep.data_ptr()
-        u = None if uniforms is None else _f32(uniforms)
+        u = _floats(uniforms)
         if prefix_len is None:
             prefix_len = self.length(seq)
-        _check(_lib.pipesd_nav_verify_begin(self.model.handle, self.handle, seq, prefix_len, _ptr(d, _i32p), k, qptr,
-                                            _ptr(u, _f32p), _stream()), "pipesd_nav_verify_begin")
+        _check(_lib.pipesd_nav_verify_begin(self.model.handle, self.handle, seq, prefix_len, d, k, qptr, u, _stream()),
+               "pipesd_nav_verify_begin")
         self._pending_keep = keep
 
     def nav_verify_done(self) -> bool:
@@ -463,14 +491,13 @@ class KVCache:
 
 def spec_accept(p, q, drafts: Sequence[int], uniforms) -> tuple:
     """Decision step alone on device tensors p [k+1][V], q [k][V] (torch CUDA float32)."""
-    d = _i32(drafts)
-    u = _f32(uniforms)
-    k = len(d)
+    d, k = _ints(drafts)
+    u = _floats(uniforms)
     vocab = p.shape[-1]
     assert p.is_contiguous() and q.is_contiguous() and p.shape[0] == k + 1 and q.shape[0] == k
     a, n = C.c_int32(-1), C.c_int32(-1)
-    _check(_lib.pipesd_spec_accept(p.data_ptr(), q.data_ptr(), _ptr(d, _i32p), k, vocab, _ptr(u, _f32p), C.byref(a),
-                                   C.byref(n), _stream()), "pipesd_spec_accept")
+    _check(_lib.pipesd_spec_accept(p.data_ptr(), q.data_ptr(), d, k, vocab, u, C.byref(a), C.byref(n), _stream()),
+           "pipesd_spec_accept")
     return a.value, n.value
 
 
@@ -478,11 +505,10 @@ def spec_accept_static(p, q, drafts: Sequence[int], uniforms, result) -> None:
     """The decision step through the entry point that allocates nothing: enqueues the work on the
     current stream and returns; `result` (torch CUDA int32 tensor of 2) holds {accepted_len,
     next_token} once the stream has been synchronised."""
-    d = _i32(drafts)
-    u = _f32(uniforms)
-    k = len(d)
+    d, k = _ints(drafts)
+    u = _floats(uniforms)
     vocab = p.shape[-1]
     assert p.is_contiguous() and q.is_contiguous() and p.shape[0] == k + 1 and q.shape[0] == k
     assert result.dtype == torch.int32 and result.numel() >= 2 and result.is_cuda
-    _check(_lib.pipesd_spec_accept_static(p.data_ptr(), q.data_ptr(), _ptr(d, _i32p), k, vocab, _ptr(u, _f32p),
-                                          result.data_ptr(), _stream()), "pipesd_spec_accept_static")
+    _check(_lib.pipesd_spec_accept_static(p.data_ptr(), q.data_ptr(), d, k, vocab, u, result.data_ptr(),
+                                          _stream()), "pipesd_spec_accept_static")
