@@ -146,11 +146,12 @@ hipError_t launch_gemm_bf16(const GemmCall& c, hipStream_t st) {
   // 2 loads a row.  With 2 rows a wave and 8 loads a row, rows 8 and up are a second go, a memory latency more in
   // front of everything (1B shape, 9 rows, this and the additions across lanes on the vector unit: QKV 9.3 -> 8.2 us, gate/up
   // 16.8 -> 16.0, head 25.4 -> 24.7), but for up to 8 rows four would only be more to add (5 rows: gate/up 15.0 -> 15.9).
-  // Eight waves have all rows in one go as it is (8B QKV with 4 loads a row 14.3 -> 14.6).
+  // Eight waves have all rows in one go as it is; half the loads: 8B QKV 14.9 -> 14.6, gate/up 40.5 -> 40.3, 32 rows 48.3 -> 48.1.
   auto launch_norm = [&](auto nt, auto epi, auto p1) {
     constexpr bool NT = decltype(nt)::value, P1 = decltype(p1)::value;
     constexpr int EPI = decltype(epi)::value;
     if constexpr (P1) {
+      if (p.W == 8) return launch(gemm_bf16_kernel<16, NT, EPI, true, false, 2, 4>);  // (K = 4096: at most 256 partial sums)
       if (p.W < 8 && c.ssq_parts <= 2 * 64) {
         if (c.m <= 2 * p.W) return launch(gemm_bf16_kernel<16, NT, EPI, true, false, 2, 2>);
         return launch(gemm_bf16_kernel<16, NT, EPI, true, false, 4, 2>);
@@ -185,7 +186,7 @@ hipError_t launch_gemm_bf16(const GemmCall& c, hipStream_t st) {
   if (c.epi < EPI_STORE || c.epi > EPI_QKV) return hipErrorInvalidValue;
   // the residual epilogue is the one without a fused norm in front of it (compile-time knowledge of the kernels)
   if ((c.ssq_in != nullptr) != (c.epi != EPI_RESID)) return hipErrorInvalidValue;
-  if (c.ssq_in != nullptr && c.ssq_parts > 64 * kSsqPerLane) return hipErrorInvalidValue;
+  if (c.ssq_in != nullptr && c.ssq_parts > 64 * (p.P == 1 && p.W == 8 ? 4 : kSsqPerLane)) return hipErrorInvalidValue;
   if (row_tiles == 1)
     launch_nt(std::true_type{});
   else

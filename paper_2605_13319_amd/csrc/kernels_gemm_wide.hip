@@ -308,20 +308,18 @@ __global__ __launch_bounds__(kWideWaves * 64) void gemm_wide_kernel(GemmArgs a, 
 // rstd of every row of the pass, one wave per row, in the narrow kernel's order: lane sums of the partial
 // sums j = lane, lane + 64, .., then the xor butterfly 32, 16, .., 1.  (Latency only: with eight rows per
 // wave, whose butterflies wait for each other, it took 7 us instead of 4.6.)
-__global__ __launch_bounds__(256) void wide_rstd_kernel(GemmArgs a, float* rstd) {
+__global__ __launch_bounds__(256) void wide_rstd_kernel(const float* __restrict__ ssq, int stride, int parts, int m, float k, float eps,
+                                                        float* __restrict__ rstd) {
   const int lane = threadIdx.x & 63, row = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6);
-  if (row >= a.m) return;
+  if (row >= m) return;
   float v[kSsqPerLane];
 #pragma unroll
-  for (int j4 = 0; j4 < kSsqPerLane; ++j4) {
-    const int j = lane + 64 * j4;
-    v[j4] = j < a.ssq_parts ? a.ssq_in[(size_t)row * a.ssq_stride + j] : 0.f;
-  }
-  float t = v[0];
+  for (int j4 = 0; j4 < kSsqPerLane; ++j4) v[j4] = ssq[(size_t)row * stride + min(lane + 64 * j4, parts - 1)];
+  float t = lane < parts ? v[0] : 0.f;
 #pragma unroll
-  for (int j4 = 1; j4 < kSsqPerLane; ++j4) t += v[j4];
+  for (int j4 = 1; j4 < kSsqPerLane; ++j4) t += lane + 64 * j4 < parts ? v[j4] : 0.f;
   t = fold_wave(t, LaneAdd{});
-  if (lane == 0) rstd[row] = 1.0f / sqrtf(t / (float)a.K + a.eps);
+  if (lane == 0) rstd[row] = 1.0f / sqrtf(t / k + eps);
 }
 
 // split mode, second half: add the W running sums of every 16 x 16 tile in the order w = 0..W-1 and
@@ -373,21 +371,21 @@ struct WideShape {
   int ct, rt;
   double step, tile, tbs;
 };
-constexpr WideShape kWideShapes[] = {{16, 2, 0.39, 0.0010, 4.2}, {16, 3, 0.44, 0.0016, 4.0}, {16, 4, 0.37, 0.0030, 5.0},
-                                     {8, 1, 0.21, 0.0008, 4.8},  {8, 2, 0.28, 0.0022, 4.4},  {8, 3, 0.30, 0.0034, 4.3}};
+constexpr WideShape kWideShapes[] = {{16, 2, 0.39, 0.0010, 4.2}, {16, 3, 0.44, 0.0016, 4.4}, {16, 4, 0.34, 0.0030, 5.2},
+                                     {8, 1, 0.21, 0.0008, 4.8},  {8, 2, 0.30, 0.0022, 4.4},  {8, 3, 0.30, 0.0034, 4.3}};
 
-// Shape of a product by a model of its time.  A workgroup takes 2.4 us and its k-steps, and 2.5 for every role
-// whose total it keeps in memory; one workgroup runs per compute unit (a last round that is not full is up to 30 %
+// Shape of a product by a model of its time.  A workgroup takes 3.4 us and its k-steps, and 1.25 for every role
+// whose total it keeps in memory; one workgroup runs per compute unit (a last round that is not full is up to 25 %
 // shorter), of the smallest shape two, in 1.84 times the time of one; 5.4 lie around it all, and the second
-// kernel of a split product takes its running sums at 4.2 TB/s.  So few rows take narrow tiles or a split of K, many
+// kernel of a split product takes 1.5 and its running sums at 3.6 TB/s.  So few rows take narrow tiles or a split of K, many
 // rows 128 x 256 outputs per workgroup, and what decides in between is how full the last round of workgroups is.
 //
 // The figures are a fit to 3000 timed products (the five of the 1B, 8B and 13B shapes, 33 to 2047 rows, every shape, whole and
-// split): the shape they choose takes 0.3 % longer than the fastest one in the mean and 11 % at most.  Before,
-// with constants from when the second kernel ran at 2.1 TB/s, 4.4 % and 56 %.  Microseconds, that choice / this one: 1B
-// down 700 rows 89.8 (8 x 1, whole) / 57.4 (16 x 3, split); 13B O 256 and 512 rows 57.9 / 38.3 and 98.0 / 69.6 (8 x 1, whole / 16 x 4,
-// split); 13B QKV 48 rows 62.5 / 48.0 (8 x 1, whole / split); 8B O 700 rows 66.2 / 50.4 (8 x 1 / 8 x 2); 8B head 96 rows 279 / 237
-// (16 x 2 / 16 x 3).
+// split), three times over, on cards that write running sums at 2 and at 4 TB/s: the shape they choose takes 0.3 to 0.75 % longer
+// than the fastest one in the mean and 17 % at most.  Before, with constants from when the second kernel
+// ran at 2.1 TB/s, 4.4 % and 56 %.  Microseconds, that choice / this one: 1B down 700 rows 89.8 (8 x 1, whole) / 57.4 (16 x 3,
+// split); 13B O 256 and 512 rows 57.9 / 38.3 and 98.0 / 69.6 (8 x 1, whole / 16 x 4, split); 13B QKV 48 rows 62.5 / 48.0 (8 x 1, whole /
+// split); 8B O 700 rows 66.2 / 50.4 (8 x 1 / 8 x 2); 8B head 96 rows 279 / 237 (16 x 2 / 16 x 3).
 static WidePlan wide_plan(int N, int K, int row_tiles, int n_cu, size_t ws_bytes) {
   int W, P;
   wide_roles(K, W, P);
@@ -402,29 +400,30 @@ static WidePlan wide_plan(int N, int K, int row_tiles, int n_cu, size_t ws_bytes
       const size_t ws = (size_t)ntiles * row_tiles * 1024 * (whole ? (P > 1 ? 1 : 0) : W);
       if (ws > (whole ? ws_bytes : std::min(ws_bytes, kWideSplitBytes))) continue;
       const int wgs = (ntiles + sh.ct - 1) / sh.ct * p.nrb * (whole ? 1 : W), steps = 16 * P * (whole ? W : 1);
-      const double one = 2.4 + steps * (sh.step + sh.tile * sh.ct * p.block_tiles) + (whole && P > 1 ? 2.5 * W : 0.0);
+      const double one = 3.4 + steps * (sh.step + sh.tile * sh.ct * p.block_tiles) + (whole && P > 1 ? 1.25 * W : 0.0);
       double us;
       if (sh.ct == 8 && sh.rt == 1) {
         const int left = wgs % (2 * n_cu);
         us = one * (1.84 * (wgs / (2 * n_cu)) + (left == 0 ? 0.0 : left <= n_cu ? 1.0 : 1.84));
       } else {
         const int left = wgs % n_cu;
-        us = one * (wgs / n_cu + (left == 0 ? 0.0 : 0.7 + 0.3 * left / n_cu));
+        us = one * (wgs / n_cu + (left == 0 ? 0.0 : 0.75 + 0.25 * left / n_cu));
       }
       us = 5.4 + std::max(us, (double)ntiles * 16 * K * 2e-6 / sh.tbs);
-      if (!whole) us += (double)ws / 4.2e6;
+      if (!whole) us += 1.5 + (double)ws / 3.6e6;
       p.us = us;
       if (best.ct == 0 || us < best.us) best = p;
     }
   return best;
 }
 
-// (The kernel that computes rstd in front of a product with a norm takes 3.5 more.)
+// Against the narrow kernel: the kernel that computes rstd in front of a product with a norm takes 3.5 more, and a split counts
+// for 1.5 more than the fit says, since it is the one that cards differ in (8B O 96 rows, narrow 20.2, split 17.7 and 23.9).
 double gemm_wide_us(const GemmCall& c) {
   const int n_cu = device_cu_count();
   if (n_cu <= 0) return 0.0;
   const WidePlan p = wide_plan(c.N, c.K, (c.m + 15) / 16, n_cu, c.wide_ws ? c.wide_ws_bytes : 0);
-  return p.us + (c.ssq_in != nullptr ? 3.5 : 0.0);
+  return p.us + (c.ssq_in != nullptr ? 3.5 : 0.0) + (p.whole ? 0.0 : 1.5);
 }
 
 // largest workspace any product with N weight rows and K columns asks for at up to max_rows rows
@@ -464,9 +463,10 @@ hipError_t launch_gemm_wide(const GemmCall& c, GemmArgs a, hipStream_t st) {
     if (c.rstd == nullptr) return hipErrorInvalidValue;
     const dim3 rgrid((c.m + 3) / 4);
     if (timed)
-      hipExtLaunchKernelGGL(wide_rstd_kernel, rgrid, dim3(256), 0, st, e0, nullptr, 0, a, c.rstd);
+      hipExtLaunchKernelGGL(wide_rstd_kernel, rgrid, dim3(256), 0, st, e0, nullptr, 0, a.ssq_in, a.ssq_stride, a.ssq_parts, c.m,
+                            (float)a.K, a.eps, c.rstd);
     else
-      wide_rstd_kernel<<<rgrid, 256, 0, st>>>(a, c.rstd);
+      wide_rstd_kernel<<<rgrid, 256, 0, st>>>(a.ssq_in, a.ssq_stride, a.ssq_parts, c.m, (float)a.K, a.eps, c.rstd);
     e0 = nullptr;
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
