@@ -106,7 +106,7 @@ static constexpr int kCounterSlots = 1 << 16;
 
 // Rows per pass of an fp32 model's prompt blocks: 128 where the matrix-core attention takes the head size (the general kernel
 // keeps a pass's query rows in LDS).  Rows beyond 32 are more workgroups of the same launches: a
-// 120-token prompt into 2 layers is 8 launches (block table, row setup, five of the first layer, the last
+// 120-token prompt into 2 layers is 7 launches (row setup, five of the first layer, the last
 // layer's QKV) instead of four passes of 32 rows.
 static int f32_pass_rows(const pipesd_config& c) { return c.head_dim % 16 == 0 ? 128 : kMaxRows; }
 

@@ -24,10 +24,10 @@ namespace pipesd {
 // x * gain is scaled by the row's rstd at the end.
 //
 // Bound by the latency of the requests, not by bandwidth (5.3 MB of weights in all for 2 layers of
-// width 256).  Two layers of that width: a round of 5 rows at a context of 128 takes 111 us, 264 with one
+// width 256).  Two layers of that width: a round of 5 rows at a context of 128 takes 99 us, 264 with one
 // wave per output column on the vector units and the norm, rotary and SiLU steps in launches of their
-// own; a prompt of 120 tokens 60 us (its last layer ends behind its keys and values), 2340 before (a
-// launch of 32 rows: 84 us, now 8 for all 119).
+// own; a prompt of 120 tokens 52 us (its last layer ends behind its keys and values), 2340 before (a
+// launch of 32 rows: 84 us, now 7 for all 119).
 constexpr int kF32Waves = 8;
 constexpr int kAheadF32 = 4;
 
