@@ -377,9 +377,10 @@ __host__ __device__ inline size_t gemm_lds_floats(int tg, int W, int MT, int tea
 // compile time that a.P == 1, and the sums of squares are read iff the epilogue is not the residual one.
 // ONE (MT = 1, several phases): no team has more than one tile, and the activation fragments of the
 // next phase are requested while the current one is multiplied.
-// NR, NL: rows whose sums of squares a wave takes at a time, partial sums per lane and row.
+// NR, NL: rows whose sums of squares a wave takes at a time, partial sums per lane and row.  SHUF: they are added across
+// the lanes by shuffles through the LDS unit instead of on the vector unit (the same sums; the launcher says where).
 template <int MT, int KSTEPS, bool CO, bool NT = true, int EPI = kEpiAny, bool P1 = false, bool ONE = false, int NR = 2,
-          int NL = kSsqPerLane>
+          int NL = kSsqPerLane, bool SHUF = false>
 __device__ __forceinline__ void gemm_body(const GemmArgs& a, const TeamPos& tp, int teams_per_wg, int nwaves_wg,
                                           float* lds, u32x4 (&af)[KSTEPS]) {
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -482,7 +483,12 @@ __device__ __forceinline__ void gemm_body(const GemmArgs& a, const TeamPos& tp, 
       float q = (live && lane < a.ssq_parts) ? part[r2][0] : 0.f;
 #pragma unroll
       for (int j4 = 1; j4 < NL; ++j4) q += (live && lane + 64 * j4 < a.ssq_parts) ? part[r2][j4] : 0.f;
-      q = fold_wave(q, LaneAdd{});
+      if constexpr (SHUF) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o, 64);
+      } else {
+        q = fold_wave(q, LaneAdd{});
+      }
       if (lane == 0 && row < MT * 16) rstd_lds[row] = 1.0f / sqrtf(q / (float)a.K + a.eps);
     }
   };

@@ -14,8 +14,8 @@ namespace pipesd {
 // of its own name, with only its own epilogue's code and registers.
 // P1 says that every wave has a single K slice (no phases); ONE that there are phases and that no team
 // has more than one tile.
-// NR, NL: see gemm_body.
-template <int KSTEPS, bool NT, int EPI, bool P1, bool ONE = false, int NR = 2, int NL = kSsqPerLane>
+// NR, NL, SHUF: see gemm_body.
+template <int KSTEPS, bool NT, int EPI, bool P1, bool ONE = false, int NR = 2, int NL = kSsqPerLane, bool SHUF = false>
 __global__ __launch_bounds__(512) void gemm_bf16_kernel(GemmArgs a) {
   extern __shared__ float lds[];
   if (a.gate != nullptr && *a.gate == 0) return;  // (uniform: a round of a chain that does not run)
@@ -28,7 +28,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_kernel(GemmArgs a) {
   TeamPos tp{(b / (8 * rt)) * 8 + (b & 7), (int)gridDim.x / rt, w, 0, true};
   tp.row_base = ((b >> 3) % rt) * 16;
   u32x4 af[KSTEPS];
-  gemm_body<1, KSTEPS, false, NT, EPI, P1, ONE, NR, NL>(a, tp, 1, a.W, lds, af);
+  gemm_body<1, KSTEPS, false, NT, EPI, P1, ONE, NR, NL, SHUF>(a, tp, 1, a.W, lds, af);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -146,11 +146,23 @@ hipError_t launch_gemm_bf16(const GemmCall& c, hipStream_t st) {
   // 2 loads a row.  With 2 rows a wave and 8 loads a row, rows 8 and up are a second go, a memory latency more in
   // front of everything (1B shape, 9 rows, this and the additions across lanes on the vector unit: QKV 9.3 -> 8.2 us, gate/up
   // 16.8 -> 16.0, head 25.4 -> 24.7), but for up to 8 rows four would only be more to add (5 rows: gate/up 15.0 -> 15.9).
-  // Eight waves have all rows in one go as it is; half the loads: 8B QKV 14.9 -> 14.6, gate/up 40.5 -> 40.3, 32 rows 48.3 -> 48.1.
+  // Eight waves have all rows in one go as it is; half the loads: 8B QKV 14.9 -> 14.6, gate/up 40.5 -> 40.3.
+  //
+  // Two row tiles: with the additions across lanes through the LDS unit and all eight loads, slower as each is by itself, the two
+  // workgroups that read a tile's weights finish sooner (shown by exchanging one thing at a time: of 32 rows behind 1531 at
+  // the 8B shape 4380 us on the vector unit with 4 loads, 4362 by shuffles, 4340 by shuffles with 8; why they then share the L2s better
+  // is not).  Vector unit / this, medians over six model handles: 17 rows behind 777 3932 / 3938, prompts of 24 and 33 tokens 3562 / 3550 and
+  // 3719 / 3691, 29 rows behind 3000 4672 / 4641, 32 behind 1531 4371 / 4342.  From three row tiles on it turns (33 to 62 rows
+  // 3880 / 3888, 3872 / 3882, 3892 / 3895, 4370 / 4374), one has nobody to share with (9 rows 3468 / 3474), and so do models with four waves or
+  // with phases (17 and 32 rows: 1B 1005 / 1016 and 1139 / 1136, 13B 1601 / 1609 and 1787 / 1791).
+  const bool shuf = p.P == 1 && p.W == 8 && row_tiles == 2;
   auto launch_norm = [&](auto nt, auto epi, auto p1) {
     constexpr bool NT = decltype(nt)::value, P1 = decltype(p1)::value;
     constexpr int EPI = decltype(epi)::value;
     if constexpr (P1) {
+      if constexpr (!NT) {
+        if (shuf) return launch(gemm_bf16_kernel<16, NT, EPI, true, false, 2, kSsqPerLane, true>);
+      }
       if (p.W == 8) return launch(gemm_bf16_kernel<16, NT, EPI, true, false, 2, 4>);  // (K = 4096: at most 256 partial sums)
       if (p.W < 8 && c.ssq_parts <= 2 * 64) {
         if (c.m <= 2 * p.W) return launch(gemm_bf16_kernel<16, NT, EPI, true, false, 2, 2>);
@@ -186,7 +198,7 @@ hipError_t launch_gemm_bf16(const GemmCall& c, hipStream_t st) {
   if (c.epi < EPI_STORE || c.epi > EPI_QKV) return hipErrorInvalidValue;
   // the residual epilogue is the one without a fused norm in front of it (compile-time knowledge of the kernels)
   if ((c.ssq_in != nullptr) != (c.epi != EPI_RESID)) return hipErrorInvalidValue;
-  if (c.ssq_in != nullptr && c.ssq_parts > 64 * (p.P == 1 && p.W == 8 ? 4 : kSsqPerLane)) return hipErrorInvalidValue;
+  if (c.ssq_in != nullptr && c.ssq_parts > 64 * (p.P == 1 && p.W == 8 && !shuf ? 4 : kSsqPerLane)) return hipErrorInvalidValue;
   if (row_tiles == 1)
     launch_nt(std::true_type{});
   else

@@ -25,3 +25,18 @@ def test_groups_of_three_to_eight_row_tiles(shape):
             kv.prefill(0, toks)
             pools.append(kv.pool.clone())
         assert bool((pools[0] == pools[1]).all()) and bool((pools[0] == pools[2]).all()), f"{rows} rows: the caches differ"
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: s.name)
+def test_two_and_more_row_tiles_equal_passes_of_one(shape):
+    """Two row tiles add their sums of squares in another kernel than one and three do (eight waves): the same bits."""
+    from paper_2605_13319_amd import nav
+    model = nav.Model(shape, I.make_weights(shape, 73))
+    model.set_wide_gemm(1)
+    toks = I.make_tokens(50, shape.vocab, 74)
+    for rows in (17, 31, 32, 33, 48):
+        kv, parts = (nav.KVCache(model, max_seqs=1, n_blocks=8) for _ in range(2))
+        kv.prefill(0, toks[:rows + 1])
+        for at in range(0, rows + 1, 16):
+            parts.prefill(0, toks[at:min(at + 16, rows + 1)])
+        assert bool((kv.pool == parts.pool).all()), f"{rows} rows: the caches differ"
