@@ -6,6 +6,7 @@
 
 #include "attn_plan.h"
 #include "device_lanes.h"
+#include "gemm_plan.h"
 
 namespace pipesd {
 
@@ -123,11 +124,6 @@ hipError_t launch_setup_rows(int dtype, const void* tok_emb, const PassTokens& t
 enum GemmEpilogue { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_QKV = 3 };
 enum PackMode { PACK_PLAIN = 0, PACK_HALVES = 1 };
 
-struct GemmPlan {  // launch shape of one GEMM
-  int K, N, ntiles;
-  int W, P, grid, tg;  // waves per workgroup, K phases per wave, workgroups, n-tiles per group
-};
-
 struct GemmCall {
   const void* wp;     // re-tiled weights [N][K]
   int N, K, m;
@@ -161,9 +157,6 @@ struct GemmCall {
 };
 hipError_t launch_gemm_bf16(const GemmCall& c, hipStream_t st);
 int device_cu_count();
-// the most bytes of GemmCall::wide_ws a product with N weight rows and K columns asks for in passes of
-// up to max_rows rows
-size_t gemm_wide_workspace_bytes(int N, int K, int max_rows);
 
 // re-tile [rows][K] bf16 row-major (up to 3 stacked sources) into 16-row x 32-column matrix-core
 // fragments; PACK_HALVES makes tile rows 8..15 the partners (second source half / second half of

@@ -68,9 +68,7 @@ struct GemmArgs {
 
 // passes of at least this many row tiles can take the wide kernel (kernels_gemm_wide.hip; below, the
 // packed activations have the layout of few rows); `a` comes filled in by launch_gemm_bf16
-constexpr int kWideMinRowTiles = 3;
 hipError_t launch_gemm_wide(const GemmCall& c, GemmArgs a, hipStream_t st);
-double gemm_wide_us(const GemmCall& c);  // about how long it takes
 
 __device__ __forceinline__ bf16x8 as_bf16x8(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
 

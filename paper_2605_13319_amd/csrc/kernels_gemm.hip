@@ -34,8 +34,6 @@ __global__ __launch_bounds__(512) void gemm_bf16_kernel(GemmArgs a) {
 // ------------------------------------------------------------------------------------------------
 // launch shape
 // ------------------------------------------------------------------------------------------------
-constexpr int kTmax16 = 7;  // n-tiles per group at W = 8 (the LDS reduce area stays under 64 KB)
-
 int device_cu_count() {
   static int n_cu = 0;
   if (n_cu == 0) {
@@ -47,57 +45,12 @@ int device_cu_count() {
   return n_cu;
 }
 
-// launch shape for `slots_cu` compute units' worth of teams (a pass of more than 16 rows puts two
-// workgroups on every team's tiles, so it plans for half the device)
-static void shape_for(int N, int K, int slots_cu, GemmPlan& p) {
-  p.K = K;
-  p.N = N;
-  p.ntiles = (N + 15) / 16;
-  const int slices = K / 512;
-  int W = 1;
-  for (int cand = 8; cand >= 1; --cand)
-    if (slices % cand == 0) { W = cand; break; }
-  p.W = W;
-  p.P = slices / W;
-  const int slots = slots_cu * (8 / W > 0 ? 8 / W : 1);
-  const int tmax = kTmax16 * 8 / W;
-  int best_tg = 1;
-  long best_cost = -1;
-  for (int tg = 1; tg <= tmax; ++tg) {
-    const int groups = (p.ntiles + tg - 1) / tg;
-    const long rounds = (groups + slots - 1) / slots;
-    const long cost = rounds * tg;
-    if (best_cost < 0 || cost <= best_cost) { best_cost = cost; best_tg = tg; }
-  }
-  p.tg = best_tg;
-  const int groups = (p.ntiles + p.tg - 1) / p.tg;
-  p.grid = groups < slots ? groups : slots;
-}
-
-// About how long this kernel takes in groups of row_tiles workgroups: a start and an end, and what a compute unit
-// reads of the weights, at 52 to 62 GB/s; phases cost another 15 %.  Within 15 % of the measured times of most products of the 1B,
-// 8B and 13B shapes at 33 to 128 rows.  8B QKV, microseconds, narrow / wide with its rstd kernel: 48 rows 18.3 / 23.8, 64
-// 20.1 / 26.0, 80 24.6 / 25.2, 112 30.7 / 28.7; 8B gate/up 48 rows 71 / 52; 1B gate/up 64 rows 26 / 28, 80 30 / 27.
-// (Beyond 8 row tiles the wide kernel runs whatever this says: groups of 10 or 12 workgroups per stream
-// took up to three times as long as groups of 8 or 16.)
-static double gemm_narrow_us(const GemmPlan& p, int row_tiles, int n_cu) {
-  const int groups = (p.ntiles + p.tg - 1) / p.tg, streams = p.grid / row_tiles;  // (the grid of whole groups)
-  const double mb = (double)((groups + streams - 1) / streams) * p.tg * p.K * 32e-6 * std::max(1.0, (double)p.grid / n_cu);
-  const double mbs = row_tiles <= 3 ? 0.052 : row_tiles <= 5 ? 0.057 : 0.062;
-  return (6.5 + mb / mbs) * (p.P > 1 ? 1.15 : 1.0);
-}
-
 hipError_t launch_gemm_bf16(const GemmCall& c, hipStream_t st) {
   const int n_cu = device_cu_count();
   if (n_cu <= 0) return hipErrorUnknown;
   if (c.m < 1 || c.m > kMaxPromptRows || c.K % 512 != 0 || c.act_tiles * 16 < c.m) return hipErrorInvalidValue;
   const int row_tiles = (c.m + 15) / 16;
-  GemmPlan p;
-  // Groups of workgroups are b, b + 8, ..: whole rounds of the 8 chiplets, and no more of them than the device holds at
-  // once (40 groups of 7 on 256 compute units, 36 rounded up, took 53 us for 8B QKV, 32 groups take 31; 96 rows of 8B gate/up in
-  // 48 groups of 6 185 us, in 40 102).
-  shape_for(c.N, c.K, row_tiles == 1 ? n_cu : std::max(8, n_cu / row_tiles / 8 * 8), p);
-  if (row_tiles > 1) p.grid = (p.grid + 7) / 8 * 8 * row_tiles;
+  const GemmPlan p = gemm_narrow_plan(c.N, c.K, row_tiles, n_cu);
   GemmArgs a{};
   a.wp = (const u32x4*)c.wp;
   a.actp = (const u32x4*)c.actp;
@@ -130,8 +83,7 @@ hipError_t launch_gemm_bf16(const GemmCall& c, hipStream_t st) {
   a.act_tiles = c.act_tiles;
   a.gate = c.gate;
   if (c.gate != nullptr && row_tiles >= kWideMinRowTiles) return hipErrorInvalidValue;  // the wide kernel has no gate
-  if (row_tiles >= kWideMinRowTiles && c.wide_mode != 1 &&
-      (c.wide_mode == 2 || row_tiles > 8 || gemm_wide_us(c) < gemm_narrow_us(p, row_tiles, n_cu)))
+  if (gemm_takes_wide(p, row_tiles, c.ssq_in != nullptr, c.wide_mode, n_cu, c.wide_ws ? c.wide_ws_bytes : 0))
     return launch_gemm_wide(c, a, st);
   if (c.m > kMaxPassRows) return hipErrorInvalidValue;
   const size_t lds = gemm_lds_floats(p.tg, p.W, 1, 1) * sizeof(float);

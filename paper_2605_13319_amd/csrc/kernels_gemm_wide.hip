@@ -349,91 +349,6 @@ __global__ __launch_bounds__(256) void gemm_wide_finish_kernel(GemmArgs a, WideA
 // ------------------------------------------------------------------------------------------------
 // launch shape
 // ------------------------------------------------------------------------------------------------
-// the narrow kernel's split of K (W waves x P phases of 512 columns), which fixes the order of the sums
-static void wide_roles(int K, int& W, int& P) {
-  W = 1;
-  for (int cand = 8; cand >= 1; --cand)
-    if ((K / 512) % cand == 0) { W = cand; break; }
-  P = K / 512 / W;
-}
-
-struct WidePlan {
-  int ct, rt;  // n-tiles per workgroup: 16 (2 x 4 waves of rt x 4 tiles) or 8 (4 x 2 waves); row tiles per wave
-  bool whole;
-  int block_tiles, nrb;
-  double us;
-};
-constexpr size_t kWideSplitBytes = (size_t)128 << 20;  // the most that split products' running sums may take
-
-// Shapes of the kernel, and what a k-step of a workgroup takes (microseconds): `step`, and `tile` for each of its 16 x 16
-// output tiles; `tbs`: the rate its weights come at from memory when nothing else holds it up (TB/s).
-struct WideShape {
-  int ct, rt;
-  double step, tile, tbs;
-};
-constexpr WideShape kWideShapes[] = {{16, 2, 0.39, 0.0010, 4.2}, {16, 3, 0.44, 0.0016, 4.4}, {16, 4, 0.34, 0.0030, 5.2},
-                                     {8, 1, 0.21, 0.0008, 4.8},  {8, 2, 0.30, 0.0022, 4.4},  {8, 3, 0.30, 0.0034, 4.3}};
-
-// Shape of a product by a model of its time.  A workgroup takes 3.4 us and its k-steps, and 1.25 for every role
-// whose total it keeps in memory; one workgroup runs per compute unit (a last round that is not full is up to 25 %
-// shorter), of the smallest shape two, in 1.84 times the time of one; 5.4 lie around it all, and the second
-// kernel of a split product takes 1.5 and its running sums at 3.6 TB/s.  So few rows take narrow tiles or a split of K, many
-// rows 128 x 256 outputs per workgroup, and what decides in between is how full the last round of workgroups is.
-//
-// The figures are a fit to 3000 timed products (the five of the 1B, 8B and 13B shapes, 33 to 2047 rows, every shape, whole and
-// split), three times over, on cards that write running sums at 2 and at 4 TB/s: the shape they choose takes 0.3 to 0.75 % longer
-// than the fastest one in the mean and 17 % at most.  Before, with constants from when the second kernel
-// ran at 2.1 TB/s, 4.4 % and 56 %.  Microseconds, that choice / this one: 1B down 700 rows 89.8 (8 x 1, whole) / 57.4 (16 x 3,
-// split); 13B O 256 and 512 rows 57.9 / 38.3 and 98.0 / 69.6 (8 x 1, whole / 16 x 4, split); 13B QKV 48 rows 62.5 / 48.0 (8 x 1, whole /
-// split); 8B O 700 rows 66.2 / 50.4 (8 x 1 / 8 x 2); 8B head 96 rows 279 / 237 (16 x 2 / 16 x 3).
-static WidePlan wide_plan(int N, int K, int row_tiles, int n_cu, size_t ws_bytes) {
-  int W, P;
-  wide_roles(K, W, P);
-  const int ntiles = (N + 15) / 16;
-  WidePlan best{};
-  for (const WideShape& sh : kWideShapes)
-    for (const bool whole : {true, false}) {
-      const int tiles = (sh.ct == 16 ? 2 : 4) * sh.rt;
-      WidePlan p{sh.ct, sh.rt, whole, 0, (row_tiles + tiles - 1) / tiles, 0.0};
-      p.block_tiles = (row_tiles + p.nrb - 1) / p.nrb;  // (spread evenly)
-      p.nrb = (row_tiles + p.block_tiles - 1) / p.block_tiles;
-      const size_t ws = (size_t)ntiles * row_tiles * 1024 * (whole ? (P > 1 ? 1 : 0) : W);
-      if (ws > (whole ? ws_bytes : std::min(ws_bytes, kWideSplitBytes))) continue;
-      const int wgs = (ntiles + sh.ct - 1) / sh.ct * p.nrb * (whole ? 1 : W), steps = 16 * P * (whole ? W : 1);
-      const double one = 3.4 + steps * (sh.step + sh.tile * sh.ct * p.block_tiles) + (whole && P > 1 ? 1.25 * W : 0.0);
-      double us;
-      if (sh.ct == 8 && sh.rt == 1) {
-        const int left = wgs % (2 * n_cu);
-        us = one * (1.84 * (wgs / (2 * n_cu)) + (left == 0 ? 0.0 : left <= n_cu ? 1.0 : 1.84));
-      } else {
-        const int left = wgs % n_cu;
-        us = one * (wgs / n_cu + (left == 0 ? 0.0 : 0.75 + 0.25 * left / n_cu));
-      }
-      us = 5.4 + std::max(us, (double)ntiles * 16 * K * 2e-6 / sh.tbs);
-      if (!whole) us += 1.5 + (double)ws / 3.6e6;
-      p.us = us;
-      if (best.ct == 0 || us < best.us) best = p;
-    }
-  return best;
-}
-
-// Against the narrow kernel: the kernel that computes rstd in front of a product with a norm takes 3.5 more, and a split counts
-// for 1.5 more than the fit says, since it is the one that cards differ in (8B O 96 rows, narrow 20.2, split 17.7 and 23.9).
-double gemm_wide_us(const GemmCall& c) {
-  const int n_cu = device_cu_count();
-  if (n_cu <= 0) return 0.0;
-  const WidePlan p = wide_plan(c.N, c.K, (c.m + 15) / 16, n_cu, c.wide_ws ? c.wide_ws_bytes : 0);
-  return p.us + (c.ssq_in != nullptr ? 3.5 : 0.0) + (p.whole ? 0.0 : 1.5);
-}
-
-// largest workspace any product with N weight rows and K columns asks for at up to max_rows rows
-size_t gemm_wide_workspace_bytes(int N, int K, int max_rows) {
-  int W, P;
-  wide_roles(K, W, P);
-  const size_t tiles = (size_t)((N + 15) / 16) * ((max_rows + 15) / 16) * 1024;
-  return std::max(P > 1 ? tiles : 0, std::min(tiles * W, kWideSplitBytes));
-}
-
 template <int WM, int WN, int RT, bool WHOLE, bool P1>
 static hipError_t launch_wide_kernel(const GemmArgs& a, const WideArgs& x, int grid, bool timed, hipEvent_t e0,
                                      hipEvent_t e1, hipStream_t st) {

@@ -14,11 +14,14 @@ SHAPES = [I.ModelShape("prompt-512", 2, 512, 8, 2, 64, 1536, 300), I.ModelShape(
 
 # rows of the first pass (tokens - 1): three and four row tiles (by product narrow or wide), five, a full and a ragged last row
 # block, one row in the last 16, and (2049 and more tokens) a second pass of one row and of a few hundred
+TOKENS = (34, 50, 65, 66, 97, 129, 130, 146, 258, 334, 690, 2049, 2050, 2381)
+
+
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: s.name)
 def test_long_passes_equal_short_ones(shape):
     from paper_2605_13319_amd import nav
     model = nav.Model(shape, I.make_weights(shape, 61))
-    for tokens in (34, 50, 65, 66, 97, 129, 130, 146, 258, 334, 690, 2049, 2050, 2381):
+    for tokens in TOKENS:
         toks = I.make_tokens(tokens, shape.vocab, 62 + tokens)
         pools = []
         for mode in (1, 0, 2):
@@ -54,13 +57,16 @@ def test_a_turn_behind_a_cached_context_equals_one_prompt():
 # tokens cached first (behind them a block of 128 rows takes 8 or 16 splits of the context), and tokens of
 # the call itself: a full block and a row, a ragged last block of a few rows (cut finer than the others),
 # a longer ragged one, and a second pass of one row
+TOKENS_BEHIND = (129, 270, 700, 2049)  # (as many rows: the pending token and all but the last)
+
+
 @pytest.mark.parametrize("shape", SHAPES[:3], ids=lambda s: s.name)
 @pytest.mark.parametrize("cached", [4500, 9001])
 def test_long_passes_behind_a_cached_context_equal_short_ones(shape, cached):
     from paper_2605_13319_amd import nav
     model = nav.Model(shape, I.make_weights(shape, 61))
     first = I.make_tokens(cached, shape.vocab, 71)
-    for tokens in (129, 270, 700, 2049):  # (as many rows: the pending token and all but the last)
+    for tokens in TOKENS_BEHIND:
         toks = I.make_tokens(tokens, shape.vocab, 72 + tokens)
         pools = []
         for mode in (1, 0, 2):

@@ -11,12 +11,14 @@ pytestmark = pytest.mark.gpu
 SHAPES = [I.ModelShape("groups-2048", 2, 2048, 16, 4, 128, 4096, 300), I.ModelShape("groups-4096", 2, 4096, 32, 8, 128, 4096, 300),
           I.ModelShape("groups-5120", 2, 5120, 40, 40, 128, 2560, 300)]
 
+ROWS = (33, 64, 79, 96, 97, 112, 113, 128)
+
 
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: s.name)
 def test_groups_of_three_to_eight_row_tiles(shape):
     from paper_2605_13319_amd import nav
     model = nav.Model(shape, I.make_weights(shape, 71))
-    for rows in (33, 64, 79, 96, 97, 112, 113, 128):
+    for rows in ROWS:
         toks = I.make_tokens(rows + 1, shape.vocab, 72 + rows)
         pools = []
         for mode in (1, 2, 0):
