@@ -123,12 +123,13 @@ __global__ __launch_bounds__(kF32Waves * 64) void gemm_f32_kernel(GemmF32Call a)
     }
   }
   // (The last products may have been issued in another basic block, where the compiler pads no wait
-  // states for the stores below: spell them out.)
-  asm volatile("s_nop 15\n\ts_nop 7" ::: "memory");
+  // states for the stores below: spell them out, tied to the sums of a row tile.)
 #pragma unroll
-  for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-    for (int j = 0; j < 8; ++j) asm volatile("" : "+v"(acc[rt][j]));
+  for (int rt = 0; rt < RT; ++rt) {
+    f32x4* s = acc[rt];
+    asm volatile("s_nop 15\n\ts_nop 7"
+                 : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]), "+v"(s[4]), "+v"(s[5]), "+v"(s[6]), "+v"(s[7]));
+  }
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
     red[w][rt][lane] = ((acc[rt][0] + acc[rt][1]) + (acc[rt][2] + acc[rt][3])) +

@@ -226,6 +226,7 @@ __global__ __launch_bounds__(kWideWaves * 64) void gemm_wide_kernel(GemmArgs a, 
       }
       // The slice is complete.  (The last products may have been issued in another basic block, where
       // the compiler pads no wait states for the adds below: spell them out.)
+      __builtin_amdgcn_sched_barrier(0);
       asm volatile("s_nop 15\n\ts_nop 7" ::: "memory");
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll

@@ -3,6 +3,7 @@ data is on its way (the compiler cannot see that it is), and no kernel may read 
 behind a basic-block boundary before the product has been delivered.  Compiles the sources to ISA
 text and runs the lints over every kernel in them."""
 import os
+import re
 import shutil
 import subprocess
 
@@ -28,7 +29,7 @@ def test_no_compiler_access_to_registers_of_loads_in_flight(source, tmp_path):
     assert isa_lint.check(str(out)) == 0
 
 
-@pytest.mark.parametrize("source", ["kernels_gemm.hip", "kernels_layers.hip", "kernels_attn.hip", "kernels_gemm_wide.hip"])
+@pytest.mark.parametrize("source", ["kernels_gemm.hip", "kernels_layers.hip", "kernels_attn.hip", "kernels_gemm_wide.hip", "kernels_f32.hip"])
 def test_no_early_read_of_matrix_core_results_across_blocks(source, tmp_path):
     if not os.path.exists(HIPCC):
         pytest.skip("hipcc not available")
@@ -39,6 +40,23 @@ def test_no_early_read_of_matrix_core_results_across_blocks(source, tmp_path):
     subprocess.run(cmd, check=True, capture_output=True)
     assert "v_mfma" in out.read_text()
     assert isa_lint.check_mfma(str(out)) == 0
+
+
+def test_wait_states_are_tied_to_the_products_in_front_of_them():
+    """A product has no memory effect, so a bare s_nop does not keep it in front: wherever the wait states are spelled out they
+    take the sums as operands, or stand between scheduling barriers."""
+    csrc = os.path.join(ROOT, "paper_2605_13319_amd", "csrc")
+    barrier, found = "__builtin_amdgcn_sched_barrier(0);", 0
+    for name in sorted(os.listdir(csrc)):
+        if not name.endswith((".h", ".hip")):
+            continue
+        with open(os.path.join(csrc, name)) as f:
+            text = re.sub(r"//[^\n]*", "", f.read())
+        for m in re.finditer(r'asm volatile\("s_nop 15\\n\\ts_nop 7"(.*?)\);', text, re.S):
+            found += 1
+            between = text[:m.start()].rstrip().endswith(barrier) and text[m.end():].lstrip().startswith(barrier)
+            assert between or '"+v"(' in m[1], f"{name}: {m[0]}"
+    assert found >= 6
 
 
 def test_lint_flags_an_early_read_of_a_matrix_core_result(tmp_path):
