@@ -120,12 +120,14 @@ def _ptr(a: Optional[np.ndarray], typ):
 
 def _ints(a):
     """(int32 values as an argument for the library, their number).  A list of Python integers goes straight into a C
-    array (1 us, by way of numpy 3); whatever that does not take, numpy converts or refuses."""
+    array (1.1 us for 8, by way of numpy 3); whatever that does not take, numpy converts or refuses.  (A tensor or an array in
+    the list would have an integer for the C array where numpy refuses the list, but makes the sum of its own type.)"""
     if type(a) is list and a:
         try:
-            buf = array("i", a)
-            return (C.c_int32 * len(buf)).from_buffer(buf), len(buf)
-        except (TypeError, OverflowError):
+            if type(sum(a)) is int:
+                buf = array("i", a)
+                return (C.c_int32 * len(buf)).from_buffer(buf), len(buf)
+        except Exception:  # (numpy says what is wrong, or takes it)
             pass
     v = _i32(a)
     return _ptr(v, _i32p), len(v)
@@ -135,9 +137,10 @@ def _floats(a):
     """The same for float32 values; None stays None."""
     if type(a) is list and a and type(a[0]) is float:
         try:
-            buf = array("f", a)
-            return (C.c_float * len(buf)).from_buffer(buf)
-        except (TypeError, OverflowError):
+            if type(sum(a)) is float:
+                buf = array("f", a)
+                return (C.c_float * len(buf)).from_buffer(buf)
+        except Exception:  # (numpy says what is wrong, or takes it)
             pass
     return None if a is None else _ptr(_f32(a), _f32p)
 

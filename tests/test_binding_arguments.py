@@ -3,6 +3,7 @@ import ctypes as C
 
 import numpy as np
 import pytest
+import torch
 
 from paper_2605_13319_amd import nav
 
@@ -29,9 +30,36 @@ def test_floats(a):
     assert nav._floats(None) is None
 
 
+class Scalar:
+    """What has a value for Python but is not a plain number: with a device tensor's refusal of numpy."""
+    def __index__(self):
+        return 5
+
+    def __float__(self):
+        return 0.5
+
+    def __array__(self, *args, **kwargs):
+        raise TypeError("not for numpy")
+
+
+@pytest.mark.parametrize("a", [[5, torch.tensor([6])], [torch.tensor([5]), 6], [5, Scalar()], [np.array([1, 2]), np.array([1, 2, 3])]])
+def test_integers_that_numpy_refuses_stay_refused(a):
+    with pytest.raises(Exception) as want:
+        nav._i32(a)
+    with pytest.raises(type(want.value)):
+        nav._ints(a)
+
+
+@pytest.mark.parametrize("a", [[0.5, np.array([0.3])], [0.5, torch.tensor([0.3])], [0.5, Scalar()], [0.5, [0.3]], [0.5, 2 + 0j]])
+def test_floats_that_numpy_refuses_stay_refused(a):
+    with pytest.raises(Exception) as want:
+        nav._f32(a)
+    with pytest.raises(type(want.value)):
+        nav._floats(a)
+
+
 @pytest.mark.gpu
 def test_the_current_stream():
-    import torch
     assert nav._stream() == torch.cuda.current_stream().cuda_stream
     s = torch.cuda.Stream()
     with torch.cuda.stream(s):
