@@ -123,13 +123,19 @@ __global__ __launch_bounds__(kF32Waves * 64) void gemm_f32_kernel(GemmF32Call a)
     }
   }
   // (The last products may have been issued in another basic block, where the compiler pads no wait
-  // states for the stores below: spell them out, tied to the sums of a row tile.)
-#pragma unroll
-  for (int rt = 0; rt < RT; ++rt) {
+  // states for the stores below: spell them out, once, behind all sums and in front of
+  // whoever reads them.)
+  auto tie = [&](int rt) {
     f32x4* s = acc[rt];
-    asm volatile("s_nop 15\n\ts_nop 7"
-                 : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]), "+v"(s[4]), "+v"(s[5]), "+v"(s[6]), "+v"(s[7]));
-  }
+    asm volatile("" : "+v"(s[0]), "+v"(s[1]), "+v"(s[2]), "+v"(s[3]), "+v"(s[4]), "+v"(s[5]), "+v"(s[6]), "+v"(s[7]));
+  };
+#pragma unroll
+  for (int rt = 1; rt < RT; ++rt) tie(rt);
+  asm volatile("s_nop 15\n\ts_nop 7"
+               : "+v"(acc[0][0]), "+v"(acc[0][1]), "+v"(acc[0][2]), "+v"(acc[0][3]), "+v"(acc[0][4]), "+v"(acc[0][5]),
+                 "+v"(acc[0][6]), "+v"(acc[0][7]));
+#pragma unroll
+  for (int rt = 1; rt < RT; ++rt) tie(rt);
 #pragma unroll
   for (int rt = 0; rt < RT; ++rt) {
     red[w][rt][lane] = ((acc[rt][0] + acc[rt][1]) + (acc[rt][2] + acc[rt][3])) +
