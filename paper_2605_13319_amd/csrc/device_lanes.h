@@ -1,7 +1,7 @@
 // Exchanges between the lanes of a wave on the vector unit.  The general shuffles go through the LDS unit, about 50 ns
 // each, one behind the other in a reduction; these take a few cycles.  Every reduction pairs the same lanes in the
-// same order as the butterfly of exchanges by xor that it stands for, so with a commutative f the results are
-// the same bits.
+// same order as the butterfly of exchanges by xor that it stands for, but both lanes of a pair may evaluate f with the same
+// first argument: f must be commutative, and then the results are the same bits.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -27,12 +27,12 @@ __device__ __forceinline__ unsigned lanes_ror(unsigned x) {
 }
 
 template <class F>
-__device__ __forceinline__ float fold16(float x, F f) {  // f(own, of lane ^ 16)
+__device__ __forceinline__ float fold16(float x, F f) {  // f(the even row's, the odd row's), in both of lanes l and l ^ 16
   const lanes_u32x2 p = lanes_xor16(__float_as_uint(x));
   return f(__uint_as_float(p.x), __uint_as_float(p.y));
 }
 template <class F>
-__device__ __forceinline__ float fold32(float x, F f) {  // f(own, of lane ^ 32)
+__device__ __forceinline__ float fold32(float x, F f) {  // f(the lower half's, the upper half's), in both of lanes l and l ^ 32
   const lanes_u32x2 p = lanes_xor32(__float_as_uint(x));
   return f(__uint_as_float(p.x), __uint_as_float(p.y));
 }
