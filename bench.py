@@ -33,7 +33,7 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-GEMM_SOURCES = ("device_gemm.h", "kernels_gemm.hip", "common.h")
+GEMM_SOURCES = ("device_gemm.h", "device_lanes.h", "gemm_plan.h", "kernels_gemm.hip", "common.h")
 TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "nav_pass_llama8b_k8_per_projection.md")
 
 

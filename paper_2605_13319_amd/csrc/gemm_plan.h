@@ -20,7 +20,8 @@ struct GemmPlan {  // launch shape of one GEMM
 
 constexpr int kTmax16 = 7;  // n-tiles per group at W = 8 (the LDS reduce area stays under 64 KB)
 
-// launch shape for `slots_cu` compute units' worth of teams
+// launch shape for the teams that `slots_cu` compute units hold at once (passes of more than one row tile: a part of the device,
+// since every team's tiles are multiplied by a workgroup per row tile)
 inline void shape_for(int N, int K, int slots_cu, GemmPlan& p) {
   p.K = K;
   p.N = N;
@@ -104,8 +105,11 @@ constexpr WideShape kWideShapes[] = {{16, 2, 0.39, 0.0010, 4.2}, {16, 3, 0.44, 0
 // rows 128 x 256 outputs per workgroup, and what decides in between is how full the last round of workgroups is.
 //
 // The figures are a fit to 3000 timed products (the five of the 1B, 8B and 13B shapes, 33 to 2047 rows, every shape, whole and
-// split), three times over, on cards that write running sums at 2 and at 4 TB/s: the shape they choose takes 0.3 to 0.75 % longer
-// than the fastest one in the mean and 17 % at most.  Before, with constants from when the second kernel
+// split), three times over, on cards that write running sums at 2 and at 4 TB/s.  Over the 297 products of a session (those
+// three and a later one) the shape they choose takes 0.3 to 0.75 % longer than the fastest one in the mean and 23 % at most (1B O at
+// 512 rows 24.5 us where 16 x 2, split, takes 19.9; over the sessions of the fit 17 %).  Over as many products of
+// three widths that the fit has not seen it is 0.7 % and 18 %: 3072 columns 0.6 and 9.5 %, 3584 0.5 and 9.9 %, 6144 0.9 and
+// 18 % (down, 300 rows, 161 us where 16 x 3, split, takes 136).  Before, with constants from when the second kernel
 // ran at 2.1 TB/s, 4.4 % and 56 %.  Microseconds, that choice / this one: 1B down 700 rows 89.8 (8 x 1, whole) / 57.4 (16 x 3,
 // split); 13B O 256 and 512 rows 57.9 / 38.3 and 98.0 / 69.6 (8 x 1, whole / 16 x 4, split); 13B QKV 48 rows 62.5 / 48.0 (8 x 1, whole /
 // split); 8B O 700 rows 66.2 / 50.4 (8 x 1 / 8 x 2); 8B head 96 rows 279 / 237 (16 x 2 / 16 x 3).
@@ -142,6 +146,10 @@ inline WidePlan wide_plan(int N, int K, int row_tiles, int n_cu, size_t ws_bytes
 
 // Against the narrow kernel: the kernel that computes rstd in front of a product with a norm takes 3.5 more, and a split counts
 // for 1.5 more than the fit says, since it is the one that cards differ in (8B O 96 rows, narrow 20.2, split 17.7 and 23.9).
+// What the choice loses against the faster of both kernels with / without that 1.5, in the mean over 35 products of 33 to 128
+// rows, in four sessions: 8B 2.1 / 0.2, 1.5 / 1.4, 1.6 / 1.9 and 1.7 / 1.3 %, 1B 0.8 to 1.1 / 0.2 to 0.6 %, 13B 0.3 to 0.5 / 0.1 to
+// 0.3 %, other widths 0.4 to 0.7 % either way.  So it pays for 8B O alone, on some cards; 1B down at 33 to 64 rows, 18.4 narrow,
+// would take 16.7 without it.
 inline double gemm_wide_us(int N, int K, int row_tiles, bool norm, int n_cu, size_t ws_bytes) {
   const WidePlan p = wide_plan(N, K, row_tiles, n_cu, ws_bytes);
   return p.us + (norm ? 3.5 : 0.0) + (p.whole ? 0.0 : 1.5);

@@ -105,8 +105,8 @@ __device__ __forceinline__ unsigned long long fixed_weight(float p, float q, boo
 // caches, without fences (a device-scope fence writes the whole L2 back), every wave makes the tests for
 // itself, and the arrival counter wraps to zero by itself, so that no launch has to clear it in front:
 // 9.7 -> 7.8 us on given probabilities at that vocabulary and 8 drafts, and 1.4 for the clearing launch.  With its sums and
-// scans on the vector unit (device_lanes.h) calls of the static entry point follow each other every 6.9 us, which is now the
-// kernel's time; the host takes 6.2 (11.3, its own, before its arguments and its stream came without detours).
+// scans on the vector unit (device_lanes.h) calls of the static entry point follow each other every 7.0 us, which is now the
+// kernel's time (11.3 before, the host's, whose arguments and stream then came by detours).
 __device__ __forceinline__ void spec_accept_body(const float* __restrict__ p, const float* __restrict__ q,
                                                  const float* __restrict__ stats, int k, int V, const int32_t* drafts,
                                                  const float* un, unsigned long long* partial, unsigned* counter,
