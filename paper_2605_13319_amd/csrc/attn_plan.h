@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <utility>
 
 #include "../../include/pipesd.h"
 
@@ -114,6 +115,33 @@ inline int attn_stream_plan(int n_q_heads, int n_kv_heads, int head_dim, int n_c
   }
   *part_floats = floats;
   return T;
+}
+
+// Several clients in the streaming kernel's launch, T query tiles per workgroup.  Items (client, tile group, split): the items of
+// a client side by side, the clients whose workgroups take longest first, so that what a round of workgroups more has left is
+// short.  Only what there is to do is launched: with a grid of splits x the tile groups of the
+// largest client 42 % of the workgroups of the 16-client call had nothing to do, but each took half a compute unit until it had
+// found that out, and a client was found by a chain of loads (75.3 -> 72.1 us a layer, the call 9235 -> 9155).  That grid ran the clients'
+// first tile groups before the others; items in the order of the clients, a split's tile groups next to each other, left long
+// workgroups for the last round: calls of 4 clients behind up to 8000 tokens, us, that grid / the clients' order / this one: 8B widths
+// (8 layers) 1513 / 1523 / 1454, 3072 columns on 8 KV heads 1009 / 1041 / 975, 1B 1497 / 1479 / 1430; 16 behind up to 4000 2771 / 2596 /
+// 2575, 1783 / 1648 / 1622 and 2377 / 2219 / 2181.
+struct StreamItems {
+  int32_t first[kMaxPassClients];  // of client i of `batch` (beyond the batch: the number of items)
+  int32_t n;                       // all items
+};
+inline StreamItems attn_stream_items(int group, int T, AttnBatch& batch) {
+  auto longest = [&](const AttnClient& c) {  // (a workgroup's steps, and how many tiles it multiplies in each)
+    return std::min((long)c.span, (long)c.start_pos + c.m) * (1 + std::min(T, attn_query_tiles(group, c.m)));
+  };
+  for (int i = 1; i < batch.n; ++i)
+    for (int j = i; j > 0 && longest(batch.c[j]) > longest(batch.c[j - 1]); --j) std::swap(batch.c[j], batch.c[j - 1]);
+  StreamItems items{};
+  for (int i = 0; i < kMaxPassClients; ++i) {
+    items.first[i] = items.n;
+    if (i < batch.n) items.n += batch.c[i].nsplit * ((attn_query_tiles(group, batch.c[i].m) + T - 1) / T);
+  }
+  return items;
 }
 
 // Which kernel takes a planned pass: 0 for the streaming kernel, else the prompt kernel, with `shares`->n[i] workgroups

@@ -143,16 +143,8 @@ constexpr size_t stream_lds_bytes(int T) {
   return stream_lds_floats(HD) * sizeof(float) + (size_t)T * (HD / 32) * 2 * 64 * 16 + 16;
 }
 
-// What the workgroups of a KV head do where several clients share the pass: items (client, split, tile group), the items
-// of a client side by side.  Only what there is to do is launched: with a grid of splits x the tile groups of the
-// largest client 42 % of the workgroups of the 16-client call had nothing to do, but each took half a compute unit until it had
-// found that out, and a client was found by a chain of loads (75.3 -> 72.1 us a layer, the call 9235 -> 9155).
-// One client's grid is (KV heads, splits, tile groups) as it is, and asks for nothing more (finding its one item 0.5 to 0.9 us).
-struct StreamItems {
-  int32_t first[kMaxPassClients];  // of client i (beyond the batch: the number of items)
-  int32_t n, nz[kMaxPassClients];  // all items; tile groups of client i
-};
-
+// (grid: kv heads, and of several clients' items (attn_stream_items), of one client's splits, tile groups: finding its one
+// item took 0.5 to 0.9 us)
 template <int HD, int T>
 __global__ __launch_bounds__(kStreamWaves * 64, 2) void attn_stream_kernel(const float* q, KvView kv, int layer, int n_q_heads,
                                                                       AttnBatch batch, StreamItems items, float* part,
@@ -167,8 +159,9 @@ __global__ __launch_bounds__(kStreamWaves * 64, 2) void attn_stream_kernel(const
     const int item = blockIdx.y;
 #pragma unroll
     for (int i = 1; i < kMaxPassClients; ++i) ci += item >= items.first[i] ? 1 : 0;
-    split = (item - items.first[ci]) / items.nz[ci];
-    zt = item - items.first[ci] - split * items.nz[ci];
+    const int ns = batch.c[ci].nsplit;
+    zt = (item - items.first[ci]) / ns;
+    split = item - items.first[ci] - zt * ns;
   }
   const AttnClient cl = batch.c[ci];
   const int group = n_q_heads / kv.n_kv_heads, m = cl.m, R = group * m;
@@ -978,14 +971,10 @@ hipError_t launch_attention(const AttnCall& c, hipStream_t st) {
         };
         return h == 128 ? go(integral_constant<int, 128>{}) : go(integral_constant<int, 64>{});
       }
-      StreamItems items{};
-      for (int i = 0; i < kMaxPassClients; ++i) {
-        items.first[i] = items.n;
-        if (i >= b.n) continue;
-        items.nz[i] = (attn_query_tiles(group, b.c[i].m) + T - 1) / T;
-        items.n += b.c[i].nsplit * items.nz[i];
-      }
-      const dim3 grid = b.n > 1 ? dim3(c.kv.n_kv_heads, items.n) : dim3(c.kv.n_kv_heads, b.c[0].nsplit, items.nz[0]);
+      AttnBatch ordered = b;
+      const StreamItems items = attn_stream_items(group, T, ordered);
+      const dim3 grid = b.n > 1 ? dim3(c.kv.n_kv_heads, items.n)
+                                : dim3(c.kv.n_kv_heads, b.c[0].nsplit, (attn_query_tiles(group, b.c[0].m) + T - 1) / T);
       const dim3 block(kStreamWaves * 64);
       auto go = [&](auto hd, auto t) -> hipError_t {
         constexpr int HD = decltype(hd)::value, TT = decltype(t)::value;
@@ -993,7 +982,7 @@ hipError_t launch_attention(const AttnCall& c, hipStream_t st) {
         constexpr size_t lds = stream_lds_bytes<HD>(TT);
         const hipError_t e = allow_lds(lds_allowed, (const void*)attn_stream_kernel<HD, TT>, lds);
         if (e != hipSuccess) return e;
-        attn_stream_kernel<HD, TT><<<grid, block, lds, st>>>(c.q, c.kv, c.layer, c.n_q_heads, b, items, c.part, (uint4*)c.outp,
+        attn_stream_kernel<HD, TT><<<grid, block, lds, st>>>(c.q, c.kv, c.layer, c.n_q_heads, ordered, items, c.part, (uint4*)c.outp,
                                                              c.act_tiles, c.gate, c.counters);
         return hipGetLastError();
       };

@@ -84,6 +84,67 @@ def test_scratch_of_a_pool_holds_every_pass(sweep, heads, n_cu):
     assert r.returncode == 0, r.stdout
 
 
+ITEMS = r"""
+#include <stdio.h>
+#include <stdlib.h>
+#include "attn_plan.h"
+using namespace pipesd;
+static unsigned seed = 4321;
+static long rnd(long n) { seed = seed * 1664525u + 1013904223u; return (long)((seed >> 8) % (unsigned long)n); }
+int main() {
+  const int heads[][3] = {{32, 8, 128}, {24, 8, 128}, {32, 8, 64}, {40, 40, 128}, {128, 1, 64}, {16, 16, 64}};
+  int checked = 0;
+  for (int t = 0; t < 6000; ++t) {
+    const int* h = heads[t % 6], group = h[0] / h[1];
+    AttnBatch b{};
+    b.n = 2 + (int)rnd(15);
+    int rows = 0;
+    for (int i = 0; i < b.n; ++i) {
+      b.c[i].row_off = rows;
+      rows += b.c[i].m = 1 + (int)rnd(17);
+      b.c[i].start_pos = (int)rnd(rnd(20000) + 1);
+    }
+    size_t floats = 0;
+    const int T = attn_stream_plan(h[0], h[1], h[2], 256, b, false, &floats);
+    if (T == 0) continue;
+    AttnBatch o = b;
+    const StreamItems items = attn_stream_items(group, T, o);
+    // every (client, tile group, split) of the plan once, found as the kernel finds it
+    static unsigned char seen[kMaxPassClients][2048][kStreamMaxSplits];
+    for (auto& c : seen) for (auto& z : c) for (auto& s : z) s = 0;
+    long last = -1;
+    for (int item = 0; item < items.n; ++item) {
+      int ci = 0;
+      for (int i = 1; i < kMaxPassClients; ++i) ci += item >= items.first[i] ? 1 : 0;
+      if (ci >= o.n) return 1;
+      const AttnClient& c = o.c[ci];
+      const int z = (item - items.first[ci]) / c.nsplit, s = item - items.first[ci] - z * c.nsplit;
+      int was = -1;
+      for (int i = 0; i < b.n; ++i) if (b.c[i].row_off == c.row_off) was = i;
+      if (was < 0 || z * T >= attn_query_tiles(group, c.m) || c.m != b.c[was].m || c.start_pos != b.c[was].start_pos || c.part_off != b.c[was].part_off ||
+          c.count_off != b.c[was].count_off || c.span != b.c[was].span || seen[was][z][s]++) return 2;
+      // no client's workgroups are longer than those of the clients before it
+      const long steps = std::min((long)c.span, (long)c.start_pos + c.m) * (1 + std::min(T, attn_query_tiles(group, c.m)));
+      if (last >= 0 && steps > last) return 3;
+      last = steps;
+    }
+    long all = 0, found = items.n;
+    for (int i = 0; i < b.n; ++i) all += (long)b.c[i].nsplit * ((attn_query_tiles(group, b.c[i].m) + T - 1) / T);
+    if (all != found || all > 65535) return 4;  // (a grid's limit)
+    ++checked;
+  }
+  return checked > 3000 ? 0 : 5;
+}
+"""
+
+
+def test_items_of_several_clients_are_each_there_once_the_longest_first(tmp_path):
+    cxx = shutil.which("g++") or shutil.which("clang++") or "/opt/rocm/llvm/bin/clang++"
+    (tmp_path / "items.cpp").write_text(ITEMS)
+    subprocess.run([cxx, "-std=c++17", "-O2", "-Wall", "-Werror", "-I", CSRC, "-o", str(tmp_path / "items"), str(tmp_path / "items.cpp")], check=True)
+    assert subprocess.run([str(tmp_path / "items")], timeout=120).returncode == 0
+
+
 ROUTES = r"""
 #include <stdio.h>
 #include <stdlib.h>
