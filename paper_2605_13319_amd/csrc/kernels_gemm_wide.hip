@@ -83,7 +83,10 @@ __device__ __forceinline__ void wide_dispatch_count(int n, F& f) {
   }
 }
 
-template <int WM, int WN, int RT, bool WHOLE, bool P1>
+// EPI: the epilogue of a whole walk (a split one has none: kEpiAny).  One kernel with all four behind branches at run time took,
+// us (that / this): 8B gate/up 33 rows 54.6 / 53.9, QKV 333 rows 62.0 / 60.9 and 2047 rows 196 / 192; 3584 columns gate/up 33 rows
+// 71.3 / 69.3; 1B gate/up 96 rows 30.3 / 29.9.
+template <int WM, int WN, int RT, bool WHOLE, bool P1, int EPI>
 __global__ __launch_bounds__(kWideWaves * 64) void gemm_wide_kernel(GemmArgs a, WideArgs x) {
   static_assert(WM * WN == kWideWaves, "eight waves");
   extern __shared__ float lds_f[];
@@ -278,11 +281,11 @@ __global__ __launch_bounds__(kWideWaves * 64) void gemm_wide_kernel(GemmArgs a, 
     float rstd[RT];
 #pragma unroll
     for (int r = 0; r < RT; ++r) rstd[r] = x.rstd != nullptr ? x.rstd[min((rt0 + r * WM + wm) * 16 + c, a.m - 1)] : 1.0f;
-    const bool resid = a.epi == EPI_RESID;
+    constexpr bool resid = EPI == EPI_RESID;
 #pragma unroll
     for (int n = 0; n < 4; ++n) {  // (an n-tile at a time: registers)
       ResidPre pre[RT];
-      if (resid) {
+      if constexpr (resid) {
 #pragma unroll
         for (int r = 0; r < RT; ++r) pre[r] = resid_pre(a, t0 + n, (rt0 + r * WM + wm) * 16 + c, lane);
       }
@@ -290,7 +293,7 @@ __global__ __launch_bounds__(kWideWaves * 64) void gemm_wide_kernel(GemmArgs a, 
       for (int r = 0; r < RT; ++r) {
         const int lt = r * WM + wm;
         if (t0 + n < a.ntiles && lt < live)
-          epilogue_quad<false>(a, t0 + n, (rt0 + lt) * 16 + c, lane, sum[n][r], rstd[r], resid, pre[r]);
+          epilogue_quad<false, EPI>(a, t0 + n, (rt0 + lt) * 16 + c, lane, sum[n][r], rstd[r], resid, pre[r]);
       }
     }
   } else {
@@ -350,19 +353,19 @@ __global__ __launch_bounds__(256) void gemm_wide_finish_kernel(GemmArgs a, WideA
 // ------------------------------------------------------------------------------------------------
 // launch shape
 // ------------------------------------------------------------------------------------------------
-template <int WM, int WN, int RT, bool WHOLE, bool P1>
+template <int WM, int WN, int RT, bool WHOLE, bool P1, int EPI>
 static hipError_t launch_wide_kernel(const GemmArgs& a, const WideArgs& x, int grid, bool timed, hipEvent_t e0,
                                      hipEvent_t e1, hipStream_t st) {
   constexpr size_t lds = wide_lds_bytes(WM, WN, RT);
   static std::atomic<uint64_t> lds_allowed;
-  const hipError_t e = allow_lds(lds_allowed, (const void*)gemm_wide_kernel<WM, WN, RT, WHOLE, P1>, lds);
+  const hipError_t e = allow_lds(lds_allowed, (const void*)gemm_wide_kernel<WM, WN, RT, WHOLE, P1, EPI>, lds);
   if (e != hipSuccess) return e;
   // start of the first kernel of the product, end of the last
   if (timed)
-    hipExtLaunchKernelGGL((gemm_wide_kernel<WM, WN, RT, WHOLE, P1>), dim3(grid), dim3(kWideWaves * 64), (uint32_t)lds, st, e0,
+    hipExtLaunchKernelGGL((gemm_wide_kernel<WM, WN, RT, WHOLE, P1, EPI>), dim3(grid), dim3(kWideWaves * 64), (uint32_t)lds, st, e0,
                           WHOLE ? e1 : nullptr, 0, a, x);
   else
-    gemm_wide_kernel<WM, WN, RT, WHOLE, P1><<<grid, kWideWaves * 64, lds, st>>>(a, x);
+    gemm_wide_kernel<WM, WN, RT, WHOLE, P1, EPI><<<grid, kWideWaves * 64, lds, st>>>(a, x);
   return hipGetLastError();
 }
 
@@ -398,10 +401,21 @@ hipError_t launch_gemm_wide(const GemmCall& c, GemmArgs a, hipStream_t st) {
   const int ntask = x.ncg * x.nrb * (p.whole ? 1 : a.W), grid = (ntask + 7) / 8 * 8;
   auto go = [&](auto wm, auto wn, auto rt) -> hipError_t {
     constexpr int WM = decltype(wm)::value, WN = decltype(wn)::value, RT = decltype(rt)::value;
-    if (p.whole && a.P == 1) return launch_wide_kernel<WM, WN, RT, true, true>(a, x, grid, timed, e0, e1, st);
-    if (p.whole) return launch_wide_kernel<WM, WN, RT, true, false>(a, x, grid, timed, e0, e1, st);
-    if (a.P == 1) return launch_wide_kernel<WM, WN, RT, false, true>(a, x, grid, timed, e0, e1, st);
-    return launch_wide_kernel<WM, WN, RT, false, false>(a, x, grid, timed, e0, e1, st);
+    if (!p.whole) {
+      if (a.P == 1) return launch_wide_kernel<WM, WN, RT, false, true, kEpiAny>(a, x, grid, timed, e0, e1, st);
+      return launch_wide_kernel<WM, WN, RT, false, false, kEpiAny>(a, x, grid, timed, e0, e1, st);
+    }
+    auto whole = [&](auto epi) {
+      constexpr int EPI = decltype(epi)::value;
+      if (a.P == 1) return launch_wide_kernel<WM, WN, RT, true, true, EPI>(a, x, grid, timed, e0, e1, st);
+      return launch_wide_kernel<WM, WN, RT, true, false, EPI>(a, x, grid, timed, e0, e1, st);
+    };
+    switch (a.epi) {
+      case EPI_STORE: return whole(std::integral_constant<int, EPI_STORE>{});
+      case EPI_RESID: return whole(std::integral_constant<int, EPI_RESID>{});
+      case EPI_SWIGLU: return whole(std::integral_constant<int, EPI_SWIGLU>{});
+      default: return whole(std::integral_constant<int, EPI_QKV>{});
+    }
   };
   using std::integral_constant;
   hipError_t e = hipErrorInvalidValue;

@@ -38,8 +38,13 @@ def test_no_early_read_of_matrix_core_results_across_blocks(source, tmp_path):
            "-packed-fp32-ops", "-S", "--cuda-device-only", "-o", str(out),
            os.path.join(ROOT, "paper_2605_13319_amd", "csrc", source)]
     subprocess.run(cmd, check=True, capture_output=True)
-    assert "v_mfma" in out.read_text()
+    text = out.read_text()
+    assert "v_mfma" in text
     assert isa_lint.check_mfma(str(out)) == 0
+    if source == "kernels_gemm_wide.hip":  # a whole walk carries the code of its own epilogue only (SiLU is the one with exponentials)
+        whole = re.findall(r"^_ZN6pipesd16gemm_wide_kernelI\w*?Lb1ELb[01]ELi(\d)EE\w*:(.*?)\n\.Lfunc_end", text, re.S | re.M)
+        assert len(whole) == 6 * 2 * 4
+        assert all(("v_exp_f32" in code) == (epi == "2") for epi, code in whole)
 
 
 def test_wait_states_are_tied_to_the_products_in_front_of_them():
