@@ -89,30 +89,30 @@ struct WidePlan {
 };
 constexpr size_t kWideSplitBytes = (size_t)128 << 20;  // the most that split products' running sums may take
 
-// Shapes of the kernel, and what a k-step of a workgroup takes (microseconds): `step`, and `tile` for each of its 16 x 16
-// output tiles; `tbs`: the rate its weights come at from memory when nothing else holds it up (TB/s).
+// Shapes of the kernel, and what a workgroup takes (microseconds): `step` for a k-step, `tile` more for each of its 16 x 16
+// output tiles, `fin` per tile behind the last one (the epilogue, where it walks all of K); `tbs`: the rate its weights come at
+// from memory when nothing else holds it up (TB/s).
 struct WideShape {
   int ct, rt;
-  double step, tile, tbs;
+  double step, tile, fin, tbs;
 };
-constexpr WideShape kWideShapes[] = {{16, 2, 0.39, 0.0010, 4.2}, {16, 3, 0.44, 0.0016, 4.4}, {16, 4, 0.34, 0.0030, 5.2},
-                                     {8, 1, 0.21, 0.0008, 4.8},  {8, 2, 0.30, 0.0022, 4.4},  {8, 3, 0.30, 0.0034, 4.3}};
+constexpr WideShape kWideShapes[] = {{16, 2, 0.35, 0.0014, 0.050, 6.2}, {16, 3, 0.44, 0.0010, 0.095, 6.3}, {16, 4, 0.49, 0.0012, 0.095, 4.9},
+                                     {8, 1, 0.25, 0.0006, 0.0, 6.2},    {8, 2, 0.38, 0.0006, 0.060, 5.6},  {8, 3, 0.31, 0.0028, 0.075, 3.6}};
 
-// Shape of a product by a model of its time.  A workgroup takes 3.4 us and its k-steps, and 1.25 for every role
-// whose total it keeps in memory; one workgroup runs per compute unit (a last round that is not full is up to 25 %
-// shorter), of the smallest shape two, in 1.84 times the time of one; 5.4 lie around it all, and the second
-// kernel of a split product takes 1.5 and its running sums at 3.6 TB/s.  So few rows take narrow tiles or a split of K, many
-// rows 128 x 256 outputs per workgroup, and what decides in between is how full the last round of workgroups is.
+// Shape of a product by a model of its time.  A workgroup takes 1.7 us, its k-steps and its end, and 1.1 for every role
+// whose total it keeps in memory; one workgroup runs per compute unit (a last round that is not full is up to 3 %
+// shorter), of the smallest shape two, in 1.74 times the time of one; 3.7 lie around it all, and the second
+// kernel of a split product takes 1.7 and its running sums at 2.1 TB/s.  So few rows take narrow tiles or a split of K, many
+// rows 128 x 256 outputs per workgroup, and what decides in between is how full the last round of workgroups is; the end of
+// large tiles, 10 us, is what a short walk (K of 512 to 1536) must not have twice.
 //
-// The figures are a fit to 3000 timed products (the five of the 1B, 8B and 13B shapes, 33 to 2047 rows, every shape, whole and
-// split), three times over, on cards that write running sums at 2 and at 4 TB/s.  Over the 297 products of a session (those
-// three and a later one) the shape they choose takes 0.3 to 0.75 % longer than the fastest one in the mean and 23 % at most (1B O at
-// 512 rows 24.5 us where 16 x 2, split, takes 19.9; over the sessions of the fit 17 %).  Over as many products of
-// three widths that the fit has not seen it is 0.7 % and 18 %: 3072 columns 0.6 and 9.5 %, 3584 0.5 and 9.9 %, 6144 0.9 and
-// 18 % (down, 300 rows, 161 us where 16 x 3, split, takes 136).  Before, with constants from when the second kernel
-// ran at 2.1 TB/s, 4.4 % and 56 %.  Microseconds, that choice / this one: 1B down 700 rows 89.8 (8 x 1, whole) / 57.4 (16 x 3,
-// split); 13B O 256 and 512 rows 57.9 / 38.3 and 98.0 / 69.6 (8 x 1, whole / 16 x 4, split); 13B QKV 48 rows 62.5 / 48.0 (8 x 1, whole /
-// split); 8B O 700 rows 66.2 / 50.4 (8 x 1 / 8 x 2); 8B head 96 rows 279 / 237 (16 x 2 / 16 x 3).
+// The figures are a fit to 25 000 timed products, two sessions: the four of 14 model shapes from 512 to 8192 columns, 33 to 2047
+// rows, every shape, whole and split.  The shape they choose takes 0.5 % longer than the fastest one in the mean, 3 % in 19 of 20
+// products and at most 31 % (512 columns, 2.5 us).  Fitted to a part of the 14 and tried on the rest it is 0.8 %, 5 % and 25 %.
+// Before: a fit to the 1B, 8B and 13B shapes alone, without `fin`, 0.85 %, 5 % and 31 % over the 14 and up to 19 % slower than
+// an earlier rule where walks are short.  Us, that rule / that fit / this one: 1024 columns, gate/up 2047 rows 66.4 / 78.8 / 66.4, QKV
+// 1200 rows 27.6 / 28.5 / 27.6; 1536 gate/up 1000 rows 125 / 145 / 125; 2560 gate/up 640 rows 131 / 141 / 129, QKV 2047 rows 141 / 155 /
+// 135.  Of the 1B, 8B and 13B widths no product is more than 1 % slower than by that fit, and calls of 33 and more rows are 0 to 1.8 % faster.
 inline WidePlan wide_plan(int N, int K, int row_tiles, int n_cu, size_t ws_bytes) {
   int W, P;
   wide_roles(K, W, P);
@@ -127,32 +127,31 @@ inline WidePlan wide_plan(int N, int K, int row_tiles, int n_cu, size_t ws_bytes
       const size_t ws = (size_t)ntiles * row_tiles * 1024 * (whole ? (P > 1 ? 1 : 0) : W);
       if (ws > (whole ? ws_bytes : std::min(ws_bytes, kWideSplitBytes))) continue;
       const int wgs = (ntiles + sh.ct - 1) / sh.ct * p.nrb * (whole ? 1 : W), steps = 16 * P * (whole ? W : 1);
-      const double one = 3.4 + steps * (sh.step + sh.tile * sh.ct * p.block_tiles) + (whole && P > 1 ? 1.25 * W : 0.0);
+      const int out = sh.ct * p.block_tiles;
+      const double one = 1.7 + steps * (sh.step + sh.tile * out) + (whole ? sh.fin * out + (P > 1 ? 1.1 * W : 0.0) : 0.0);
       double us;
       if (sh.ct == 8 && sh.rt == 1) {
         const int left = wgs % (2 * n_cu);
-        us = one * (1.84 * (wgs / (2 * n_cu)) + (left == 0 ? 0.0 : left <= n_cu ? 1.0 : 1.84));
+        us = one * (1.74 * (wgs / (2 * n_cu)) + (left == 0 ? 0.0 : left <= n_cu ? 1.0 : 1.74));
       } else {
         const int left = wgs % n_cu;
-        us = one * (wgs / n_cu + (left == 0 ? 0.0 : 0.75 + 0.25 * left / n_cu));
+        us = one * (wgs / n_cu + (left == 0 ? 0.0 : 0.97 + 0.03 * left / n_cu));
       }
-      us = 5.4 + std::max(us, (double)ntiles * 16 * K * 2e-6 / sh.tbs);
-      if (!whole) us += 1.5 + (double)ws / 3.6e6;
+      us = 3.7 + std::max(us, (double)ntiles * 16 * K * 2e-6 / sh.tbs);
+      if (!whole) us += 1.7 + (double)ws / 2.1e6;
       p.us = us;
       if (best.ct == 0 || us < best.us) best = p;
     }
   return best;
 }
 
-// Against the narrow kernel: the kernel that computes rstd in front of a product with a norm takes 3.5 more, and a split counts
+// Against the narrow kernel: the kernel that computes rstd in front of a product with a norm takes 2.7 more, and a split counts
 // for 1.5 more than the fit says, since it is the one that cards differ in (8B O 96 rows, narrow 20.2, split 17.7 and 23.9).
-// What the choice loses against the faster of both kernels with / without that 1.5, in the mean over 35 products of 33 to 128
-// rows, in four sessions: 8B 2.1 / 0.2, 1.5 / 1.4, 1.6 / 1.9 and 1.7 / 1.3 %, 1B 0.8 to 1.1 / 0.2 to 0.6 %, 13B 0.3 to 0.5 / 0.1 to
-// 0.3 %, other widths 0.4 to 0.7 % either way.  So it pays for 8B O alone, on some cards; 1B down at 33 to 64 rows, 18.4 narrow,
-// would take 16.7 without it.
+// What the choice loses against the faster of both kernels with 0 / 1.5 / 3 there, in the mean over the products of 33 to 128 rows of
+// the 14 model shapes: 0.72 / 0.52 / 0.60 % (of the 1B, 8B and 13B widths 0.62 / 0.33 / 0.38 %).
 inline double gemm_wide_us(int N, int K, int row_tiles, bool norm, int n_cu, size_t ws_bytes) {
   const WidePlan p = wide_plan(N, K, row_tiles, n_cu, ws_bytes);
-  return p.us + (norm ? 3.5 : 0.0) + (p.whole ? 0.0 : 1.5);
+  return p.us + (norm ? 2.7 : 0.0) + (p.whole ? 0.0 : 1.5);
 }
 
 // mode: GemmCall::wide_mode

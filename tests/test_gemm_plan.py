@@ -88,8 +88,28 @@ def test_gpu_cases_reach_every_form_the_models_take(forms):
         reached |= set(forms(shape, both(rows), False))
     for shape in wide.HEADS:
         reached |= {f for f in forms(shape, [(n, 0) for n in wide.HEAD_ROWS], True) if f[0] == "head"}
-    for shape in (I.LLAMA_1B, I.LLAMA_8B, I.LLAMA_13B):
+    other = [I.ModelShape("3072", 1, 3072, 24, 8, 128, 8192, 32000), I.ModelShape("6144", 1, 6144, 48, 8, 128, 16384, 32000)]
+    for shape in (I.LLAMA_1B, I.LLAMA_8B, I.LLAMA_13B, *other):
         taken = forms(shape, [(n, 0) for n in range(33, 2049)], True)
         assert len(taken) > 40
         missing = {f: rows for f, rows in taken.items() if f not in reached}
         assert not missing, f"{shape.name}: forms that no GPU test compares, and the first rows that take them: {missing}"
+
+
+# Products whose walks are short: (model columns, query columns, KV columns, FFN), rows, epilogue, and what the shapes (n-tiles per
+# workgroup, row tiles per wave), walking all of K, took on an MI355X (us; splits take longer).  The end of a large tile is what
+# decides; a model of the time without it chose 16 x 4 in all of them but the QKV product of 1200 rows.
+SHORT = [((1024, 1024, 512, 3072), 2047, "swiglu", {(8, 1): 66.4, (16, 2): 70.2, (8, 2): 71.2, (16, 4): 78.8, (16, 3): 88.4, (8, 3): 88.6}),
+         ((1024, 1024, 512, 3072), 1200, "qkv", {(8, 1): 27.6, (16, 2): 28.2, (8, 2): 28.5, (8, 3): 35.6, (16, 3): 36.0, (16, 4): 43.2}),
+         ((1536, 1536, 256, 9216), 1000, "swiglu", {(8, 1): 124.8, (8, 2): 140.8, (16, 2): 141.9, (16, 4): 144.6, (16, 3): 148.8, (8, 3): 148.9}),
+         ((2560, 4096, 1024, 9728), 2047, "qkv", {(16, 2): 133.5, (8, 2): 134.6, (8, 1): 141.4, (16, 4): 154.6, (16, 3): 172.6, (8, 3): 176.6}),
+         ((2560, 4096, 1024, 9728), 640, "swiglu", {(8, 2): 128.6, (16, 2): 130.7, (8, 1): 134.9, (16, 4): 141.1, (8, 3): 148.4, (16, 3): 151.4})]
+
+
+@pytest.mark.parametrize("widths,rows,epilogue,us", SHORT)
+def test_short_walks_take_one_of_the_fastest_shapes(forms, widths, rows, epilogue, us):
+    d, q, kv, ffn = widths
+    shape = I.ModelShape("short", 1, d, q // 64, kv // 64, 64, ffn, 32000)
+    chosen = {f[1:4] for f in forms(shape, [(rows, 0)], False) if f[0] == epilogue}
+    (ct, rt, whole), = chosen
+    assert whole and us[ct, rt] <= 1.02 * min(us.values())

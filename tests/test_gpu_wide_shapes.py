@@ -1,4 +1,4 @@
-"""Every form of the wide products' kernel that passes of the 1B, 8B and 13B widths take, against the narrow kernel: the
+"""Every form of the wide products' kernel that passes of the 1B, 8B and 13B widths and of two others take, against the narrow kernel: the
 same caches, bit for bit, and (the LM head, which only calls of several clients run on it) the same probabilities.
 tests/test_gemm_plan.py counts the forms."""
 import numpy as np
@@ -10,8 +10,10 @@ from tests.test_gpu_prompt import SHAPES
 pytestmark = pytest.mark.gpu
 
 # rows of a prompt's first pass: what tests/test_gpu_prompt.py and tests/test_gpu_row_groups.py leave out
-ROWS = [(SHAPES[2], (513, 577, 1281)), (SHAPES[3], (193, 769, 897, 1089, 1153, 1537, 1601)),
-        (I.ModelShape("prompt-5120", 2, 5120, 40, 40, 128, 13824, 300), (33, 65, 129, 257, 321, 577, 769, 897, 1217, 1537))]
+ROWS = [(SHAPES[2], (513, 577, 673, 1281)), (SHAPES[3], (193, 769, 897, 1089, 1153, 1281, 1537, 1601)),
+        (I.ModelShape("prompt-5120", 2, 5120, 40, 40, 128, 13824, 300), (33, 65, 129, 257, 321, 577, 769, 897, 1217, 1537)),
+        (I.ModelShape("prompt-3072", 2, 3072, 24, 8, 128, 8192, 300), (129, 193, 289, 673, 801, 1281, 1345, 1537)),
+        (I.ModelShape("prompt-6144", 2, 6144, 48, 8, 128, 1024, 300), (33, 65, 97, 129, 321))]
 
 
 @pytest.mark.parametrize("shape,rows", ROWS, ids=[s.name for s, _ in ROWS])
@@ -31,7 +33,7 @@ def test_caches_of_the_wide_kernel_are_the_narrow_ones(shape, rows):
 
 
 HEADS = [I.ModelShape("head-2048", 1, 2048, 32, 8, 64, 512, 32000), I.ModelShape("head-5120", 1, 5120, 40, 40, 128, 512, 32000)]
-HEAD_ROWS = (33, 64, 112, 144, 176, 256)
+HEAD_ROWS = (33, 64, 112, 144, 176, 192, 256)
 
 
 @pytest.mark.parametrize("shape", HEADS, ids=lambda s: s.name)
